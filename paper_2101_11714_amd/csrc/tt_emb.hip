@@ -20,6 +20,7 @@
 #include "tt_group.h"
 #include "tt_fwd_owner.h"
 #include "tt_bwd_owner.h"
+#include "tt_flex.h"
 #include "tt_freq.h"
 #include "tt_dense.h"
 #include "tt_init.h"
@@ -197,6 +198,12 @@ size_t split_ws_bytes_max(const Params &p, int64_t L)
     return a > b ? a : b;
 }
 
+// what the run-time-shape backward (tt_flex.h) adds for the shapes without a specialised kernel
+size_t flex_ws_bytes(const Params &p, int64_t L)
+{
+    return !fast_bwd_supported(p) && flex_fits(p, L) ? flex_ws_layout(nullptr, p, L).bytes : 0;
+}
+
 // tiles_possible: false for a call that brings no kept T0 (the tiled backward needs one) or that has a cache
 size_t split_ws_bytes(const Params &p, int64_t L, bool grouped, bool tiles_possible)
 {
@@ -238,7 +245,7 @@ size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags
     Params p;
     if (check_shape(shape, &p) != TT_OK || L < 0) return 0;
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
-    return fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L);
+    return fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L);
 }
 
 size_t tt_emb_dedup_workspace_bytes(int64_t L)
@@ -280,6 +287,11 @@ static int fwd_common(const tt_shape_t *shape, const float *const cores[3],
         int frc = fast_fwd(p, cores[0], cores[1], cores[2], indices, offsets, L, (int)n_bags, alpha, cd, output,
                            keep_t0 ? t0_out : nullptr, st);
         if (frc == 0) {
+            hipError_t e = hipGetLastError();
+            return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
+        }
+        if (flex_supported(p)) {
+            flex_fwd(p, cores[0], cores[1], cores[2], indices, offsets, (int)n_bags, alpha, cd, output, st);
             hipError_t e = hipGetLastError();
             return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
         }
@@ -414,7 +426,11 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     // gradients of the cores, in the workspace
     const size_t gc_bytes = fused && cd.K ? align256((size_t)cd.K * p.N * 4) : 0;
     size_t g_bytes[3] = {0, 0, 0};
-    if (fused && !fast)
+    // shapes without a specialised kernel: the kernels of tt_flex.h where they take the shape and the caller's workspace has
+    // room for them (a workspace is not required of a short call without a cache), else those of tt_generic.h
+    const size_t fx_bytes = !fast && g_fast_path && L > 0 ? flex_ws_bytes(p, L) : 0;
+    const bool flex = fx_bytes && workspace && workspace_bytes >= need_bwd + gc_bytes + fx_bytes;
+    if (fused && !fast && !flex)
         for (int k = 0; k < 3; ++k) g_bytes[k] = align256((size_t)core_floats[k] * 4);
     // long streams with a kept T0: the products of Eq. 4 over tiles of positions, on the matrix cores (tt_bwd_owner.h)
     // (with a cache the list owners stay: the cached rows' sums ride along in their launches, multi-hot table 0: 113 against 140 us)
@@ -423,7 +439,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     // tiled backward only where the table has room for them (tt_group.h: L / 32 + slices + 1 entries)
     int tile_tp = bo_tp(p, L, tiled && !fwd_from_lists(p, L, cd.K, t0 != nullptr));
     if (bo_tiles(p, L, tile_tp) > L / 32 + p.m1 + p.m2 + p.m3 + cd.K + 1) tile_tp = 128 / p.n1;
-    const size_t sp_bytes = fast ? split_ws_bytes(p, L, grouped, t0 != nullptr && (!cd.K || g_bwd_tiles)) : 0;
+    const size_t sp_bytes = fast ? split_ws_bytes(p, L, grouped, t0 != nullptr && (!cd.K || g_bwd_tiles)) : (flex ? fx_bytes : 0);
     const size_t need = need_bwd + gc_bytes + g_bytes[0] + g_bytes[1] + g_bytes[2] + sp_bytes;
     const bool wants_ws = cd.K || grouped || (fused && !fast) || sp_bytes;
     if (wants_ws && (!workspace || workspace_bytes < need))
@@ -437,7 +453,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
                             (size_t)(max_slice + p.sA + p.sC + p.n1 * p.cols + p.N) * sizeof(float);
     const int G = WG / p.N > 0 ? WG / p.N : 1;
     const size_t lds_cache = sizeof(SelectLds<GEN_CH>) + (size_t)G * p.N * sizeof(float);
-    if (!fast && (rc = allow_lds(bwd_generic_kernel, lds_core))) return rc;
+    if (!fast && !flex && (rc = allow_lds(bwd_generic_kernel, lds_core))) return rc;
     if (cd.K && !grouped && (rc = allow_lds(bwd_cache_kernel, lds_cache))) return rc;
 
     float *split_ws = sp_bytes ? (float *)((char *)workspace + need - sp_bytes) : nullptr;
@@ -451,7 +467,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
             if (!(grouped && L > 0) && phase != BWD_REST)                 // the grouping pre-pass clears it itself
                 hipLaunchKernelGGL(fill_f32_kernel, dim3(cdiv(n, WG) < 1024 ? cdiv(n, WG) : 1024), dim3(WG), 0, st, grad_cache, n, 0.f);
         }
-        if (!fast) {
+        if (!fast && !flex) {
             for (int k = 0; k < 3; ++k) {
                 gtmp[k] = (float *)q;
                 q += g_bytes[k];
@@ -539,6 +555,15 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
         if (fast) {
             fast_bwd(p, cores[0], cores[1], cores[2], indices, (int)L, offsets, (int)n_bags, alpha, slot, grad_output,
                      d1, d2, d3, nullptr, nullptr, nullptr, lr, o1, o2, o3, t0, split_ws, nullptr, nullptr, 0, st);
+        } else if (flex) {
+            FlexArgs fa{p, flex_dims(p, L), cores[0], cores[1], cores[2], indices, offsets, (int)L, (int)n_bags, alpha, slot, grad_output,
+                        {}, {}, fused ? -lr : 1.f, flex_ws_layout(split_ws, p, L)};
+            for (int k = 0; k < 3; ++k) {
+                fa.src[k] = fused ? cores[k] : grad_cores[k];
+                fa.dst[k] = fused ? cores_out[k] : grad_cores[k];
+            }
+            hipError_t ef = flex_bwd(fa, st);
+            if (ef != hipSuccess) return hip_fail(ef, "backward launch");
         } else if (L > 0) {
             hipLaunchKernelGGL(bwd_generic_kernel, dim3(p.m1 + p.m2 + p.m3), dim3(WG), lds_core, st, p,
                                cores[0], cores[1], cores[2], indices, (int)L, offsets, (int)n_bags, alpha, slot,
@@ -546,7 +571,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
         }
     }
     if (fused) {
-        if (!fast)
+        if (!fast && !flex)
             for (int k = 0; k < 3; ++k)
                 hipLaunchKernelGGL(sgd_out_kernel, dim3(cdiv(core_floats[k], WG) < 2048 ? cdiv(core_floats[k], WG) : 2048),
                                    dim3(WG), 0, st, cores[k], gtmp[k], cores_out[k], core_floats[k], lr);
@@ -874,7 +899,7 @@ size_t tt_emb_bwd_sgd_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_
     Params p;
     if (check_shape(shape, &p) != TT_OK || L < 0) return 0;
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
-    size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + align256((size_t)cache_rows * p.N * 4);
+    size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L) + align256((size_t)cache_rows * p.N * 4);
     n += align256((size_t)p.m1 * p.sA * 4) + align256((size_t)p.m2 * p.sB * 4) + align256((size_t)p.m3 * p.sC * 4);
     return n;
 }
