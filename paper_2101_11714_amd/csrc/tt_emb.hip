@@ -22,6 +22,7 @@
 #include "tt_bwd_owner.h"
 #include "tt_flex.h"
 #include "tt_freq.h"
+#include "tt_topk.h"
 #include "tt_dense.h"
 #include "tt_init.h"
 #include "tt_anyd.h"
@@ -977,20 +978,16 @@ int tt_cache_build(const tt_shape_t *shape, const float *const cores[3],
     const int K = (int)out->K, n = (int)n_cand;
     SortWs ws = sort_ws_layout(workspace, n_cand);
 
-    // 1. order the candidates: most used first, ties by row id
-    hipLaunchKernelGGL(cand_keys_kernel, dim3(cdiv(n, WG)), dim3(WG), 0, st, cand_rows, cand_counts, n, ws.k0);
-    uint64_t *ks; uint32_t *vs;
-    hipError_t e = radix_sort(ws, n, 64, st, &ks, &vs);
-    if (e != hipSuccess) return hip_fail(e, "cache sort");
-    // 2. the first K become slots 0..K-1
-    hipLaunchKernelGGL(take_keys_kernel, dim3(cdiv(K, WG)), dim3(WG), 0, st, ks, K, out->keys);
-    // 3. row -> slot map
+    // 1. the most used candidates, ties by row id, become slots 0..K-1
+    hipError_t e = topk_rows(ws, cand_rows, cand_counts, n, K, shape->num_rows, out->keys, st);
+    if (e != hipSuccess) return hip_fail(e, "cache selection");
+    // 2. row -> slot map
     hipLaunchKernelGGL(fill_u64_kernel, dim3(cdiv(out->capacity, WG)), dim3(WG), 0, st, out->table,
                        out->capacity, CACHE_EMPTY);
     hipLaunchKernelGGL(cache_insert_kernel, dim3(cdiv(K, WG)), dim3(WG), 0, st, out->keys, K, out->table,
                        (uint32_t)(out->capacity - 1));
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "cache build launch");
-    // 4. lines initialised from the cores: one bag per cached row, no cache consulted
+    // 3. lines initialised from the cores: one bag per cached row, no cache consulted
     return tt_emb_fwd(shape, cores, out->keys, K, nullptr, K, nullptr, nullptr, out->rows, nullptr, 0, stream);
 }
 
@@ -1027,23 +1024,17 @@ int tt_cache_refill(const tt_shape_t *shape, const float *const cores[3],
     float *new_rows = (float *)((char *)new_keys + align256((size_t)K * 8));
 
     // 1. the K most used candidates, most used first, ties by row id
-    hipLaunchKernelGGL(cand_keys_kernel, dim3(cdiv(n, WG)), dim3(WG), 0, st, cand_rows, cand_counts, n, ws.k0);
-    uint64_t *ks; uint32_t *vs;
-    hipError_t e = radix_sort(ws, n, 64, st, &ks, &vs);
-    if (e != hipSuccess) return hip_fail(e, "cache sort");
-    hipLaunchKernelGGL(take_keys_kernel, dim3(cdiv(K, WG)), dim3(WG), 0, st, ks, K, new_keys);
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "cache refill launch");
+    hipError_t e = topk_rows(ws, cand_rows, cand_counts, n, K, shape->num_rows, new_keys, st);
+    if (e != hipSuccess) return hip_fail(e, "cache selection");
     // 2. their lines: a forward pass of one bag per row THROUGH THE OLD CACHE, so a row that stays
     //    cached keeps its line and a row that enters is rebuilt from the cores
     rc = tt_emb_fwd(shape, cores, new_keys, K, nullptr, K, nullptr, cache, new_rows, nullptr, 0, stream);
     if (rc) return rc;
     // 3. the new set replaces the old one
     const int64_t nr = (int64_t)K * p.N;
-    hipLaunchKernelGGL(copy_i64_kernel, dim3(cdiv(K, WG)), dim3(WG), 0, st, new_keys, cache->keys, (int64_t)K);
-    hipLaunchKernelGGL(copy_f32_kernel, dim3(cdiv(nr, WG) < 2048 ? cdiv(nr, WG) : 2048), dim3(WG), 0, st, new_rows,
-                       cache->rows, nr);
-    hipLaunchKernelGGL(fill_u64_kernel, dim3(cdiv(cache->capacity, WG)), dim3(WG), 0, st, cache->table,
-                       cache->capacity, CACHE_EMPTY);
+    const int64_t n4 = nr / 4 > cache->capacity ? nr / 4 : cache->capacity;
+    hipLaunchKernelGGL(cache_replace_kernel, dim3(cdiv(n4, WG) < 2048 ? cdiv(n4, WG) : 2048), dim3(WG), 0, st, new_keys, cache->keys, K,
+                       new_rows, cache->rows, nr, cache->table, cache->capacity);
     hipLaunchKernelGGL(cache_insert_kernel, dim3(cdiv(K, WG)), dim3(WG), 0, st, cache->keys, K, cache->table,
                        (uint32_t)(cache->capacity - 1));
     e = hipGetLastError();
@@ -1097,7 +1088,7 @@ int tt_freq_export(const tt_freq_t *tracker, int64_t *rows, int64_t *counts, int
     if (!rows || !counts || !n_out) return fail(TT_ERR_NULL, "NULL array");
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(freq_zero_kernel, dim3(1), dim3(64), 0, st, (unsigned long long *)n_out);
-    hipLaunchKernelGGL(freq_export_kernel, dim3(cdiv(tracker->capacity, WG)), dim3(WG), 0, st, f, rows, counts,
+    hipLaunchKernelGGL(freq_export_kernel, dim3(cdiv(tracker->capacity, FQ_EXPORT)), dim3(WG), 0, st, f, rows, counts,
                        (unsigned long long *)n_out);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? TT_OK : hip_fail(e, "tracker export launch");

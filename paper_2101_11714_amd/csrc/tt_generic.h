@@ -427,21 +427,4 @@ __global__ __launch_bounds__(WG) void copy_perm_kernel(const uint32_t *__restric
     if (i < n) perm[i] = (int32_t)v[i];
 }
 
-// Candidate (row, count) -> sort key: most used first, then lower row id (Section 4.2, ties by row).
-__global__ __launch_bounds__(WG) void cand_keys_kernel(const int64_t *__restrict__ rows, const int64_t *__restrict__ counts,
-                                                       int n, uint64_t *__restrict__ keys)
-{
-    const int i = blockIdx.x * WG + threadIdx.x;
-    if (i >= n) return;
-    const uint64_t c = (uint64_t)counts[i];
-    const uint32_t inv = 0xFFFFFFFFu - (uint32_t)(c > 0xFFFFFFFFull ? 0xFFFFFFFFull : c);
-    keys[i] = ((uint64_t)inv << 32) | (uint32_t)rows[i];
-}
-
-__global__ __launch_bounds__(WG) void take_keys_kernel(const uint64_t *__restrict__ sorted, int K, int64_t *__restrict__ keys)
-{
-    const int s = blockIdx.x * WG + threadIdx.x;
-    if (s < K) keys[s] = (int64_t)(uint32_t)sorted[s];
-}
-
 }  // namespace tt
