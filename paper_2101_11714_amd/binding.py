@@ -1,15 +1,18 @@
-"""Thin ctypes binding of the C-ABI library declared in include/tt_emb.h.
+"""Thin binding of the C-ABI library declared in include/tt_emb.h.
 
 Argument marshalling only: every step of the path runs in the HIP kernels of
 ``libtt_emb.so``.  PyTorch supplies device memory (tensors) and the current HIP
-stream; nothing here computes.  There is no CPU fallback: if the library has not
-been built (``python -c "import __graft_entry__ as g; g.build()"``) loading
-raises.
+stream; nothing here computes.  The calls of a training or serving step are
+marshalled by a compiled extension (``_tt_call.so``, csrc/tt_python.cpp), the
+queries and the rarer calls by ctypes.  There is no CPU fallback: if the libraries
+have not been built (``python -c "import __graft_entry__ as g; g.build()"``)
+loading raises.
 """
 
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import List, Optional, Sequence
 
@@ -17,6 +20,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtt_emb.so")
+CALL_PATH = os.path.join(_HERE, "_tt_call.so")
 
 TT_OK = 0
 ERR_NAMES = {0: "TT_OK", -1: "TT_ERR_NULL", -2: "TT_ERR_BAD_SHAPE", -3: "TT_ERR_BAD_ARG",
@@ -119,6 +123,24 @@ def lib():
     return _lib
 
 
+class _Call:
+    """The functions of the compiled extension, which is loaded when the first of them is asked for."""
+
+    def __getattr__(self, name):
+        if not os.path.exists(LIB_PATH) or not os.path.exists(CALL_PATH):
+            raise RuntimeError("%s or %s is missing: run __graft_entry__.build() first" % (LIB_PATH, CALL_PATH))
+        spec = importlib.util.spec_from_file_location("_tt_call", CALL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        for k, v in vars(module).items():
+            if not k.startswith("__"):
+                setattr(self, k, v)
+        return getattr(module, name)
+
+
+_call = _Call()
+
+
 def _check(rc: int):
     if rc != TT_OK:
         raise TTError(rc, lib().tt_last_error().decode())
@@ -192,17 +214,9 @@ def tt_emb_fwd(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Ten
                offsets: Optional[torch.Tensor], n_bags: int, output: torch.Tensor,
                alpha: Optional[torch.Tensor] = None, cache: Optional[Cache] = None,
                workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(output, torch.float32)
-    assert output.numel() == n_bags * shape.n[0] * shape.n[1] * shape.n[2]
-    wsb = workspace.numel() if workspace is not None else 0
-    _check(lib().tt_emb_fwd(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets), n_bags,
-                            _ptr(alpha), cache.ref() if cache else None, _ptr(output), _ptr(workspace), wsb, _stream()))
+    rc = _call.emb_fwd(shape, cores, indices, offsets, n_bags, output, alpha, cache, workspace)
+    if rc:
+        _check(rc)
     return output
 
 
@@ -233,17 +247,9 @@ def t0_floats(shape: TTShape) -> int:
 def tt_emb_fwd_keep_t0(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Tensor,
                        offsets: Optional[torch.Tensor], n_bags: int, output: torch.Tensor, t0: torch.Tensor,
                        alpha: Optional[torch.Tensor] = None, cache: Optional[Cache] = None) -> torch.Tensor:
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(output, torch.float32)
-    _dev(t0, torch.float32)
-    assert t0.numel() >= indices.numel() * t0_floats(shape)
-    _check(lib().tt_emb_fwd_keep_t0(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets),
-                                    n_bags, _ptr(alpha), cache.ref() if cache else None, _ptr(output), _ptr(t0), _stream()))
+    rc = _call.emb_fwd_keep_t0(shape, cores, indices, offsets, n_bags, output, t0, alpha, cache)
+    if rc:
+        _check(rc)
     return output
 
 
@@ -256,21 +262,9 @@ def tt_emb_fwd_prepared(shape: TTShape, cores: Sequence[torch.Tensor], indices: 
                         t0: Optional[torch.Tensor] = None, alpha: Optional[torch.Tensor] = None,
                         cache: Optional[Cache] = None) -> torch.Tensor:
     """The forward pass after tt_emb_bwd_prepare into the same workspace (t0: keep the intermediate there)."""
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(output, torch.float32)
-    _dev(workspace, torch.uint8)
-    if t0 is not None:
-        _dev(t0, torch.float32)
-        assert t0.numel() >= indices.numel() * t0_floats(shape)
-    assert output.numel() == n_bags * shape.n[0] * shape.n[1] * shape.n[2]
-    _check(lib().tt_emb_fwd_prepared(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets),
-                                     n_bags, _ptr(alpha), cache.ref() if cache else None, _ptr(output), _ptr(t0),
-                                     _ptr(workspace), workspace.numel(), _stream()))
+    rc = _call.emb_fwd_prepared(shape, cores, indices, offsets, n_bags, output, workspace, t0, alpha, cache)
+    if rc:
+        _check(rc)
     return output
 
 
@@ -279,27 +273,9 @@ def tt_emb_bwd(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Ten
                grad_cores: Sequence[torch.Tensor], alpha: Optional[torch.Tensor] = None,
                cache: Optional[Cache] = None, grad_cache: Optional[torch.Tensor] = None,
                workspace: Optional[torch.Tensor] = None, t0: Optional[torch.Tensor] = None) -> None:
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(grad_output, torch.float32)
-    for k in range(3):
-        assert grad_cores[k].numel() == cores[k].numel()
-    if grad_cache is not None:
-        _dev(grad_cache, torch.float32)
-    wsb = workspace.numel() if workspace is not None else 0
-    if t0 is not None:
-        _dev(t0, torch.float32)
-        _check(lib().tt_emb_bwd_t0(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets),
-                                   n_bags, _ptr(alpha), cache.ref() if cache else None, _ptr(grad_output), _ptr(t0),
-                                   _ptr_array(grad_cores), _ptr(grad_cache), _ptr(workspace), wsb, _stream()))
-        return
-    _check(lib().tt_emb_bwd(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets), n_bags,
-                            _ptr(alpha), cache.ref() if cache else None, _ptr(grad_output), _ptr_array(grad_cores),
-                            _ptr(grad_cache), _ptr(workspace), wsb, _stream()))
+    rc = _call.emb_bwd(shape, cores, indices, offsets, n_bags, grad_output, grad_cores, alpha, cache, grad_cache, workspace, t0)
+    if rc:
+        _check(rc)
 
 
 def bwd_has_prepass(shape: TTShape, L: int, cache_rows: int = 0, kept_t0: bool = False) -> bool:
@@ -314,10 +290,9 @@ def tt_emb_bwd_prepare(shape: TTShape, indices: torch.Tensor, offsets: Optional[
                        cache: Optional[Cache] = None, workspace: Optional[torch.Tensor] = None,
                        kept_t0: bool = False) -> None:
     """The index-only part of the fused step, on the current stream; tt_emb_bwd_sgd(..., prepared=True) does the rest."""
-    _dev(indices, torch.int64)
-    wsb = workspace.numel() if workspace is not None else 0
-    _check(lib().tt_emb_bwd_prepare(C.byref(shape), _ptr(indices), indices.numel(), _ptr(offsets), n_bags,
-                                    cache.ref() if cache else None, int(kept_t0), _ptr(workspace), wsb, _stream()))
+    rc = _call.emb_bwd_prepare(shape, indices, offsets, n_bags, cache, workspace, kept_t0)
+    if rc:
+        _check(rc)
 
 
 def kept_bytes(shape: TTShape, L: int) -> int:
@@ -328,41 +303,18 @@ def kept_has_lists(shape: TTShape, L: int) -> bool:
     return bool(lib().tt_emb_kept_has_lists(C.byref(shape), int(L)))
 
 
-class TTNextBatch(C.Structure):
-    _fields_ = [("indices", C.c_void_p), ("L", C.c_int64), ("kept", C.c_void_p), ("kept_bytes", C.c_size_t)]
-
-
-def _next(next_batch):
-    """next_batch: None or (indices, kept) of the batch whose lists the call files as well."""
-    if next_batch is None:
-        return None
-    indices, kept = next_batch
-    _dev(indices, torch.int64)
-    _dev(kept, torch.uint8)
-    return C.byref(TTNextBatch(indices.data_ptr(), indices.numel(), kept.data_ptr(), kept.numel()))
-
-
 def tt_emb_kept_prepare(shape: TTShape, indices: torch.Tensor, kept: torch.Tensor, cache: Optional["Cache"] = None) -> None:
-    _dev(indices, torch.int64)
-    _dev(kept, torch.uint8)
-    _check(lib().tt_emb_kept_prepare(C.byref(shape), _ptr(indices), indices.numel(), cache.ref() if cache else None,
-                                     _ptr(kept), kept.numel(), _stream()))
+    rc = _call.emb_kept_prepare(shape, indices, kept, cache)
+    if rc:
+        _check(rc)
 
 
 def tt_emb_fwd_keep(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Tensor, offsets: Optional[torch.Tensor],
                     n_bags: int, output: torch.Tensor, kept: torch.Tensor, alpha: Optional[torch.Tensor] = None,
                     cache: Optional["Cache"] = None, lists_ready: bool = False) -> None:
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(output, torch.float32)
-    _dev(kept, torch.uint8)
-    _check(lib().tt_emb_fwd_keep(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets), n_bags,
-                                 _ptr(alpha), cache.ref() if cache else None, _ptr(output), _ptr(kept), kept.numel(),
-                                 1 if lists_ready else 0, _stream()))
+    rc = _call.emb_fwd_keep(shape, cores, indices, offsets, n_bags, output, kept, alpha, cache, lists_ready)
+    if rc:
+        _check(rc)
 
 
 def tt_emb_bwd_kept(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Tensor, offsets: Optional[torch.Tensor],
@@ -370,29 +322,20 @@ def tt_emb_bwd_kept(shape: TTShape, cores: Sequence[torch.Tensor], indices: torc
                     alpha: Optional[torch.Tensor] = None, cache: Optional["Cache"] = None,
                     grad_cache: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                     next_batch=None) -> None:
-    _dev(indices, torch.int64)
-    _dev(grad_output, torch.float32)
-    _dev(kept, torch.uint8)
-    wsb = workspace.numel() if workspace is not None else 0
-    _check(lib().tt_emb_bwd_kept(C.byref(shape), _ptr_array(cores), _ptr(indices), indices.numel(), _ptr(offsets), n_bags,
-                                 _ptr(alpha), cache.ref() if cache else None, _ptr(grad_output), _ptr(kept), kept.numel(),
-                                 _ptr_array(grad_cores), _ptr(grad_cache), _next(next_batch), _ptr(workspace), wsb, _stream()))
+    rc = _call.emb_bwd_kept(shape, cores, indices, offsets, n_bags, grad_output, kept, grad_cores, alpha, cache, grad_cache,
+                            workspace, next_batch)
+    if rc:
+        _check(rc)
 
 
 def tt_emb_bwd_sgd_kept(shape: TTShape, cores: Sequence[torch.Tensor], cores_out: Sequence[torch.Tensor],
                         indices: torch.Tensor, offsets: Optional[torch.Tensor], n_bags: int, grad_output: torch.Tensor,
                         kept: torch.Tensor, lr: float, alpha: Optional[torch.Tensor] = None, cache: Optional["Cache"] = None,
                         workspace: Optional[torch.Tensor] = None, next_batch=None) -> None:
-    _dev(indices, torch.int64)
-    _dev(grad_output, torch.float32)
-    _dev(kept, torch.uint8)
-    for k in range(3):
-        assert cores_out[k].numel() == cores[k].numel()
-    wsb = workspace.numel() if workspace is not None else 0
-    _check(lib().tt_emb_bwd_sgd_kept(C.byref(shape), _ptr_array(cores), _ptr_array(cores_out), _ptr(indices), indices.numel(),
-                                     _ptr(offsets), n_bags, _ptr(alpha), cache.ref() if cache else None, _ptr(grad_output),
-                                     _ptr(kept), kept.numel(), C.c_float(lr), _next(next_batch), _ptr(workspace), wsb,
-                                     _stream()))
+    rc = _call.emb_bwd_sgd_kept(shape, cores, cores_out, indices, offsets, n_bags, grad_output, kept, lr, alpha, cache, workspace,
+                                next_batch)
+    if rc:
+        _check(rc)
 
 
 def tt_emb_debug_kept_lists(shape: TTShape, kept: torch.Tensor, L: int):
@@ -407,18 +350,9 @@ def tt_emb_bwd_sgd_static(shape: TTShape, cores: Sequence[torch.Tensor], cores_o
                           indices: torch.Tensor, offsets: Optional[torch.Tensor], n_bags: int, grad_output: torch.Tensor,
                           lr: float, alpha: Optional[torch.Tensor] = None, cache: Optional[Cache] = None) -> None:
     """tt_emb_bwd_sgd with the library's own static scratch array instead of a workspace (allocates nothing)."""
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(grad_output, torch.float32)
-    for k in range(3):
-        assert cores_out[k].numel() == cores[k].numel()
-    _check(lib().tt_emb_bwd_sgd_static(C.byref(shape), _ptr_array(cores), _ptr_array(cores_out), _ptr(indices),
-                                       indices.numel(), _ptr(offsets), n_bags, _ptr(alpha),
-                                       cache.ref() if cache else None, _ptr(grad_output), C.c_float(lr), _stream()))
+    rc = _call.emb_bwd_sgd_static(shape, cores, cores_out, indices, offsets, n_bags, grad_output, lr, alpha, cache)
+    if rc:
+        _check(rc)
 
 
 def static_scratch_bytes() -> int:
@@ -430,53 +364,26 @@ def tt_emb_bwd_sgd(shape: TTShape, cores: Sequence[torch.Tensor], cores_out: Seq
                    lr: float, alpha: Optional[torch.Tensor] = None, cache: Optional[Cache] = None,
                    workspace: Optional[torch.Tensor] = None, t0: Optional[torch.Tensor] = None,
                    prepared: bool = False) -> None:
-    _dev(indices, torch.int64)
-    if offsets is not None:
-        _dev(offsets, torch.int64)
-        assert offsets.numel() == n_bags + 1
-    if alpha is not None:
-        _dev(alpha, torch.float32)
-    _dev(grad_output, torch.float32)
-    for k in range(3):
-        assert cores_out[k].numel() == cores[k].numel()
-    wsb = workspace.numel() if workspace is not None else 0
-    if prepared:
-        if t0 is not None:
-            _dev(t0, torch.float32)
-        _check(lib().tt_emb_bwd_sgd_prepared(C.byref(shape), _ptr_array(cores), _ptr_array(cores_out), _ptr(indices),
-                                             indices.numel(), _ptr(offsets), n_bags, _ptr(alpha),
-                                             cache.ref() if cache else None, _ptr(grad_output), _ptr(t0), C.c_float(lr),
-                                             _ptr(workspace), wsb, _stream()))
-        return
-    if t0 is not None:
-        _dev(t0, torch.float32)
-        _check(lib().tt_emb_bwd_sgd_t0(C.byref(shape), _ptr_array(cores), _ptr_array(cores_out), _ptr(indices),
-                                       indices.numel(), _ptr(offsets), n_bags, _ptr(alpha),
-                                       cache.ref() if cache else None, _ptr(grad_output), _ptr(t0), C.c_float(lr),
-                                       _ptr(workspace), wsb, _stream()))
-        return
-    _check(lib().tt_emb_bwd_sgd(C.byref(shape), _ptr_array(cores), _ptr_array(cores_out), _ptr(indices), indices.numel(),
-                                _ptr(offsets), n_bags, _ptr(alpha), cache.ref() if cache else None, _ptr(grad_output),
-                                C.c_float(lr), _ptr(workspace), wsb, _stream()))
+    rc = _call.emb_bwd_sgd(shape, cores, cores_out, indices, offsets, n_bags, grad_output, lr, alpha, cache, workspace, t0, prepared)
+    if rc:
+        _check(rc)
 
 
 def tt_emb_sgd_update(shape: TTShape, cores: Sequence[torch.Tensor], grad_cores: Sequence[torch.Tensor], lr: float,
                       cache: Optional[Cache] = None, grad_cache: Optional[torch.Tensor] = None,
                       zero_grad: bool = False) -> None:
-    _check(lib().tt_emb_sgd_update(C.byref(shape), _ptr_array(cores), _ptr_array(grad_cores), C.c_float(lr),
-                                   cache.ref() if cache else None, _ptr(grad_cache), int(zero_grad), _stream()))
+    rc = _call.emb_sgd_update(shape, cores, grad_cores, lr, cache, grad_cache, zero_grad)
+    if rc:
+        _check(rc)
 
 
 def tt_cache_build(shape: TTShape, cores: Sequence[torch.Tensor], cand_rows: torch.Tensor,
                    cand_counts: torch.Tensor, cache: Cache, workspace: Optional[torch.Tensor] = None) -> Cache:
-    _dev(cand_rows, torch.int64)
-    _dev(cand_counts, torch.int64)
-    n = cand_rows.numel()
-    assert cand_counts.numel() == n
     if workspace is None:
-        workspace = _ws(lib().tt_cache_build_workspace_bytes(C.byref(shape), n, cache.K), cand_rows.device)
-    _check(lib().tt_cache_build(C.byref(shape), _ptr_array(cores), _ptr(cand_rows), _ptr(cand_counts), n, cache.ref(),
-                                _ptr(workspace), workspace.numel(), _stream()))
+        workspace = _ws(lib().tt_cache_build_workspace_bytes(C.byref(shape), cand_rows.numel(), cache.K), cand_rows.device)
+    rc = _call.cache_build(shape, cores, cand_rows, cand_counts, cache, workspace)
+    if rc:
+        _check(rc)
     return cache
 
 
@@ -516,16 +423,15 @@ def tt_freq_reset(freq: Freq) -> None:
 
 
 def tt_freq_update(freq: Freq, indices: torch.Tensor) -> None:
-    _dev(indices, torch.int64)
-    _check(lib().tt_freq_update(freq.ref(), _ptr(indices), indices.numel(), _stream()))
+    rc = _call.freq_update(freq, indices)
+    if rc:
+        _check(rc)
 
 
 def tt_freq_export(freq: Freq, rows: torch.Tensor, counts: torch.Tensor, n_out: torch.Tensor) -> None:
-    _dev(rows, torch.int64)
-    _dev(counts, torch.int64)
-    _dev(n_out, torch.int64)
-    assert rows.numel() >= freq.capacity and counts.numel() >= freq.capacity
-    _check(lib().tt_freq_export(freq.ref(), _ptr(rows), _ptr(counts), _ptr(n_out), _stream()))
+    rc = _call.freq_export(freq, rows, counts, n_out)
+    if rc:
+        _check(rc)
 
 
 def tt_cache_lookup(cache: Cache, indices: torch.Tensor, slot: torch.Tensor) -> torch.Tensor:
