@@ -20,6 +20,7 @@
 #include "tt_group.h"
 #include "tt_fwd_owner.h"
 #include "tt_bwd_owner.h"
+#include "tt_rows_pass.h"
 #include "tt_flex.h"
 #include "tt_freq.h"
 #include "tt_topk.h"
@@ -240,13 +241,20 @@ int64_t tt_cache_table_capacity(int64_t K)
     return cap;
 }
 
+// What a step over distinct rows (tt_rows.h) needs of the workspace, 0 where the shape has none.
+static size_t rows_ws_bytes(const Params &p, int64_t L, int64_t K)
+{
+    return !K && rw_supported(p) ? 256 + rw_ws_layout(nullptr, p, L, rw_tile_wgs(p, L)).bytes : 0;
+}
+static size_t larger(size_t a, size_t b) { return a > b ? a : b; }
+
 size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows)
 {
     (void)n_bags;
     Params p;
     if (check_shape(shape, &p) != TT_OK || L < 0) return 0;
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
-    return fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L);
+    return larger(fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L), rows_ws_bytes(p, L, cache_rows));
 }
 
 size_t tt_emb_dedup_workspace_bytes(int64_t L)
@@ -330,9 +338,16 @@ static bool bwd_groups(const Params &p, int64_t L, int64_t K, bool kept_t0)
     return fast && (g_fast_path == 2 || L >= group_min_l(p, K, kept_t0, false));
 }
 
+// Does a step whose positions are grouped work on its distinct rows (tt_rows.h)?
+static bool works_on_rows(const Params &p, int64_t L, int64_t K, bool kept_t0)
+{
+    return L > 0 && kept_t0 && !K && rw_supported(p) && bwd_tiles_wanted(p, L);
+}
+
 // does tt_emb_fwd_prepared work from the pre-pass's lists for such a call?
 static bool fwd_from_lists(const Params &p, int64_t L, int64_t K, bool kept_t0)
 {
+    if (works_on_rows(p, L, K, kept_t0)) return g_fast_path == 2 || L >= GROUP_MIN_L;
     // (only for the long streams: at 8,192 positions, where the (4,4,4) backward already groups, the wave per bag is ahead: 31 against 36 us)
     return L > 0 && fwd_lists_pay(p, K) && bwd_groups(p, L, K, kept_t0) && (g_fast_path == 2 || L >= (K ? GROUP_MIN_L_CACHE : GROUP_MIN_L)) &&
            3 * L < (1ll << 31);
@@ -362,11 +377,17 @@ int tt_emb_fwd_prepared(const tt_shape_t *shape, const float *const cores[3],
         return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, cache, output, t0, t0 != nullptr, stream);
     if (!cores || !cores[0] || !cores[1] || !cores[2]) return fail(TT_ERR_NULL, "cores is NULL");
     if (!output) return fail(TT_ERR_NULL, "output is NULL");
-    const size_t need = fwd_bwd_ws_bytes(p, L, cd.K);
+    const bool rows = works_on_rows(p, L, cd.K, t0 != nullptr);
+    const size_t need = rows ? rows_ws_bytes(p, L, cd.K) : fwd_bwd_ws_bytes(p, L, cd.K);
     if (!workspace || workspace_bytes < need)
         return fail(TT_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
     if (misaligned({cores[0], cores[1], cores[2], output, t0, cd.rows, workspace}))
         return fail(TT_ERR_BAD_ARG, "cores, output, t0, cache rows and workspace must be 16-byte aligned");
+    if (rows) {
+        hipError_t e = rw_fwd(p, cores[0], cores[1], cores[2], L, offsets, (int)n_bags, alpha, output, t0,
+                              rw_ws_layout(workspace, p, L, rw_tile_wgs(p, L)), (hipStream_t)stream);
+        return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
+    }
     const int nbins = p.m1 + p.m2 + p.m3 + cd.K;
     GroupWs g = group_ws_layout((char *)workspace + slot_ws_bytes(L, cd.K != 0), L, nbins, p.N, fwd_rows_n(p, cd.K));
     int bits = 1;
@@ -378,6 +399,14 @@ int tt_emb_fwd_prepared(const tt_shape_t *shape, const float *const cores[3],
     hipError_t e = fwd_owner(p, cores[0], cores[1], cores[2], indices, L, offsets, (int)n_bags, alpha, cd, vs, have_info ? g.info : nullptr, g.tiles,
                              g.rows, output, t0, (hipStream_t)stream);
     return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
+}
+
+// a guess for the bag of a position, which the kernels check: all bags have one length
+static void guess_bag_length(Params *p, const int64_t *offsets, int64_t L, int64_t n_bags)
+{
+    if (!offsets || n_bags <= 0 || L <= 0 || L % n_bags) return;
+    p->bagP = (uint32_t)(L / n_bags);
+    p->mgP = p->bagP > 1 ? (uint32_t)(((1ull << 32) + p->bagP - 1) / (uint64_t)p->bagP) : 0u;
 }
 
 enum BwdPhase { BWD_ALL, BWD_PREPARE, BWD_REST };
@@ -436,6 +465,21 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     // long streams with a kept T0: the products of Eq. 4 over tiles of positions, on the matrix cores (tt_bwd_owner.h)
     // (with a cache the list owners stay: the cached rows' sums ride along in their launches, multi-hot table 0: 113 against 140 us)
     const bool tiled = grouped && t0 && (!cd.K || g_bwd_tiles) && bwd_tiles_wanted(p, L);
+    if (tiled && works_on_rows(p, L, cd.K, t0 != nullptr)) {
+        const size_t need = rows_ws_bytes(p, L, cd.K);
+        if (!workspace || workspace_bytes < need)
+            return fail(TT_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+        guess_bag_length(&p, offsets, L, n_bags);
+        const RowsWs ws = rw_ws_layout(workspace, p, L, rw_tile_wgs(p, L));
+        hipError_t e = hipSuccess;
+        if (phase != BWD_REST) e = rw_prepare(p, indices, (int)L, offsets, (int)n_bags, rw_tp(p, L), ws, (hipStream_t)stream);
+        if (!prep && e == hipSuccess) {
+            const float *const src[3] = {fused ? cores[0] : grad_cores[0], fused ? cores[1] : grad_cores[1], fused ? cores[2] : grad_cores[2]};
+            e = rw_bwd(p, cores[0], cores[1], cores[2], L, alpha, grad_output, t0, src, fused ? cores_out : grad_cores, fused ? -lr : 1.f, ws,
+                       (hipStream_t)stream);
+        }
+        return e == hipSuccess ? TT_OK : hip_fail(e, "backward launch");
+    }
     // positions per tile of the tile table: 128 / n1 where the forward pass works from it too; the smaller tiles of the
     // tiled backward only where the table has room for them (tt_group.h: L / 32 + slices + 1 entries)
     int tile_tp = bo_tp(p, L, tiled && !fwd_from_lists(p, L, cd.K, t0 != nullptr));
@@ -484,10 +528,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     float *d1 = grad_cores ? grad_cores[0] : nullptr, *d2 = grad_cores ? grad_cores[1] : nullptr,
           *d3 = grad_cores ? grad_cores[2] : nullptr;
 
-    if (offsets && n_bags > 0 && L > 0 && L % n_bags == 0) {              // a guess for the bag of a position
-        p.bagP = (uint32_t)(L / n_bags);
-        p.mgP = p.bagP > 1 ? (uint32_t)(((1ull << 32) + p.bagP - 1) / (uint64_t)p.bagP) : 0u;
-    }
+    guess_bag_length(&p, offsets, L, n_bags);
     bool cache_merged = false;
     int32_t *slot = nullptr;
     if (cd.K && L > 0 && !grouped) {                                      // the grouping pre-pass probes the cache itself
@@ -801,10 +842,7 @@ static int bwd_kept_common(const tt_shape_t *shape, const float *const cores[3],
         (fused ? misaligned({cores_out[0], cores_out[1], cores_out[2]})
                : misaligned({grad_cores[0], grad_cores[1], grad_cores[2]})))
         return fail(TT_ERR_BAD_ARG, "cores, gradients and kept buffer must be 16-byte aligned");
-    if (offsets && n_bags > 0 && L % n_bags == 0) {                         // a guess for the bag of a position
-        p.bagP = (uint32_t)(L / n_bags);
-        p.mgP = p.bagP > 1 ? (uint32_t)(((1ull << 32) + p.bagP - 1) / (uint64_t)p.bagP) : 0u;
-    }
+    guess_bag_length(&p, offsets, L, n_bags);
     const KeptDev kd = kept_dev(const_cast<void *>(kept), kept_layout(p, L));
     kept_bwd(p, cores[0], cores[1], cores[2], (int)L, offsets, (int)n_bags, alpha, grad_output,
              fused ? nullptr : grad_cores[0], fused ? nullptr : grad_cores[1], fused ? nullptr : grad_cores[2], lr,
@@ -902,7 +940,7 @@ size_t tt_emb_bwd_sgd_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
     size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L) + align256((size_t)cache_rows * p.N * 4);
     n += align256((size_t)p.m1 * p.sA * 4) + align256((size_t)p.m2 * p.sB * 4) + align256((size_t)p.m3 * p.sC * 4);
-    return n;
+    return larger(n, rows_ws_bytes(p, L, cache_rows));
 }
 
 int tt_emb_sgd_update(const tt_shape_t *shape, float *const cores[3], float *const grad_cores[3],

@@ -1,0 +1,633 @@
+// Long index streams with a kept T0: grouping by distinct row, and what works from it.
+//
+// The positions of a long stream repeat: of 204,800 Zipf-distributed lookups of the Kaggle-shaped table 70,000 are
+// distinct, of 8,192 of the Terabyte-shaped one 3,600.  Both passes are linear per row, so the products of Eq. 3 and Eq. 4
+// are needed once per distinct row: the forward pass computes a row once and hands it to its positions, the backward pass
+// adds up the upstream gradients of a row's positions first.  (Working position by position, the three product kernels
+// of that step took 118, 164 and 115 us.)
+//
+// Pre-pass (index only, five launches; the host never learns how many rows there are):
+//   rw_count / rw_scatter   positions grouped by their second digit: one stable counting pass over m2 bins
+//   rw_group                a slice's positions in windows of up to RW_WIN: equal rows of a window are found in an LDS hash
+//                           table and numbered in the order of their first positions; the window's positions are put in
+//                           the order of those numbers.  A row in two windows counts as two: the passes are linear.
+//   rw_scan, rw_lists       the distinct rows grouped by first and by third digit (counts per window, column sums, places),
+//                           and the table of tiles: up to TP distinct rows of one slice of the second core
+// A distinct row is known by its index u = (first place of its window) + (number); places of a window past its distinct
+// rows stay unused, so that no count has to travel to the host.
+// Everything is stable, so every sum below has a fixed order and results repeat bit for bit.
+#pragma once
+
+#include "tt_common.h"
+#include "tt_fast.h"
+#include "tt_fast_bwd.h"
+#include "tt_sort.h"
+
+namespace tt {
+
+constexpr int RW_WIN = 2048;                     // positions of a window, at most (see rw_win)
+constexpr int RW_T = 512, RW_NW = RW_T / WAVE;   // threads / waves of the window kernels
+constexpr int RW_TILE = 2048;                    // positions per workgroup of the counting pass
+constexpr int RW_HASH = 4096;
+constexpr int RW_MAX_M2 = 1024;                  // bins of the counting pass
+constexpr int RW_MAX_M13 = 4096;                 // slices of the first and third core together
+constexpr int RW_OFF = 1024;                     // samples of the offsets array kept in LDS
+constexpr int RW_PIECE = 512;                    // distinct rows per workgroup of the final sums
+
+struct RowsWs {
+    uint32_t *hist;      // [tiles][m2 rounded up to 4]
+    uint32_t *lk, *lrow; // [L] positions and their rows grouped by second digit
+    int *goff;           // [m2 + 1] bounds of those groups
+    int *inv;            // [L] position -> u
+    int2 *gkb;           // [L] {position, bag}: the positions of a row are neighbours
+    int *gu;             // [L] u of the same places
+    int4 *rec;           // [L] by u: {first digit, third digit, first place in gkb, positions} (positions = 0: unused)
+    int *wd, *wfirst, *wslice;   // [windows] distinct rows, first place, slice
+    uint32_t *hist2;     // [windows][m1 + m3] distinct rows per slice, then those of earlier windows
+    uint32_t *tot2;      // [m1 + m3]
+    int *off13;          // [m1 + m3 + 1] bounds of the slices in l13
+    int2 *l13;           // [2 L] {u, its first position}, by first digit, then by third digit
+    int4 *tiles;         // {slice of the second core, first u, rows, 0}
+    int *tile_base;      // [m2 + 1] first tile of every slice
+    int *nwin;           // [1] windows in use
+    uint32_t *arrived;   // [m1 + m3] workgroups of the final sums that have left a partial sum
+    float *rows;         // [L][N] by u: rows of the forward pass
+    float *dym;          // [L][N] by u: summed upstream gradients
+    float *pbuf;         // [L][sA] by u: G1 gradients
+    float *part2;        // [m2 + workgroups of the tile kernel][sB] parts of the second core's gradients
+    float *part13;       // [pieces][row] partial sums of slices with more than RW_PIECE rows
+    size_t bytes;
+};
+
+static inline bool rw_supported(const Params &p)
+{
+    const int cfg = fast_config(p);
+    return cfg >= 2 && cfg <= 5 && p.m2 <= RW_MAX_M2 && p.m1 + p.m3 <= RW_MAX_M13;
+}
+
+// Positions per window.  Longer windows merge more; shorter ones cut a hot row's positions into pieces that different
+// workgroups handle, which is what short streams need (8,192 positions, a hot row of 740: one workgroup added these up
+// for 13 us).
+static inline int rw_win(int64_t L) { return L < 65536 ? 256 : RW_WIN; }
+static inline int rw_windows(const Params &p, int64_t L) { return (int)(L / rw_win(L)) + p.m2; }
+static inline int rw_tiles(const Params &p, int64_t L, int tp) { return (int)(L / tp) + rw_windows(p, L); }
+static inline int rw_pieces(const Params &p, int64_t L) { return (int)(2 * (L / RW_PIECE)) + p.m1 + p.m3; }
+static inline int rw_hist_blocks(int64_t L) { return (int)((L + RW_TILE - 1) / RW_TILE); }
+
+// tile_wgs: workgroups of the tile kernel
+static inline RowsWs rw_ws_layout(void *ws, const Params &p, int64_t L, int tile_wgs)
+{
+    RowsWs w;
+    char *base = (char *)ws;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { char *q = base ? base + off : nullptr; off += align256(bytes); return q; };
+    const size_t n = L > 0 ? (size_t)L : 1, nw = (size_t)rw_windows(p, L), m13 = (size_t)p.m1 + p.m3;
+    w.hist = (uint32_t *)take((size_t)rw_hist_blocks((int64_t)n) * ((p.m2 + 3) & ~3) * 4);
+    w.lk = (uint32_t *)take(n * 4);
+    w.lrow = (uint32_t *)take(n * 4);
+    w.goff = (int *)take(((size_t)p.m2 + 1) * 4);
+    w.inv = (int *)take(n * 4);
+    w.gkb = (int2 *)take(n * 8);
+    w.gu = (int *)take(n * 4);
+    w.rec = (int4 *)take(n * 16);
+    w.wd = (int *)take(nw * 4);
+    w.wfirst = (int *)take(nw * 4);
+    w.wslice = (int *)take(nw * 4);
+    w.hist2 = (uint32_t *)take(nw * m13 * 4);
+    w.tot2 = (uint32_t *)take(m13 * 4);
+    w.off13 = (int *)take((m13 + 1) * 4);
+    w.l13 = (int2 *)take(2 * n * 8);
+    w.tiles = (int4 *)take((size_t)rw_tiles(p, L, 16) * 16);
+    w.tile_base = (int *)take(((size_t)p.m2 + 1) * 4);
+    w.nwin = (int *)take(4);
+    w.arrived = (uint32_t *)take(m13 * 4);
+    w.rows = (float *)take(n * p.N * 4);
+    w.dym = (float *)take(n * p.N * 4);
+    w.pbuf = (float *)take(n * p.sA * 4);
+    w.part2 = (float *)take(((size_t)p.m2 + tile_wgs) * p.sB * 4);
+    w.part13 = (float *)take((size_t)rw_pieces(p, L) * (p.sA > p.sC ? p.sA : p.sC) * 4);
+    w.bytes = off;
+    return w;
+}
+
+// ---- pre-pass --------------------------------------------------------------------------------------------------------
+
+// second digits of a tile of positions, and how many of each
+__global__ __launch_bounds__(WG) void rw_count_kernel(Params p, const int64_t *__restrict__ indices, int L, RowsWs ws)
+{
+    __shared__ uint32_t h[RW_MAX_M2];
+    const int t = threadIdx.x, m2p = (p.m2 + 3) & ~3, base = blockIdx.x * RW_TILE;
+    uint32_t row[RW_TILE / WG];
+#pragma unroll
+    for (int q = 0; q < RW_TILE / WG; ++q) row[q] = (uint32_t)indices[min(base + q * WG + t, L - 1)];
+    for (int x = t; x < m2p; x += WG) h[x] = 0u;
+    for (int x = blockIdx.x * WG + t; x < p.m1 + p.m3; x += gridDim.x * WG) ws.arrived[x] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < RW_TILE / WG; ++q)
+        if (base + q * WG + t < L) atomicAdd(&h[(int)select_digit_f64(p, 1, (double)row[q])], 1u);
+    __syncthreads();
+    for (int x = t; x < m2p; x += WG) ws.hist[(size_t)blockIdx.x * m2p + x] = h[x];
+}
+
+// Stable placement by second digit.  Every workgroup derives its own starting places from the counts of all tiles (a few
+// independent 16-byte loads per thread); wave w ranks its 512 consecutive positions round by round.
+__global__ __launch_bounds__(WG) void rw_scatter_kernel(Params p, const int64_t *__restrict__ indices, int L, int nblk, int bits, RowsWs ws)
+{
+    constexpr int NR = RW_TILE / WG;
+    __shared__ __align__(16) uint32_t s_cnt[NWAVE][RW_MAX_M2];      // first the partial sums of the counts
+    __shared__ uint32_t s_start[RW_MAX_M2];
+    __shared__ int s_tmp[NWAVE + 1];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m2p = (p.m2 + 3) & ~3, base = blockIdx.x * RW_TILE + w * (RW_TILE / NWAVE);
+    uint32_t row[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) row[q] = (uint32_t)indices[min(base + q * WAVE + lane, L - 1)];
+    {
+        const int q4 = m2p >> 2, nrg = WG / q4, c = t % q4, rg = t / q4;      // q4 <= 256
+        uint4 t4 = make_uint4(0u, 0u, 0u, 0u), p4 = t4;
+        if (rg < nrg) {
+            const uint4 *h4 = reinterpret_cast<const uint4 *>(ws.hist);
+            for (int b0 = rg; b0 < nblk; b0 += 16 * nrg) {         // 16 loads in flight (clamped, so none is conditional)
+                uint4 v[16];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) v[q] = h4[(size_t)min(b0 + q * nrg, nblk - 1) * q4 + c];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) {
+                    const int b = b0 + q * nrg;
+                    const uint32_t in = b < nblk ? 0xffffffffu : 0u, m = b < (int)blockIdx.x ? 0xffffffffu : 0u;
+                    t4.x += v[q].x & in; t4.y += v[q].y & in; t4.z += v[q].z & in; t4.w += v[q].w & in;
+                    p4.x += v[q].x & m; p4.y += v[q].y & m; p4.z += v[q].z & m; p4.w += v[q].w & m;
+                }
+            }
+        }
+        uint32_t *ptot = &s_cnt[0][0], *ppre = ptot + 2 * RW_MAX_M2;          // [row group][bin]: nrg m2p <= 1024 + ...
+        if (rg < nrg) {
+            *reinterpret_cast<uint4 *>(&ptot[rg * m2p + 4 * c]) = t4;
+            *reinterpret_cast<uint4 *>(&ppre[rg * m2p + 4 * c]) = p4;
+        }
+        __syncthreads();
+        // thread t owns 4 neighbouring bins
+        uint32_t tot[4], pre[4], sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int bin = 4 * t + q;
+            tot[q] = pre[q] = 0u;
+            if (bin < m2p)
+                for (int g = 0; g < nrg; ++g) { tot[q] += ptot[g * m2p + bin]; pre[q] += ppre[g * m2p + bin]; }
+            sum += tot[q];
+        }
+        int total;
+        uint32_t before = (uint32_t)block_excl_scan((int)sum, s_tmp, &total);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int bin = 4 * t + q;
+            if (bin < m2p) {
+                s_start[bin] = before + pre[q];
+                if (blockIdx.x == 0 && bin <= p.m2) ws.goff[bin] = (int)before;
+            }
+            before += tot[q];
+        }
+        if (blockIdx.x == 0 && t == 0) ws.goff[p.m2] = L;
+    }
+    __syncthreads();
+    for (int x = t; x < NWAVE * RW_MAX_M2; x += WG) (&s_cnt[0][0])[x] = 0u;
+    __syncthreads();
+    int dg[NR], rank[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const bool in = base + q * WAVE + lane < L;
+        dg[q] = (int)select_digit_f64(p, 1, (double)row[q]);
+        uint64_t same = __ballot(in);
+        for (int b = 0; b < bits; ++b) {                           // uniform
+            const uint64_t bal = __ballot((dg[q] >> b) & 1);
+            same &= (dg[q] >> b) & 1 ? bal : ~bal;
+        }
+        rank[q] = 0;
+        if (in) {
+            const uint32_t old = s_cnt[w][dg[q]];
+            const int r = (int)__popcll(same & lanemask_lt());
+            rank[q] = (int)old + r;
+            __builtin_amdgcn_wave_barrier();
+            if (r == 0) s_cnt[w][dg[q]] = old + (uint32_t)__popcll(same);
+        }
+        __builtin_amdgcn_wave_barrier();                           // (LDS of one wave is in order: only the compiler has to keep it)
+    }
+    __syncthreads();
+    for (int bin = t; bin < p.m2; bin += WG) {
+        uint32_t at = s_start[bin];
+#pragma unroll
+        for (int q = 0; q < NWAVE; ++q) {
+            const uint32_t c = s_cnt[q][bin];
+            s_cnt[q][bin] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const int k = base + q * WAVE + lane;
+        if (k < L) {
+            const uint32_t at = s_cnt[w][dg[q]] + (uint32_t)rank[q];
+            ws.lk[at] = (uint32_t)k;
+            ws.lrow[at] = row[q];
+        }
+    }
+}
+
+// exclusive scan of one int per thread over the RW_T threads; tmp: RW_NW ints
+__device__ __forceinline__ int rw_scan(int v, int *tmp, int *total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(inc, d);
+        if (lane >= d) inc += o;
+    }
+    __syncthreads();
+    if (lane == 63) tmp[w] = inc;
+    __syncthreads();
+    int at = inc - v, all = 0;
+#pragma unroll
+    for (int q = 0; q < RW_NW; ++q) {
+        const int x = tmp[q];
+        if (q < w) at += x;
+        all += x;
+    }
+    *total = all;
+    return at;
+}
+
+// One window of one slice's positions: see the file comment.
+__global__ __launch_bounds__(RW_T) void rw_group_kernel(Params p, int L, int win, const int64_t *__restrict__ offsets, int n_bags, RowsWs ws)
+{
+    constexpr int NCH = RW_WIN / WAVE, PER = RW_WIN / RW_T;
+    __shared__ __align__(16) uint32_t h_row[RW_HASH];
+    __shared__ __align__(16) int h_min[RW_HASH];                   // later the counters of the digits
+    __shared__ int h_cnt[NCH * 64];
+    __shared__ uint32_t u_r[RW_WIN];
+    __shared__ uint16_t u_at[RW_WIN], u_rank[RW_WIN], s_start[RW_WIN + 1];
+    __shared__ uint64_t s_heads[NCH];
+    __shared__ int s_off[RW_OFF + 1], s_tmp[RW_NW], s_win[2];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m13 = p.m1 + p.m3;
+    // which window this is: slice and number in the slice
+    {
+        int nwin[2], sum = 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int s = 2 * t + q;
+            nwin[q] = s < p.m2 ? (ws.goff[s + 1] - ws.goff[s] + win - 1) / win : 0;
+            sum += nwin[q];
+        }
+        int total;
+        int at = rw_scan(sum, s_tmp, &total);
+        if (t == 0 && blockIdx.x == 0) *ws.nwin = total;
+        if ((int)blockIdx.x >= total) return;                      // uniform
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if ((int)blockIdx.x >= at && (int)blockIdx.x < at + nwin[q]) { s_win[0] = 2 * t + q; s_win[1] = blockIdx.x - at; }
+            at += nwin[q];
+        }
+    }
+    const int ostep = (n_bags + RW_OFF - 1) / RW_OFF;
+    const bool search = offsets && !p.bagP;                        // (bags of one length are found without)
+    if (search)
+        for (int x = t; x <= RW_OFF; x += RW_T) s_off[x] = (int)offsets[min(x * ostep, n_bags)];
+    for (int x = t; x < RW_HASH / 4; x += RW_T) {
+        reinterpret_cast<uint4 *>(h_row)[x] = make_uint4(0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu);
+        reinterpret_cast<int4 *>(h_min)[x] = make_int4(0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff);
+    }
+    for (int x = t; x < NCH * 64; x += RW_T) h_cnt[x] = 0;
+    __syncthreads();
+    const int slice = s_win[0], first = ws.goff[slice] + s_win[1] * win;
+    const int n = min(win, ws.goff[slice + 1] - first), nch = (n + WAVE - 1) / WAVE;
+    uint32_t myk[PER];
+    {
+        uint32_t row[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = min(q * RW_T + t, n - 1);
+            row[q] = ws.lrow[first + i];
+            myk[q] = ws.lk[first + i];
+        }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = q * RW_T + t;
+            if (i >= n) continue;
+            u_r[i] = row[q];
+            uint32_t h = cache_hash(row[q], RW_HASH - 1);
+            for (;;) {                                             // ends: at most RW_WIN rows in RW_HASH places
+                const uint32_t old = atomicCAS(&h_row[h], 0xffffffffu, row[q]);
+                if (old == 0xffffffffu || old == row[q]) break;
+                h = (h + 1) & (RW_HASH - 1);
+            }
+            atomicMin(&h_min[h], i);
+            u_at[i] = (uint16_t)h;
+        }
+    }
+    __syncthreads();
+    for (int ch = w; ch < nch; ch += RW_NW) {
+        const int i = ch * WAVE + lane;
+        const uint64_t head = __ballot(i < n && h_min[u_at[min(i, n - 1)]] == i);
+        if (lane == 0) s_heads[ch] = head;
+    }
+    __syncthreads();
+    int D = 0;
+    for (int c = 0; c < nch; ++c) {
+        const uint64_t head = s_heads[c];
+        if ((c & (RW_NW - 1)) == w && ((head >> lane) & 1)) h_min[u_at[c * WAVE + lane]] = D + (int)__popcll(head & lanemask_lt());
+        D += (int)__popcll(head);
+    }
+    __syncthreads();
+    // numbers of the entries, entries of every number (at most RW_WIN numbers)
+    uint32_t *count = h_row;                                       // then: its number among those with several entries
+    constexpr uint32_t ONE = 0xffffu;
+    for (int x = t; x < RW_WIN; x += RW_T) count[x] = 0u;
+    __syncthreads();
+    for (int i = t; i < n; i += RW_T) {
+        const int num = h_min[u_at[i]];
+        u_at[i] = (uint16_t)num;
+        atomicAdd(&count[num], 1u);
+    }
+    __syncthreads();
+    int M;
+    {
+        uint32_t c[PER];
+        int sum = 0, several = 0, total;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            c[q] = count[t * PER + q];
+            sum += (int)c[q];
+            several += c[q] > 1u;
+        }
+        int at = rw_scan(sum, s_tmp, &total), m = rw_scan(several, s_tmp, &M);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int num = t * PER + q;
+            if (num <= D) s_start[num] = (uint16_t)at;
+            count[num] = c[q] > 1u ? (uint32_t)m : ONE;
+            at += (int)c[q];
+            m += c[q] > 1u;
+        }
+        if (t == 0) s_start[D] = (uint16_t)n;
+    }
+    // entries of a row with several: their places by a stable counting sort over 64 such rows at a time
+    for (int m0 = 0; m0 < M; m0 += 64) {                           // uniform
+        if (m0) {
+            __syncthreads();
+            for (int x = t; x < nch * 64; x += RW_T) h_cnt[x] = 0;
+        }
+        __syncthreads();
+        for (int ch = w; ch < nch; ch += RW_NW) {
+            const int i = ch * WAVE + lane, v = i < n ? (int)count[u_at[i]] - m0 : -1;
+            const bool in = (unsigned)v < 64u;
+            uint64_t same = __ballot(in);
+            if (!same) continue;                                   // uniform
+#pragma unroll
+            for (int bit = 0; bit < 6; ++bit) {
+                const uint64_t bal = __ballot((v >> bit) & 1);
+                same &= (v >> bit) & 1 ? bal : ~bal;
+            }
+            if (in) {
+                const int rank = (int)__popcll(same & lanemask_lt());
+                u_rank[i] = (uint16_t)rank;
+                if (rank == 0) h_cnt[ch * 64 + v] = (int)__popcll(same);
+            }
+        }
+        __syncthreads();
+        if (w == 0) {                                              // lane = row: counts of the chunks to places
+            int sum = 0;
+            for (int c = 0; c < nch; ++c) {
+                const int x = h_cnt[c * 64 + lane];
+                h_cnt[c * 64 + lane] = sum;
+                sum += x;
+            }
+        }
+        __syncthreads();
+        for (int i = t; i < n; i += RW_T) {
+            const int v = (int)count[u_at[i]] - m0;
+            if ((unsigned)v < 64u) u_rank[i] = (uint16_t)(h_cnt[(i >> 6) * 64 + v] + u_rank[i]);
+        }
+    }
+    __syncthreads();
+    for (int x = t; x < m13; x += RW_T) h_min[x] = 0;              // (the table is not needed any more)
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int i = q * RW_T + t;
+        if (i >= n) continue;
+        const int k = (int)myk[q], num = u_at[i];
+        int bag = k;
+        if (offsets) {
+            if (search) {
+                int lo = 0, hi = RW_OFF;                           // last sample with offset <= k
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_off[mid] <= k) lo = mid; else hi = mid;
+                }
+                bag = min(lo * ostep, n_bags - 1);
+                int b1 = min(bag + ostep, n_bags);
+                while (b1 - bag > 1) {
+                    const int mid = (bag + b1) >> 1;
+                    if (offsets[mid] <= (int64_t)k) bag = mid; else b1 = mid;
+                }
+            } else {
+                bag = grp_bag(p, offsets, n_bags, k);
+            }
+        }
+        const int at = first + s_start[num] + (count[num] != ONE ? (int)u_rank[i] : 0);
+        ws.gkb[at] = make_int2(k, bag);
+        ws.gu[at] = first + num;
+        ws.inv[k] = first + num;
+        if ((s_heads[i >> 6] >> (i & 63)) & 1) {
+            int i1, i2, i3;
+            decode_f64(p, u_r[i], i1, i2, i3);
+            ws.rec[first + num] = make_int4(i1, i3, first + s_start[num], s_start[num + 1] - s_start[num]);
+            atomicAdd(&h_min[i1], 1);
+            atomicAdd(&h_min[p.m1 + i3], 1);
+        }
+        if (i >= D) ws.rec[first + i] = make_int4(0, 0, 0, 0);     // unused places
+    }
+    __syncthreads();
+    for (int x = t; x < m13; x += RW_T) ws.hist2[(size_t)blockIdx.x * m13 + x] = (uint32_t)h_min[x];
+    if (t == 0) {
+        ws.wd[blockIdx.x] = D;
+        ws.wfirst[blockIdx.x] = first;
+        ws.wslice[blockIdx.x] = slice;
+    }
+}
+
+// Workgroups before the last: for 32 bins each (slices of the first and third core) the windows' counts become the sums of
+// the earlier windows.  The last one numbers the tiles.
+__global__ __launch_bounds__(RW_T) void rw_scan_kernel(Params p, int tp, RowsWs ws)
+{
+    __shared__ uint32_t s_sum[16][32];
+    __shared__ int s_tmp[RW_NW];
+    const int t = threadIdx.x, m13 = p.m1 + p.m3, nw = *ws.nwin;
+    if (blockIdx.x + 1 < gridDim.x) {
+        constexpr int NF = 8;
+        const int b = t & 31, g = t >> 5, bin = (int)blockIdx.x * 32 + b, per = (nw + 15) / 16;
+        const int w0 = min(nw, g * per), w1 = min(nw, w0 + per);
+        const bool on = bin < m13;
+        uint32_t *h = ws.hist2 + (on ? bin : 0);
+        uint32_t sum = 0;
+        for (int x = w0; x < w1; x += NF) {
+            uint32_t v[NF];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) v[q] = h[(size_t)min(x + q, w1 - 1) * m13];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) sum += x + q < w1 ? v[q] : 0u;
+        }
+        s_sum[g][b] = sum;
+        __syncthreads();
+        uint32_t at = 0, all = 0;
+        for (int q = 0; q < 16; ++q) {
+            const uint32_t v = s_sum[q][b];
+            if (q < g) at += v;
+            all += v;
+        }
+        if (!on) return;
+        if (g == 0) ws.tot2[bin] = all;
+        for (int x = w0; x < w1; x += NF) {
+            uint32_t v[NF];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) v[q] = h[(size_t)min(x + q, w1 - 1) * m13];
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if (x + q < w1) { h[(size_t)(x + q) * m13] = at; at += v[q]; }
+        }
+        return;
+    }
+    int base = 0;
+    for (int w0 = 0; w0 < nw; w0 += RW_T) {                        // uniform
+        const int x = w0 + t;
+        const int D = x < nw ? ws.wd[x] : 0, nt = (D + tp - 1) / tp;
+        int total;
+        const int at = base + rw_scan(nt, s_tmp, &total);
+        if (x < nw) {
+            const int s = ws.wslice[x], before = x ? ws.wslice[x - 1] : -1, first = ws.wfirst[x];
+            for (int q = before + 1; q <= s; ++q) ws.tile_base[q] = at;        // (slices without positions as well)
+            for (int q = 0; q < nt; ++q) ws.tiles[at + q] = make_int4(s, first + q * tp, min(tp, D - q * tp), 0);
+        }
+        base += total;
+    }
+    const int last = nw ? ws.wslice[nw - 1] : -1;
+    for (int q = last + 1 + t; q <= p.m2; q += RW_T) ws.tile_base[q] = base;
+}
+
+// The distinct rows of a window to their places among those of their slices of the first and of the third core.
+__global__ __launch_bounds__(RW_T) void rw_lists_kernel(Params p, int bits1, int bits3, RowsWs ws)
+{
+    extern __shared__ __align__(16) uint32_t rw_lds[];             // [m13] starts, then [RW_NW][m13] 16-bit counts
+    __shared__ int s_tmp[RW_NW];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m13 = p.m1 + p.m3;
+    if ((int)blockIdx.x >= *ws.nwin) return;                       // uniform
+    uint32_t *start = rw_lds;
+    uint16_t *cnt = reinterpret_cast<uint16_t *>(rw_lds + m13);
+    const int D = ws.wd[blockIdx.x], first = ws.wfirst[blockIdx.x];
+    constexpr int PB = RW_MAX_M13 / RW_T;                          // bins per thread: neighbouring ones
+    {
+        uint32_t v[PB];
+        int sum = 0;
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
+            v[q] = t * PB + q < m13 ? ws.tot2[t * PB + q] : 0u;
+            sum += (int)v[q];
+        }
+        int total;
+        uint32_t at = (uint32_t)rw_scan(sum, s_tmp, &total);
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
+            const int bin = t * PB + q;
+            if (bin < m13) {
+                start[bin] = at + ws.hist2[(size_t)blockIdx.x * m13 + bin];
+                if (blockIdx.x == 0) ws.off13[bin] = (int)at;
+            }
+            at += v[q];
+        }
+        if (blockIdx.x == 0 && t == 0) ws.off13[m13] = total;
+    }
+    for (int x = t; x < RW_NW * m13; x += RW_T) cnt[x] = 0;
+    __syncthreads();
+    // wave w has the w-th eighth of the window's rows (whole chunks of 64)
+    constexpr int NR = RW_WIN / RW_T;
+    const int per = ((D + RW_NW - 1) / RW_NW + WAVE - 1) / WAVE * WAVE;
+    int d1[NR], d3[NR], r1[NR], r3[NR], k0[NR];
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const int i = w * per + q * WAVE + lane;
+        const bool in = q * WAVE < per && i < D;
+        d1[q] = -1; d3[q] = 0; r1[q] = r3[q] = k0[q] = 0;
+        if (in) {
+            const int4 rc = ws.rec[first + i];
+            d1[q] = rc.x; d3[q] = rc.y;
+            k0[q] = ws.gkb[rc.z].x;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+        const bool in = d1[q] >= 0;
+        const uint64_t any = __ballot(in);
+        if (!any) continue;                                        // uniform
+        auto rank = [&](int dg, int bits, int bin) {
+            uint64_t same = any;
+            for (int b = 0; b < bits; ++b) {                       // uniform
+                const uint64_t bal = __ballot((dg >> b) & 1);
+                same &= (dg >> b) & 1 ? bal : ~bal;
+            }
+            int r = 0;
+            if (in) {
+                const int old = cnt[w * m13 + bin], x = (int)__popcll(same & lanemask_lt());
+                r = old + x;
+                __builtin_amdgcn_wave_barrier();
+                if (x == 0) cnt[w * m13 + bin] = (uint16_t)(old + (int)__popcll(same));
+            }
+            __builtin_amdgcn_wave_barrier();
+            return r;
+        };
+        r1[q] = rank(d1[q], bits1, d1[q]);
+        r3[q] = rank(d3[q], bits3, p.m1 + d3[q]);
+    }
+    __syncthreads();
+    for (int bin = t; bin < m13; bin += RW_T) {
+        int at = 0;
+#pragma unroll
+        for (int q = 0; q < RW_NW; ++q) {
+            const int c = cnt[q * m13 + bin];
+            cnt[q * m13 + bin] = (uint16_t)at;
+            at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NR; ++q)
+        if (d1[q] >= 0) {
+            const int2 e = make_int2(first + w * per + q * WAVE + lane, k0[q]);
+            ws.l13[start[d1[q]] + cnt[w * m13 + d1[q]] + r1[q]] = e;
+            ws.l13[start[p.m1 + d3[q]] + cnt[w * m13 + p.m1 + d3[q]] + r3[q]] = e;
+        }
+}
+
+// Index-only part of a step: five launches.  tp: distinct rows per tile.
+static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int L, const int64_t *offsets, int n_bags, int tp, const RowsWs &ws,
+                                    hipStream_t st)
+{
+    const int nblk = rw_hist_blocks(L), nw = rw_windows(p, L), m13 = p.m1 + p.m3;
+    auto bits_of = [](int m) { int b = 0; while ((1 << b) < m) ++b; return b; };
+    const size_t lds = (size_t)m13 * 4 + (size_t)RW_NW * m13 * 2;              // at most 80 KB
+    static bool allowed = false;                                               // (one device per process)
+    if (!allowed) {
+        hipError_t e = hipFuncSetAttribute((const void *)rw_lists_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
+        if (e != hipSuccess) return e;
+        allowed = true;
+    }
+    hipLaunchKernelGGL(rw_count_kernel, dim3(nblk), dim3(WG), 0, st, p, indices, L, ws);
+    hipLaunchKernelGGL(rw_scatter_kernel, dim3(nblk), dim3(WG), 0, st, p, indices, L, nblk, bits_of(p.m2), ws);
+    hipLaunchKernelGGL(rw_group_kernel, dim3(nw), dim3(RW_T), 0, st, p, L, rw_win(L), offsets, n_bags, ws);
+    hipLaunchKernelGGL(rw_scan_kernel, dim3((m13 + 31) / 32 + 1), dim3(RW_T), 0, st, p, tp, ws);
+    hipLaunchKernelGGL(rw_lists_kernel, dim3(nw), dim3(RW_T), lds, st, p, bits_of(p.m1), bits_of(p.m3), ws);
+    return hipGetLastError();
+}
+
+}  // namespace tt

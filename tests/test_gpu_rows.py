@@ -1,0 +1,90 @@
+"""Grouping by distinct row (tt_rows.h, tt_rows_pass.h) where it changes course: a hot row over several windows, slices of the
+first and third core with more rows than one workgroup adds up (the last of several finishes them), slices without any row,
+every row different, every position the same row, streams on either side of the window sizes.  Forward, gradients and fused
+step against the oracle, and the step twice, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tt_oracle as ora
+from paper_2101_11714_amd import binding as B
+from paper_2101_11714_amd import workloads as W
+from gpu_util import DeviceTable, assert_close, dev
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [((2, 2, 4), 32), ((2, 2, 4), 64), ((4, 4, 4), 32), ((4, 4, 4), 64)]
+
+
+@pytest.fixture
+def always_rows():
+    old = B.set_fast_path(3)                       # groups whatever the number of positions
+    yield
+    B.set_fast_path(old)
+
+
+def _rows(kind, t, L, rng):
+    m1, m2, m3 = t.m
+    i1, i2, i3 = rng.integers(0, m1, L), rng.integers(0, m2, L), rng.integers(0, m3, L)
+    if kind == "first digit":                      # all rows in one slice of the first core: more than RW_PIECE of them
+        i1[:] = m1 - 1
+    elif kind == "third digit":
+        i3[:] = 1
+    elif kind == "second digit":                   # one slice of the second core: windows and tiles of one slice
+        i2[:] = m2 - 1
+    elif kind == "one row":
+        i1[:], i2[:], i3[:] = 2, 1, 3
+    idx = (i1 * m2 + i2) * m3 + i3
+    if kind == "hot row":
+        idx[rng.random(L) < 0.6] = idx[0]
+    return np.minimum(idx, t.num_rows - 1).astype(np.int64)
+
+
+def _table(kind, n, R, L, n_bags, seed):
+    t = W.TableShape(30 * 20 * 40 - 3, (30, 20, 40), n, (1, R, R, 1))
+    rng = np.random.default_rng([seed, L])
+    idx = _rows(kind, t, L, rng)
+    cuts = np.sort(rng.integers(0, L + 1, n_bags - 1))
+    off = np.concatenate([[0], cuts, [L]]).astype(np.int64)
+    batch = W.Batch(idx, off, rng.standard_normal((n_bags, t.dim)).astype(np.float32), (0.5 + rng.random(L)).astype(np.float32))
+    return DeviceTable(W.Workload("rows", (t,), n_bags, (0, 9), "uniform", 0.0, "normal0.1", seed), batch=batch)
+
+
+def _check(d, name, sample=None):
+    assert B.fwd_uses_lists(d.shape, d.L, 0, True)
+    b = d.batch
+    ws = torch.full((B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
+    steps = []
+    for _ in range(2):
+        out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+        t0 = torch.full((d.L, B.t0_floats(d.shape)), float("nan"), dtype=torch.float32, device=dev())
+        new = [torch.full_like(x, float("nan")) for x in d.g]
+        B.tt_emb_bwd_prepare(d.shape, d.idx, d.off, d.n_bags, workspace=ws, kept_t0=True)
+        B.tt_emb_fwd_prepared(d.shape, d.g, d.idx, d.off, d.n_bags, out, ws, t0=t0, alpha=d.alpha)
+        B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha, workspace=ws, t0=t0, prepared=True)
+        torch.cuda.synchronize()
+        steps.append([out, t0] + new)
+    assert all(torch.equal(x, y) for x, y in zip(*steps))
+    out, t0, new = steps[0][0], steps[0][1], steps[0][2:]
+    assert_close(out.cpu().numpy(), ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha), name + " forward")
+    assert not torch.isnan(t0).any()
+    pick = np.random.default_rng(1).choice(d.L, min(d.L, 40), replace=False)
+    assert_close(t0.cpu().numpy()[pick], np.stack([ora.t0(d.oshape, d.cores, int(b.indices[k])).reshape(-1) for k in pick]), name + " T0")
+    rg, _ = ora.bwd(d.oshape, d.cores, b.indices, b.offsets, b.grad_output, alpha=b.alpha)
+    dg, _ = d.bwd(t0=t0, grad_cores=[torch.full_like(x, 0.25) for x in d.g])
+    for k in range(3):
+        assert_close(new[k].cpu().numpy(), ora.sgd(d.cores[k], rg[k], 0.05), "%s core %d" % (name, k + 1))
+        assert_close(dg[k].cpu().numpy() - 0.25, rg[k], "%s dG%d" % (name, k + 1))
+
+
+@pytest.mark.parametrize("n,R", SHAPES)
+@pytest.mark.parametrize("kind,L", [("spread", 1), ("spread", 700), ("hot row", 1500), ("first digit", 1300), ("third digit", 1300),
+                                    ("second digit", 900), ("one row", 700)])
+def test_small_streams(n, R, kind, L, always_rows):
+    _check(_table(kind, n, R, L, max(1, L // 3), 61), "%s %s R %d L %d" % (kind, n, R, L))
+
+
+@pytest.mark.parametrize("kind", ["hot row", "first digit"])
+def test_long_streams_with_long_windows(kind):
+    # 70,000 positions: windows of 2,048, by the library's own choice
+    _check(_table(kind, (2, 2, 4), 32, 70_000, 9_000, 62), "%s long" % kind)
