@@ -85,12 +85,14 @@ __global__ __launch_bounds__(WG) void topk_class_kernel(const uint64_t *__restri
     __syncthreads();
     for (int x = t; x < NB; x += WG)
         if (h[x]) atomicAdd(&hist[x], h[x]);
-    // (the barrier waits until this workgroup's adds have been performed; they and the loads below go to the point where the
-    // whole device meets, so no fence has to write the caches back)
+    // This workgroup's adds have to be performed before it counts itself as done.  A barrier alone does not wait for them; they
+    // and the loads below go to the point where the whole device meets, so that no fence has to write the caches back.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (t == 0) s_last = atomicAdd(&state->blocks, 1u) == gridDim.x - 1;
     __syncthreads();
     if (!s_last) return;
+    const uint32_t want = state->remaining;      // 1 <= want <= total; read by everyone before the scan's barriers, written after them
     uint32_t v[PER];
     int sum = 0;
 #pragma unroll
@@ -101,7 +103,6 @@ __global__ __launch_bounds__(WG) void topk_class_kernel(const uint64_t *__restri
     }
     int total;
     uint32_t before = (uint32_t)block_excl_scan(sum, s_tmp, &total);
-    const uint32_t want = state->remaining;      // 1 <= want <= total
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         if (before < want && want <= before + v[q]) {                        // one thread, one class
