@@ -472,7 +472,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
         guess_bag_length(&p, offsets, L, n_bags);
         const RowsWs ws = rw_ws_layout(workspace, p, L, rw_tile_wgs(p, L));
         hipError_t e = hipSuccess;
-        if (phase != BWD_REST) e = rw_prepare(p, indices, (int)L, offsets, (int)n_bags, rw_tp(p, L), ws, (hipStream_t)stream);
+        if (phase != BWD_REST) e = rw_prepare(p, indices, (int)L, offsets, (int)n_bags, rw_tp(p), ws, (hipStream_t)stream);
         if (!prep && e == hipSuccess) {
             const float *const src[3] = {fused ? cores[0] : grad_cores[0], fused ? cores[1] : grad_cores[1], fused ? cores[2] : grad_cores[2]};
             e = rw_bwd(p, cores[0], cores[1], cores[2], L, alpha, grad_output, t0, src, fused ? cores_out : grad_cores, fused ? -lr : 1.f, ws,

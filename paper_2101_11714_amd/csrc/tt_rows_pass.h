@@ -733,7 +733,10 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
         if (t < w4) reinterpret_cast<float4 *>(ws.part13 + (size_t)slot * WMAX)[t] = sum;
         __threadfence();
         __syncthreads();
-        if (t == 0) s_last = atomicAdd(&ws.arrived[bin], 1u) == (uint32_t)(np - 1);
+        if (t == 0) {
+            s_last = atomicAdd(&ws.arrived[bin], 1u) == (uint32_t)(np - 1);
+            if (s_last) atomicExch(&ws.arrived[bin], 0u);                     // (as the pre-pass left it)
+        }
         __syncthreads();
         if (!s_last) return;                                                  // uniform
         __threadfence();
@@ -774,15 +777,14 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
 
 // ---- host side -------------------------------------------------------------------------------------------------------
 
-// Distinct rows per tile: 128 stacked rows; at rank 64 of the (4,4,4) shape 64 for short streams (a tile then leaves room for
-// a second workgroup on the compute unit, and a slice has few rows anyway: 8,192 positions over 200 slices).
-static inline int rw_tp(const Params &p, int64_t L) { return 128 / p.n1; }
+// distinct rows per tile: 128 stacked rows
+static inline int rw_tp(const Params &p) { return 128 / p.n1; }
 
 // workgroups of the tile kernel: what the compute units hold, more only where one would get more tiles than it has room for
 static inline int rw_tile_wgs(const Params &p, int64_t L)
 {
     const int n = (p.R1 >= 64 ? 1 : 2) * bo_compute_units();
-    const int least = (rw_tiles(p, L, rw_tp(p, L)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
+    const int least = (rw_tiles(p, L, rw_tp(p)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
     return n > least ? n : least;
 }
 
@@ -812,8 +814,7 @@ static inline hipError_t rw_fwd(const Params &p, const float *G1, const float *G
     case 2: return launch_rw_fwd<Cfg224R32, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
     case 3: return launch_rw_fwd<Cfg224R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
     case 4: return launch_rw_fwd<Cfg444R32, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
-    case 5: return rw_tp(p, L) == 16 ? launch_rw_fwd<Cfg444R64, 64>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st)
-                                     : launch_rw_fwd<Cfg444R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
+    case 5: return launch_rw_fwd<Cfg444R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -849,8 +850,7 @@ static inline hipError_t rw_bwd(const Params &p, const float *G1, const float *G
     case 2: return launch_rw_bwd<Cfg224R32, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
     case 3: return launch_rw_bwd<Cfg224R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
     case 4: return launch_rw_bwd<Cfg444R32, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
-    case 5: return rw_tp(p, L) == 16 ? launch_rw_bwd<Cfg444R64, 64>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st)
-                                     : launch_rw_bwd<Cfg444R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
+    case 5: return launch_rw_bwd<Cfg444R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
     default: return hipErrorInvalidValue;
     }
 }
