@@ -3,7 +3,8 @@
 // attributes and the current stream, per call) took 6-9 us, more than most of the kernels of a step.  Host time of a pass:
 // a forward of 64 lookups 8.7 -> 3.4 us, the two calls of the Kaggle-shaped step 20 -> 7 us, of which the launches are 2-3 us each.
 // Every function takes its arguments by position, returns the library's return code, and raises AssertionError for a
-// tensor of the wrong device, type, layout or size.  binding.py documents and wraps them.
+// tensor of the wrong device, type, layout or size.  binding.py documents and wraps them.  What torch throws on the way
+// (a tensor without storage, as tracing and vmap make them) becomes a RuntimeError.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -93,13 +94,13 @@ struct Args {
         return v > 0;
     }
 
-    // offsets[n_bags + 1] or None
-    const int64_t *offsets(int i, int64_t n_bags)
+    // offsets[n_bags + 1] or None; longer: a call that takes an array with more entries as well
+    const int64_t *offsets(int i, int64_t n_bags, bool longer = false)
     {
         if (!ok || a[i] == Py_None) return nullptr;
         int64_t n = 0;
         const int64_t *p = i64(i, &n);
-        if (ok && n != n_bags + 1) fail("offsets must have n_bags + 1 entries");
+        if (ok && (longer ? n < n_bags + 1 : n != n_bags + 1)) fail("offsets must have n_bags + 1 entries");
         return p;
     }
 
@@ -180,17 +181,31 @@ struct Lookup {
     const int64_t *indices, *offsets;
     int64_t L = 0, n_bags;
 
-    explicit Lookup(Args &g)
+    explicit Lookup(Args &g, bool longer_offsets = false)
     {
         shape = g.shape(0);
         g.cores(1, cores, nullptr, sizes);
         indices = g.i64(2, &L);
         n_bags = g.integer(4);
-        offsets = g.offsets(3, n_bags);
+        offsets = g.offsets(3, n_bags, longer_offsets);
     }
 };
 
 #define TT_FUNCTION(name) PyObject *name(PyObject *, PyObject *const *args, Py_ssize_t nargs)
+
+// no C++ exception may leave a function that Python calls
+template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
+TT_FUNCTION(guarded)
+{
+    try {
+        return F(nullptr, args, nargs);
+    } catch (const c10::Error &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return nullptr;
+}
 
 // shape cores indices offsets n_bags output alpha cache workspace
 TT_FUNCTION(emb_fwd)
@@ -277,7 +292,7 @@ TT_FUNCTION(emb_bwd_prepare)
     const tt_shape_t *shape = g.shape(0);
     const int64_t *indices = g.i64(1, &L);
     const int64_t n_bags = g.integer(3);
-    const int64_t *offsets = g.offsets(2, n_bags);
+    const int64_t *offsets = g.offsets(2, n_bags, true);
     const tt_cache_t *cache = g.cache(4);
     void *ws = g.bytes_or_null(5, &wsb);
     const bool kept = g.truth(6);
@@ -372,7 +387,7 @@ TT_FUNCTION(emb_bwd_kept)
 {
     Args g(args, nargs, 13);
     if (!g.ok) return nullptr;
-    Lookup q(g);
+    Lookup q(g, true);
     int64_t kb = 0;
     size_t wsb;
     float *grads[3] = {};
@@ -405,7 +420,7 @@ TT_FUNCTION(emb_bwd_sgd_kept)
     g.cores(2, outs, sizes);
     const int64_t *indices = g.i64(3, &L);
     const int64_t n_bags = g.integer(5);
-    const int64_t *offsets = g.offsets(4, n_bags);
+    const int64_t *offsets = g.offsets(4, n_bags, true);
     const float *go = g.f32(6);
     const uint8_t *kept = g.u8(7, &kb);
     const float lr = g.real(8);
@@ -501,14 +516,25 @@ TT_FUNCTION(freq_export)
     return call([&](void *st) { return tt_freq_export(f, rows, counts, n_out, st); });
 }
 
-#define TT_METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
+#define TT_METHOD(name, function) {name, (PyCFunction)(void (*)(void))guarded<function>, METH_FASTCALL, nullptr}
 
 PyMethodDef methods[] = {
-    TT_METHOD(emb_fwd), TT_METHOD(emb_fwd_keep_t0), TT_METHOD(emb_fwd_prepared), TT_METHOD(emb_bwd), TT_METHOD(emb_bwd_prepare),
-    TT_METHOD(emb_bwd_sgd), TT_METHOD(emb_kept_prepare), TT_METHOD(emb_fwd_keep), TT_METHOD(emb_bwd_kept), TT_METHOD(emb_bwd_sgd_kept),
-    TT_METHOD(emb_bwd_sgd_static), TT_METHOD(emb_sgd_update), TT_METHOD(freq_update), TT_METHOD(freq_export),
-    {"cache_build", (PyCFunction)(void (*)(void))cache_fill<tt_cache_build>, METH_FASTCALL, nullptr},
-    {"cache_refill", (PyCFunction)(void (*)(void))cache_fill<tt_cache_refill>, METH_FASTCALL, nullptr},
+    TT_METHOD("emb_fwd", emb_fwd),
+    TT_METHOD("emb_fwd_keep_t0", emb_fwd_keep_t0),
+    TT_METHOD("emb_fwd_prepared", emb_fwd_prepared),
+    TT_METHOD("emb_bwd", emb_bwd),
+    TT_METHOD("emb_bwd_prepare", emb_bwd_prepare),
+    TT_METHOD("emb_bwd_sgd", emb_bwd_sgd),
+    TT_METHOD("emb_kept_prepare", emb_kept_prepare),
+    TT_METHOD("emb_fwd_keep", emb_fwd_keep),
+    TT_METHOD("emb_bwd_kept", emb_bwd_kept),
+    TT_METHOD("emb_bwd_sgd_kept", emb_bwd_sgd_kept),
+    TT_METHOD("emb_bwd_sgd_static", emb_bwd_sgd_static),
+    TT_METHOD("emb_sgd_update", emb_sgd_update),
+    TT_METHOD("freq_update", freq_update),
+    TT_METHOD("freq_export", freq_export),
+    TT_METHOD("cache_build", cache_fill<tt_cache_build>),
+    TT_METHOD("cache_refill", cache_fill<tt_cache_refill>),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tt_call", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -260,3 +260,15 @@ def test_general_d_shape_and_argument_checks():
         assert l.tt_embd_sgd_update(C.byref(bad), arr, arr, C.c_float(0.1), 0, None) == code
     holes = (C.c_void_p * 4)(16, None, 16, 16)
     assert l.tt_embd_bwd(C.byref(good), arr, one, 1, None, 1, None, one, holes, None) == -1
+
+
+def test_tensors_without_storage_raise():
+    # what torch throws in the compiled extension arrives as a Python exception (vmap's tensors have no storage of their own)
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode():
+        cores = [torch.empty(k, dtype=torch.float32, device="cuda") for k in (160, 1280, 320)]
+        out = torch.empty((2, 128), dtype=torch.float32, device="cuda")
+        idx = torch.zeros((2, 8), dtype=torch.int64, device="cuda")
+        with pytest.raises(RuntimeError, match="storage"):
+            torch.func.vmap(lambda i, o: B.tt_emb_fwd(good_shape(), cores, i, None, 8, o))(idx, out)
