@@ -59,11 +59,29 @@ constexpr int64_t GROUP_MIN_L_CACHE = 16384;    // with a cache (the grouped pat
 // for the two-call form, whose first call can run beside other work (Terabyte-shaped, 8,192 positions: 84 against
 // 101 us; (2,2,4) at rank 32 / 64, 20,480 positions: 38 against 59 / 64 against 90 us).
 constexpr int64_t GROUP_MIN_L_TILES_444 = 8192, GROUP_MIN_L_TILES_224 = 16384;
+// At rank 64 the passes over distinct rows (tt_rows.h) are ahead of the scanning owners earlier still.  Step in two calls,
+// owners / rows: (4,4,4) 2,048 positions 47 / 83 us, 4,096 92 / 93, 7,000 126 / 86; (2,2,4) 4,096 positions 42 / 75 us, 8,192
+// 65 / 84, 12,000 (bags of 5-15) 126 / 116, 14,000 103 / 82.  At rank 32 they only draw level (7,000 positions: 68 / 72 us).
+constexpr int64_t GROUP_MIN_L_ROWS_444 = 6144, GROUP_MIN_L_ROWS_224 = 12288;
+// From where on the forward pass after such a pre-pass works from its rows instead of a wave per bag.  Step, wave per bag /
+// rows, rank 64: (4,4,4) 8,192 positions 92 / 88 us (but a first step 129 / 132), 12,288 124 / 114; (2,2,4) bags of 5-15:
+// 17,000 positions 104 / 70 us, 29,000 153 / 96.  Rank 32 stays at GROUP_MIN_L: 3-6 % at most, within what two runs differ.
+constexpr int64_t ROWS_FWD_MIN_L_444 = 10240, ROWS_FWD_MIN_L_224 = GROUP_MIN_L_ROWS_224;
+
+int64_t tiles_min_l(const Params &p) { return p.n1 == 4 ? GROUP_MIN_L_TILES_444 : GROUP_MIN_L_TILES_224; }
+
+int64_t rows_fwd_min_l(const Params &p)
+{
+    if (p.R1 < 64) return GROUP_MIN_L;
+    return p.n1 == 4 ? ROWS_FWD_MIN_L_444 : ROWS_FWD_MIN_L_224;
+}
 
 int64_t group_min_l(const Params &p, int64_t K, bool kept_t0, bool two_calls)
 {
-    if (two_calls && kept_t0 && !K && g_fast_path == 1 && bwd_owner_supported(p))
-        return p.n1 == 4 ? GROUP_MIN_L_TILES_444 : GROUP_MIN_L_TILES_224;
+    if (two_calls && kept_t0 && !K && g_fast_path == 1 && bwd_owner_supported(p)) {
+        if (rw_supported(p) && p.R1 >= 64) return p.n1 == 4 ? GROUP_MIN_L_ROWS_444 : GROUP_MIN_L_ROWS_224;
+        return tiles_min_l(p);
+    }
     return K ? GROUP_MIN_L_CACHE : GROUP_MIN_L;
 }
 
@@ -347,7 +365,7 @@ static bool works_on_rows(const Params &p, int64_t L, int64_t K, bool kept_t0)
 // does tt_emb_fwd_prepared work from the pre-pass's lists for such a call?
 static bool fwd_from_lists(const Params &p, int64_t L, int64_t K, bool kept_t0)
 {
-    if (works_on_rows(p, L, K, kept_t0)) return g_fast_path == 2 || L >= GROUP_MIN_L;
+    if (works_on_rows(p, L, K, kept_t0)) return g_fast_path == 2 || L >= rows_fwd_min_l(p);
     // (only for the long streams: at 8,192 positions, where the (4,4,4) backward already groups, the wave per bag is ahead: 31 against 36 us)
     return L > 0 && fwd_lists_pay(p, K) && bwd_groups(p, L, K, kept_t0) && (g_fast_path == 2 || L >= (K ? GROUP_MIN_L_CACHE : GROUP_MIN_L)) &&
            3 * L < (1ll << 31);
@@ -373,11 +391,14 @@ int tt_emb_fwd_prepared(const tt_shape_t *shape, const float *const cores[3],
     if ((rc = check_cache(cache, &cd, true))) return rc;
     if (t0 && fast_config(p) < 0) return fail(TT_ERR_UNSUPPORTED, "no kernel keeps T0 for this shape");
     // the lists exist if the backward of this call groups its positions; else the forward needs none
-    if (!(n_bags > 0 && fwd_from_lists(p, L, cd.K, t0 != nullptr)))
+    const bool rows = works_on_rows(p, L, cd.K, t0 != nullptr);
+    // (between the two limits the lists are a choice: without room for them the pass is the wave per bag)
+    const bool no_room = rows && g_fast_path == 1 && L < GROUP_MIN_L &&
+                         (!workspace || workspace_bytes < rows_ws_bytes(p, L, cd.K) || misaligned({workspace}));
+    if (no_room || !(n_bags > 0 && fwd_from_lists(p, L, cd.K, t0 != nullptr)))
         return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, cache, output, t0, t0 != nullptr, stream);
     if (!cores || !cores[0] || !cores[1] || !cores[2]) return fail(TT_ERR_NULL, "cores is NULL");
     if (!output) return fail(TT_ERR_NULL, "output is NULL");
-    const bool rows = works_on_rows(p, L, cd.K, t0 != nullptr);
     const size_t need = rows ? rows_ws_bytes(p, L, cd.K) : fwd_bwd_ws_bytes(p, L, cd.K);
     if (!workspace || workspace_bytes < need)
         return fail(TT_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
@@ -448,7 +469,10 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
                        : misaligned({grad_cores[0], grad_cores[1], grad_cores[2], grad_cache}))))
         return fail(TT_ERR_BAD_ARG, "cores, gradients, t0, cache rows and workspace must be 16-byte aligned");
     const bool fast = (g_fast_path || t0) && fast_bwd_supported(p);
-    const bool grouped = fast && (g_fast_path == 2 || L >= group_min_l(p, cd.K, t0 != nullptr, phase != BWD_ALL));
+    // (below the tiles' limit grouping is a choice: both calls of a pair whose workspace has no room for it scan instead)
+    const bool no_room = g_fast_path == 1 && L < tiles_min_l(p) && works_on_rows(p, L, cd.K, t0 != nullptr) &&
+                         (!workspace || workspace_bytes < rows_ws_bytes(p, L, cd.K));
+    const bool grouped = fast && !no_room && (g_fast_path == 2 || L >= group_min_l(p, cd.K, t0 != nullptr, phase != BWD_ALL));
     if (grouped && 3 * L >= (1ll << 31)) return fail(TT_ERR_UNSUPPORTED, "3 L >= 2^31");
     const size_t need_bwd = grouped ? fwd_bwd_ws_bytes(p, L, cd.K) : 256 + slot_ws_bytes(L, cd.K != 0);
     const int64_t core_floats[3] = {(int64_t)p.m1 * p.sA, (int64_t)p.m2 * p.sB, (int64_t)p.m3 * p.sC};

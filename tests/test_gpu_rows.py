@@ -88,3 +88,28 @@ def test_small_streams(n, R, kind, L, always_rows):
 def test_long_streams_with_long_windows(kind):
     # 70,000 positions: windows of 2,048, by the library's own choice
     _check(_table(kind, (2, 2, 4), 32, 70_000, 9_000, 62), "%s long" % kind)
+
+
+@pytest.mark.parametrize("n,L", [((4, 4, 4), 6144), ((4, 4, 4), 10_240), ((2, 2, 4), 12_288), ((2, 2, 4), 17_001)])
+def test_rank_64_by_choice(n, L):
+    # the lengths from which the library groups by itself, and the same pair where the workspace has no room for it
+    d = _table("spread", n, 64, L, L // 4, 63)
+    assert B.bwd_has_prepass(d.shape, L, 0, True) and B.bwd_has_prepass(d.shape, (6143 if n[0] == 4 else 12_287), 0, True) is False
+    b = d.batch
+    rg, _ = ora.bwd(d.oshape, d.cores, b.indices, b.offsets, b.grad_output, alpha=b.alpha)
+    want = [ora.sgd(d.cores[k], rg[k], 0.05) for k in range(3)]
+    out_want = ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha)
+    full = B.bwd_sgd_workspace_bytes(d.shape, L, d.n_bags, 0)
+    # (what the scanning owners take: the part of the size that does not grow with the positions' rows; enough of it, and too
+    # little for the rows, is half of the whole)
+    for size in ([full, full // 2] if L < (8192 if n[0] == 4 else 16_384) else [full]):
+        ws = torch.full((size,), 0x7F, dtype=torch.uint8, device=dev())
+        out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+        t0 = torch.full((L, B.t0_floats(d.shape)), float("nan"), dtype=torch.float32, device=dev())
+        new = [torch.full_like(x, float("nan")) for x in d.g]
+        B.tt_emb_bwd_prepare(d.shape, d.idx, d.off, d.n_bags, workspace=ws, kept_t0=True)
+        B.tt_emb_fwd_prepared(d.shape, d.g, d.idx, d.off, d.n_bags, out, ws, t0=t0, alpha=d.alpha)
+        B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha, workspace=ws, t0=t0, prepared=True)
+        assert_close(out.cpu().numpy(), out_want, "forward, workspace %d" % size)
+        for k in range(3):
+            assert_close(new[k].cpu().numpy(), want[k], "core %d, workspace %d" % (k + 1, size))
