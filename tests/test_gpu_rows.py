@@ -100,8 +100,8 @@ def test_rank_64_by_choice(n, L):
     want = [ora.sgd(d.cores[k], rg[k], 0.05) for k in range(3)]
     out_want = ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha)
     full = B.bwd_sgd_workspace_bytes(d.shape, L, d.n_bags, 0)
-    # (what the scanning owners take: the part of the size that does not grow with the positions' rows; enough of it, and too
-    # little for the rows, is half of the whole)
+    # (half of the full size is enough for the scanning owners, 2.8 / 1.4 MB for these tables, and too little for the rows, which
+    # take more than 15 MB)
     for size in ([full, full // 2] if L < (8192 if n[0] == 4 else 16_384) else [full]):
         ws = torch.full((size,), 0x7F, dtype=torch.uint8, device=dev())
         out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
