@@ -155,6 +155,10 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
  * grad_cache:  fp32 [K][N], added to; required iff cache != NULL.
  * Duplicate indices are combined inside the library; no atomics are used, and the
  * result is bit-identical from run to run.
+ * Shapes without a specialised kernel: a workspace of the queried size makes the call 10 to 50
+ * times as fast as none, from where a plain kernel does the work; a smaller one costs speed only
+ * (more passes over fewer positions, same result bit for bit) down to about 32 MiB, below which
+ * the plain kernel takes over (another order of the fp32 sums).
  */
 int tt_emb_bwd(const tt_shape_t *shape, const float *const cores[3],
                const int64_t *indices, int64_t L, const int64_t *offsets, int64_t n_bags,
@@ -303,8 +307,10 @@ int tt_emb_bwd_sgd(const tt_shape_t *shape, const float *const cores[3], float *
  * array of tt_emb_static_scratch_bytes() (32 MiB) bytes inside the library's device image, of
  * which every GPU the library runs on holds its own copy until the process ends.  The call
  * allocates and frees nothing.  A call that needs more scratch memory than that (long index
- * lists, large caches: what tt_emb_bwd_sgd_workspace_bytes says, minus its allowance for
- * shapes without a specialised kernel) fails with TT_ERR_WORKSPACE and enqueues nothing.
+ * lists, large caches) fails with TT_ERR_WORKSPACE and enqueues nothing.  With a specialised
+ * kernel the need is at most what tt_emb_bwd_sgd_workspace_bytes says; without one the call
+ * works through the positions in passes that fit, in the order of sums that the call with a
+ * workspace has too, and fails only where neither one pass nor the gradients of the cores fit.
  * The first call on a device also looks the array's address up (hipGetSymbolAddress): make
  * that call outside a capture.  All calls on one GPU share the array, which keeps what the
  * last call left in it (the kernels initialise what they read): calls that overlap on one GPU,

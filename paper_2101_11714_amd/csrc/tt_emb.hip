@@ -218,10 +218,37 @@ size_t split_ws_bytes_max(const Params &p, int64_t L)
     return a > b ? a : b;
 }
 
-// what the run-time-shape backward (tt_flex.h) adds for the shapes without a specialised kernel
+// gradients of the cached rows, and of the three cores, where a call keeps them in the workspace
+size_t cache_grad_bytes(const Params &p, int64_t K) { return K ? align256((size_t)K * p.N * 4) : 0; }
+size_t core_grad_bytes(const Params &p)
+{
+    return align256((size_t)p.m1 * p.sA * 4) + align256((size_t)p.m2 * p.sB * 4) + align256((size_t)p.m3 * p.sC * 4);
+}
+
+// Does a backward call of a shape without a specialised kernel take the kernels of tt_flex.h (else those of tt_generic.h),
+// and in which order do they add?  That is a function of the shape, the length and the cache alone: with any workspace of
+// at least flex_ws_least the results are the same, the static scratch memory of tt_emb_bwd_sgd_static among them.  So
+// pieces are made short enough, and the second core is left to one segment, where that memory would not do otherwise; where
+// nothing helps (second cores of more than 26 MB) the plain kernels stay as long as it is enough for those.
+bool flex_plan(const Params &p, int64_t L, int64_t K, FlexDims *d)
+{
+    if (fast_bwd_supported(p) || !flex_supported(p) || L <= 0 || L > INT32_MAX - (1 << 21)) return false;   // (ends of segments are ints)
+    const size_t other = 256 + slot_ws_bytes(L, K != 0) + cache_grad_bytes(p, K);
+    for (int most : {FX_SEGMENTS, 1})
+        for (size_t bytes = FX_PIECE_BYTES;; bytes /= 2) {
+            *d = flex_dims(p, L, bytes, most);
+            if (other + flex_ws_least(p, *d, L) <= STATIC_SCRATCH_BYTES) return true;
+            if (d->whole == FX_ROUND) break;
+        }
+    *d = flex_dims(p, L, FX_PIECE_BYTES, FX_SEGMENTS);
+    return other + core_grad_bytes(p) > STATIC_SCRATCH_BYTES;
+}
+
+// what the queries add for it
 size_t flex_ws_bytes(const Params &p, int64_t L)
 {
-    return !fast_bwd_supported(p) && flex_fits(p, L) ? flex_ws_layout(nullptr, p, L).bytes : 0;
+    if (fast_bwd_supported(p) || !flex_supported(p)) return 0;
+    return flex_ws_query(p, flex_dims(p, L, FX_PIECE_BYTES, FX_SEGMENTS), L);
 }
 
 // tiles_possible: false for a call that brings no kept T0 (the tiled backward needs one) or that has a cache
@@ -478,12 +505,20 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     const int64_t core_floats[3] = {(int64_t)p.m1 * p.sA, (int64_t)p.m2 * p.sB, (int64_t)p.m3 * p.sC};
     // the fused step keeps the gradient of the cached rows, and without a specialised kernel the
     // gradients of the cores, in the workspace
-    const size_t gc_bytes = fused && cd.K ? align256((size_t)cd.K * p.N * 4) : 0;
+    const size_t gc_bytes = fused ? cache_grad_bytes(p, cd.K) : 0;
     size_t g_bytes[3] = {0, 0, 0};
-    // shapes without a specialised kernel: the kernels of tt_flex.h where they take the shape and the caller's workspace has
-    // room for them (a workspace is not required of a short call without a cache), else those of tt_generic.h
-    const size_t fx_bytes = !fast && g_fast_path && L > 0 ? flex_ws_bytes(p, L) : 0;
-    const bool flex = fx_bytes && workspace && workspace_bytes >= need_bwd + gc_bytes + fx_bytes;
+    // Shapes without a specialised kernel: the kernels of tt_flex.h where they take the call, in passes as long as the
+    // workspace allows.  A call that brings less than they can do with (tt_emb_bwd without a cache may bring none) still
+    // runs, on those of tt_generic.h.
+    FlexDims fx;
+    int64_t fx_pass = 0;
+    size_t fx_bytes = 0;
+    if (!fast && g_fast_path && workspace && workspace_bytes > need_bwd + gc_bytes && flex_plan(p, L, cd.K, &fx)) {
+        const size_t room = workspace_bytes - need_bwd - gc_bytes;
+        if ((fx_pass = flex_pass(p, fx, L, room)))
+            fx_bytes = flex_ws_layout(nullptr, p, fx, L, fx_pass).bytes;
+    }
+    const bool flex = fx_pass > 0;
     if (fused && !fast && !flex)
         for (int k = 0; k < 3; ++k) g_bytes[k] = align256((size_t)core_floats[k] * 4);
     // long streams with a kept T0: the products of Eq. 4 over tiles of positions, on the matrix cores (tt_bwd_owner.h)
@@ -622,13 +657,13 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
             fast_bwd(p, cores[0], cores[1], cores[2], indices, (int)L, offsets, (int)n_bags, alpha, slot, grad_output,
                      d1, d2, d3, nullptr, nullptr, nullptr, lr, o1, o2, o3, t0, split_ws, nullptr, nullptr, 0, st);
         } else if (flex) {
-            FlexArgs fa{p, flex_dims(p, L), cores[0], cores[1], cores[2], indices, offsets, (int)L, (int)n_bags, alpha, slot, grad_output,
-                        {}, {}, fused ? -lr : 1.f, flex_ws_layout(split_ws, p, L)};
+            FlexArgs fa{p, fx, cores[0], cores[1], cores[2], indices, offsets, (int)L, (int)n_bags, alpha, slot, grad_output,
+                        {}, {}, fused ? -lr : 1.f, flex_ws_layout(split_ws, p, fx, L, fx_pass)};
             for (int k = 0; k < 3; ++k) {
                 fa.src[k] = fused ? cores[k] : grad_cores[k];
                 fa.dst[k] = fused ? cores_out[k] : grad_cores[k];
             }
-            hipError_t ef = flex_bwd(fa, st);
+            hipError_t ef = flex_bwd(fa, fx_pass, st);
             if (ef != hipSuccess) return hip_fail(ef, "backward launch");
         } else if (L > 0) {
             hipLaunchKernelGGL(bwd_generic_kernel, dim3(p.m1 + p.m2 + p.m3), dim3(WG), lds_core, st, p,
@@ -962,8 +997,8 @@ size_t tt_emb_bwd_sgd_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_
     Params p;
     if (check_shape(shape, &p) != TT_OK || L < 0) return 0;
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
-    size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L) + align256((size_t)cache_rows * p.N * 4);
-    n += align256((size_t)p.m1 * p.sA * 4) + align256((size_t)p.m2 * p.sB * 4) + align256((size_t)p.m3 * p.sC * 4);
+    const size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L) + cache_grad_bytes(p, cache_rows) +
+                     core_grad_bytes(p);
     return larger(n, rows_ws_bytes(p, L, cache_rows));
 }
 

@@ -14,6 +14,11 @@
 //      the first position k of the row, and rec[k] says which slices they belong to.
 //   2. flex_sum_kernel: one workgroup per slice of the first and of the third core scans rec for its rows and adds them
 //      up in the order of k; more workgroups add the parts of the second core where S > 1.
+// P and Q of every position of a long stream may need more room than there is: then the two launches are made several
+// times, for as many positions as fit, and the sums so far wait in the workspace.  Results are the same bit for bit: lists
+// are worked off wherever a pass may end, whether one does or not.  That costs a stream beyond FX_PIECE_BYTES something:
+// 100,000 positions, (2,4,4) at rank 24 339 -> 357 us, (2,4,8) at rank 64 1,384 -> 1,598 us; in passes within 32 MiB the
+// same calls take 460 and 6,250 us, with the plain kernels 10,500 and 64,400.
 // No atomics; every sum has a fixed order, so results repeat bit for bit.
 //
 // What bounds it (4,096 positions, (4,4,4) at rank 16): latency.  A workgroup is a chain of index scan, list, gathers of
@@ -47,7 +52,10 @@ struct FlexDims {
     int JB;              // values of j2 per pass
     int R1p, LDA;        // R1 rounded up to 16; row stride of the stacked G1 rows
     uint32_t mgSC;       // ceil(2^32 / sC)
-    int S, seg;          // workgroups per slice of the second core, positions of each
+    int S, seg;          // workgroups per slice of the second core (segments of the stream), positions of each
+    int piece;           // a pass has this many positions or a multiple (of a segment: or what is left of it): whole
+                         // segments, or a part of one.  Streams of up to `whole` positions take one pass.
+    int whole;
     int lds_floats;      // of the tile area
 };
 
@@ -59,9 +67,19 @@ static inline bool flex_supported(const Params &p)
     return p.R1 <= 64 && p.R2 <= 64 && p.n1 <= 16 && p.n2 * p.n3 <= 64 && p.N <= 256 && p.sC <= 1024 && p.n1 * p.cols <= 4096;
 }
 
-static inline FlexDims flex_dims(const Params &p, int64_t L)
+// P, Q and rec of a piece, where the static scratch memory has room for that; of the passes that a queried workspace allows.
+// (The second: (4,4,4) at rank 16 starts a second pass beyond 516,000 positions.)
+constexpr int FX_SEGMENTS = 16;                  // segments of a stream, at most
+constexpr size_t FX_PIECE_BYTES = (size_t)16 << 20, FX_PASS_BYTES = (size_t)256 << 20;
+
+static inline size_t flex_row_bytes(const Params &p) { return 8 + 4 * ((size_t)p.sA + p.sC); }
+
+// piece_bytes: see FX_PIECE_BYTES; most: the largest number of segments
+static inline FlexDims flex_dims(const Params &p, int64_t L, size_t piece_bytes, int most)
 {
     FlexDims d;
+    const int64_t rounds = (int64_t)(piece_bytes / flex_row_bytes(p) / FX_ROUND);
+    d.whole = FX_ROUND * (int)(rounds < 1 ? 1 : rounds);
     d.TP = FX_ROWS / p.n1;
     if (d.TP > FX_TILE / p.sC) d.TP = FX_TILE / p.sC;
     if (d.TP > FX_TILE / p.N) d.TP = FX_TILE / p.N;
@@ -70,9 +88,12 @@ static inline FlexDims flex_dims(const Params &p, int64_t L)
     d.LDA = d.R1p + 4;
     d.mgSC = magic_div((uint32_t)p.sC);
     // a workgroup of its own for every 8,192 positions of a slice (four scan rounds), at most 16
-    const int64_t s = (L + 8191) / 8192;
-    d.S = (int)(s < 1 ? 1 : (s > 16 ? 16 : s));
-    d.seg = (int)(((L + d.S - 1) / d.S + FX_ROUND - 1) / FX_ROUND * FX_ROUND);
+    int64_t s = (L + 8191) / 8192;
+    s = s < 1 ? 1 : (s > most ? most : s);
+    d.seg = (int)(((L + s - 1) / s + FX_ROUND - 1) / FX_ROUND * FX_ROUND);
+    if (d.seg < FX_ROUND) d.seg = FX_ROUND;
+    d.S = (int)(L > 0 ? (L + d.seg - 1) / d.seg : 1);
+    d.piece = d.whole >= d.seg ? d.whole / d.seg * d.seg : d.whole;
     const int tile = FX_ROWS * (d.LDA + 2 * FX_LD) + d.R1p * FX_LD + 2 * ((d.TP * p.sC + 3) & ~3) + d.TP * p.N + 16;
     const int lists = 5 * FX_CAP + 2 * FX_HASH + FX_OFF + 8;   // the unsorted list and its hash table lie in the tile area
     d.lds_floats = tile > lists ? tile : lists;
@@ -80,31 +101,72 @@ static inline FlexDims flex_dims(const Params &p, int64_t L)
 }
 
 struct FlexWs {
-    int2 *rec;           // [L] {i1, i3} of a position that stands for a distinct row, else {-1, -1}
-    float *pbuf, *cbuf;  // [L][sA], [L][sC]: gradients of the first and third core's slices of that row
-    float *part;         // [S][m2][sB]
+    // (n: positions of a pass, at most)
+    int2 *rec;           // [n] {i1, i3} of a position that stands for a distinct row, else {-1, -1}
+    float *pbuf, *cbuf;  // [n][sA], [n][sC]: gradients of the first and third core's slices of that row
+    float *part;         // [segments of a pass][m2][sB]
+    float *acc;          // [m1][sA], [m3][sC], [m2][sB] (S > 1): sums of the passes so far
     size_t bytes;
 };
 
-static inline FlexWs flex_ws_layout(void *ws, const Params &p, int64_t L)
+// n: positions of a pass; several: a call of more than one
+static inline FlexWs flex_ws_layout(void *ws, const Params &p, const FlexDims &d, int64_t n, int parts, bool several)
 {
     FlexWs w;
     char *base = (char *)ws;
     size_t off = 0;
     auto take = [&](size_t bytes) { char *q = base ? base + off : nullptr; off += (bytes + 255) & ~(size_t)255; return q; };
-    const size_t n = L > 0 ? (size_t)L : 1;
-    w.rec = (int2 *)take(n * 8);
-    w.pbuf = (float *)take(n * p.sA * 4);
-    w.cbuf = (float *)take(n * p.sC * 4);
-    w.part = (float *)take((size_t)flex_dims(p, L).S * p.m2 * p.sB * 4);
+    if (n < 1) n = 1;
+    w.rec = (int2 *)take((size_t)n * 8);
+    w.pbuf = (float *)take((size_t)n * p.sA * 4);
+    w.cbuf = (float *)take((size_t)n * p.sC * 4);
+    w.part = (float *)take((size_t)parts * p.m2 * p.sB * 4);
+    w.acc = (float *)take(!several ? 0 : ((size_t)p.m1 * p.sA + (size_t)p.m3 * p.sC + (d.S > 1 ? (size_t)p.m2 * p.sB : 0)) * 4);
     w.bytes = off;
     return w;
 }
 
-// Is the workspace of the two launches reasonable (else the kernels of tt_generic.h, which need next to none)?
-static inline bool flex_fits(const Params &p, int64_t L)
+// for passes of `pass` positions of a stream of L
+static inline FlexWs flex_ws_layout(void *ws, const Params &p, const FlexDims &d, int64_t L, int64_t pass)
 {
-    return flex_supported(p) && flex_ws_layout(nullptr, p, L).bytes <= ((size_t)1 << 30);
+    const int64_t n = L < pass ? L : pass;
+    return flex_ws_layout(ws, p, d, n, n < 1 ? 1 : (int)((n + d.seg - 1) / d.seg), pass < L);
+}
+
+// the least that a call can do with
+static inline size_t flex_ws_least(const Params &p, const FlexDims &d, int64_t L)
+{
+    return flex_ws_layout(nullptr, p, d, L, L <= d.whole ? L : d.piece).bytes;
+}
+
+// what a query answers: enough for passes of FX_PASS_BYTES (or a piece), for every length up to L
+static inline size_t flex_ws_query(const Params &p, const FlexDims &d, int64_t L)
+{
+    int64_t n = (int64_t)(FX_PASS_BYTES / flex_row_bytes(p));
+    if (n < d.whole) n = d.whole;
+    const int64_t parts = (L + 8191) / 8192;                     // (d.S may fall where the segments get longer)
+    return flex_ws_layout(nullptr, p, d, L < n ? L : n, parts < 1 ? 1 : (parts < FX_SEGMENTS ? (int)parts : FX_SEGMENTS), true).bytes;
+}
+
+// Positions of a pass for `room` bytes: all, or as many pieces as fit (whole segments where a piece is shorter); 0: too
+// little room.
+static inline int64_t flex_pass(const Params &p, const FlexDims &d, int64_t L, size_t room)
+{
+    auto fits = [&](int64_t n) { return flex_ws_layout(nullptr, p, d, L, n).bytes <= room; };
+    if (fits(L)) return L;
+    if (L <= d.whole) return 0;
+    if (d.piece >= d.seg || fits(d.seg)) {
+        const int64_t unit = d.piece >= d.seg ? d.piece : d.seg;
+        int64_t n = L / unit * unit;                              // (at most FX_SEGMENTS of them)
+        while (n > 0 && !fits(n)) n -= unit;
+        return n;
+    }
+    int64_t lo = 0, hi = d.seg / d.piece + 1;                     // pieces: lo fit (or none), hi do not
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) / 2;
+        if (mid * d.piece < d.seg && fits(mid * d.piece)) lo = mid; else hi = mid;
+    }
+    return lo * d.piece;
 }
 
 struct FlexArgs {
@@ -120,6 +182,10 @@ struct FlexArgs {
     float *dst[3];
     float mul;
     FlexWs w;
+    // the pass: positions [k0, k1) (whole segments, or a part of one), whether it continues a segment, whether it is the
+    // first and the last one, and whether the parts of the second core are added up after it (never, where S = 1)
+    int k0, k1;
+    bool cont, first, fin, fold;
 };
 
 // V4: n3 = 4 and both ranks are multiples of 4, so that everything moves as float4
@@ -138,7 +204,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = t & 15, q16 = (t >> 4) & 3, gid = t >> 4;
     const int n1 = p.n1, n2 = p.n2, n3 = V4 ? 4 : p.n3, R1 = p.R1, R2 = p.R2, N = p.N, cols = p.cols, sA = p.sA, sC = p.sC, LDA = d.LDA;
     const int i2 = blockIdx.x % p.m2, sp = blockIdx.x / p.m2;
-    const int k_lo = sp * d.seg, k_hi = min(a.L, k_lo + d.seg);
+    const int k_lo = a.k0 + sp * d.seg, k_hi = min(a.k1, k_lo + d.seg);
 
     float *As = fx_lds;                              // [64][LDA]    stacked rows of G1
     float *dT = As + FX_ROWS * LDA;                  // [64][FX_LD]  dT0'
@@ -173,7 +239,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
         cb[i] = (l16 + 16 * i) - cj[i] * R2;
     }
 
-    bool in_part = false;                            // this workgroup's slice gradient so far is in `part`
+    bool in_part = a.cont;                           // this workgroup's slice gradient so far is in `part`
     const float *src2 = a.src[1] + (size_t)i2 * p.sB;
     float *dst2 = a.dst[1] + (size_t)i2 * p.sB;
     float *part = a.w.part + ((size_t)sp * p.m2 + i2) * p.sB;
@@ -491,7 +557,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
                         }
                     };
                     if (jc + jn < n2) put(q);
-                    else put(a.w.cbuf + (size_t)s_k[s_start[d0 + e]] * sC + b * n3 + j3);
+                    else put(a.w.cbuf + (size_t)(s_k[s_start[d0 + e]] - a.k0) * sC + b * n3 + j3);
                 }
             }
             __syncthreads();                                      // the tile area is rewritten
@@ -502,7 +568,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = 16 * prb + 4 * q16 + r;
-                if (row < nrow && aa < R1) a.w.pbuf[(size_t)s_k[s_start[d0 + s_re[row]]] * sA + s_rj[row] * R1 + aa] = accp[i][r];
+                if (row < nrow && aa < R1) a.w.pbuf[(size_t)(s_k[s_start[d0 + s_re[row]]] - a.k0) * sA + s_rj[row] * R1 + aa] = accp[i][r];
             }
         }
     };
@@ -600,7 +666,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
                 int x1, x2, x3;
                 decode_f64(p, row, x1, x2, x3);
                 const bool is_head = (s_heads[i >> 6] >> (i & 63)) & 1;
-                a.w.rec[k] = is_head ? make_int2(x1, x3) : make_int2(-1, -1);
+                a.w.rec[k - a.k0] = is_head ? make_int2(x1, x3) : make_int2(-1, -1);
                 if (is_head) s_row[num] = row;
                 s_k[at] = k; s_bag[at] = bag_find(k);
             }
@@ -647,7 +713,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
         for (int q = 0; q < 4; ++q) {
             const int k = base + w * 256 + q * 64 + lane;
             m[q] = __ballot(k < k_hi && sl[q] < 0 && select_digit_f64(p, 1, (double)row[q]) == (double)i2);
-            if (sl[q] >= 0 && i2 == 0 && k < k_hi) a.w.rec[k] = make_int2(-1, -1);         // a cached position stands for no row
+            if (sl[q] >= 0 && i2 == 0 && k < k_hi) a.w.rec[k - a.k0] = make_int2(-1, -1);  // a cached position stands for no row
             mine += __popcll(m[q]);
         }
         if (lane == 0) s_cnt[parity][w] = mine;
@@ -669,16 +735,18 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
             at += __popcll(m[q]);
         }
         const bool last = base + FX_ROUND >= k_hi;
-        if (cnt > 0 && (last || cnt > FX_CAP - FX_ROUND)) {       // uniform
+        // (a pass that starts inside a segment starts at a piece)
+        const bool end = last || (base - k_lo + FX_ROUND) % d.piece == 0;
+        if (cnt > 0 && (end || cnt > FX_CAP - FX_ROUND)) {        // uniform
             __syncthreads();
-            work(cnt, last);
-            if (last) done = d.S == 1;
+            work(cnt, last && a.fin);
+            if (last) done = d.S == 1 && a.fin;
             cnt = 0;
         }
     }
     if (!done) {                                                  // no positions, or none in the last window
         __syncthreads();
-        if (d.S > 1) {
+        if (d.S > 1 || !a.fin) {
             if (!in_part)
                 for (int x = t; x < p.sB; x += FX_T) part[x] = 0.f;
         } else if (in_part) {
@@ -689,7 +757,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
     }
 }
 
-// Workgroups [0, m1): slices of the first core, [m1, m1 + m3): of the third; the rest: sums of the S parts of the second.
+// Workgroups [0, m1): slices of the first core, [m1, m1 + m3): of the third; the rest (a.fold): sums of the parts of the second.
 __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
 {
     constexpr int CAP = FX_ROUND + 512, NF = 8;
@@ -702,10 +770,15 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
     const int b = blockIdx.x;
     if (b >= p.m1 + p.m3) {
         const int64_t n = (int64_t)p.m2 * p.sB;
+        const int parts = (a.k1 - a.k0 + a.d.seg - 1) / a.d.seg;
+        const bool more = a.k0 >= a.d.seg;                        // earlier segments are in acc
+        float *acc = a.w.acc + (size_t)p.m1 * p.sA + (size_t)p.m3 * p.sC;
         for (int64_t i = (int64_t)(b - p.m1 - p.m3) * WG + t; i < n; i += (int64_t)(gridDim.x - p.m1 - p.m3) * WG) {
-            float s = 0.f;
-            for (int q = 0; q < a.d.S; ++q) s += a.w.part[q * n + i];
-            a.dst[1][i] = fmaf(a.mul, s, a.src[1][i]);
+            float s = a.w.part[i];
+            if (more) s = acc[i] + s;
+            for (int q = 1; q < parts; ++q) s += a.w.part[q * n + i];
+            if (a.fin) a.dst[1][i] = fmaf(a.mul, s, a.src[1][i]);
+            else acc[i] = s;
         }
         return;
     }
@@ -714,7 +787,11 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
     const float *buf = third ? a.w.cbuf : a.w.pbuf;
     const float *src = (third ? a.src[2] : a.src[0]) + (size_t)s * width;
     float *dst = (third ? a.dst[2] : a.dst[0]) + (size_t)s * width;
-    bool any = false;
+    float *acc = a.w.acc + (third ? (size_t)p.m1 * p.sA : 0) + (size_t)s * width;
+    const int n = a.k1 - a.k0;                                    // positions of the pass
+    bool any = !a.first;
+    if (any)                                                      // (added to by the threads that add_up's barriers order)
+        for (int x = t; x < width; x += WG) s_acc[x] = acc[x];
 
     // adds the listed rows up: a power of two of lanes per row, the groups of lanes take every ng-th entry
     auto add_up = [&](int n, auto vw) {
@@ -760,15 +837,15 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
     };
 
     int cnt = 0, parity = 0;
-    for (int base = 0; base < a.L; base += FX_ROUND, parity ^= 1) {
+    for (int base = 0; base < n; base += FX_ROUND, parity ^= 1) {
         int2 rc[FX_ROUND / WG];
 #pragma unroll
-        for (int q = 0; q < FX_ROUND / WG; ++q) rc[q] = a.w.rec[min(base + w * (FX_ROUND / NWAVE) + q * 64 + lane, a.L - 1)];
+        for (int q = 0; q < FX_ROUND / WG; ++q) rc[q] = a.w.rec[min(base + w * (FX_ROUND / NWAVE) + q * 64 + lane, n - 1)];
         uint64_t m[FX_ROUND / WG];
         int mine = 0;
 #pragma unroll
         for (int q = 0; q < FX_ROUND / WG; ++q) {
-            m[q] = __ballot(base + w * (FX_ROUND / NWAVE) + q * 64 + lane < a.L && (third ? rc[q].y : rc[q].x) == s);
+            m[q] = __ballot(base + w * (FX_ROUND / NWAVE) + q * 64 + lane < n && (third ? rc[q].y : rc[q].x) == s);
             mine += __popcll(m[q]);
         }
         if (lane == 0) s_cnt[parity][w] = mine;
@@ -785,15 +862,26 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
             if ((m[q] >> lane) & 1) s_list[at + __popcll(m[q] & lanemask_lt())] = base + w * (FX_ROUND / NWAVE) + q * 64 + lane;
             at += __popcll(m[q]);
         }
-        if (cnt > 0 && (base + FX_ROUND >= a.L || cnt > CAP - FX_ROUND)) {    // uniform
+        const int in_seg = (a.k0 + base) % a.d.seg + FX_ROUND;    // (the segment's length is a multiple of the round's)
+        bool end = base + FX_ROUND >= n;
+        if (a.L > a.d.whole)                                      // uniform
+            end |= a.d.piece >= a.d.seg ? (a.k0 + base + FX_ROUND) % a.d.piece == 0 : in_seg == a.d.seg || in_seg % a.d.piece == 0;
+        if (cnt > 0 && (end || cnt > CAP - FX_ROUND)) {           // uniform
             __syncthreads();
             if ((width & 3) == 0) add_up(cnt, std::integral_constant<int, 4>{});
             else add_up(cnt, std::integral_constant<int, 1>{});
             cnt = 0;
         }
     }
-    if (any) {
-        for (int x = t; x < width; x += WG) dst[x] = fmaf(a.mul, s_acc[x], src[x]);
+    if (!a.fin) {                                                 // (-0 + x is x, whatever x is)
+        __syncthreads();
+        for (int x = t; x < width; x += WG) acc[x] = any ? s_acc[x] : -0.f;
+    } else if (any) {
+        __syncthreads();
+        for (int x = t; x < width; x += WG) {
+            const float v = s_acc[x];
+            dst[x] = v == 0.f ? src[x] : fmaf(a.mul, v, src[x]);  // (a slice without positions in any of several passes: copied)
+        }
     } else if (dst != src) {
         for (int x = t; x < width; x += WG) dst[x] = src[x];
     }
@@ -939,7 +1027,8 @@ static inline void flex_fwd(const Params &p, const float *G1, const float *G2, c
 #undef FX_FWD
 }
 
-static inline hipError_t flex_bwd(const FlexArgs &a, hipStream_t st)
+// pass: what flex_pass says for the workspace that a.w lies in
+static inline hipError_t flex_bwd(FlexArgs a, int64_t pass, hipStream_t st)
 {
     const Params &p = a.p;
     static bool allowed = false;                                  // (one device per process)
@@ -951,11 +1040,23 @@ static inline hipError_t flex_bwd(const FlexArgs &a, hipStream_t st)
         allowed = true;
     }
     const int fin = a.d.S > 1 ? (int)(((int64_t)p.m2 * p.sB + 4 * WG - 1) / (4 * WG)) : 0;
-    const dim3 grid(p.m2 * a.d.S), wg(FX_T);
     const size_t lds = (size_t)a.d.lds_floats * sizeof(float);
-    if (p.n3 == 4 && ((p.R1 | p.R2) & 3) == 0) hipLaunchKernelGGL(flex_g2_kernel<true>, grid, wg, lds, st, a);
-    else hipLaunchKernelGGL(flex_g2_kernel<false>, grid, wg, lds, st, a);
-    hipLaunchKernelGGL(flex_sum_kernel, dim3(p.m1 + p.m3 + (fin < 4096 ? fin : 4096)), dim3(WG), 0, st, a);
+    for (int64_t k = 0; k < a.L; k = a.k1) {
+        const int64_t seg_end = (k / a.d.seg + 1) * a.d.seg;
+        int64_t end = k + pass;
+        if (pass < a.d.seg && end > seg_end) end = seg_end;
+        if (end > a.L) end = a.L;
+        a.k0 = (int)k;
+        a.k1 = (int)end;
+        a.cont = k % a.d.seg != 0;
+        a.first = k == 0;
+        a.fin = end == a.L;
+        a.fold = a.d.S > 1 && (a.fin || end % a.d.seg == 0);
+        const dim3 grid(p.m2 * (int)((end - k + a.d.seg - 1) / a.d.seg)), wg(FX_T);
+        if (p.n3 == 4 && ((p.R1 | p.R2) & 3) == 0) hipLaunchKernelGGL(flex_g2_kernel<true>, grid, wg, lds, st, a);
+        else hipLaunchKernelGGL(flex_g2_kernel<false>, grid, wg, lds, st, a);
+        hipLaunchKernelGGL(flex_sum_kernel, dim3(p.m1 + p.m3 + (!a.fold ? 0 : fin < 4096 ? fin : 4096)), dim3(WG), 0, st, a);
+    }
     return hipGetLastError();
 }
 

@@ -68,13 +68,35 @@ def test_windows_and_several_workgroups_per_slice(bags, longest):
     _check(_table((5, 2, 6), (2, 2, 3), (5, 6), bags, longest, 43, hot=0.2), "%d bags" % bags)
 
 
+# 60,000 positions of the first shape take one pass in 45 MB and whole segments of 8,192 in less; of the second, 4.3 KB each,
+# a segment of 8,192 takes more than 32 MiB and is cut into pieces of 2,048.
+@pytest.mark.parametrize("n,r,bags,longest,sizes", [((2, 4, 4), (24, 24), 20_000, 6, (32 << 20, 38 << 20)), ((16, 1, 16), (64, 3), 3500, 12, (18 << 20, 32 << 20, 64 << 20))])
+def test_several_passes_add_in_the_same_order(n, r, bags, longest, sizes):
+    d = _table((5, 40, 6), n, r, bags, longest, 47, hot=0.1)
+    _check(d, "n %s, %d positions" % (n, d.L))
+    full = B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags)
+    assert full > max(sizes)
+    got = []
+    for size in (full,) + sizes:
+        ws = torch.full((size,), 0x7F, dtype=torch.uint8, device=dev())
+        new = [torch.full_like(x, float("nan")) for x in d.g]
+        B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha, workspace=ws)
+        dg = [torch.full_like(x, 0.25) for x in d.g]
+        B.tt_emb_bwd(d.shape, d.g, d.idx, d.off, d.n_bags, d.go, dg, alpha=d.alpha, workspace=ws)
+        torch.cuda.synchronize()
+        got.append(new + dg)
+    for other in got[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(got[0], other))
+
+
 def test_slices_without_positions_are_copied():
     d = _table((5, 400, 6), (2, 4, 4), (12, 12), 60, 3, 44)
     _check(d, "sparse")
 
 
-def test_with_cache():
-    d = _table((7, 6, 9), (2, 4, 4), (24, 24), 300, 5, 45)
+@pytest.mark.parametrize("bags", [300, 13_000])
+def test_with_cache(bags):
+    d = _table((7, 6, 9), (2, 4, 4), (24, 24), bags, 5, 45)     # one pass, two passes
     rows, counts = np.unique(d.batch.indices, return_counts=True)
     cache, _, _ = d.build_cache(20, rows.astype(np.int64), counts.astype(np.int64))
     keys = ora.cache_select(rows, counts, 20)

@@ -10,6 +10,7 @@ import torch
 from paper_2101_11714_amd import binding as B
 from paper_2101_11714_amd import workloads as W
 from gpu_util import DeviceTable, dev
+from test_gpu_flex import _table
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +83,20 @@ def test_static_scratch_rejects_what_does_not_fit():
     assert e.value.code == -4 and "static" in str(e.value)
     torch.cuda.synchronize()
     assert all(float(o.abs().max()) == 0.0 for o in out)     # nothing was enqueued
+
+
+# Run-time shapes: lengths on either side of what one pass over all positions would have fitted into the scratch memory
+# (24 MB at 20,000 positions of the first shape, 35 MB at 41,000), second cores of 26 MB (the shortest pass fits beside
+# them) and of 30 MB (it does not: the plain kernels in both calls), and a cache.
+@pytest.mark.parametrize("m,n,r,bags,longest,K", [((200, 200, 250), (2, 4, 4), (24, 24), 20_000, 1, 0), ((200, 200, 250), (2, 4, 4), (24, 24), 41_000, 1, 0),
+                                                  ((200, 200, 250), (2, 4, 4), (24, 24), 20_000, 9, 0), ((7, 200, 9), (8, 8, 4), (64, 64), 1500, 3, 0),
+                                                  ((7, 230, 9), (8, 8, 4), (64, 64), 700, 3, 0), ((60, 50, 40), (4, 4, 8), (16, 16), 41_000, 1, 100)])
+def test_static_scratch_equals_workspace_call_for_run_time_shapes(m, n, r, bags, longest, K):
+    d = _table(m, n, r, bags, longest, 48, hot=0.1)
+    caches = None
+    if K:
+        rows, counts = np.unique(d.batch.indices, return_counts=True)
+        caches = [d.build_cache(K, rows.astype(np.int64), counts.astype(np.int64))[0] for _ in range(2)]
+    a, b = _both(d, 0.05, caches)
+    for x, y in zip(a, b):
+        assert np.isfinite(x).all() and np.array_equal(x, y)
