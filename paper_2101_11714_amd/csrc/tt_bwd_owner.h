@@ -669,15 +669,13 @@ __global__ __launch_bounds__(WG) void bo_fix_kernel(BoSegArgs s1, BoSegArgs s3, 
 
 // ---- host side -------------------------------------------------------------------------------------
 
-// compute units of the current device (asked once)
+// compute units of a device (asked once: workspace sizes and the kernels that use them have to agree, on every device)
 static inline int bo_compute_units()
 {
-    static int cus = 0;
-    if (!cus) {
+    static const int cus = [] {
         int dev = 0, n = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
-        else cus = 256;
-    }
+        return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+    }();
     return cus;
 }
 
@@ -731,12 +729,9 @@ static inline hipError_t launch_bo_tiles(const Params &p, const float *G1, const
                                          int ntiles, int *nwg_out, hipStream_t st)
 {
     const size_t lds = bo_lds_bytes<C, ROWS_>();
-    static bool allowed = false;                                             // (one device per process)
-    if (!allowed) {
-        hipError_t e = hipFuncSetAttribute((const void *)bo_tile_kernel<C, ROWS_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
+    static OncePerDevice once;
+    hipError_t e = allow_dynamic_lds(once, (const void *)bo_tile_kernel<C, ROWS_>, lds);
+    if (e != hipSuccess) return e;
     // one or two workgroups per compute unit (what the tile's LDS and registers allow), more only where a workgroup would
     // get more tiles than it can hold descriptors of (the table's size is an upper bound of the tiles in use)
     int nwg = BoCfg<C, ROWS_>::WGS_PER_CU * bo_compute_units();

@@ -4,7 +4,18 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tt_once.h"
+
 namespace tt {
+
+// lets `kernel` have `bytes` of dynamic LDS on the current device; `once`: that kernel's own
+static inline hipError_t allow_dynamic_lds(OncePerDevice &once, const void *kernel, size_t bytes)
+{
+    int dev = -1;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    return (hipError_t)once(dev, [&] { return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); });
+}
 
 constexpr int WG = 256;          // threads per workgroup in every kernel here
 constexpr int WAVE = 64;         // CDNA wavefront width

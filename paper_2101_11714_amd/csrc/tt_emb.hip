@@ -167,15 +167,11 @@ int hip_fail(hipError_t e, const char *what)
 
 size_t lds_limit()
 {
-    static size_t lim = 0;
-    if (!lim) {
+    static const size_t lim = [] {
         int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
-            lim = (size_t)v;
-        else
-            lim = 64 * 1024;
-    }
+        return hipGetDevice(&dev) == hipSuccess &&
+               hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0 ? (size_t)v : (size_t)64 * 1024;
+    }();
     return lim;
 }
 

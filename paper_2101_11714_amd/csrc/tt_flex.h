@@ -1031,14 +1031,10 @@ static inline void flex_fwd(const Params &p, const float *G1, const float *G2, c
 static inline hipError_t flex_bwd(FlexArgs a, int64_t pass, hipStream_t st)
 {
     const Params &p = a.p;
-    static bool allowed = false;                                  // (one device per process)
-    if (!allowed) {
-        for (const void *f : {(const void *)flex_g2_kernel<true>, (const void *)flex_g2_kernel<false>}) {
-            hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, FX_MAX_LDS);
-            if (e != hipSuccess) return e;
-        }
-        allowed = true;
-    }
+    const bool v4 = p.n3 == 4 && ((p.R1 | p.R2) & 3) == 0;
+    static OncePerDevice once[2];
+    hipError_t e = allow_dynamic_lds(once[v4], v4 ? (const void *)flex_g2_kernel<true> : (const void *)flex_g2_kernel<false>, FX_MAX_LDS);
+    if (e != hipSuccess) return e;
     const int fin = a.d.S > 1 ? (int)(((int64_t)p.m2 * p.sB + 4 * WG - 1) / (4 * WG)) : 0;
     const size_t lds = (size_t)a.d.lds_floats * sizeof(float);
     for (int64_t k = 0; k < a.L; k = a.k1) {
@@ -1053,7 +1049,7 @@ static inline hipError_t flex_bwd(FlexArgs a, int64_t pass, hipStream_t st)
         a.fin = end == a.L;
         a.fold = a.d.S > 1 && (a.fin || end % a.d.seg == 0);
         const dim3 grid(p.m2 * (int)((end - k + a.d.seg - 1) / a.d.seg)), wg(FX_T);
-        if (p.n3 == 4 && ((p.R1 | p.R2) & 3) == 0) hipLaunchKernelGGL(flex_g2_kernel<true>, grid, wg, lds, st, a);
+        if (v4) hipLaunchKernelGGL(flex_g2_kernel<true>, grid, wg, lds, st, a);
         else hipLaunchKernelGGL(flex_g2_kernel<false>, grid, wg, lds, st, a);
         hipLaunchKernelGGL(flex_sum_kernel, dim3(p.m1 + p.m3 + (!a.fold ? 0 : fin < 4096 ? fin : 4096)), dim3(WG), 0, st, a);
     }

@@ -276,12 +276,9 @@ static inline hipError_t launch_fwd_owner(const Params &p, const float *G1, cons
                                           float *t0_out, hipStream_t st)
 {
     const size_t lds = fo_lds_bytes<C>();
-    static bool allowed = false;                                             // (one device per process)
-    if (!allowed) {
-        hipError_t e = hipFuncSetAttribute((const void *)fwd_owner_kernel<C>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
+    static OncePerDevice once;
+    hipError_t e = allow_dynamic_lds(once, (const void *)fwd_owner_kernel<C>, lds);
+    if (e != hipSuccess) return e;
     // How many of the table's entries are in use is only known on the device (cached positions are in no list):
     // at most FO_GRID_TILES tiles are started, each workgroup goes on to later tiles while there are any.
     const int ntiles = fwd_owner_tiles(p, L);

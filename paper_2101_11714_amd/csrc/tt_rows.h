@@ -615,13 +615,9 @@ static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int
     const int nblk = rw_hist_blocks(L), nw = rw_windows(p, L), m13 = p.m1 + p.m3;
     auto bits_of = [](int m) { int b = 0; while ((1 << b) < m) ++b; return b; };
     const size_t lds = (size_t)m13 * 4 + (size_t)RW_NW * m13 * 2;              // at most 80 KB
-    static bool allowed = false;                                               // (one device per process)
-    if (!allowed) {
-        hipError_t e = hipFuncSetAttribute((const void *)rw_lists_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
+    static OncePerDevice once;
+    hipError_t e = allow_dynamic_lds(once, (const void *)rw_lists_kernel, RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(rw_count_kernel, dim3(nblk), dim3(WG), 0, st, p, indices, L, ws);
     hipLaunchKernelGGL(rw_scatter_kernel, dim3(nblk), dim3(WG), 0, st, p, indices, L, nblk, bits_of(p.m2), ws);
     hipLaunchKernelGGL(rw_group_kernel, dim3(nw), dim3(RW_T), 0, st, p, L, rw_win(L), offsets, n_bags, ws);

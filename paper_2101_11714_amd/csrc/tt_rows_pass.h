@@ -793,12 +793,9 @@ static inline hipError_t launch_rw_fwd(const Params &p, const float *G1, const f
                                        const float *alpha, float *out, float *t0, const RowsWs &ws, hipStream_t st)
 {
     const size_t lds = (size_t)RfCfg<C, ROWS_>::LDS_FLOATS * sizeof(float);
-    static bool allowed = false;                                              // (one device per process)
-    if (!allowed) {
-        hipError_t e = hipFuncSetAttribute((const void *)rw_fwd_kernel<C, ROWS_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
+    static OncePerDevice once;
+    hipError_t e = allow_dynamic_lds(once, (const void *)rw_fwd_kernel<C, ROWS_>, lds);
+    if (e != hipSuccess) return e;
     // how many tiles are in use is only known on the device: some workgroups find none, or more than one
     const int tiles = rw_tiles(p, L, ROWS_ / C::N1), started = tiles < 2048 ? tiles : 2048;
     hipLaunchKernelGGL((rw_fwd_kernel<C, ROWS_>), dim3(started * C::N2), dim3(WG), lds, st, p, G1, G2, G3, (int)L, ws.rec, ws.gkb, ws.gu,
@@ -825,12 +822,9 @@ static inline hipError_t launch_rw_bwd(const Params &p, const float *G1, const f
                                        hipStream_t st)
 {
     const size_t lds = bo_lds_bytes<C, ROWS_>();
-    static bool allowed = false;                                              // (one device per process)
-    if (!allowed) {
-        hipError_t e = hipFuncSetAttribute((const void *)rw_tile_kernel<C, ROWS_>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        allowed = true;
-    }
+    static OncePerDevice once;
+    hipError_t e = allow_dynamic_lds(once, (const void *)rw_tile_kernel<C, ROWS_>, lds);
+    if (e != hipSuccess) return e;
     const int nwg = rw_tile_wgs(p, L), per = (C::sB / 4 + 2 * RW_T - 1) / (2 * RW_T);
     constexpr int MT = C::N > 16 ? 512 : 256;
     hipLaunchKernelGGL((rw_merge_kernel<C::N, MT>), dim3((unsigned)((L + RM_ROWS - 1) / RM_ROWS)), dim3(MT), 0, st, (int)L, ws.rec, ws.gkb, alpha, go,
