@@ -389,14 +389,11 @@ def tt_cache_build(shape: TTShape, cores: Sequence[torch.Tensor], cand_rows: tor
 
 def tt_cache_refill(shape: TTShape, cores: Sequence[torch.Tensor], cand_rows: torch.Tensor,
                     cand_counts: torch.Tensor, cache: Cache, workspace: Optional[torch.Tensor] = None) -> Cache:
-    _dev(cand_rows, torch.int64)
-    _dev(cand_counts, torch.int64)
-    n = cand_rows.numel()
-    assert cand_counts.numel() == n
     if workspace is None:
-        workspace = _ws(lib().tt_cache_refill_workspace_bytes(C.byref(shape), n, cache.K), cand_rows.device)
-    _check(lib().tt_cache_refill(C.byref(shape), _ptr_array(cores), _ptr(cand_rows), _ptr(cand_counts), n, cache.ref(),
-                                 _ptr(workspace), workspace.numel(), _stream()))
+        workspace = _ws(lib().tt_cache_refill_workspace_bytes(C.byref(shape), cand_rows.numel(), cache.K), cand_rows.device)
+    rc = _call.cache_refill(shape, cores, cand_rows, cand_counts, cache, workspace)
+    if rc:
+        _check(rc)
     return cache
 
 

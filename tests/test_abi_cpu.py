@@ -272,3 +272,10 @@ def test_tensors_without_storage_raise():
         idx = torch.zeros((2, 8), dtype=torch.int64, device="cuda")
         with pytest.raises(RuntimeError, match="storage"):
             torch.func.vmap(lambda i, o: B.tt_emb_fwd(good_shape(), cores, i, None, 8, o))(idx, out)
+
+
+def test_every_function_of_the_extension_has_a_caller():
+    source = open(os.path.join(ROOT, "paper_2101_11714_amd", "binding.py")).read()
+    B._call.emb_fwd                                                                                  # loads it
+    functions = {k for k, v in vars(B._call).items() if callable(v)}
+    assert functions == set(re.findall(r"_call\.([a-z_0-9]+)\(", source))
