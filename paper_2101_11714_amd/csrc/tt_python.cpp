@@ -62,14 +62,18 @@ struct Args {
     uint8_t *u8(int i, int64_t *n = nullptr) { return (uint8_t *)dev(a[i], at::kByte, n); }
     float *f32_or_null(int i, int64_t *n = nullptr) { return ok && a[i] != Py_None ? f32(i, n) : nullptr; }
 
-    // an array of bytes, whatever its type
+    // a contiguous array of the device, of whatever type (or pinned host memory, which the device reads and writes as well)
     void *bytes_or_null(int i, size_t *n)
     {
         *n = 0;
         if (!ok || a[i] == Py_None) return nullptr;
         const at::Tensor *t = tensor(a[i]);
         if (!t) return nullptr;
-        *n = (size_t)t->numel();
+        if (!t->is_contiguous() || !(t->is_cuda() || t->is_pinned())) {
+            fail("a contiguous workspace on the device is expected");
+            return nullptr;
+        }
+        *n = (size_t)t->numel() * t->element_size();
         return t->data_ptr();
     }
 
