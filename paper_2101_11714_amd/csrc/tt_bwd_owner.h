@@ -415,7 +415,13 @@ __device__ __forceinline__ void bo_g2_finish_body(int vblock, const BoFinishArgs
 // wave; the kernels take the smallest power of two from 8 on with which the items in the range (known on the device
 // only: cached positions have no items) still fit that many waves.
 // (measured: 8,192 positions of the (4,4,4) shape at rank 64, 64 -> 8 items: 77 -> 27 us; 204,800 positions: 64 is best)
-static inline int bo_seg_st(int64_t L) { return L >= 131072 ? 64 : (L >= 65536 ? 32 : (L >= 32768 ? 16 : 8)); }
+constexpr int64_t BO_SEG_STEPS[3] = {32768, 65536, 131072};
+static inline int bo_seg_st(int64_t L)
+{
+    int st = 8;
+    for (int64_t step : BO_SEG_STEPS) st <<= L >= step;
+    return st;
+}
 __device__ __forceinline__ int bo_seg_st_dev(int n, int cap)
 {
     int st = 8;

@@ -207,11 +207,17 @@ size_t fwd_bwd_ws_bytes(const Params &p, int64_t L, int64_t K)
 // several workgroups and, for the (4,4,4) shapes, the per-row G1 gradients
 size_t split_ws_bytes(const Params &p, int64_t L, bool grouped, bool tiles_possible = true);
 
-// enough for either way of running the backward
-size_t split_ws_bytes_max(const Params &p, int64_t L)
+size_t larger(size_t a, size_t b) { return a > b ? a : b; }
+
+// Enough for either way of running the backward with a cache of K rows, for every length up to L (the tiled backward needs
+// less again from the lengths on at which its sums take more items per wave).
+size_t split_ws_bytes_max(const Params &p, int64_t L, int64_t K)
 {
-    const size_t a = split_ws_bytes(p, L, false), b = split_ws_bytes(p, L, true);
-    return a > b ? a : b;
+    const bool tiles = K ? g_bwd_tiles != 0 : !rw_supported(p);       // (without a cache the passes over distinct rows come first)
+    size_t bytes = larger(split_ws_bytes(p, L, false), split_ws_bytes(p, L, true, tiles));
+    for (int64_t step : BO_SEG_STEPS)
+        if (tiles && step <= L) bytes = larger(bytes, split_ws_bytes(p, step - 1, true, true));
+    return bytes;
 }
 
 // gradients of the cached rows, and of the three cores, where a call keeps them in the workspace
@@ -287,7 +293,13 @@ static size_t rows_ws_bytes(const Params &p, int64_t L, int64_t K)
 {
     return !K && rw_supported(p) ? 256 + rw_ws_layout(nullptr, p, L, rw_tile_wgs(p, L)).bytes : 0;
 }
-static size_t larger(size_t a, size_t b) { return a > b ? a : b; }
+// What the queries say for it, enough for every length up to L: nothing below the first length at which a step can group its
+// positions, and from RW_LONG_MIN_L on, where longer windows need fewer counters, not less than just below it.
+static size_t rows_ws_query(const Params &p, int64_t L, int64_t K)
+{
+    if (K || !rw_supported(p) || !bwd_tiles_wanted(p, L) || (g_fast_path == 1 && L < group_min_l(p, 0, true, true))) return 0;
+    return larger(rows_ws_bytes(p, L, K), L >= RW_LONG_MIN_L ? rows_ws_bytes(p, RW_LONG_MIN_L - 1, K) : 0);
+}
 
 size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows)
 {
@@ -295,7 +307,7 @@ size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags
     Params p;
     if (check_shape(shape, &p) != TT_OK || L < 0) return 0;
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
-    return larger(fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L), rows_ws_bytes(p, L, cache_rows));
+    return larger(fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L, cache_rows) + flex_ws_bytes(p, L), rows_ws_query(p, L, cache_rows));
 }
 
 size_t tt_emb_dedup_workspace_bytes(int64_t L)
@@ -993,9 +1005,9 @@ size_t tt_emb_bwd_sgd_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_
     Params p;
     if (check_shape(shape, &p) != TT_OK || L < 0) return 0;
     if (cache_rows < 0 || cache_rows > (1 << 24)) return 0;
-    const size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L) + flex_ws_bytes(p, L) + cache_grad_bytes(p, cache_rows) +
+    const size_t n = fwd_bwd_ws_bytes(p, L, cache_rows) + split_ws_bytes_max(p, L, cache_rows) + flex_ws_bytes(p, L) + cache_grad_bytes(p, cache_rows) +
                      core_grad_bytes(p);
-    return larger(n, rows_ws_bytes(p, L, cache_rows));
+    return larger(n, rows_ws_query(p, L, cache_rows));
 }
 
 int tt_emb_sgd_update(const tt_shape_t *shape, float *const cores[3], float *const grad_cores[3],

@@ -68,7 +68,8 @@ static inline bool rw_supported(const Params &p)
 // Positions per window.  Longer windows merge more; shorter ones cut a hot row's positions into pieces that different
 // workgroups handle, which is what short streams need (8,192 positions, a hot row of 740: one workgroup added these up
 // for 13 us).
-static inline int rw_win(int64_t L) { return L < 65536 ? 256 : RW_WIN; }
+constexpr int64_t RW_LONG_MIN_L = 65536;
+static inline int rw_win(int64_t L) { return L < RW_LONG_MIN_L ? 256 : RW_WIN; }
 static inline int rw_windows(const Params &p, int64_t L) { return (int)(L / rw_win(L)) + p.m2; }
 static inline int rw_tiles(const Params &p, int64_t L, int tp) { return (int)(L / tp) + rw_windows(p, L); }
 static inline int rw_pieces(const Params &p, int64_t L) { return (int)(2 * (L / RW_PIECE)) + p.m1 + p.m3; }

@@ -279,3 +279,36 @@ def test_every_function_of_the_extension_has_a_caller():
     B._call.emb_fwd                                                                                  # loads it
     functions = {k for k, v in vars(B._call).items() if callable(v)}
     assert functions == set(re.findall(r"_call\.([a-z_0-9]+)\(", source))
+
+
+def _queries(m, n, r, L, K):
+    s = B.make_shape(min(m[0] * m[1] * m[2], 2**31 - 1), m, n, (1, r, r, 1))
+    return [B.workspace_bytes(s, L, L, K), B.bwd_sgd_workspace_bytes(s, L, L, K)]
+
+
+@pytest.mark.parametrize("mode", [1, 2, 3])
+@pytest.mark.parametrize("K", [0, 1000])
+def test_workspace_for_a_length_is_enough_for_every_shorter_one(K, mode):
+    # on both sides of every length at which a path, a window or a split changes
+    lengths = sorted({0, 1} | {b + d for b in (64, 256, 2048, 4096, 6144, 8192, 10_240, 12_288, 16_384, 24_576, 28_672, 32_768, 40_960, 65_536, 131_072,
+                                              262_144, 524_288, 2_000_000) for d in (-1, 0, 1)} | {2_100_000, 16_000_000})
+    old = B.set_fast_path(mode)
+    try:
+        for m, n, r in [((200, 220, 250), (2, 2, 4), 8), ((200, 220, 250), (2, 2, 4), 32), ((200, 220, 250), (2, 2, 4), 64), ((200, 200, 1000), (4, 4, 4), 32),
+                        ((200, 200, 1000), (4, 4, 4), 64), ((3000, 200, 2000), (4, 4, 4), 64), ((20, 1200, 20), (2, 2, 4), 32),
+                        ((200, 200, 250), (4, 4, 4), 16), ((200, 200, 250), (2, 4, 4), 24), ((200, 200, 250), (4, 4, 8), 64), ((6, 5, 7), (3, 2, 5), 7)]:
+            last = [0, 0]
+            for L in lengths:
+                now = _queries(m, n, r, L, K)
+                assert now[0] >= last[0] and now[1] >= last[1], (m, n, r, L, last, now)
+                last = now
+    finally:
+        B.set_fast_path(old)
+
+
+def test_workspace_holds_nothing_that_no_call_uses():
+    # Kaggle-shaped, rank 32, 2,048 positions: the scanning owners' alone (7.6 MB with the row passes', which start at 16,384);
+    # 40 M rows, (4,4,4), rank 64, 65,535 positions: the row passes' 124 MB and the grouped lists' (272 MB with the position tiles',
+    # which such a call never takes)
+    assert _queries((200, 220, 250), (2, 2, 4), 32, 2048, 0)[1] < 3e6
+    assert _queries((200, 200, 1000), (4, 4, 4), 64, 65_535, 0)[1] < 140e6

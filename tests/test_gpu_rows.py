@@ -50,10 +50,10 @@ def _table(kind, n, R, L, n_bags, seed):
     return DeviceTable(W.Workload("rows", (t,), n_bags, (0, 9), "uniform", 0.0, "normal0.1", seed), batch=batch)
 
 
-def _check(d, name, sample=None):
+def _check(d, name, ws=None):
     assert B.fwd_uses_lists(d.shape, d.L, 0, True)
     b = d.batch
-    ws = torch.full((B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
+    ws = ws if ws is not None else torch.full((B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
     steps = []
     for _ in range(2):
         out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
@@ -113,3 +113,11 @@ def test_rank_64_by_choice(n, L):
         assert_close(out.cpu().numpy(), out_want, "forward, workspace %d" % size)
         for k in range(3):
             assert_close(new[k].cpu().numpy(), want[k], "core %d, workspace %d" % (k + 1, size))
+
+
+def test_one_workspace_on_either_side_of_the_longer_windows():
+    # 65,536 positions on: windows of 2,048 instead of 256, and fewer counters; a workspace for the longer batch does for the shorter
+    a, b = _table("hot row", (2, 2, 4), 32, 65_536, 9_000, 64), _table("hot row", (2, 2, 4), 32, 65_535, 9_000, 65)
+    ws = torch.full((B.bwd_sgd_workspace_bytes(a.shape, a.L, a.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
+    for d in (a, b):
+        _check(d, "%d positions" % d.L, ws=ws)
