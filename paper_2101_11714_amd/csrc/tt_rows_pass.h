@@ -555,17 +555,20 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(BoCfg<C, ROW
 }
 
 // ---- the sums that finish the three cores -----------------------------------------------------------------------------
-// Workgroups [0, m1 + m3): the first RW_PIECE rows of a slice of the first (third) core; the next RS_EXTRA: what slices have
-// beyond that; the rest: the parts of the slices of the second core.  A slice of one piece (nearly all: equal rows are one)
-// is finished on the spot; of a longer one every piece leaves a partial sum and the workgroup that arrives last adds them, in
-// their order.
-constexpr int RS_EXTRA = 64;
+// Workgroups [0, m1 + m3): the first piece (rw_piece rows) of a slice of the first (third) core; the next `extra`: what slices
+// have beyond that; the rest: the parts of the slices of the second core.  A slice of one piece (nearly all, where rows repeat:
+// equal rows are one) is finished on the spot; of a longer one every piece leaves a partial sum and the workgroup that arrives
+// last adds them, in their order.  How many extra pieces there are is only known on the device: as many workgroups are started
+// for them as there can be, or as the device runs at once (with 64 of them a step of 300,000 uniform
+// positions, Kaggle-shaped at rank 32, took 901 us, 600 of them here; so it takes 290).
+constexpr int RS_MAX_EXTRA = 1024;
 
 struct RsArgs {
     const float *src[3];
     float *dst[3];
     float mul;
     int nwg;                 // workgroups of the tile kernel
+    int piece, extra;        // rows of a piece (RW_PIECE at most); workgroups for the extra pieces
 };
 
 template <typename C>
@@ -580,10 +583,10 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
     __shared__ int s_tmp[RW_NW], s_at[3], s_last;
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), m13 = p.m1 + p.m3;
 
-    if ((int)blockIdx.x >= m13 + RS_EXTRA) {
+    if ((int)blockIdx.x >= m13 + a.extra) {
         // dst[i2] = src[i2] + mul * (parts of slice i2, in the order of their workgroups)
         constexpr int FIN = 2 * RW_T, PER = (sB4 + FIN - 1) / FIN, NP = 8;
-        const int vb = blockIdx.x - m13 - RS_EXTRA, i2 = vb / PER, e0 = (vb % PER) * FIN + t;
+        const int vb = blockIdx.x - m13 - a.extra, i2 = vb / PER, e0 = (vb % PER) * FIN + t;
         if (i2 >= p.m2) return;
         const int tb = ws.tile_base[i2], te = ws.tile_base[i2 + 1], ch = bo_chunk(ws.tile_base[p.m2], a.nwg);
         const float4 *src = reinterpret_cast<const float4 *>(a.src[1]) + (size_t)i2 * sB4;
@@ -630,7 +633,7 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
         for (int q = 0; q < PB; ++q) {
             const int bin = t * PB + q;
             const int len = bin < m13 ? ws.off13[bin + 1] - ws.off13[bin] : 0;
-            v[q] = len > RW_PIECE ? (len - 1) / RW_PIECE : 0;
+            v[q] = len > a.piece ? (len - 1) / a.piece : 0;
             sum += v[q];
         }
         int total;
@@ -729,9 +732,17 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
     // a partial sum in place `slot`; whoever arrives last adds all of the slice's up (extra: its first extra piece, -1: unknown)
     auto leave = [&](int bin, float4 sum, int slot, int extra) {
         const bool third = bin >= p.m1;
-        const int w4 = third ? R : sA4, len = ws.off13[bin + 1] - ws.off13[bin], np = (len + RW_PIECE - 1) / RW_PIECE;
-        if (t < w4) reinterpret_cast<float4 *>(ws.part13 + (size_t)slot * WMAX)[t] = sum;
-        __threadfence();
+        const int w4 = third ? R : sA4, len = ws.off13[bin + 1] - ws.off13[bin], np = (len + a.piece - 1) / a.piece;
+        if (t < w4) {
+            float *to = ws.part13 + (size_t)slot * WMAX + 4 * t;
+            __hip_atomic_store(to + 0, sum.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(to + 1, sum.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(to + 2, sum.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(to + 3, sum.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // The sum has to be where the whole device meets before this workgroup counts itself as arrived; a barrier alone does not
+        // wait for that.  (The stores and the loads below go there by themselves, so no fence has to write the caches back.)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (t == 0) {
             s_last = atomicAdd(&ws.arrived[bin], 1u) == (uint32_t)(np - 1);
@@ -739,7 +750,6 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
         }
         __syncthreads();
         if (!s_last) return;                                                  // uniform
-        __threadfence();
         if (extra < 0) {
             find_extra(0, bin);
             extra = s_at[1];
@@ -758,19 +768,19 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
 
     if ((int)blockIdx.x < m13) {
         const int bin = blockIdx.x, i0 = ws.off13[bin], i1 = ws.off13[bin + 1];
-        const float4 sum = add_up(bin, i0, min(i1, i0 + RW_PIECE));
-        if (i1 - i0 <= RW_PIECE) finish(bin, sum, i1 == i0);
+        const float4 sum = add_up(bin, i0, min(i1, i0 + a.piece));
+        if (i1 - i0 <= a.piece) finish(bin, sum, i1 == i0);
         else leave(bin, sum, bin, -1);
         return;
     }
-    for (int x = blockIdx.x - m13;; x += RS_EXTRA) {
+    for (int x = blockIdx.x - m13;; x += a.extra) {
         __syncthreads();
         find_extra(x, -1);
         if (x >= s_at[2]) return;                                             // uniform
         const int bin = s_at[0], first = s_at[1];
-        const int i0 = ws.off13[bin] + (x - first + 1) * RW_PIECE;
+        const int i0 = ws.off13[bin] + (x - first + 1) * a.piece;
         __syncthreads();
-        const float4 sum = add_up(bin, i0, min(ws.off13[bin + 1], i0 + RW_PIECE));
+        const float4 sum = add_up(bin, i0, min(ws.off13[bin + 1], i0 + a.piece));
         leave(bin, sum, m13 + x, first);
     }
 }
@@ -831,8 +841,9 @@ static inline hipError_t launch_rw_bwd(const Params &p, const float *G1, const f
                        ws.dym);
     hipLaunchKernelGGL((rw_tile_kernel<C, ROWS_>), dim3(nwg), dim3(WG), lds, st, p, G1, G2, G3, (int)L, ws.dym, ws.rec, ws.tiles, ws.tile_base,
                        ws.part2, ws.pbuf, src[1], dst[1], mul);
-    const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg};
-    hipLaunchKernelGGL((rw_sum_kernel<C>), dim3(p.m1 + p.m3 + RS_EXTRA + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
+    const int most = rw_extra(p, L), extra = most < RS_MAX_EXTRA ? most : RS_MAX_EXTRA;
+    const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg, rw_piece(p, L), extra};
+    hipLaunchKernelGGL((rw_sum_kernel<C>), dim3(p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
                        ws.dym, ws.pbuf, ws.l13);
     return hipGetLastError();
 }

@@ -40,8 +40,8 @@ def _rows(kind, t, L, rng):
     return np.minimum(idx, t.num_rows - 1).astype(np.int64)
 
 
-def _table(kind, n, R, L, n_bags, seed):
-    t = W.TableShape(30 * 20 * 40 - 3, (30, 20, 40), n, (1, R, R, 1))
+def _table(kind, n, R, L, n_bags, seed, m=(30, 20, 40)):
+    t = W.TableShape(m[0] * m[1] * m[2] - 3, m, n, (1, R, R, 1))
     rng = np.random.default_rng([seed, L])
     idx = _rows(kind, t, L, rng)
     cuts = np.sort(rng.integers(0, L + 1, n_bags - 1))
@@ -88,6 +88,11 @@ def test_small_streams(n, R, kind, L, always_rows):
 def test_long_streams_with_long_windows(kind):
     # 70,000 positions: windows of 2,048, by the library's own choice
     _check(_table(kind, (2, 2, 4), 32, 70_000, 9_000, 62), "%s long" % kind)
+
+
+def test_more_pieces_of_the_final_sums_than_workgroups():
+    # some 340,000 distinct rows on 70 slices of the first and third core: about 1,300 pieces of 512 beyond the first ones
+    _check(_table("spread", (2, 2, 4), 32, 400_000, 50_000, 64, m=(30, 1000, 40)), "many pieces")
 
 
 @pytest.mark.parametrize("n,L", [((4, 4, 4), 6144), ((4, 4, 4), 10_240), ((2, 2, 4), 12_288), ((2, 2, 4), 17_001)])
