@@ -1,6 +1,7 @@
-"""The backward pass that works on tiles of positions on the matrix cores (the grouped backward with a kept T0 and no
-cache; tt_emb_debug_set_fast_path(3) forces it for every length and with a cache): against the oracle, against the
-list owners, and for bit-identical repeats."""
+"""The grouped backward with a kept T0 on the matrix cores (tt_emb_debug_set_fast_path(3) forces it for every length and
+with a cache): against the oracle, against the list owners, and for bit-identical repeats.  Without a cache the
+workloads' tables go through the passes over distinct rows (tt_rows.h); the tiles of positions (tt_bwd_owner.h) run with
+a cache, and without one for tables of more than 4,096 slices in the first and third core (WIDE)."""
 import dataclasses
 
 import numpy as np
@@ -16,6 +17,16 @@ from test_gpu_fwd_owner import SHAPES, _ragged
 pytestmark = pytest.mark.gpu
 
 
+# more slices in the first and third core than the passes over distinct rows take; few in the second, so that tiles fill up
+WIDE = [((2, 2, 4), 32), ((2, 2, 4), 64), ((4, 4, 4), 32), ((4, 4, 4), 64)]
+
+
+def _wide(n, R, seed, n_bags=260, longest=40):
+    t = W.TableShape(2100 * 6 * 2000 - 1, (2100, 6, 2000), n, (1, R, R, 1))
+    return DeviceTable(W.Workload("wide", (t,), n_bags, (0, longest), "uniform", 0.0, "normal0.1", seed),
+                       batch=_ragged(t, seed, n_bags=n_bags, longest=longest))
+
+
 @pytest.fixture
 def always_grouped():
     old = B.set_fast_path(3)                      # groups whatever the number of positions, then the tile kernels
@@ -26,7 +37,17 @@ def always_grouped():
 @pytest.mark.parametrize("name,table", SHAPES)
 def test_gradients_and_fused_step_match_oracle(name, table, always_grouped):
     wl = W.WORKLOADS[name]
-    d = DeviceTable(wl, table=table, batch=_ragged(wl.tables[table], 41 + table))
+    _gradients_and_step(DeviceTable(wl, table=table, batch=_ragged(wl.tables[table], 41 + table)), name)
+
+
+# (4,4,4) at rank 64 works on 64 stacked rows where the forward pass does not share the table of tiles: below 32,768 positions
+# in two calls by the library's own choice, see test_wide_tables_in_two_calls
+@pytest.mark.parametrize("n,R", WIDE)
+def test_wide_tables_without_a_cache(n, R, always_grouped):
+    _gradients_and_step(_wide(n, R, 43), "wide %s R %d" % (n, R))
+
+
+def _gradients_and_step(d, name):
     _, t0 = d.fwd_keep_t0()
     ref, _ = ora.bwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets, d.batch.grad_output, alpha=d.batch.alpha)
     dg, _ = d.bwd(t0=t0)
@@ -120,8 +141,8 @@ def _full_size(name):
 @pytest.mark.parametrize("name,n_bags,longest", [("terabyte_r64", 800, 24), ("sweep_r32", 1800, 24), ("sweep_r64", 1800, 24)])
 def test_two_call_form_groups_earlier_and_matches_oracle(name, n_bags, longest):
     """The default kernel selection: with a kept T0 and no cache the pair tt_emb_bwd_prepare + tt_emb_bwd_sgd_prepared
-    works on tiles from lengths on at which the one call still runs the slice owners (for the Terabyte-shaped table
-    on tiles of 64 stacked rows).  Ragged, weighted bags with a hot row; both forms against the oracle, the pair twice."""
+    works on distinct rows from lengths on at which the one call still runs the slice owners.
+    Ragged, weighted bags with a hot row; both forms against the oracle, the pair twice."""
     wl = W.WORKLOADS[name]
     t = wl.tables[0]
     d = DeviceTable(wl, batch=_ragged(t, 7, n_bags=n_bags, longest=longest))
@@ -139,10 +160,34 @@ def test_two_call_form_groups_earlier_and_matches_oracle(name, n_bags, longest):
         assert torch.equal(two[k], again[k]), "core %d differs between two runs of the pair" % (k + 1)
 
 
+@pytest.mark.parametrize("n,R,n_bags", [((4, 4, 4), 64, 800), ((4, 4, 4), 32, 800), ((2, 2, 4), 64, 1700), ((2, 2, 4), 32, 3300)])
+def test_wide_tables_in_two_calls(n, R, n_bags):
+    """The library's own choice for a table too wide for the passes over distinct rows: the pair works on tiles of positions,
+    (4,4,4) at rank 64 on those of 64 stacked rows, and the forward pass between the two calls is the wave per bag, or from
+    32,768 positions on (the last table) the one that works from the lists."""
+    d = _wide(n, R, 44, n_bags=n_bags, longest=24)
+    assert B.bwd_has_prepass(d.shape, d.L, 0, True) and B.fwd_uses_lists(d.shape, d.L, 0, True) == (d.L >= 32_768)
+    assert (d.L >= 32_768) == (n_bags == 3300)
+    ws = torch.full((B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
+    out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+    t0 = torch.full((d.L, B.t0_floats(d.shape)), float("nan"), dtype=torch.float32, device=dev())
+    new = [torch.full_like(x, float("nan")) for x in d.g]
+    B.tt_emb_bwd_prepare(d.shape, d.idx, d.off, d.n_bags, workspace=ws, kept_t0=True)
+    B.tt_emb_fwd_prepared(d.shape, d.g, d.idx, d.off, d.n_bags, out, ws, t0=t0, alpha=d.alpha)
+    B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha, workspace=ws, t0=t0, prepared=True)
+    torch.cuda.synchronize()
+    b = d.batch
+    assert_close(out.cpu().numpy(), ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha), "wide forward")
+    assert not torch.isnan(t0).any()
+    ref, _ = ora.bwd(d.oshape, d.cores, b.indices, b.offsets, b.grad_output, alpha=b.alpha)
+    for k in range(3):
+        assert_close(new[k].cpu().numpy(), ora.sgd(d.cores[k], ref[k], 0.05), "wide core %d in two calls" % (k + 1))
+
+
 @pytest.mark.parametrize("name,table,n_bags,longest", [("multihot_cache", 0, 3600, 24), ("sweep_r64", 0, 7000, 24)])
 def test_medium_streams_in_one_call(name, table, n_bags, longest):
     """Between 32,768 and 131,072 positions, default kernel selection, no cache, one call: the backward groups the
-    positions and works on tiles, and the segmented sums take 16 or 32 items per wave (worked out on the device).
+    positions and works on distinct rows, in windows on either side of 65,536 positions.
     Ragged, weighted bags with a hot row; gradients and the fused step against the oracle."""
     wl = W.WORKLOADS[name]
     t = wl.tables[table]

@@ -255,8 +255,8 @@ def test_adversarial_identity_rank_map(path):
         assert_close(dg[k].cpu().numpy(), ref[k], "identity map dG%d" % (k + 1))
 
 
-def test_other_shapes_take_the_generic_kernels():
-    # unequal factors and ranks (no specialised kernel exists for them)
+def test_other_shapes(path):
+    # unequal factors and ranks (no specialised kernel exists for them: the run-time-shape kernels, or under selection 0 the plain ones)
     shape = W.TableShape(2 * 3 * 5 * 7, (6, 5, 7), (3, 2, 5), (1, 4, 7, 1))
     wl = W.Workload("odd", (shape,), 50, (0, 6), "uniform", 0.0, "normal0.1", 21)
     d = DeviceTable(wl, with_alpha=True)

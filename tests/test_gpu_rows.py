@@ -1,6 +1,7 @@
 """Grouping by distinct row (tt_rows.h, tt_rows_pass.h) where it changes course: a hot row over several windows, slices of the
 first and third core with more rows than one workgroup adds up (the last of several finishes them), slices without any row,
-every row different, every position the same row, streams on either side of the window sizes.  Forward, gradients and fused
+every row different, every position the same row, streams on either side of the window sizes, tables at the limits of the
+passes.  Forward, gradients and fused
 step against the oracle, and the step twice, bit for bit."""
 import numpy as np
 import pytest
@@ -50,8 +51,8 @@ def _table(kind, n, R, L, n_bags, seed, m=(30, 20, 40)):
     return DeviceTable(W.Workload("rows", (t,), n_bags, (0, 9), "uniform", 0.0, "normal0.1", seed), batch=batch)
 
 
-def _check(d, name, ws=None):
-    assert B.fwd_uses_lists(d.shape, d.L, 0, True)
+def _check(d, name, ws=None, lists=True):
+    assert B.fwd_uses_lists(d.shape, d.L, 0, True) == lists
     b = d.batch
     ws = ws if ws is not None else torch.full((B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
     steps = []
@@ -82,6 +83,14 @@ def _check(d, name, ws=None):
                                     ("second digit", 900), ("one row", 700)])
 def test_small_streams(n, R, kind, L, always_rows):
     _check(_table(kind, n, R, L, max(1, L // 3), 61), "%s %s R %d L %d" % (kind, n, R, L))
+
+
+# (4,096 slices of the first and third core are all the counters of a window and of its lists; 1,024 of the second the bins of
+# the counting pass; one more of either, and the position tiles or the list owners take over)
+@pytest.mark.parametrize("n,R", [((2, 2, 4), 32), ((4, 4, 4), 64)])
+@pytest.mark.parametrize("m", [(3072, 6, 1024), (1, 4, 4095), (3072, 6, 1025), (30, 1024, 40), (7, 1021, 9), (30, 1025, 40), (5, 1, 6)])
+def test_tables_at_the_limits(n, R, m, always_rows):
+    _check(_table("hot row", n, R, 2600, 700, 66, m=m), "%s %s R %d" % (m, n, R), lists=m[1] <= 1024)
 
 
 @pytest.mark.parametrize("kind", ["hot row", "first digit"])
