@@ -116,8 +116,10 @@ int64_t tt_cache_table_capacity(int64_t K);
  * none.  tt_emb_bwd needs none for a short index stream without a cache; with a cache, or from
  * 4096 positions on (from there on, depending on the shape, several workgroups share a slice and
  * leave partial sums in the workspace; from 32768 positions on, 16384 with a cache, the positions
- * are grouped with a device sort first), it reports TT_ERR_WORKSPACE if the workspace is missing
- * or too small.  Returns 0 on a bad shape. */
+ * are grouped first, by distinct row where the call brings a kept T0 and no cache at rank 32 or 64,
+ * else with a device sort by slice), it reports TT_ERR_WORKSPACE if the workspace is missing
+ * or too small.  That is said of the shapes with a specialised kernel; for the others see
+ * tt_emb_bwd.  Returns 0 on a bad shape. */
 size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows);
 
 /* Bytes of device workspace tt_cache_build needs for n_cand candidates. */
@@ -338,6 +340,11 @@ size_t tt_emb_static_scratch_bytes(void);
  * kept_t0 != 0 says that the second call will pass a t0.  The workspace must not be
  * used by anything else between the two calls, and one prepare serves one step.
  * For a short list without a cache the first call has nothing to do and enqueues nothing.
+ * At rank 64, with a kept T0 and no cache, the pair groups from 6,144 ((4,4,4)) or 12,288 ((2,2,4))
+ * positions on.  Below 8,192 / 16,384 that is a choice: a workspace too small for it (smaller
+ * than the query says) makes the pair work as it does for shorter lists instead of failing, although
+ * tt_emb_bwd_has_prepass answers 1 (it knows no workspace).  From there on the pair fails with
+ * TT_ERR_WORKSPACE.
  */
 int tt_emb_bwd_prepare(const tt_shape_t *shape, const int64_t *indices, int64_t L,
                        const int64_t *offsets, int64_t n_bags, const tt_cache_t *cache, int kept_t0,
@@ -352,13 +359,17 @@ int tt_emb_bwd_two_calls_group_earlier(const tt_shape_t *shape, int64_t L, int64
  * The forward pass of a call whose index-only pre-pass has run: tt_emb_fwd / tt_emb_fwd_keep_t0
  * (t0 != NULL) for a caller that has enqueued tt_emb_bwd_prepare with the same shape, indices,
  * offsets, cache and workspace (and kept_t0 = (t0 != NULL)) before it.  Where that pre-pass
- * groups the positions by the slices they touch (long index streams, tt_emb_bwd_has_prepass)
- * and the shape has such a kernel, the forward pass works from the lists: a workgroup takes
- * positions of one slice of the second core, multiplies their stacked first-core rows with
- * the slice on the matrix cores (Eq. 3, first product), and the rows of each bag are pooled
- * afterwards in position order.  Otherwise the call is tt_emb_fwd / tt_emb_fwd_keep_t0.
+ * groups the positions (long index streams, tt_emb_bwd_has_prepass) and the shape has such a
+ * kernel, the forward pass works from its lists: a workgroup takes positions of one slice of the
+ * second core, multiplies their stacked first-core rows with the slice on the matrix cores (Eq. 3,
+ * first product), and the rows of each bag are pooled afterwards in position order.  With a kept T0
+ * and no cache the lists are of distinct rows: a row is computed once, or once per few hundred to
+ * two thousand positions of its slice, and its T0 copied to all its positions.  Otherwise the call is
+ * tt_emb_fwd / tt_emb_fwd_keep_t0.
  * The workspace is read (lists) and written (one row per position, in a part of it that the
- * backward calls do not use); the backward call that follows takes the same workspace.
+ * backward calls do not use); the backward call that follows takes the same workspace, of the same
+ * workspace_bytes: below 32768 positions a call with a kept T0, no cache and a workspace too small for the
+ * lists (smaller than the query says) is tt_emb_fwd_keep_t0, although tt_emb_fwd_uses_lists answers 1.
  * Same results as tt_emb_fwd up to the order of the fp32 sums over the rank indices.
  */
 /* 1 if tt_emb_fwd_prepared works from the pre-pass's lists for such a call (then the forward pass has to
