@@ -352,7 +352,7 @@ static int fwd_common(const tt_shape_t *shape, const float *const cores[3],
             hipError_t e = hipGetLastError();
             return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
         }
-        if (flex_supported(p)) {
+        if (flex_supported(p) && flex_fwd_pays(p)) {
             flex_fwd(p, cores[0], cores[1], cores[2], indices, offsets, (int)n_bags, alpha, cd, output, st);
             hipError_t e = hipGetLastError();
             return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");

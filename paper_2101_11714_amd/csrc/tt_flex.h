@@ -2,7 +2,7 @@
 // limits of flex_supported): every size is a run-time value, the products of Eq. 4 run on the matrix cores all the same.
 //
 // Forward: a wave per bag, lane l owns V columns of the unfolded second core, T0 in registers, then through LDS to the
-// second product (flex_fwd_kernel).
+// second product (flex_fwd_kernel), where that is ahead of the plain kernel (flex_fwd_pays).
 //
 // Backward, two launches:
 //   1. flex_g2_kernel: one workgroup per slice of the second core (times S for long streams, each on a part of the
@@ -1009,6 +1009,32 @@ __global__ __launch_bounds__(WG) void flex_fwd_kernel(Params p, const float *__r
 
 // ---- host side -------------------------------------------------------------------------------------------------------
 
+// columns per lane of the forward pass: no more than leave every lane some, and whole vectors
+static inline int flex_fwd_v(const Params &p) { return p.cols > 128 && p.cols % 4 == 0 ? 4 : (p.cols > 64 && p.cols % 2 == 0 ? 2 : 1); }
+static inline int flex_fwd_j(const Params &p) { return p.n1 <= 2 ? 2 : 4; }
+
+// Is the wave per bag ahead of the plain kernel, which gives a bag four waves and a position three barriers?  The wave pays for
+// turns over rows j1 that are not all there, for lanes without columns and, eight loads or one at a time, for ranks and outputs
+// off its steps; the plain kernel for its rounds of 256 values and one load after the other along the ranks.  What a position
+// takes is estimated for both, in units of 10 ns, from timings of 100 shapes in bags of 60 positions (the estimates are off by 9 and 5 % at the
+// median).  Few bags, many short ones and many single ones all come out the same way; wave / plain, 64 bags of 60: (4,4,8) at
+// rank 64 657 / 1,966 us, (2,4,4) at 24 137 / 239, (4,4,4) at 16 152 / 171, (4,4,4) at 8 110 / 99, (5,3,7) at (17,33)
+// 469 / 293, (6,6,6) at 7 272 / 97, (16,1,16) at (64,3) 1,269 / 313.  The kernel so chosen was the slower one by more than 10 %, and
+// by up to 31 %, for three of the 100.
+static inline bool flex_fwd_pays(const Params &p)
+{
+    auto up = [](int a, int b) { return (a + b - 1) / b; };
+    auto trips = [](int n) { return n > 0 ? n / 8 + n % 8 : 0; };              // (the last ones one at a time)
+    const int V = flex_fwd_v(p), J = flex_fwd_j(p), turns = up(p.n1, J) * up(p.cols, WAVE * V);
+    int parts = 1;
+    if ((p.N & (p.N - 1)) == 0)
+        while (2 * parts * p.N <= WAVE) parts <<= 1;
+    const int per = up(p.R2, parts), outs = parts > 1 ? 1 : up(p.N, WAVE);     // values of b per lane, outputs per lane
+    const double wave = 90 + turns * (44 + 4.5 * trips(p.R1) + 0.64 * p.R1 * J * V) + 5.6 * (trips(per - 16) + (outs - 1) * trips(per)) + 1.7 * outs * per;
+    const double plain = 55 + 8.3 * up(p.n1 * p.cols, WG) * p.R1 + 5.3 * p.R2;
+    return wave <= plain;
+}
+
 static inline size_t flex_fwd_lds(const Params &p) { return (size_t)NWAVE * p.n1 * p.cols * sizeof(float); }
 
 static inline void flex_fwd(const Params &p, const float *G1, const float *G2, const float *G3, const int64_t *idx, const int64_t *off,
@@ -1016,10 +1042,9 @@ static inline void flex_fwd(const Params &p, const float *G1, const float *G2, c
 {
     const dim3 grid((n_bags + NWAVE - 1) / NWAVE), wg(WG);
     const size_t lds = flex_fwd_lds(p);
-    // columns per lane: no more than leave every lane some, and whole vectors
-    const int V = p.cols > 128 && p.cols % 4 == 0 ? 4 : (p.cols > 64 && p.cols % 2 == 0 ? 2 : 1);
+    const int V = flex_fwd_v(p);
 #define FX_FWD(J, VV) hipLaunchKernelGGL((flex_fwd_kernel<J, VV>), grid, wg, lds, st, p, G1, G2, G3, idx, off, n_bags, alpha, cd, out)
-    if (p.n1 <= 2) {
+    if (flex_fwd_j(p) == 2) {
         if (V == 4) FX_FWD(2, 4); else if (V == 2) FX_FWD(2, 2); else FX_FWD(2, 1);
     } else {
         if (V == 4) FX_FWD(4, 4); else if (V == 2) FX_FWD(4, 2); else FX_FWD(4, 1);

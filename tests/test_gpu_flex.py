@@ -53,7 +53,8 @@ def _check(d, name, cache=None, keys=None, crow=None):
 
 @pytest.mark.parametrize("n,r", [((4, 4, 4), (16, 16)), ((4, 4, 4), (8, 8)), ((2, 4, 4), (24, 24)), ((2, 2, 4), (48, 48)),
                                  ((4, 4, 8), (16, 16)), ((3, 2, 5), (4, 7)), ((1, 1, 1), (1, 1)), ((16, 1, 16), (64, 3)),
-                                 ((1, 64, 1), (5, 64)), ((2, 4, 8), (64, 64)), ((5, 3, 7), (17, 33)), ((4, 2, 4), (33, 15))])
+                                 ((1, 64, 1), (5, 64)), ((2, 4, 8), (64, 64)), ((5, 3, 7), (17, 33)), ((4, 2, 4), (33, 15)),
+                                 ((8, 3, 6), (50, 50)), ((2, 4, 1), (33, 33)), ((3, 2, 3), (64, 64))])
 def test_shapes_off_the_tile_edges(n, r):
     _check(_table((7, 6, 9), n, r, 300, 5, 41), "n %s r %s" % (n, r))
 
