@@ -158,7 +158,8 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
  * Duplicate indices are combined inside the library; no atomics are used, and the
  * result is bit-identical from run to run.
  * Shapes without a specialised kernel: a workspace of the queried size makes the call 10 to 50
- * times as fast as none, from where a plain kernel does the work; a smaller one costs speed only
+ * times as fast as none, from where a plain kernel does the work (so it does for some hundred
+ * positions at most where it is ahead, by the shape and L); a smaller one costs speed only
  * (more passes over fewer positions, same result bit for bit) down to about 32 MiB, below which
  * the plain kernel takes over (another order of the fp32 sums).
  */

@@ -227,6 +227,25 @@ size_t core_grad_bytes(const Params &p)
     return align256((size_t)p.m1 * p.sA * 4) + align256((size_t)p.m2 * p.sB * 4) + align256((size_t)p.m3 * p.sC * 4);
 }
 
+// LDS of the plain backward kernel
+size_t plain_bwd_lds(const Params &p)
+{
+    const int max_slice = p.sA > p.sB ? (p.sA > p.sC ? p.sA : p.sC) : (p.sB > p.sC ? p.sB : p.sC);
+    return sizeof(SelectLds<GEN_CH>) + (GEN_CH + 4) * sizeof(int) + (size_t)(max_slice + p.sA + p.sC + p.n1 * p.cols + p.N) * sizeof(float);
+}
+
+// Short streams of shapes whose second core takes many turns: a workgroup of tt_flex.h goes through FX_CW columns at a time,
+// with barriers between, for as little as one position; the plain kernel starts slower but has no such turns.  Both estimated in
+// us from timings at 1 to 512 positions (22 shapes).  Step of 1 / 64 positions, tt_flex.h / plain: (1,64,1) at ranks (5,64),
+// 64 turns, 181 / 52 and 183 / 90 us; (2,8,8) at 33, 8 turns, 56 / 35 and 58 / 65; (4,4,4) at 16, one, 17 / 28 and 18 / 42.
+// Only where the plain kernel runs anywhere, in the static scratch memory too.
+bool plain_bwd_pays(const Params &p, int64_t L, int64_t K)
+{
+    const int at_once = FX_CW / p.R2 > 1 ? FX_CW / p.R2 : 1, turns = (p.n2 + at_once - 1) / at_once;
+    if (14 + turns * (2 + 0.07 * p.R1) <= (20 + 0.0016 * p.sB) * (1 + L / 64.0)) return false;
+    return plain_bwd_lds(p) <= 64 * 1024 && 256 + slot_ws_bytes(L, K != 0) + cache_grad_bytes(p, K) + core_grad_bytes(p) <= STATIC_SCRATCH_BYTES;
+}
+
 // Does a backward call of a shape without a specialised kernel take the kernels of tt_flex.h (else those of tt_generic.h),
 // and in which order do they add?  That is a function of the shape, the length and the cache alone: with any workspace of
 // at least flex_ws_least the results are the same, the static scratch memory of tt_emb_bwd_sgd_static among them.  So
@@ -517,11 +536,12 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     size_t g_bytes[3] = {0, 0, 0};
     // Shapes without a specialised kernel: the kernels of tt_flex.h where they take the call, in passes as long as the
     // workspace allows.  A call that brings less than they can do with (tt_emb_bwd without a cache may bring none) still
-    // runs, on those of tt_generic.h.
+    // runs, on those of tt_generic.h; so does a short one that those are ahead for, if it brings what they need.
     FlexDims fx;
     int64_t fx_pass = 0;
     size_t fx_bytes = 0;
-    if (!fast && g_fast_path && workspace && workspace_bytes > need_bwd + gc_bytes && flex_plan(p, L, cd.K, &fx)) {
+    const bool plain = !fast && plain_bwd_pays(p, L, cd.K) && (!fused || workspace_bytes >= need_bwd + gc_bytes + core_grad_bytes(p));
+    if (!fast && !plain && g_fast_path && workspace && workspace_bytes > need_bwd + gc_bytes && flex_plan(p, L, cd.K, &fx)) {
         const size_t room = workspace_bytes - need_bwd - gc_bytes;
         if ((fx_pass = flex_pass(p, fx, L, room)))
             fx_bytes = flex_ws_layout(nullptr, p, fx, L, fx_pass).bytes;
@@ -560,9 +580,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     hipStream_t st = (hipStream_t)stream;
 
     // LDS needs of the generic kernels, checked before anything is enqueued
-    const int max_slice = p.sA > p.sB ? (p.sA > p.sC ? p.sA : p.sC) : (p.sB > p.sC ? p.sB : p.sC);
-    const size_t lds_core = sizeof(SelectLds<GEN_CH>) + (GEN_CH + 4) * sizeof(int) +
-                            (size_t)(max_slice + p.sA + p.sC + p.n1 * p.cols + p.N) * sizeof(float);
+    const size_t lds_core = plain_bwd_lds(p);
     const int G = WG / p.N > 0 ? WG / p.N : 1;
     const size_t lds_cache = sizeof(SelectLds<GEN_CH>) + (size_t)G * p.N * sizeof(float);
     if (!fast && !flex && (rc = allow_lds(bwd_generic_kernel, lds_core))) return rc;

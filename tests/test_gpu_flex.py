@@ -90,6 +90,32 @@ def test_several_passes_add_in_the_same_order(n, r, bags, longest, sizes):
         assert all(torch.equal(x, y) for x, y in zip(got[0], other))
 
 
+# positions, and whether the plain kernels take them, on either side of where they stop being ahead
+@pytest.mark.parametrize("n,r,L", [((1, 64, 1), (5, 64), 1), ((1, 64, 1), (5, 64), 130), ((1, 64, 1), (5, 64), 140), ((2, 8, 8), (33, 33), 20),
+                                   ((2, 8, 8), (33, 33), 30), ((4, 12, 1), (2, 48), 50)])
+def test_short_streams_of_many_turns(n, r, L):
+    d = _table((7, 6, 9), n, r, L, 1, 48)
+    _check(d, "n %s, %d positions" % (n, L))
+    # the same bits from the static scratch memory
+    full, static = d.bwd_sgd(0.05), [torch.full_like(x, float("nan")) for x in d.g]
+    B.tt_emb_bwd_sgd_static(d.shape, d.g, static, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(full, static))
+
+
+def test_short_stream_without_room_for_the_plain_kernels():
+    # one position: 492,544 bytes for the kernels of longer streams, 494,336 for the plain ones, which keep the gradients of the cores
+    d = _table((7, 6, 9), (1, 64, 1), (5, 64), 1, 1, 49)
+    b = d.batch
+    rg, _ = ora.bwd(d.oshape, d.cores, b.indices, b.offsets, b.grad_output, alpha=b.alpha)
+    new = [torch.full_like(x, float("nan")) for x in d.g]
+    ws = torch.full((493_000,), 0x7F, dtype=torch.uint8, device=dev())
+    B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha, workspace=ws)
+    torch.cuda.synchronize()
+    for k in range(3):
+        assert_close(new[k].cpu().numpy(), ora.sgd(d.cores[k], rg[k], 0.05), "core %d" % (k + 1))
+
+
 def test_slices_without_positions_are_copied():
     d = _table((5, 400, 6), (2, 4, 4), (12, 12), 60, 3, 44)
     _check(d, "sparse")
