@@ -188,8 +188,10 @@ struct FlexArgs {
     bool cont, first, fin, fold;
 };
 
-// V4: n3 = 4 and both ranks are multiples of 4, so that everything moves as float4
-template <bool V4>
+// V4: n3 = 4 and both ranks are multiples of 4, so that everything moves as float4.  ONE: a stream of up to `whole` positions,
+// which takes one pass (without what several need the two kernels of a step of 4,096 positions take 28 us instead of 29: it is cold
+// kernel arguments and instructions).
+template <bool V4, bool ONE>
 __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
 {
     extern __shared__ __align__(16) float fx_lds[];
@@ -203,8 +205,10 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
     const FlexDims &d = a.d;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, l16 = t & 15, q16 = (t >> 4) & 3, gid = t >> 4;
     const int n1 = p.n1, n2 = p.n2, n3 = V4 ? 4 : p.n3, R1 = p.R1, R2 = p.R2, N = p.N, cols = p.cols, sA = p.sA, sC = p.sC, LDA = d.LDA;
+    const int k0 = ONE ? 0 : a.k0, k1 = ONE ? a.L : a.k1;
+    const bool fin = ONE || a.fin;
     const int i2 = blockIdx.x % p.m2, sp = blockIdx.x / p.m2;
-    const int k_lo = a.k0 + sp * d.seg, k_hi = min(a.k1, k_lo + d.seg);
+    const int k_lo = k0 + sp * d.seg, k_hi = min(k1, k_lo + d.seg);
 
     float *As = fx_lds;                              // [64][LDA]    stacked rows of G1
     float *dT = As + FX_ROWS * LDA;                  // [64][FX_LD]  dT0'
@@ -239,7 +243,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
         cb[i] = (l16 + 16 * i) - cj[i] * R2;
     }
 
-    bool in_part = a.cont;                           // this workgroup's slice gradient so far is in `part`
+    bool in_part = !ONE && a.cont;                   // this workgroup's slice gradient so far is in `part`
     const float *src2 = a.src[1] + (size_t)i2 * p.sB;
     float *dst2 = a.dst[1] + (size_t)i2 * p.sB;
     float *part = a.w.part + ((size_t)sp * p.m2 + i2) * p.sB;
@@ -557,7 +561,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
                         }
                     };
                     if (jc + jn < n2) put(q);
-                    else put(a.w.cbuf + (size_t)(s_k[s_start[d0 + e]] - a.k0) * sC + b * n3 + j3);
+                    else put(a.w.cbuf + (size_t)(s_k[s_start[d0 + e]] - k0) * sC + b * n3 + j3);
                 }
             }
             __syncthreads();                                      // the tile area is rewritten
@@ -568,7 +572,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = 16 * prb + 4 * q16 + r;
-                if (row < nrow && aa < R1) a.w.pbuf[(size_t)(s_k[s_start[d0 + s_re[row]]] - a.k0) * sA + s_rj[row] * R1 + aa] = accp[i][r];
+                if (row < nrow && aa < R1) a.w.pbuf[(size_t)(s_k[s_start[d0 + s_re[row]]] - k0) * sA + s_rj[row] * R1 + aa] = accp[i][r];
             }
         }
     };
@@ -666,7 +670,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
                 int x1, x2, x3;
                 decode_f64(p, row, x1, x2, x3);
                 const bool is_head = (s_heads[i >> 6] >> (i & 63)) & 1;
-                a.w.rec[k - a.k0] = is_head ? make_int2(x1, x3) : make_int2(-1, -1);
+                a.w.rec[k - k0] = is_head ? make_int2(x1, x3) : make_int2(-1, -1);
                 if (is_head) s_row[num] = row;
                 s_k[at] = k; s_bag[at] = bag_find(k);
             }
@@ -713,7 +717,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
         for (int q = 0; q < 4; ++q) {
             const int k = base + w * 256 + q * 64 + lane;
             m[q] = __ballot(k < k_hi && sl[q] < 0 && select_digit_f64(p, 1, (double)row[q]) == (double)i2);
-            if (sl[q] >= 0 && i2 == 0 && k < k_hi) a.w.rec[k - a.k0] = make_int2(-1, -1);  // a cached position stands for no row
+            if (sl[q] >= 0 && i2 == 0 && k < k_hi) a.w.rec[k - k0] = make_int2(-1, -1);    // a cached position stands for no row
             mine += __popcll(m[q]);
         }
         if (lane == 0) s_cnt[parity][w] = mine;
@@ -736,17 +740,17 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
         }
         const bool last = base + FX_ROUND >= k_hi;
         // (a pass that starts inside a segment starts at a piece)
-        const bool end = last || (base - k_lo + FX_ROUND) % d.piece == 0;
+        const bool end = last || (!ONE && (base - k_lo + FX_ROUND) % d.piece == 0);
         if (cnt > 0 && (end || cnt > FX_CAP - FX_ROUND)) {        // uniform
             __syncthreads();
-            work(cnt, last && a.fin);
-            if (last) done = d.S == 1 && a.fin;
+            work(cnt, last && fin);
+            if (last) done = d.S == 1 && fin;
             cnt = 0;
         }
     }
     if (!done) {                                                  // no positions, or none in the last window
         __syncthreads();
-        if (d.S > 1 || !a.fin) {
+        if (d.S > 1 || !fin) {
             if (!in_part)
                 for (int x = t; x < p.sB; x += FX_T) part[x] = 0.f;
         } else if (in_part) {
@@ -758,6 +762,7 @@ __global__ __launch_bounds__(FX_T) void flex_g2_kernel(FlexArgs a)
 }
 
 // Workgroups [0, m1): slices of the first core, [m1, m1 + m3): of the third; the rest (a.fold): sums of the parts of the second.
+template <bool ONE>
 __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
 {
     constexpr int CAP = FX_ROUND + 512, NF = 8;
@@ -766,18 +771,20 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
     __shared__ __align__(16) float s_red[WG * 4];
     __shared__ int s_cnt[2][NWAVE];
     const Params &p = a.p;
+    const int k0 = ONE ? 0 : a.k0, k1 = ONE ? a.L : a.k1;
+    const bool fin = ONE || a.fin;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int b = blockIdx.x;
     if (b >= p.m1 + p.m3) {
         const int64_t n = (int64_t)p.m2 * p.sB;
-        const int parts = (a.k1 - a.k0 + a.d.seg - 1) / a.d.seg;
-        const bool more = a.k0 >= a.d.seg;                        // earlier segments are in acc
+        const int parts = (k1 - k0 + a.d.seg - 1) / a.d.seg;
+        const bool more = k0 >= a.d.seg;                          // earlier segments are in acc
         float *acc = a.w.acc + (size_t)p.m1 * p.sA + (size_t)p.m3 * p.sC;
         for (int64_t i = (int64_t)(b - p.m1 - p.m3) * WG + t; i < n; i += (int64_t)(gridDim.x - p.m1 - p.m3) * WG) {
             float s = a.w.part[i];
             if (more) s = acc[i] + s;
             for (int q = 1; q < parts; ++q) s += a.w.part[q * n + i];
-            if (a.fin) a.dst[1][i] = fmaf(a.mul, s, a.src[1][i]);
+            if (fin) a.dst[1][i] = fmaf(a.mul, s, a.src[1][i]);
             else acc[i] = s;
         }
         return;
@@ -788,8 +795,8 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
     const float *src = (third ? a.src[2] : a.src[0]) + (size_t)s * width;
     float *dst = (third ? a.dst[2] : a.dst[0]) + (size_t)s * width;
     float *acc = a.w.acc + (third ? (size_t)p.m1 * p.sA : 0) + (size_t)s * width;
-    const int n = a.k1 - a.k0;                                    // positions of the pass
-    bool any = !a.first;
+    const int n = k1 - k0;                                        // positions of the pass
+    bool any = !ONE && !a.first;
     if (any)                                                      // (added to by the threads that add_up's barriers order)
         for (int x = t; x < width; x += WG) s_acc[x] = acc[x];
 
@@ -862,10 +869,11 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
             if ((m[q] >> lane) & 1) s_list[at + __popcll(m[q] & lanemask_lt())] = base + w * (FX_ROUND / NWAVE) + q * 64 + lane;
             at += __popcll(m[q]);
         }
-        const int in_seg = (a.k0 + base) % a.d.seg + FX_ROUND;    // (the segment's length is a multiple of the round's)
         bool end = base + FX_ROUND >= n;
-        if (a.L > a.d.whole)                                      // uniform
-            end |= a.d.piece >= a.d.seg ? (a.k0 + base + FX_ROUND) % a.d.piece == 0 : in_seg == a.d.seg || in_seg % a.d.piece == 0;
+        if constexpr (!ONE) {
+            const int in_seg = (k0 + base) % a.d.seg + FX_ROUND;  // (the segment's length is a multiple of the round's)
+            end |= a.d.piece >= a.d.seg ? (k0 + base + FX_ROUND) % a.d.piece == 0 : in_seg == a.d.seg || in_seg % a.d.piece == 0;
+        }
         if (cnt > 0 && (end || cnt > CAP - FX_ROUND)) {           // uniform
             __syncthreads();
             if ((width & 3) == 0) add_up(cnt, std::integral_constant<int, 4>{});
@@ -873,14 +881,14 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
             cnt = 0;
         }
     }
-    if (!a.fin) {                                                 // (-0 + x is x, whatever x is)
+    if (!fin) {                                                   // (-0 + x is x, whatever x is)
         __syncthreads();
         for (int x = t; x < width; x += WG) acc[x] = any ? s_acc[x] : -0.f;
     } else if (any) {
-        __syncthreads();
+        if constexpr (!ONE) __syncthreads();
         for (int x = t; x < width; x += WG) {
             const float v = s_acc[x];
-            dst[x] = v == 0.f ? src[x] : fmaf(a.mul, v, src[x]);  // (a slice without positions in any of several passes: copied)
+            dst[x] = !ONE && v == 0.f ? src[x] : fmaf(a.mul, v, src[x]);   // (a slice without positions in any of several passes: copied)
         }
     } else if (dst != src) {
         for (int x = t; x < width; x += WG) dst[x] = src[x];
@@ -1057,8 +1065,10 @@ static inline hipError_t flex_bwd(FlexArgs a, int64_t pass, hipStream_t st)
 {
     const Params &p = a.p;
     const bool v4 = p.n3 == 4 && ((p.R1 | p.R2) & 3) == 0;
-    static OncePerDevice once[2];
-    hipError_t e = allow_dynamic_lds(once[v4], v4 ? (const void *)flex_g2_kernel<true> : (const void *)flex_g2_kernel<false>, FX_MAX_LDS);
+    const bool one = a.L <= a.d.whole;
+    void (*const g2)(FlexArgs) = v4 ? (one ? flex_g2_kernel<true, true> : flex_g2_kernel<true, false>) : (one ? flex_g2_kernel<false, true> : flex_g2_kernel<false, false>);
+    static OncePerDevice once[4];
+    hipError_t e = allow_dynamic_lds(once[2 * v4 + one], (const void *)g2, FX_MAX_LDS);
     if (e != hipSuccess) return e;
     const int fin = a.d.S > 1 ? (int)(((int64_t)p.m2 * p.sB + 4 * WG - 1) / (4 * WG)) : 0;
     const size_t lds = (size_t)a.d.lds_floats * sizeof(float);
@@ -1074,9 +1084,8 @@ static inline hipError_t flex_bwd(FlexArgs a, int64_t pass, hipStream_t st)
         a.fin = end == a.L;
         a.fold = a.d.S > 1 && (a.fin || end % a.d.seg == 0);
         const dim3 grid(p.m2 * (int)((end - k + a.d.seg - 1) / a.d.seg)), wg(FX_T);
-        if (v4) hipLaunchKernelGGL(flex_g2_kernel<true>, grid, wg, lds, st, a);
-        else hipLaunchKernelGGL(flex_g2_kernel<false>, grid, wg, lds, st, a);
-        hipLaunchKernelGGL(flex_sum_kernel, dim3(p.m1 + p.m3 + (!a.fold ? 0 : fin < 4096 ? fin : 4096)), dim3(WG), 0, st, a);
+        hipLaunchKernelGGL(g2, grid, wg, lds, st, a);
+        hipLaunchKernelGGL(one ? flex_sum_kernel<true> : flex_sum_kernel<false>, dim3(p.m1 + p.m3 + (!a.fold ? 0 : fin < 4096 ? fin : 4096)), dim3(WG), 0, st, a);
     }
     return hipGetLastError();
 }
