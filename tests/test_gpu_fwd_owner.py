@@ -143,9 +143,10 @@ def test_short_streams_and_other_shapes_fall_back():
 
 @pytest.mark.parametrize("name,table,with_cache", [("sweep_r32", 0, False), ("terabyte_r64", 0, False), ("sweep_r64", 0, True)])
 def test_ragged_weighted_bags_with_item_records(name, table, with_cache):
-    """Where the backward that follows runs on tiles, the pre-pass also writes a record per sorted item (position, digits,
-    bag) and the forward takes its tiles' positions and digits from those instead of reading and decoding the rows:
-    ragged, weighted bags with a hot row, with and without a cache, the kept T0 as well."""
+    """Where the backward that follows runs on tiles of positions, the pre-pass also writes a record per sorted item (position,
+    digits, bag) and the forward takes its tiles' positions and digits from those instead of reading and decoding the rows:
+    ragged, weighted bags with a hot row and a cache, the kept T0 as well.  (Without a cache these tables go through the
+    passes over distinct rows; test_gpu_bwd_tiles.py has wider ones that do not.)"""
     old = B.set_fast_path(3)                       # groups whatever the number of positions; the backward on tiles, also with a cache
     try:
         wl = W.WORKLOADS[name]
