@@ -144,6 +144,21 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
                float *output, void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * tt_emb_fwd without a cache, over the distinct rows of the batch: the positions are grouped by the slice of the second
+ * core they read, equal rows of up to 512 neighbouring positions of a slice are computed once, on the matrix cores, and the
+ * bags are pooled from those rows in position order.  Same results as tt_emb_fwd up to the order of the fp32 sums over the
+ * rank indices; bit-identical from run to run.  For n = (2,2,4) or (4,4,4), equal ranks 32 or 64, m2 <= 1024 and
+ * m1 + m3 <= 4096; TT_ERR_UNSUPPORTED otherwise.  workspace: scratch memory of
+ * tt_emb_fwd_rows_workspace_bytes bytes (0 for a shape or length without such a pass), 16-byte aligned.
+ * tt_emb_fwd_rows_pays: 1 where the call was measured ahead of tt_emb_fwd, which is a question of the shape and of L.
+ */
+size_t tt_emb_fwd_rows_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags);
+int tt_emb_fwd_rows_pays(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows);
+int tt_emb_fwd_rows(const tt_shape_t *shape, const float *const cores[3],
+                    const int64_t *indices, int64_t L, const int64_t *offsets, int64_t n_bags,
+                    const float *alpha, float *output, void *workspace, size_t workspace_bytes, void *stream);
+
+/*
  * Backward pass (Section 3.1, Eq. 4; Section 4.1, Alg. 2): gradients of
  * <output, grad_output> with respect to the cores and, with a cache, the cached
  * rows.  Positions whose row is cached contribute to grad_cache only, the others

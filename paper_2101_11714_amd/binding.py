@@ -29,6 +29,7 @@ ERR_NAMES = {0: "TT_OK", -1: "TT_ERR_NULL", -2: "TT_ERR_BAD_SHAPE", -3: "TT_ERR_
 EXPORTS = ("tt_last_error", "tt_cache_table_capacity", "tt_emb_workspace_bytes",
            "tt_cache_build_workspace_bytes", "tt_emb_dedup_workspace_bytes",
            "tt_emb_bwd_sgd_workspace_bytes", "tt_cache_refill_workspace_bytes", "tt_cache_refill",
+           "tt_emb_fwd_rows_workspace_bytes", "tt_emb_fwd_rows_pays", "tt_emb_fwd_rows",
            "tt_emb_mean_weights", "tt_init_sampled_gaussian", "tt_embd_fwd", "tt_embd_bwd", "tt_embd_sgd_update", "tt_freq_reset", "tt_freq_update", "tt_freq_export", "tt_dense_bag_fwd", "tt_dense_bag_bwd_sgd", "tt_dense_bag_bwd_sgd_merged", "tt_dense_bag_bwd_workspace_bytes",
            "tt_emb_validate", "tt_emb_debug_launch_probe", "tt_emb_kept_bytes", "tt_emb_kept_has_lists", "tt_emb_kept_prepare", "tt_emb_fwd_keep", "tt_emb_bwd_kept", "tt_emb_bwd_sgd_kept", "tt_emb_debug_kept_lists", "tt_emb_bwd_sgd_static", "tt_emb_static_scratch_bytes", "tt_emb_fwd_keep_t0", "tt_emb_bwd_t0", "tt_emb_bwd_sgd_t0", "tt_emb_bwd_prepare", "tt_emb_fwd_prepared", "tt_emb_fwd_uses_lists", "tt_emb_bwd_sgd_prepared", "tt_emb_bwd_has_prepass", "tt_emb_bwd_two_calls_group_earlier",
            "tt_emb_fwd", "tt_emb_bwd", "tt_emb_bwd_sgd", "tt_emb_sgd_update", "tt_cache_build", "tt_cache_lookup",
@@ -73,6 +74,10 @@ def lib():
         l.tt_emb_dedup_workspace_bytes.argtypes = [C.c_int64]
         vp, i64, f32 = C.c_void_p, C.c_int64, C.c_float
         l.tt_emb_fwd.argtypes = [vp, vp, vp, i64, vp, i64, vp, vp, vp, vp, C.c_size_t, vp]
+        l.tt_emb_fwd_rows.argtypes = [vp, vp, vp, i64, vp, i64, vp, vp, vp, C.c_size_t, vp]
+        l.tt_emb_fwd_rows_pays.argtypes = [vp, i64, i64, i64]
+        l.tt_emb_fwd_rows_workspace_bytes.restype = C.c_size_t
+        l.tt_emb_fwd_rows_workspace_bytes.argtypes = [vp, i64, i64]
         l.tt_emb_bwd.argtypes = [vp, vp, vp, i64, vp, i64, vp, vp, vp, vp, vp, vp, C.c_size_t, vp]
         l.tt_emb_fwd_keep_t0.argtypes = [vp, vp, vp, i64, vp, i64, vp, vp, vp, vp, vp]
         l.tt_emb_bwd_t0.argtypes = [vp, vp, vp, i64, vp, i64, vp, vp, vp, vp, vp, vp, vp, C.c_size_t, vp]
@@ -214,7 +219,24 @@ def tt_emb_fwd(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Ten
                offsets: Optional[torch.Tensor], n_bags: int, output: torch.Tensor,
                alpha: Optional[torch.Tensor] = None, cache: Optional[Cache] = None,
                workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """Where tt_emb_fwd_rows_pays, tt_emb_fwd_rows in scratch memory of torch's allocator (but not under capture)."""
     rc = _call.emb_fwd(shape, cores, indices, offsets, n_bags, output, alpha, cache, workspace)
+    if rc:
+        _check(rc)
+    return output
+
+
+def fwd_rows_workspace_bytes(shape: TTShape, L: int, n_bags: int) -> int:
+    return int(lib().tt_emb_fwd_rows_workspace_bytes(C.byref(shape), int(L), int(n_bags)))
+
+
+def fwd_rows_pays(shape: TTShape, L: int, n_bags: int, cache_rows: int = 0) -> bool:
+    return bool(lib().tt_emb_fwd_rows_pays(C.byref(shape), int(L), int(n_bags), int(cache_rows)))
+
+
+def tt_emb_fwd_rows(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Tensor, offsets: Optional[torch.Tensor],
+                    n_bags: int, output: torch.Tensor, workspace: torch.Tensor, alpha: Optional[torch.Tensor] = None) -> torch.Tensor:
+    rc = _call.emb_fwd_rows(shape, cores, indices, offsets, n_bags, output, alpha, workspace)
     if rc:
         _check(rc)
     return output

@@ -21,6 +21,7 @@
 #include "tt_fwd_owner.h"
 #include "tt_bwd_owner.h"
 #include "tt_rows_pass.h"
+#include "tt_rows_fwd.h"
 #include "tt_flex.h"
 #include "tt_freq.h"
 #include "tt_topk.h"
@@ -67,6 +68,19 @@ constexpr int64_t GROUP_MIN_L_ROWS_444 = 6144, GROUP_MIN_L_ROWS_224 = 12288;
 // rows, rank 64: (4,4,4) 8,192 positions 92 / 88 us (but a first step 129 / 132), 12,288 124 / 114; (2,2,4) bags of 5-15:
 // 17,000 positions 104 / 70 us, 29,000 153 / 96.  Rank 32 stays at GROUP_MIN_L: 3-6 % at most, within what two runs differ.
 constexpr int64_t ROWS_FWD_MIN_L_444 = 10240, ROWS_FWD_MIN_L_224 = GROUP_MIN_L_ROWS_224;
+
+// From where on a forward pass without a cache that has scratch memory works on its distinct rows (tt_emb_fwd_rows).  Grouping
+// costs some 17 us whatever the length, a wave per bag as much per position as the second core's slice is long; bags of one position are
+// the ones that it is fastest with (tt_fast.h).  Wave per bag / rows, Zipf-distributed and (uniform) rows: (4,4,4) rank 32, bags of
+// 1-8: 18,000 positions 27 / 32 us, 37,000 47 / 33 (47 / 44), 73,000 82 / 41 (82 / 61), of one: 16,384 25 / 34, 32,768 44 / 39 (45 / 49);
+// (4,4,4) rank 64, 1-8: 18,000 89 / 62 (125 / 64), of one: 16,384 50 / 62, 32,768 95 / 70 (97 / 106); (2,2,4) rank 64: 8,192
+// 21 / 29, 16,384 38 / 32 (38 / 33); (2,2,4) rank 32: 73,000 27 / 30, 81,000 34 / 29 (35 / 37), 204,800 58 / 40 (61 / 58).
+int64_t fwd_rows_min_l(const Params &p, int64_t L, int64_t n_bags)
+{
+    if (p.n1 == 2) return p.R1 >= 64 ? 14336 : 131072;
+    if (L < 2 * n_bags) return 40960;
+    return p.R1 >= 64 ? 12288 : 28672;
+}
 
 int64_t tiles_min_l(const Params &p) { return p.n1 == 4 ? GROUP_MIN_L_TILES_444 : GROUP_MIN_L_TILES_224; }
 
@@ -393,6 +407,44 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
 {
     (void)workspace; (void)workspace_bytes;
     return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, cache, output, nullptr, false, stream);
+}
+
+size_t tt_emb_fwd_rows_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags)
+{
+    (void)n_bags;
+    Params p;
+    if (check_shape(shape, &p) != TT_OK || L <= 0 || L >= (1ll << 31) || !rw_supported(p)) return 0;
+    return rf_ws_layout(nullptr, p, L).bytes;
+}
+
+int tt_emb_fwd_rows_pays(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows)
+{
+    Params p;
+    if (cache_rows || g_fast_path != 1 || check_shape(shape, &p) != TT_OK || L >= (1ll << 31) || !rw_supported(p)) return 0;
+    return L >= fwd_rows_min_l(p, L, n_bags) && rf_ws_layout(nullptr, p, L).bytes <= RF_MAX_BYTES ? 1 : 0;
+}
+
+int tt_emb_fwd_rows(const tt_shape_t *shape, const float *const cores[3],
+                    const int64_t *indices, int64_t L, const int64_t *offsets, int64_t n_bags,
+                    const float *alpha, float *output, void *workspace, size_t workspace_bytes, void *stream)
+{
+    Params p;
+    int rc = check_shape(shape, &p);
+    if (rc) return rc;
+    if ((rc = check_lookup_args(indices, L, n_bags, offsets, p.N))) return rc;
+    if (!cores || !cores[0] || !cores[1] || !cores[2]) return fail(TT_ERR_NULL, "cores is NULL");
+    if (n_bags > 0 && !output) return fail(TT_ERR_NULL, "output is NULL");
+    if (!rw_supported(p)) return fail(TT_ERR_UNSUPPORTED, "no forward pass over distinct rows for this shape");
+    if (L == 0 || n_bags == 0)
+        return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, nullptr, output, nullptr, false, stream);
+    const size_t need = rf_ws_layout(nullptr, p, L).bytes;
+    if (!workspace || workspace_bytes < need)
+        return fail(TT_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
+    if (misaligned({cores[0], cores[1], cores[2], output, workspace}))
+        return fail(TT_ERR_BAD_ARG, "cores, output and workspace must be 16-byte aligned");
+    hipError_t e = rows_fwd(p, cores[0], cores[1], cores[2], indices, L, offsets, (int)n_bags, alpha, output, rf_ws_layout(workspace, p, L),
+                               (hipStream_t)stream);
+    return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
 }
 
 int tt_emb_fwd_keep_t0(const tt_shape_t *shape, const float *const cores[3],

@@ -211,6 +211,20 @@ TT_FUNCTION(guarded)
     return nullptr;
 }
 
+// Scratch memory of torch's allocator for the current stream (the kernels that use it are enqueued there before it is given
+// back), or nothing: while the stream is captured, since a graph's scratch memory has to live as long as the graph, and where
+// there is no room for it.
+at::DataPtr scratch(size_t bytes, void *st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!bytes || hipStreamIsCapturing((hipStream_t)st, &status) != hipSuccess || status != hipStreamCaptureStatusNone) return {};
+    try {
+        return c10::GetAllocator(c10::DeviceType::CUDA)->allocate(bytes);
+    } catch (const c10::OutOfMemoryError &) {
+        return {};
+    }
+}
+
 // shape cores indices offsets n_bags output alpha cache workspace
 TT_FUNCTION(emb_fwd)
 {
@@ -225,7 +239,30 @@ TT_FUNCTION(emb_fwd)
     void *ws = g.bytes_or_null(8, &wsb);
     if (g.ok && no != q.n_bags * dim(q.shape)) g.fail("output has another size");
     if (!g.ok) return nullptr;
+    const int64_t cached = cache ? cache->K : 0;
+    if (tt_emb_fwd_rows_pays(q.shape, q.L, q.n_bags, cached)) {
+        const size_t bytes = tt_emb_fwd_rows_workspace_bytes(q.shape, q.L, q.n_bags);
+        const at::DataPtr mem = scratch(bytes, stream());
+        if (mem)
+            return call([&](void *st) { return tt_emb_fwd_rows(q.shape, q.cores, q.indices, q.L, q.offsets, q.n_bags, alpha, out, mem.get(), bytes, st); });
+    }
     return call([&](void *st) { return tt_emb_fwd(q.shape, q.cores, q.indices, q.L, q.offsets, q.n_bags, alpha, cache, out, ws, wsb, st); });
+}
+
+// shape cores indices offsets n_bags output alpha workspace
+TT_FUNCTION(emb_fwd_rows)
+{
+    Args g(args, nargs, 8);
+    if (!g.ok) return nullptr;
+    Lookup q(g);
+    int64_t no = 0;
+    size_t wsb;
+    float *out = g.f32(5, &no);
+    const float *alpha = g.f32_or_null(6);
+    void *ws = g.bytes_or_null(7, &wsb);
+    if (g.ok && no != q.n_bags * dim(q.shape)) g.fail("output has another size");
+    if (!g.ok) return nullptr;
+    return call([&](void *st) { return tt_emb_fwd_rows(q.shape, q.cores, q.indices, q.L, q.offsets, q.n_bags, alpha, out, ws, wsb, st); });
 }
 
 // shape cores indices offsets n_bags output t0 alpha cache
@@ -524,6 +561,7 @@ TT_FUNCTION(freq_export)
 
 PyMethodDef methods[] = {
     TT_METHOD("emb_fwd", emb_fwd),
+    TT_METHOD("emb_fwd_rows", emb_fwd_rows),
     TT_METHOD("emb_fwd_keep_t0", emb_fwd_keep_t0),
     TT_METHOD("emb_fwd_prepared", emb_fwd_prepared),
     TT_METHOD("emb_bwd", emb_bwd),

@@ -27,7 +27,7 @@ namespace tt {
 
 constexpr int RW_WIN = 2048;                     // positions of a window, at most (see rw_win)
 constexpr int RW_T = 512, RW_NW = RW_T / WAVE;   // threads / waves of the window kernels
-constexpr int RW_TILE = 2048;                    // positions per workgroup of the counting pass
+constexpr int RW_TILE = 2048, RW_TILE_SHORT = 512;   // positions per workgroup of the counting pass (see rw_tile)
 constexpr int RW_HASH = 4096;
 constexpr int RW_MAX_M2 = 1024;                  // bins of the counting pass
 constexpr int RW_MAX_M13 = 4096;                 // slices of the first and third core together
@@ -70,7 +70,8 @@ static inline bool rw_supported(const Params &p)
 // for 13 us).
 constexpr int64_t RW_LONG_MIN_L = 65536;
 static inline int rw_win(int64_t L) { return L < RW_LONG_MIN_L ? 256 : RW_WIN; }
-static inline int rw_windows(const Params &p, int64_t L) { return (int)(L / rw_win(L)) + p.m2; }
+static inline int rw_windows(const Params &p, int64_t L, int win) { return (int)(L / win) + p.m2; }
+static inline int rw_windows(const Params &p, int64_t L) { return rw_windows(p, L, rw_win(L)); }
 static inline int rw_tiles(const Params &p, int64_t L, int tp) { return (int)(L / tp) + rw_windows(p, L); }
 // Distinct rows per workgroup of the final sums: fewer where a table has few slices, so that the sums still spread over the
 // device (step of 34,000 positions, (4,4,4) at rank 32, 40 slices per core, uniform rows: 214 us with 512 throughout, 155 so).
@@ -88,7 +89,10 @@ static inline int rw_pieces(const Params &p, int64_t L)
     const int64_t small = 2 * (L / 64) < 1024 ? 2 * (L / 64) : 1024, whole = 2 * (L / RW_PIECE);
     return (int)(small > whole ? small : whole) + p.m1 + p.m3;
 }
-static inline int rw_hist_blocks(int64_t L) { return (int)((L + RW_TILE - 1) / RW_TILE); }
+// Positions per workgroup of the counting pass: a workgroup's rounds are one chain, which short streams wait for; with more
+// workgroups every one of them has more counts to read.
+static inline int rw_tile(int64_t L) { return L < RW_LONG_MIN_L ? RW_TILE_SHORT : RW_TILE; }
+static inline int rw_hist_blocks(int64_t L) { return (int)((L + rw_tile(L) - 1) / rw_tile(L)); }
 
 // tile_wgs: workgroups of the tile kernel
 static inline RowsWs rw_ws_layout(void *ws, const Params &p, int64_t L, int tile_wgs)
@@ -129,32 +133,35 @@ static inline RowsWs rw_ws_layout(void *ws, const Params &p, int64_t L, int tile
 // ---- pre-pass --------------------------------------------------------------------------------------------------------
 
 // second digits of a tile of positions, and how many of each
+template <int TILE>
 __global__ __launch_bounds__(WG) void rw_count_kernel(Params p, const int64_t *__restrict__ indices, int L, RowsWs ws)
 {
     __shared__ uint32_t h[RW_MAX_M2];
-    const int t = threadIdx.x, m2p = (p.m2 + 3) & ~3, base = blockIdx.x * RW_TILE;
-    uint32_t row[RW_TILE / WG];
+    const int t = threadIdx.x, m2p = (p.m2 + 3) & ~3, base = blockIdx.x * TILE;
+    uint32_t row[TILE / WG];
 #pragma unroll
-    for (int q = 0; q < RW_TILE / WG; ++q) row[q] = (uint32_t)indices[min(base + q * WG + t, L - 1)];
+    for (int q = 0; q < TILE / WG; ++q) row[q] = (uint32_t)indices[min(base + q * WG + t, L - 1)];
     for (int x = t; x < m2p; x += WG) h[x] = 0u;
-    for (int x = blockIdx.x * WG + t; x < p.m1 + p.m3; x += gridDim.x * WG) ws.arrived[x] = 0u;
+    if (ws.arrived)
+        for (int x = blockIdx.x * WG + t; x < p.m1 + p.m3; x += gridDim.x * WG) ws.arrived[x] = 0u;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < RW_TILE / WG; ++q)
+    for (int q = 0; q < TILE / WG; ++q)
         if (base + q * WG + t < L) atomicAdd(&h[(int)select_digit_f64(p, 1, (double)row[q])], 1u);
     __syncthreads();
     for (int x = t; x < m2p; x += WG) ws.hist[(size_t)blockIdx.x * m2p + x] = h[x];
 }
 
 // Stable placement by second digit.  Every workgroup derives its own starting places from the counts of all tiles (a few
-// independent 16-byte loads per thread); wave w ranks its 512 consecutive positions round by round.
+// independent 16-byte loads per thread); wave w ranks its TILE / 4 consecutive positions round by round.
+template <int TILE>
 __global__ __launch_bounds__(WG) void rw_scatter_kernel(Params p, const int64_t *__restrict__ indices, int L, int nblk, int bits, RowsWs ws)
 {
-    constexpr int NR = RW_TILE / WG;
+    constexpr int NR = TILE / WG;
     __shared__ __align__(16) uint32_t s_cnt[NWAVE][RW_MAX_M2];      // first the partial sums of the counts
     __shared__ uint32_t s_start[RW_MAX_M2];
     __shared__ int s_tmp[NWAVE + 1];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m2p = (p.m2 + 3) & ~3, base = blockIdx.x * RW_TILE + w * (RW_TILE / NWAVE);
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, m2p = (p.m2 + 3) & ~3, base = blockIdx.x * TILE + w * (TILE / NWAVE);
     uint32_t row[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) row[q] = (uint32_t)indices[min(base + q * WAVE + lane, L - 1)];
@@ -274,6 +281,30 @@ __device__ __forceinline__ int rw_scan(int v, int *tmp, int *total)
     return at;
 }
 
+// Which window a workgroup has: its slice and its number in the slice, in s_win (to be read after a barrier); false if there
+// is none.
+__device__ __forceinline__ bool rw_find_window(const Params &p, int win, const RowsWs &ws, int *s_tmp, int *s_win)
+{
+    const int t = threadIdx.x;
+    int nwin[2], sum = 0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int s = 2 * t + q;
+        nwin[q] = s < p.m2 ? (ws.goff[s + 1] - ws.goff[s] + win - 1) / win : 0;
+        sum += nwin[q];
+    }
+    int total;
+    int at = rw_scan(sum, s_tmp, &total);
+    if (t == 0 && blockIdx.x == 0) *ws.nwin = total;
+    if ((int)blockIdx.x >= total) return false;                    // uniform
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if ((int)blockIdx.x >= at && (int)blockIdx.x < at + nwin[q]) { s_win[0] = 2 * t + q; s_win[1] = blockIdx.x - at; }
+        at += nwin[q];
+    }
+    return true;
+}
+
 // One window of one slice's positions: see the file comment.
 __global__ __launch_bounds__(RW_T) void rw_group_kernel(Params p, int L, int win, const int64_t *__restrict__ offsets, int n_bags, RowsWs ws)
 {
@@ -286,25 +317,7 @@ __global__ __launch_bounds__(RW_T) void rw_group_kernel(Params p, int L, int win
     __shared__ uint64_t s_heads[NCH];
     __shared__ int s_off[RW_OFF + 1], s_tmp[RW_NW], s_win[2];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, m13 = p.m1 + p.m3;
-    // which window this is: slice and number in the slice
-    {
-        int nwin[2], sum = 0;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int s = 2 * t + q;
-            nwin[q] = s < p.m2 ? (ws.goff[s + 1] - ws.goff[s] + win - 1) / win : 0;
-            sum += nwin[q];
-        }
-        int total;
-        int at = rw_scan(sum, s_tmp, &total);
-        if (t == 0 && blockIdx.x == 0) *ws.nwin = total;
-        if ((int)blockIdx.x >= total) return;                      // uniform
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if ((int)blockIdx.x >= at && (int)blockIdx.x < at + nwin[q]) { s_win[0] = 2 * t + q; s_win[1] = blockIdx.x - at; }
-            at += nwin[q];
-        }
-    }
+    if (!rw_find_window(p, win, ws, s_tmp, s_win)) return;          // uniform
     const int ostep = (n_bags + RW_OFF - 1) / RW_OFF;
     const bool search = offsets && !p.bagP;                        // (bags of one length are found without)
     if (search)
@@ -624,21 +637,39 @@ __global__ __launch_bounds__(RW_T) void rw_lists_kernel(Params p, int bits1, int
         }
 }
 
+static inline int rw_bits(int m)
+{
+    int b = 0;
+    while ((1 << b) < m) ++b;
+    return b;
+}
+
+// positions and rows grouped by second digit: two launches
+static inline void rw_place(const Params &p, const int64_t *indices, int L, int tile, const RowsWs &ws, hipStream_t st)
+{
+    const int nblk = (L + tile - 1) / tile, bits = rw_bits(p.m2);
+    if (tile == RW_TILE_SHORT) {
+        hipLaunchKernelGGL(rw_count_kernel<RW_TILE_SHORT>, dim3(nblk), dim3(WG), 0, st, p, indices, L, ws);
+        hipLaunchKernelGGL(rw_scatter_kernel<RW_TILE_SHORT>, dim3(nblk), dim3(WG), 0, st, p, indices, L, nblk, bits, ws);
+    } else {
+        hipLaunchKernelGGL(rw_count_kernel<RW_TILE>, dim3(nblk), dim3(WG), 0, st, p, indices, L, ws);
+        hipLaunchKernelGGL(rw_scatter_kernel<RW_TILE>, dim3(nblk), dim3(WG), 0, st, p, indices, L, nblk, bits, ws);
+    }
+}
+
 // Index-only part of a step: five launches.  tp: distinct rows per tile.
 static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int L, const int64_t *offsets, int n_bags, int tp, const RowsWs &ws,
                                     hipStream_t st)
 {
-    const int nblk = rw_hist_blocks(L), nw = rw_windows(p, L), m13 = p.m1 + p.m3;
-    auto bits_of = [](int m) { int b = 0; while ((1 << b) < m) ++b; return b; };
+    const int nw = rw_windows(p, L), m13 = p.m1 + p.m3;
     const size_t lds = (size_t)m13 * 4 + (size_t)RW_NW * m13 * 2;              // at most 80 KB
     static OncePerDevice once;
     hipError_t e = allow_dynamic_lds(once, (const void *)rw_lists_kernel, RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rw_count_kernel, dim3(nblk), dim3(WG), 0, st, p, indices, L, ws);
-    hipLaunchKernelGGL(rw_scatter_kernel, dim3(nblk), dim3(WG), 0, st, p, indices, L, nblk, bits_of(p.m2), ws);
+    rw_place(p, indices, L, rw_tile(L), ws, st);
     hipLaunchKernelGGL(rw_group_kernel, dim3(nw), dim3(RW_T), 0, st, p, L, rw_win(L), offsets, n_bags, ws);
     hipLaunchKernelGGL(rw_scan_kernel, dim3((m13 + 31) / 32 + 1), dim3(RW_T), 0, st, p, tp, ws);
-    hipLaunchKernelGGL(rw_lists_kernel, dim3(nw), dim3(RW_T), lds, st, p, bits_of(p.m1), bits_of(p.m3), ws);
+    hipLaunchKernelGGL(rw_lists_kernel, dim3(nw), dim3(RW_T), lds, st, p, rw_bits(p.m1), rw_bits(p.m3), ws);
     return hipGetLastError();
 }
 

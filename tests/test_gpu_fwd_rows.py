@@ -1,0 +1,83 @@
+"""The forward pass over distinct rows (tt_rows_fwd.h, tt_emb_fwd_rows) at the edges of its windows, blocks and counting tiles:
+one position, a window one short of full, full and one over, every row different, one row, one slice, empty and ragged bags,
+weights, few and many slices.  Against the oracle and bit for bit against itself; the binding's tt_emb_fwd takes it by the rule
+of tt_emb_fwd_rows_pays, and the wave per bag where the stream is captured."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tt_oracle as ora
+from paper_2101_11714_amd import binding as B
+from paper_2101_11714_amd import workloads as W
+from gpu_util import DeviceTable, assert_close, dev
+from test_gpu_rows import SHAPES, _rows
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(kind, n, R, L, n_bags, m=(30, 20, 40), alpha=True):
+    t = W.TableShape(m[0] * m[1] * m[2] - 3, m, n, (1, R, R, 1))
+    rng = np.random.default_rng([L, R, n[0]])
+    off = np.concatenate([[0], np.sort(rng.integers(0, L + 1, n_bags - 1)), [L]]).astype(np.int64)
+    batch = W.Batch(_rows(kind, t, L, rng), off, np.zeros((n_bags, t.dim), np.float32), (0.5 + rng.random(L)).astype(np.float32) if alpha else None)
+    return DeviceTable(W.Workload("fwd rows", (t,), n_bags, (0, 9), "uniform", 0.0, "normal0.1", 5), batch=batch)
+
+
+def _run(d):
+    outs = []
+    for fill in (0x7F, 0xFF):                                # what was in the scratch memory does not matter
+        ws = torch.full((B.fwd_rows_workspace_bytes(d.shape, d.L, d.n_bags),), fill, dtype=torch.uint8, device=dev())
+        out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+        B.tt_emb_fwd_rows(d.shape, d.g, d.idx, d.off, d.n_bags, out, ws, alpha=d.alpha)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert torch.equal(*outs)
+    return outs[0].cpu().numpy()
+
+
+@pytest.mark.parametrize("n,R", SHAPES)
+@pytest.mark.parametrize("kind,L,n_bags,m", [("uniform", 1, 3, (30, 20, 40)), ("second digit", 511, 40, (30, 20, 40)), ("second digit", 513, 1, (30, 20, 40)),
+                                             ("uniform", 5000, 700, (30, 20, 40)), ("hot row", 9000, 300, (30, 20, 40)), ("one row", 3000, 17, (30, 20, 40)),
+                                             ("uniform", 6001, 900, (3, 1024, 5)), ("uniform", 4100, 2000, (900, 1, 700))])
+def test_forward_over_distinct_rows(n, R, kind, L, n_bags, m):
+    d = _table(kind, n, R, L, n_bags, m)
+    b = d.batch
+    ref = ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha)
+    assert_close(_run(d), ref, kind)
+
+
+def test_the_binding_takes_it_by_the_rule():
+    # either side of the longest limit, (4,4,4) with bags of one position (40,960), and of the counting pass's tiles (131,072 at (2,2,4), rank 32)
+    for n, R, L, n_bags in [((4, 4, 4), 32, 40_959, 40_959), ((4, 4, 4), 32, 40_960, 40_960), ((2, 2, 4), 32, 131_071, 9000), ((2, 2, 4), 32, 131_072, 9000)]:
+        d = _table("hot row", n, R, L, n_bags, m=(200, 200, 50), alpha=False)
+        pays = B.fwd_rows_pays(d.shape, L, n_bags)
+        assert pays == (L in (40_960, 131_072)) and not B.fwd_rows_pays(d.shape, L, n_bags, 10)
+        out = d.fwd()
+        assert_close(out, ora.fwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets), str((n, R, L)))
+        assert np.array_equal(out, _run(d)) == pays or L == n_bags         # (single rows may round alike)
+        old = B.set_fast_path(2)
+        wave = d.fwd()
+        B.set_fast_path(old)
+        got = torch.full((n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            B.tt_emb_fwd(d.shape, d.g, d.idx, d.off, d.n_bags, got)
+        for _ in range(3):
+            got.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(got.cpu().numpy(), wave)
+
+
+def test_scratch_memory_that_is_too_small_is_refused():
+    d = _table("uniform", (4, 4, 4), 32, 1000, 10)
+    need = B.fwd_rows_workspace_bytes(d.shape, d.L, d.n_bags)
+    out = torch.zeros((d.n_bags, d.t.dim), dtype=torch.float32, device=dev())
+    for bytes_ in (need - 1, 0):
+        with pytest.raises(B.TTError) as e:
+            B.tt_emb_fwd_rows(d.shape, d.g, d.idx, d.off, d.n_bags, out, torch.empty(bytes_, dtype=torch.uint8, device=dev()), alpha=d.alpha)
+        assert e.value.code == -4
+    torch.cuda.synchronize()
+    assert float(out.abs().max()) == 0.0
