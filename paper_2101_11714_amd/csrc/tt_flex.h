@@ -898,7 +898,9 @@ __global__ __launch_bounds__(WG) void flex_sum_kernel(FlexArgs a)
 // ---- forward -------------------------------------------------------------------------------------------------------
 // A wave per bag.  J rows j1 at a time, V columns per lane: T0[j1][c] = sum_a A[j1][a] Bm[a][c] in registers (A through
 // scalar loads), to the wave's part of LDS; then lane (part, j) adds every parts-th value of b of output j.
-template <int J, int V>
+// NCH: the rank R1 in eights where it is a multiple and one turn over j1 and over the columns does (J == n1, cols <= 64 V):
+// then every load of a position is in flight at once.  0: whatever the shape.
+template <int J, int V, int NCH>
 __global__ __launch_bounds__(WG) void flex_fwd_kernel(Params p, const float *__restrict__ G1, const float *__restrict__ G2,
                                                       const float *__restrict__ G3, const int64_t *__restrict__ indices,
                                                       const int64_t *__restrict__ offsets, int n_bags, const float *__restrict__ alpha,
@@ -947,42 +949,65 @@ __global__ __launch_bounds__(WG) void flex_fwd_kernel(Params p, const float *__r
             float cpre[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) cpre[q] = C[min(part + q * parts, R2 - 1) * n3 + o3[0]];
-            for (int jc = 0; jc < n1; jc += J)
-                for (int c0 = lane * V; c0 < cols; c0 += WAVE * V) {
-                    float t0[J][V];
+            if constexpr (NCH > 0) {
+                constexpr int RR = 8 * NCH;
+                const int c0 = min(lane * V, cols - V);            // (lanes without columns: any, not stored)
+                float bv[RR][V], t0[J][V];
 #pragma unroll
-                    for (int q = 0; q < J; ++q)
+                for (int x = 0; x < RR; ++x) load_vec<V>(Bm + x * cols + c0, bv[x]);
 #pragma unroll
-                        for (int v = 0; v < V; ++v) t0[q][v] = 0.f;
-                    const float *B = Bm + c0;
-                    int a = 0;
-                    for (; a + 8 <= R1; a += 8) {                  // eight row loads in flight
-                        float bv[8][V];
+                for (int q = 0; q < J; ++q)
 #pragma unroll
-                        for (int x = 0; x < 8; ++x) load_vec<V>(B + (a + x) * cols, bv[x]);
+                    for (int v = 0; v < V; ++v) t0[q][v] = 0.f;
 #pragma unroll
-                        for (int x = 0; x < 8; ++x)
+                for (int x = 0; x < RR; ++x)
+#pragma unroll
+                    for (int q = 0; q < J; ++q) {
+                        const float av = A[q * RR + x];
+#pragma unroll
+                        for (int v = 0; v < V; ++v) t0[q][v] = fmaf(av, bv[x][v], t0[q][v]);
+                    }
+                if (lane * V < cols)
+#pragma unroll
+                    for (int q = 0; q < J; ++q) store_vec<V>(T + q * cols + c0, t0[q]);
+            } else {
+                for (int jc = 0; jc < n1; jc += J)
+                    for (int c0 = lane * V; c0 < cols; c0 += WAVE * V) {
+                        float t0[J][V];
+#pragma unroll
+                        for (int q = 0; q < J; ++q)
+#pragma unroll
+                            for (int v = 0; v < V; ++v) t0[q][v] = 0.f;
+                        const float *B = Bm + c0;
+                        int a = 0;
+                        for (; a + 8 <= R1; a += 8) {                  // eight row loads in flight
+                            float bv[8][V];
+#pragma unroll
+                            for (int x = 0; x < 8; ++x) load_vec<V>(B + (a + x) * cols, bv[x]);
+#pragma unroll
+                            for (int x = 0; x < 8; ++x)
+#pragma unroll
+                                for (int q = 0; q < J; ++q) {
+                                    const float av = A[min(jc + q, n1 - 1) * R1 + a + x];
+#pragma unroll
+                                    for (int v = 0; v < V; ++v) t0[q][v] = fmaf(av, bv[x][v], t0[q][v]);
+                                }
+                        }
+                        for (; a < R1; ++a) {
+                            float bv[V];
+                            load_vec<V>(B + a * cols, bv);
 #pragma unroll
                             for (int q = 0; q < J; ++q) {
-                                const float av = A[min(jc + q, n1 - 1) * R1 + a + x];
+                                const float av = A[min(jc + q, n1 - 1) * R1 + a];
 #pragma unroll
-                                for (int v = 0; v < V; ++v) t0[q][v] = fmaf(av, bv[x][v], t0[q][v]);
+                                for (int v = 0; v < V; ++v) t0[q][v] = fmaf(av, bv[v], t0[q][v]);
                             }
-                    }
-                    for (; a < R1; ++a) {
-                        float bv[V];
-                        load_vec<V>(B + a * cols, bv);
-#pragma unroll
-                        for (int q = 0; q < J; ++q) {
-                            const float av = A[min(jc + q, n1 - 1) * R1 + a];
-#pragma unroll
-                            for (int v = 0; v < V; ++v) t0[q][v] = fmaf(av, bv[v], t0[q][v]);
                         }
-                    }
 #pragma unroll
-                    for (int q = 0; q < J; ++q)
-                        if (jc + q < n1) store_vec<V>(T + (jc + q) * cols + c0, t0[q]);
-                }
+                        for (int q = 0; q < J; ++q)
+                            if (jc + q < n1) store_vec<V>(T + (jc + q) * cols + c0, t0[q]);
+                    }
+            }
             __builtin_amdgcn_wave_barrier();                       // (LDS of one wave is in order: only the compiler has to keep it)
 #pragma unroll
             for (int u = 0; u < 4; ++u)
@@ -991,9 +1016,11 @@ __global__ __launch_bounds__(WG) void flex_fwd_kernel(Params p, const float *__r
                     const float *Tq = T + oq[u] * R2, *Cq = C + o3[u];
                     int b = part;
                     if (u == 0) {
+                        float tq[16];                              // (read at once, picked afterwards)
 #pragma unroll
-                        for (int q = 0; q < 16; ++q, b += parts)
-                            if (b < R2) s = fmaf(Tq[b], cpre[q], s);
+                        for (int q = 0; q < 16; ++q) tq[q] = Tq[min(part + q * parts, R2 - 1)];
+#pragma unroll
+                        for (int q = 0; q < 16; ++q, b += parts) s = b < R2 ? fmaf(tq[q], cpre[q], s) : s;
                     }
                     for (; b + 7 * parts < R2; b += 8 * parts) {   // eight loads in flight
                         float x[8];
@@ -1021,16 +1048,26 @@ __global__ __launch_bounds__(WG) void flex_fwd_kernel(Params p, const float *__r
 static inline int flex_fwd_v(const Params &p) { return p.cols > 128 && p.cols % 4 == 0 ? 4 : (p.cols > 64 && p.cols % 2 == 0 ? 2 : 1); }
 static inline int flex_fwd_j(const Params &p) { return p.n1 <= 2 ? 2 : 4; }
 
+// One turn and the rank in eights (see flex_fwd_kernel): ahead of the plain kernel for all of 25 such shapes.  4,096 bags of one
+// position / 64 of 60, eight rows at a time, this, plain: (4,4,4) at rank 16 11.0 / 151, 7.4 / 64 and 10.6 / 171 us, (2,4,4) at 24
+// 10.7 / 136, 9.4 / 74, 12.7 / 239, (4,4,4) at 8 -, 6.5 / 51, 7.8 / 102, (4,3,4) at (32,16) 14.2 / 211, 9.0 / 104, 13.5 / 269.
+static inline bool flex_fwd_one_turn(const Params &p)
+{
+    const int V = flex_fwd_v(p);
+    return p.n1 == flex_fwd_j(p) && p.cols <= WAVE * V && p.cols % V == 0 && p.R1 % 8 == 0 && p.R1 <= 32;
+}
+
 // Is the wave per bag ahead of the plain kernel, which gives a bag four waves and a position three barriers?  The wave pays for
 // turns over rows j1 that are not all there, for lanes without columns and, eight loads or one at a time, for ranks and outputs
 // off its steps; the plain kernel for its rounds of 256 values and one load after the other along the ranks.  What a position
 // takes is estimated for both, in units of 10 ns, from timings of 100 shapes in bags of 60 positions (the estimates are off by 9 and 5 % at the
 // median).  Few bags, many short ones and many single ones all come out the same way; wave / plain, 64 bags of 60: (4,4,8) at
-// rank 64 657 / 1,966 us, (2,4,4) at 24 137 / 239, (4,4,4) at 16 152 / 171, (4,4,4) at 8 110 / 99, (5,3,7) at (17,33)
+// rank 64 657 / 1,966 us, (5,3,7) at (17,33)
 // 469 / 293, (6,6,6) at 7 272 / 97, (16,1,16) at (64,3) 1,269 / 313.  The kernel so chosen was the slower one by more than 10 %, and
 // by up to 31 %, for three of the 100.
 static inline bool flex_fwd_pays(const Params &p)
 {
+    if (flex_fwd_one_turn(p)) return true;
     auto up = [](int a, int b) { return (a + b - 1) / b; };
     auto trips = [](int n) { return n > 0 ? n / 8 + n % 8 : 0; };              // (the last ones one at a time)
     const int V = flex_fwd_v(p), J = flex_fwd_j(p), turns = up(p.n1, J) * up(p.cols, WAVE * V);
@@ -1051,13 +1088,27 @@ static inline void flex_fwd(const Params &p, const float *G1, const float *G2, c
     const dim3 grid((n_bags + NWAVE - 1) / NWAVE), wg(WG);
     const size_t lds = flex_fwd_lds(p);
     const int V = flex_fwd_v(p);
-#define FX_FWD(J, VV) hipLaunchKernelGGL((flex_fwd_kernel<J, VV>), grid, wg, lds, st, p, G1, G2, G3, idx, off, n_bags, alpha, cd, out)
-    if (flex_fwd_j(p) == 2) {
-        if (V == 4) FX_FWD(2, 4); else if (V == 2) FX_FWD(2, 2); else FX_FWD(2, 1);
-    } else {
-        if (V == 4) FX_FWD(4, 4); else if (V == 2) FX_FWD(4, 2); else FX_FWD(4, 1);
-    }
-#undef FX_FWD
+    const int J = flex_fwd_j(p);
+    auto launch = [&](auto j, auto v) {
+        auto go = [&](auto nch) {
+            hipLaunchKernelGGL((flex_fwd_kernel<decltype(j)::value, decltype(v)::value, decltype(nch)::value>), grid, wg, lds, st, p, G1, G2, G3,
+                               idx, off, n_bags, alpha, cd, out);
+        };
+        switch (flex_fwd_one_turn(p) ? p.R1 / 8 : 0) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 3: go(std::integral_constant<int, 3>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        default: go(std::integral_constant<int, 0>{});
+        }
+    };
+    auto with_v = [&](auto j) {
+        if (V == 4) launch(j, std::integral_constant<int, 4>{});
+        else if (V == 2) launch(j, std::integral_constant<int, 2>{});
+        else launch(j, std::integral_constant<int, 1>{});
+    };
+    if (J == 2) with_v(std::integral_constant<int, 2>{});
+    else with_v(std::integral_constant<int, 4>{});
 }
 
 // pass: what flex_pass says for the workspace that a.w lies in

@@ -139,3 +139,13 @@ def test_no_workspace_takes_the_plain_kernels():
     rg, _ = ora.bwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets, d.batch.grad_output, alpha=d.batch.alpha)
     for k in range(3):
         assert_close(dg[k].cpu().numpy(), rg[k], "no workspace dG%d" % (k + 1))
+
+
+# ranks in eights with one turn over j1 and the columns (every load of a position at once): 8 to 32, two and four rows j1, one, two and four
+# columns per lane, lanes without columns, outputs beyond a wave and of odd number; next to them the first ranks and columns that are not
+@pytest.mark.parametrize("n,r", [((4, 4, 4), (8, 8)), ((2, 4, 4), (16, 16)), ((4, 4, 4), (24, 24)), ((2, 3, 5), (24, 20)), ((2, 2, 4), (32, 64)), ((4, 8, 8), (32, 32)),
+                                 ((4, 3, 1), (16, 23)), ((2, 1, 2), (8, 2)), ((2, 4, 4), (40, 24)), ((2, 4, 8), (24, 65)), ((4, 4, 8), (20, 16)), ((3, 4, 4), (16, 16))])
+def test_forward_with_ranks_in_eights(n, r):
+    d = _table((7, 6, 9), n, r, 200, 70, 47, hot=0.1)
+    b = d.batch
+    assert_close(d.fwd(), ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha), "n %s r %s" % (n, r))
