@@ -324,13 +324,13 @@ int64_t tt_cache_table_capacity(int64_t K)
 // What a step over distinct rows (tt_rows.h) needs of the workspace, 0 where the shape has none.
 static size_t rows_ws_bytes(const Params &p, int64_t L, int64_t K)
 {
-    return !K && rw_supported(p) ? 256 + rw_ws_layout(nullptr, p, L, rw_tile_wgs(p, L)).bytes : 0;
+    return rw_supported(p) && rw_cache_supported(p, K) ? 256 + rw_ws_layout(nullptr, p, L, K, rw_tile_wgs(p, L, K)).bytes : 0;
 }
 // What the queries say for it, enough for every length up to L: nothing below the first length at which a step can group its
 // positions, and from RW_LONG_MIN_L on, where longer windows need fewer counters, not less than just below it.
 static size_t rows_ws_query(const Params &p, int64_t L, int64_t K)
 {
-    if (K || !rw_supported(p) || !bwd_tiles_wanted(p, L) || (g_fast_path == 1 && L < group_min_l(p, 0, true, true))) return 0;
+    if (!rw_supported(p) || !rw_cache_supported(p, K) || !bwd_tiles_wanted(p, L) || (g_fast_path == 1 && L < group_min_l(p, K, true, true))) return 0;
     return larger(rows_ws_bytes(p, L, K), L >= RW_LONG_MIN_L ? rows_ws_bytes(p, RW_LONG_MIN_L - 1, K) : 0);
 }
 
@@ -465,13 +465,14 @@ static bool bwd_groups(const Params &p, int64_t L, int64_t K, bool kept_t0)
 // Does a step whose positions are grouped work on its distinct rows (tt_rows.h)?
 static bool works_on_rows(const Params &p, int64_t L, int64_t K, bool kept_t0)
 {
-    return L > 0 && kept_t0 && !K && rw_supported(p) && bwd_tiles_wanted(p, L);
+    return L > 0 && kept_t0 && rw_supported(p) && (!K || (rw_cache_supported(p, K) && g_fast_path == 1)) && bwd_tiles_wanted(p, L) &&
+           (!K || L >= GROUP_MIN_L_CACHE);
 }
 
 // does tt_emb_fwd_prepared work from the pre-pass's lists for such a call?
-static bool fwd_from_lists(const Params &p, int64_t L, int64_t K, bool kept_t0)
+static bool fwd_from_lists(const Params &p, int64_t L, int64_t K, bool kept_t0, bool rows_room = true)
 {
-    if (works_on_rows(p, L, K, kept_t0)) return g_fast_path == 2 || L >= rows_fwd_min_l(p);
+    if (rows_room && works_on_rows(p, L, K, kept_t0)) return g_fast_path == 2 || L >= rows_fwd_min_l(p);
     // (only for the long streams: at 8,192 positions, where the (4,4,4) backward already groups, the wave per bag is ahead: 31 against 36 us)
     return L > 0 && fwd_lists_pay(p, K) && bwd_groups(p, L, K, kept_t0) && (g_fast_path == 2 || L >= (K ? GROUP_MIN_L_CACHE : GROUP_MIN_L)) &&
            3 * L < (1ll << 31);
@@ -497,11 +498,12 @@ int tt_emb_fwd_prepared(const tt_shape_t *shape, const float *const cores[3],
     if ((rc = check_cache(cache, &cd, true))) return rc;
     if (t0 && fast_config(p) < 0) return fail(TT_ERR_UNSUPPORTED, "no kernel keeps T0 for this shape");
     // the lists exist if the backward of this call groups its positions; else the forward needs none
-    const bool rows = works_on_rows(p, L, cd.K, t0 != nullptr);
+    // (with a cache they are of distinct rows only where the workspace has room for that, as in bwd_common)
+    const bool room = workspace && workspace_bytes >= rows_ws_bytes(p, L, cd.K) && !misaligned({workspace});
+    const bool rows = works_on_rows(p, L, cd.K, t0 != nullptr) && (!cd.K || room);
     // (between the two limits the lists are a choice: without room for them the pass is the wave per bag)
-    const bool no_room = rows && g_fast_path == 1 && L < GROUP_MIN_L &&
-                         (!workspace || workspace_bytes < rows_ws_bytes(p, L, cd.K) || misaligned({workspace}));
-    if (no_room || !(n_bags > 0 && fwd_from_lists(p, L, cd.K, t0 != nullptr)))
+    const bool no_room = rows && g_fast_path == 1 && L < GROUP_MIN_L && !room;
+    if (no_room || !(n_bags > 0 && fwd_from_lists(p, L, cd.K, t0 != nullptr, rows)))
         return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, cache, output, t0, t0 != nullptr, stream);
     if (!cores || !cores[0] || !cores[1] || !cores[2]) return fail(TT_ERR_NULL, "cores is NULL");
     if (!output) return fail(TT_ERR_NULL, "output is NULL");
@@ -511,8 +513,8 @@ int tt_emb_fwd_prepared(const tt_shape_t *shape, const float *const cores[3],
     if (misaligned({cores[0], cores[1], cores[2], output, t0, cd.rows, workspace}))
         return fail(TT_ERR_BAD_ARG, "cores, output, t0, cache rows and workspace must be 16-byte aligned");
     if (rows) {
-        hipError_t e = rw_fwd(p, cores[0], cores[1], cores[2], L, offsets, (int)n_bags, alpha, output, t0,
-                              rw_ws_layout(workspace, p, L, rw_tile_wgs(p, L)), (hipStream_t)stream);
+        hipError_t e = rw_fwd(p, cores[0], cores[1], cores[2], L, offsets, (int)n_bags, alpha, cd, output, t0,
+                              rw_ws_layout(workspace, p, L, cd.K, rw_tile_wgs(p, L, cd.K)), (hipStream_t)stream);
         return e == hipSuccess ? TT_OK : hip_fail(e, "forward launch");
     }
     const int nbins = p.m1 + p.m2 + p.m3 + cd.K;
@@ -604,24 +606,28 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     // long streams with a kept T0: the products of Eq. 4 over tiles of positions, on the matrix cores (tt_bwd_owner.h)
     // (with a cache the list owners stay: the cached rows' sums ride along in their launches, multi-hot table 0: 113 against 140 us)
     const bool tiled = grouped && t0 && (!cd.K || g_bwd_tiles) && bwd_tiles_wanted(p, L);
-    if (tiled && works_on_rows(p, L, cd.K, t0 != nullptr)) {
+    // (with a cache, a workspace without room for the passes over distinct rows is one for the list owners: both calls of a pair
+    // decide by the same size)
+    if (grouped && works_on_rows(p, L, cd.K, t0 != nullptr) && (cd.K ? workspace && workspace_bytes >= rows_ws_bytes(p, L, cd.K) : tiled)) {
         const size_t need = rows_ws_bytes(p, L, cd.K);
         if (!workspace || workspace_bytes < need)
             return fail(TT_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need, workspace_bytes);
         guess_bag_length(&p, offsets, L, n_bags);
-        const RowsWs ws = rw_ws_layout(workspace, p, L, rw_tile_wgs(p, L));
+        const RowsWs ws = rw_ws_layout(workspace, p, L, cd.K, rw_tile_wgs(p, L, cd.K));
         hipError_t e = hipSuccess;
-        if (phase != BWD_REST) e = rw_prepare(p, indices, (int)L, offsets, (int)n_bags, rw_tp(p), ws, (hipStream_t)stream);
+        if (phase != BWD_REST) e = rw_prepare(p, indices, (int)L, offsets, (int)n_bags, cd, rw_tp(p), ws, (hipStream_t)stream);
         if (!prep && e == hipSuccess) {
             const float *const src[3] = {fused ? cores[0] : grad_cores[0], fused ? cores[1] : grad_cores[1], fused ? cores[2] : grad_cores[2]};
-            e = rw_bwd(p, cores[0], cores[1], cores[2], L, alpha, grad_output, t0, src, fused ? cores_out : grad_cores, fused ? -lr : 1.f, ws,
-                       (hipStream_t)stream);
+            float *lines = !cd.K ? nullptr : fused ? cache->rows : grad_cache;
+            e = rw_bwd(p, cores[0], cores[1], cores[2], L, alpha, grad_output, t0, src, fused ? cores_out : grad_cores, fused ? -lr : 1.f, cd.K,
+                       lines, ws, (hipStream_t)stream);
         }
         return e == hipSuccess ? TT_OK : hip_fail(e, "backward launch");
     }
     // positions per tile of the tile table: 128 / n1 where the forward pass works from it too; the smaller tiles of the
     // tiled backward only where the table has room for them (tt_group.h: L / 32 + slices + 1 entries)
-    int tile_tp = bo_tp(p, L, tiled && !fwd_from_lists(p, L, cd.K, t0 != nullptr));
+    const bool fwd_lists = fwd_from_lists(p, L, cd.K, t0 != nullptr, !cd.K);   // (with a cache: not of rows, or the call had ended above)
+    int tile_tp = bo_tp(p, L, tiled && !fwd_lists);
     if (bo_tiles(p, L, tile_tp) > L / 32 + p.m1 + p.m2 + p.m3 + cd.K + 1) tile_tp = 128 / p.n1;
     const size_t sp_bytes = fast ? split_ws_bytes(p, L, grouped, t0 != nullptr && (!cd.K || g_bwd_tiles)) : (flex ? fx_bytes : 0);
     const size_t need = need_bwd + gc_bytes + g_bytes[0] + g_bytes[1] + g_bytes[2] + sp_bytes;
@@ -696,7 +702,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
             if (tiled)
                 hipLaunchKernelGGL(grp_info_kernel, dim3(cdiv(n, WG)), dim3(WG), 0, st, p, indices, (int)L, offsets, (int)n_bags, ks, vs,
                                    nb3, g.info);
-            if (fwd_from_lists(p, L, cd.K, t0 != nullptr) || tiled) {       // for tt_emb_fwd_prepared and the tiled backward
+            if (fwd_lists || tiled) {       // for tt_emb_fwd_prepared and the tiled backward
                 const int ntiles = bo_tiles(p, L, tile_tp);
                 hipLaunchKernelGGL(grp_tiles_kernel, dim3(cdiv(ntiles, WG)), dim3(WG), 0, st, p.m1, p.m2, (int)L, tile_tp,
                                    g.off, g.end, g.tiles, ntiles, g.tile_base);

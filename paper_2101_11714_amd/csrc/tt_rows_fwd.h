@@ -29,7 +29,7 @@ static inline RowsWs rf_ws_layout(void *ws, const Params &p, int64_t L)
     char *base = (char *)ws;
     size_t off = 0;
     auto take = [&](size_t bytes) { char *q = base ? base + off : nullptr; off += align256(bytes); return q; };
-    const size_t n = L > 0 ? (size_t)L : 1, nw = (size_t)rw_windows(p, L, RF_WIN);
+    const size_t n = L > 0 ? (size_t)L : 1, nw = (size_t)rw_windows_of(p, L, RF_WIN);
     w.hist = (uint32_t *)take((size_t)((n + rf_tile(L) - 1) / rf_tile(L)) * ((p.m2 + 3) & ~3) * 4);
     w.lk = (uint32_t *)take(n * 4);
     w.lrow = (uint32_t *)take(n * 4);
@@ -243,11 +243,12 @@ static inline hipError_t launch_rows_fwd(const Params &p, const float *G1, const
     static OncePerDevice once;
     hipError_t e = allow_dynamic_lds(once, (const void *)rf_rows_kernel<C>, F::LDS);
     if (e != hipSuccess) return e;
-    const int nw = rw_windows(p, L, RF_WIN);
-    rw_place(p, indices, (int)L, rf_tile(L), ws, st);
+    const int nw = rw_windows_of(p, L, RF_WIN);
+    const CacheDev none{nullptr, nullptr, 0, 0};
+    rw_place(p, indices, (int)L, none, rf_tile(L), ws, st);
     hipLaunchKernelGGL(rf_group_kernel, dim3(nw), dim3(RW_T), 0, st, p, ws);
     hipLaunchKernelGGL(rf_rows_kernel<C>, dim3(nw * F::PARTS), dim3(F::NW * WAVE), F::LDS, st, p, G1, G2, G3, (int)L, ws);
-    hipLaunchKernelGGL(rw_pool_kernel, dim3((n_bags + NWAVE - 1) / NWAVE), dim3(WG), 0, st, C::N, ws.rows, ws.inv, off, n_bags, alpha, out);
+    hipLaunchKernelGGL(rw_pool_kernel, dim3((n_bags + NWAVE - 1) / NWAVE), dim3(WG), 0, st, C::N, ws.rows, ws.inv, (const float *)nullptr, off, n_bags, alpha, out);
     return hipGetLastError();
 }
 

@@ -175,8 +175,9 @@ __global__ __launch_bounds__(WG) void rw_fwd_kernel(Params p, const float *__res
 }
 
 // out[bag] = sum over the bag's positions of alpha[k] rows[inv[k]], one wave per bag: the wave looks at up to 64 positions
-// at once, then lane (sub, f) adds float4 f of every (64 / (N/4))-th of them, four in flight.
-__global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restrict__ rows, const int *__restrict__ inv,
+// at once, then lane (sub, f) adds float4 f of every (64 / (N/4))-th of them, four in flight.  With a cache (lines), the line
+// ~inv[k] where that is not negative.
+__global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
                                                      const int64_t *__restrict__ offsets, int n_bags, const float *__restrict__ alpha,
                                                      float *__restrict__ out)
 {
@@ -199,7 +200,8 @@ __global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restr
             for (int q = 0; q < 4; ++q) {
                 const int pi = min(q0 + q * per, cnt - 1);
                 wgt[q] = __shfl(myw, pi);
-                x[q] = *reinterpret_cast<const float4 *>(rows + (size_t)__shfl(myu, pi) * N + 4 * f);
+                const int u = __shfl(myu, pi);
+                x[q] = *reinterpret_cast<const float4 *>((lines && u < 0 ? lines + (size_t)~u * N : rows + (size_t)u * N) + 4 * f);
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(BoCfg<C, ROW
 }
 
 // ---- the sums that finish the three cores -----------------------------------------------------------------------------
-// Workgroups [0, m1 + m3): the first piece (rw_piece rows) of a slice of the first (third) core; the next `extra`: what slices
+// Workgroups [0, cwgs): gradients of cached rows; then, counted from there, [0, m1 + m3): the first piece (rw_piece rows) of a slice of the first (third) core; the next `extra`: what slices
 // have beyond that; the rest: the parts of the slices of the second core.  A slice of one piece (nearly all, where rows repeat:
 // equal rows are one) is finished on the spot; of a longer one every piece leaves a partial sum and the workgroup that arrives
 // last adds them, in their order.  How many extra pieces there are is only known on the device: as many workgroups are started
@@ -569,6 +571,8 @@ struct RsArgs {
     float mul;
     int nwg;                 // workgroups of the tile kernel
     int piece, extra;        // rows of a piece (RW_PIECE at most); workgroups for the extra pieces
+    int K, cwgs;             // cached rows, and the workgroups that add their gradients up
+    float *lines;            // lines[slot] += mul * gradient
 };
 
 template <typename C>
@@ -583,10 +587,39 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
     __shared__ int s_tmp[RW_NW], s_at[3], s_last;
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), m13 = p.m1 + p.m3;
 
-    if ((int)blockIdx.x >= m13 + a.extra) {
+    if ((int)blockIdx.x < a.cwgs) {
+        // the gradient of a cached row: over the windows of its bin, in their order; N / 4 lanes per slot, eight windows in flight
+        constexpr int NQ = N / 4, NF = 8;
+        const int slot = ((int)blockIdx.x * RW_T + t) / NQ, f = t % NQ;
+        if (slot >= a.K) return;
+        const int bin = slot % RW_CBINS, j = slot / RW_CBINS, w0 = ws.cwin[bin], w1 = ws.cwin[bin + 1];
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+        bool any = false;
+        for (int x = w0; x < w1; x += NF) {
+            int u[NF];
+            float4 v[NF];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) u[q] = ws.cu[(size_t)min(x + q, w1 - 1) * ws.spb + j];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) v[q] = *reinterpret_cast<const float4 *>(dym + (size_t)max(u[q], 0) * N + 4 * f);
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if (x + q < w1 && u[q] >= 0) {
+                    sum.x += v[q].x; sum.y += v[q].y; sum.z += v[q].z; sum.w += v[q].w;
+                    any = true;
+                }
+        }
+        if (!any) return;
+        const size_t at = (size_t)slot * N + 4 * f;
+        const float4 o = *reinterpret_cast<const float4 *>(a.lines + at);
+        *reinterpret_cast<float4 *>(a.lines + at) = make_float4(fmaf(a.mul, sum.x, o.x), fmaf(a.mul, sum.y, o.y), fmaf(a.mul, sum.z, o.z), fmaf(a.mul, sum.w, o.w));
+        return;
+    }
+    const int wg = (int)blockIdx.x - a.cwgs;
+    if (wg >= m13 + a.extra) {
         // dst[i2] = src[i2] + mul * (parts of slice i2, in the order of their workgroups)
         constexpr int FIN = 2 * RW_T, PER = (sB4 + FIN - 1) / FIN, NP = 8;
-        const int vb = blockIdx.x - m13 - a.extra, i2 = vb / PER, e0 = (vb % PER) * FIN + t;
+        const int vb = wg - m13 - a.extra, i2 = vb / PER, e0 = (vb % PER) * FIN + t;
         if (i2 >= p.m2) return;
         const int tb = ws.tile_base[i2], te = ws.tile_base[i2 + 1], ch = bo_chunk(ws.tile_base[p.m2], a.nwg);
         const float4 *src = reinterpret_cast<const float4 *>(a.src[1]) + (size_t)i2 * sB4;
@@ -766,14 +799,14 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
         finish(bin, tot, false);
     };
 
-    if ((int)blockIdx.x < m13) {
-        const int bin = blockIdx.x, i0 = ws.off13[bin], i1 = ws.off13[bin + 1];
+    if (wg < m13) {
+        const int bin = wg, i0 = ws.off13[bin], i1 = ws.off13[bin + 1];
         const float4 sum = add_up(bin, i0, min(i1, i0 + a.piece));
         if (i1 - i0 <= a.piece) finish(bin, sum, i1 == i0);
         else leave(bin, sum, bin, -1);
         return;
     }
-    for (int x = blockIdx.x - m13;; x += a.extra) {
+    for (int x = wg - m13;; x += a.extra) {
         __syncthreads();
         find_extra(x, -1);
         if (x >= s_at[2]) return;                                             // uniform
@@ -791,71 +824,72 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
 static inline int rw_tp(const Params &p) { return 128 / p.n1; }
 
 // workgroups of the tile kernel: what the compute units hold, more only where one would get more tiles than it has room for
-static inline int rw_tile_wgs(const Params &p, int64_t L)
+static inline int rw_tile_wgs(const Params &p, int64_t L, int64_t K)
 {
     const int n = (p.R1 >= 64 ? 1 : 2) * bo_compute_units();
-    const int least = (rw_tiles(p, L, rw_tp(p)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
+    const int least = (rw_tiles(p, L, K, rw_tp(p)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
     return n > least ? n : least;
 }
 
 template <typename C, int ROWS_>
 static inline hipError_t launch_rw_fwd(const Params &p, const float *G1, const float *G2, const float *G3, int64_t L, const int64_t *off, int n_bags,
-                                       const float *alpha, float *out, float *t0, const RowsWs &ws, hipStream_t st)
+                                       const float *alpha, const CacheDev &cache, float *out, float *t0, const RowsWs &ws, hipStream_t st)
 {
     const size_t lds = (size_t)RfCfg<C, ROWS_>::LDS_FLOATS * sizeof(float);
     static OncePerDevice once;
     hipError_t e = allow_dynamic_lds(once, (const void *)rw_fwd_kernel<C, ROWS_>, lds);
     if (e != hipSuccess) return e;
     // how many tiles are in use is only known on the device: some workgroups find none, or more than one
-    const int tiles = rw_tiles(p, L, ROWS_ / C::N1), started = tiles < 2048 ? tiles : 2048;
+    const int tiles = rw_tiles(p, L, cache.K, ROWS_ / C::N1), started = tiles < 2048 ? tiles : 2048;
     hipLaunchKernelGGL((rw_fwd_kernel<C, ROWS_>), dim3(started * C::N2), dim3(WG), lds, st, p, G1, G2, G3, (int)L, ws.rec, ws.gkb, ws.gu,
                        ws.tiles, ws.tile_base, ws.rows, t0);
-    hipLaunchKernelGGL(rw_pool_kernel, dim3((n_bags + NWAVE - 1) / NWAVE), dim3(WG), 0, st, C::N, ws.rows, ws.inv, off, n_bags, alpha, out);
+    hipLaunchKernelGGL(rw_pool_kernel, dim3((n_bags + NWAVE - 1) / NWAVE), dim3(WG), 0, st, C::N, ws.rows, ws.inv, cache.K ? cache.rows : (const float *)nullptr, off, n_bags, alpha, out);
     return hipGetLastError();
 }
 
 static inline hipError_t rw_fwd(const Params &p, const float *G1, const float *G2, const float *G3, int64_t L, const int64_t *off, int n_bags,
-                                const float *alpha, float *out, float *t0, const RowsWs &ws, hipStream_t st)
+                                const float *alpha, const CacheDev &cache, float *out, float *t0, const RowsWs &ws, hipStream_t st)
 {
     switch (fast_config(p)) {
-    case 2: return launch_rw_fwd<Cfg224R32, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
-    case 3: return launch_rw_fwd<Cfg224R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
-    case 4: return launch_rw_fwd<Cfg444R32, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
-    case 5: return launch_rw_fwd<Cfg444R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, out, t0, ws, st);
+    case 2: return launch_rw_fwd<Cfg224R32, 128>(p, G1, G2, G3, L, off, n_bags, alpha, cache, out, t0, ws, st);
+    case 3: return launch_rw_fwd<Cfg224R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, cache, out, t0, ws, st);
+    case 4: return launch_rw_fwd<Cfg444R32, 128>(p, G1, G2, G3, L, off, n_bags, alpha, cache, out, t0, ws, st);
+    case 5: return launch_rw_fwd<Cfg444R64, 128>(p, G1, G2, G3, L, off, n_bags, alpha, cache, out, t0, ws, st);
     default: return hipErrorInvalidValue;
     }
 }
 
 template <typename C, int ROWS_>
 static inline hipError_t launch_rw_bwd(const Params &p, const float *G1, const float *G2, const float *G3, int64_t L, const float *alpha,
-                                       const float *go, const float *t0, const float *const src[3], float *const dst[3], float mul, const RowsWs &ws,
+                                       const float *go, const float *t0, const float *const src[3], float *const dst[3], float mul, int K, float *lines, const RowsWs &ws,
                                        hipStream_t st)
 {
     const size_t lds = bo_lds_bytes<C, ROWS_>();
     static OncePerDevice once;
     hipError_t e = allow_dynamic_lds(once, (const void *)rw_tile_kernel<C, ROWS_>, lds);
     if (e != hipSuccess) return e;
-    const int nwg = rw_tile_wgs(p, L), per = (C::sB / 4 + 2 * RW_T - 1) / (2 * RW_T);
+    const int nwg = rw_tile_wgs(p, L, K), cwgs = (int)(((int64_t)K * (C::N / 4) + RW_T - 1) / RW_T), per = (C::sB / 4 + 2 * RW_T - 1) / (2 * RW_T);
     constexpr int MT = C::N > 16 ? 512 : 256;
     hipLaunchKernelGGL((rw_merge_kernel<C::N, MT>), dim3((unsigned)((L + RM_ROWS - 1) / RM_ROWS)), dim3(MT), 0, st, (int)L, ws.rec, ws.gkb, alpha, go,
                        ws.dym);
     hipLaunchKernelGGL((rw_tile_kernel<C, ROWS_>), dim3(nwg), dim3(WG), lds, st, p, G1, G2, G3, (int)L, ws.dym, ws.rec, ws.tiles, ws.tile_base,
                        ws.part2, ws.pbuf, src[1], dst[1], mul);
     const int most = rw_extra(p, L), extra = most < RS_MAX_EXTRA ? most : RS_MAX_EXTRA;
-    const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg, rw_piece(p, L), extra};
-    hipLaunchKernelGGL((rw_sum_kernel<C>), dim3(p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
+    const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg, rw_piece(p, L), extra, K, cwgs, lines};
+    hipLaunchKernelGGL((rw_sum_kernel<C>), dim3(cwgs + p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
                        ws.dym, ws.pbuf, ws.l13);
     return hipGetLastError();
 }
 
 static inline hipError_t rw_bwd(const Params &p, const float *G1, const float *G2, const float *G3, int64_t L, const float *alpha, const float *go,
-                                const float *t0, const float *const src[3], float *const dst[3], float mul, const RowsWs &ws, hipStream_t st)
+                                const float *t0, const float *const src[3], float *const dst[3], float mul, int K, float *lines,
+                                const RowsWs &ws, hipStream_t st)
 {
     switch (fast_config(p)) {
-    case 2: return launch_rw_bwd<Cfg224R32, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
-    case 3: return launch_rw_bwd<Cfg224R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
-    case 4: return launch_rw_bwd<Cfg444R32, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
-    case 5: return launch_rw_bwd<Cfg444R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, ws, st);
+    case 2: return launch_rw_bwd<Cfg224R32, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, K, lines, ws, st);
+    case 3: return launch_rw_bwd<Cfg224R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, K, lines, ws, st);
+    case 4: return launch_rw_bwd<Cfg444R32, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, K, lines, ws, st);
+    case 5: return launch_rw_bwd<Cfg444R64, 128>(p, G1, G2, G3, L, alpha, go, t0, src, dst, mul, K, lines, ws, st);
     default: return hipErrorInvalidValue;
     }
 }

@@ -135,3 +135,78 @@ def test_one_workspace_on_either_side_of_the_longer_windows():
     ws = torch.full((B.bwd_sgd_workspace_bytes(a.shape, a.L, a.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
     for d in (a, b):
         _check(d, "%d positions" % d.L, ws=ws)
+
+
+# With a cache: slots in one bin of 128 and several, the last bin's slots missing, as many as the passes take and one more (the list owners);
+# no position cached, all of them, a hot slot over many windows; streams on either side of the window sizes.
+@pytest.mark.parametrize("n,R,L,K,share", [((4, 4, 4), 32, 16_384, 1, 0.7), ((4, 4, 4), 32, 20_001, 129, 0.8), ((2, 2, 4), 32, 66_000, 300, 0.9),
+                                           ((2, 2, 4), 64, 17_000, 1000, 0.0), ((4, 4, 4), 64, 16_500, 128, 1.0), ((2, 2, 4), 32, 16_400, 8192, 0.5),
+                                           ((2, 2, 4), 32, 16_400, 8193, 0.5)])
+def test_with_a_cache(n, R, L, K, share):
+    rng = np.random.default_rng([L, K])
+    t = W.TableShape(30 * 20 * 40 - 3, (30, 20, 40), n, (1, R, R, 1))
+    keys = np.sort(rng.choice(t.num_rows, K, replace=False)).astype(np.int64)
+    other = np.setdiff1d(np.arange(t.num_rows), keys)
+    idx = np.where(rng.random(L) < share, rng.choice(keys, L), rng.choice(other, L)).astype(np.int64)
+    if share > 0:
+        idx[rng.random(L) < 0.3 * share] = keys[K // 2]
+    n_bags = 900
+    off = np.concatenate([[0], np.sort(rng.integers(0, L + 1, n_bags - 1)), [L]]).astype(np.int64)
+    batch = W.Batch(idx, off, rng.standard_normal((n_bags, t.dim)).astype(np.float32), (0.5 + rng.random(L)).astype(np.float32))
+    d = DeviceTable(W.Workload("rows", (t,), n_bags, (0, 9), "uniform", 0.0, "normal0.1", 3), batch=batch)
+    counts = np.arange(K, 0, -1).astype(np.int64)
+    cache, _, _ = d.build_cache(K, keys, counts)
+    sel = ora.cache_select(keys, counts, K)
+    lines = cache.rows.clone()
+    crow = lines.cpu().numpy()[:K].copy()
+    ref = ora.fwd(d.oshape, d.cores, idx, off, alpha=batch.alpha, cache_keys=sel, cache_rows=crow)
+    rg, rc = ora.bwd(d.oshape, d.cores, idx, off, batch.grad_output, alpha=batch.alpha, cache_keys=sel)
+    need = B.bwd_sgd_workspace_bytes(d.shape, L, n_bags, K)
+    got = []
+    for two_calls in (True, True, False):
+        cache.rows.copy_(lines)
+        ws = torch.full((need,), 0x7F, dtype=torch.uint8, device=dev())
+        out = torch.full((n_bags, t.dim), float("nan"), dtype=torch.float32, device=dev())
+        t0 = torch.full((L, B.t0_floats(d.shape)), float("nan"), dtype=torch.float32, device=dev())
+        new = [torch.full_like(x, float("nan")) for x in d.g]
+        B.tt_emb_bwd_prepare(d.shape, d.idx, d.off, n_bags, cache=cache, workspace=ws, kept_t0=True)
+        B.tt_emb_fwd_prepared(d.shape, d.g, d.idx, d.off, n_bags, out, ws, t0=t0, alpha=d.alpha, cache=cache)
+        B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, n_bags, d.go, 0.05, alpha=d.alpha, cache=cache, workspace=ws, t0=t0, prepared=two_calls)
+        torch.cuda.synchronize()
+        got.append([out] + new + [cache.rows.clone()])
+    assert all(torch.equal(x, y) for other_run in got[1:] for x, y in zip(got[0], other_run))
+    assert_close(got[0][0].cpu().numpy(), ref, "forward")
+    for k in range(3):
+        assert_close(got[0][1 + k].cpu().numpy(), ora.sgd(d.cores[k], rg[k], 0.05), "core %d" % (k + 1))
+    assert_close(got[0][4].cpu().numpy()[:K], ora.sgd(crow, rc, 0.05), "cache lines")
+    # gradients on their own are added to what is there
+    cache.rows.copy_(lines)
+    gc = torch.full_like(cache.rows, 0.5)
+    dg, dc = d.bwd(cache=cache, grad_cores=[torch.full_like(x, 0.25) for x in d.g], grad_cache=gc, t0=t0)
+    for k in range(3):
+        assert_close(dg[k].cpu().numpy() - 0.25, rg[k], "dG%d" % (k + 1))
+    assert_close(dc.cpu().numpy()[:K] - 0.5, rc, "dCache")
+
+
+def test_with_a_cache_and_little_room_the_list_owners_run():
+    d = _table("hot row", (2, 2, 4), 32, 16_384, 500, 9)
+    rows, counts = np.unique(d.batch.indices, return_counts=True)
+    cache, _, _ = d.build_cache(100, rows.astype(np.int64), counts.astype(np.int64))
+    lines = cache.rows.clone()
+    full = B.bwd_sgd_workspace_bytes(d.shape, d.L, d.n_bags, 100)
+    out = []
+    for size in (full, 12 << 20):                  # distinct rows take 15 MB here, the list owners 9
+        cache.rows.copy_(lines)
+        ws = torch.full((size,), 0x7F, dtype=torch.uint8, device=dev())
+        o, t0 = d.fwd_keep_t0(cache=cache)
+        o2 = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+        new = [torch.full_like(x, float("nan")) for x in d.g]
+        B.tt_emb_bwd_prepare(d.shape, d.idx, d.off, d.n_bags, cache=cache, workspace=ws, kept_t0=True)
+        B.tt_emb_fwd_prepared(d.shape, d.g, d.idx, d.off, d.n_bags, o2, ws, t0=t0, alpha=d.alpha, cache=cache)
+        B.tt_emb_bwd_sgd(d.shape, d.g, new, d.idx, d.off, d.n_bags, d.go, 0.05, alpha=d.alpha, cache=cache, workspace=ws, t0=t0, prepared=True)
+        torch.cuda.synchronize()
+        assert_close(o2.cpu().numpy(), o, "forward")
+        out.append([x.cpu().numpy() for x in new] + [cache.rows.cpu().numpy()])
+    for x, y in zip(*out):
+        assert np.isfinite(x).all()
+        assert_close(x, y, "rows against list owners")
