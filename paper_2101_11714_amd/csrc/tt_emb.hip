@@ -55,6 +55,11 @@ bool bwd_tiles_wanted(const Params &p, int64_t L)
 // from this many positions on the backward groups them first (tt_group.h)
 constexpr int64_t GROUP_MIN_L = 32768;          // without a cache
 constexpr int64_t GROUP_MIN_L_CACHE = 16384;    // with a cache (the grouped path also has the faster cached-row reduction)
+// With a cache, a kept T0 and room for the passes over distinct rows (tt_rows.h), one call or two: without them the owners of the
+// cache's slots scan all positions, a hot slot's one after the other.  Step, scanning owners / rows, hit rates of 80, 45 and 5 %: (4,4,4)
+// rank 32 5,120 positions 296 / 55, 205 / 85, 100 / 87 us, 15,360 752 / 83, 455 / 97, 154 / 118; (2,2,4) rank 32 3,000 236 / 68,
+// 165 / 68, 52 / 67, 5,120 391 / 57, 249 / 65, 60 / 53; rank 64 4,000 317 / 65, 219 / 79, 120 / 96.
+constexpr int64_t GROUP_MIN_L_CACHE_ROWS = 4096;
 // With a kept T0 and no cache the grouped backward runs on tiles (tt_bwd_owner.h), which are ahead of the scanning
 // owners much earlier, but only if the pre-pass (about 30 us of small kernels) does not count: so these limits hold
 // for the two-call form, whose first call can run beside other work (Terabyte-shaped, 8,192 positions: 84 against
@@ -96,6 +101,7 @@ int64_t group_min_l(const Params &p, int64_t K, bool kept_t0, bool two_calls)
         if (rw_supported(p) && p.R1 >= 64) return p.n1 == 4 ? GROUP_MIN_L_ROWS_444 : GROUP_MIN_L_ROWS_224;
         return tiles_min_l(p);
     }
+    if (K && kept_t0 && g_fast_path == 1 && rw_supported(p) && rw_cache_supported(p, K)) return GROUP_MIN_L_CACHE_ROWS;
     return K ? GROUP_MIN_L_CACHE : GROUP_MIN_L;
 }
 
@@ -466,7 +472,7 @@ static bool bwd_groups(const Params &p, int64_t L, int64_t K, bool kept_t0)
 static bool works_on_rows(const Params &p, int64_t L, int64_t K, bool kept_t0)
 {
     return L > 0 && kept_t0 && rw_supported(p) && (!K || (rw_cache_supported(p, K) && g_fast_path == 1)) && bwd_tiles_wanted(p, L) &&
-           (!K || L >= GROUP_MIN_L_CACHE);
+           (!K || L >= GROUP_MIN_L_CACHE_ROWS);
 }
 
 // does tt_emb_fwd_prepared work from the pre-pass's lists for such a call?
@@ -578,7 +584,7 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
         return fail(TT_ERR_BAD_ARG, "cores, gradients, t0, cache rows and workspace must be 16-byte aligned");
     const bool fast = (g_fast_path || t0) && fast_bwd_supported(p);
     // (below the tiles' limit grouping is a choice: both calls of a pair whose workspace has no room for it scan instead)
-    const bool no_room = g_fast_path == 1 && L < tiles_min_l(p) && works_on_rows(p, L, cd.K, t0 != nullptr) &&
+    const bool no_room = g_fast_path == 1 && L < (cd.K ? GROUP_MIN_L_CACHE : tiles_min_l(p)) && works_on_rows(p, L, cd.K, t0 != nullptr) &&
                          (!workspace || workspace_bytes < rows_ws_bytes(p, L, cd.K));
     const bool grouped = fast && !no_room && (g_fast_path == 2 || L >= group_min_l(p, cd.K, t0 != nullptr, phase != BWD_ALL));
     if (grouped && 3 * L >= (1ll << 31)) return fail(TT_ERR_UNSUPPORTED, "3 L >= 2^31");
