@@ -115,8 +115,9 @@ int64_t tt_cache_table_capacity(int64_t K);
  * positions in n_bags bags and a cache of cache_rows rows (0 = no cache).  tt_emb_fwd needs
  * none.  tt_emb_bwd needs none for a short index stream without a cache; with a cache, or from
  * 4096 positions on (from there on, depending on the shape, several workgroups share a slice and
- * leave partial sums in the workspace; from 32768 positions on, 16384 with a cache, the positions
- * are grouped first, by distinct row where the call brings a kept T0 and no cache at rank 32 or 64,
+ * leave partial sums in the workspace; from 32768 positions on, 16384 with a cache (4096 with a cache of
+ * up to 8192 rows and a kept T0 at rank 32 or 64), the positions
+ * are grouped first, by distinct row where the call brings a kept T0 at rank 32 or 64,
  * else with a device sort by slice), it reports TT_ERR_WORKSPACE if the workspace is missing
  * or too small.  That is said of the shapes with a specialised kernel; for the others see
  * tt_emb_bwd.  Returns 0 on a bad shape. */
@@ -379,13 +380,13 @@ int tt_emb_bwd_two_calls_group_earlier(const tt_shape_t *shape, int64_t L, int64
  * kernel, the forward pass works from its lists: a workgroup takes positions of one slice of the
  * second core, multiplies their stacked first-core rows with the slice on the matrix cores (Eq. 3,
  * first product), and the rows of each bag are pooled afterwards in position order.  With a kept T0
- * and no cache the lists are of distinct rows: a row is computed once, or once per few hundred to
+ * (and no cache, or one of up to 8192 rows) the lists are of distinct rows: a row is computed once, or once per few hundred to
  * two thousand positions of its slice, and its T0 copied to all its positions.  Otherwise the call is
  * tt_emb_fwd / tt_emb_fwd_keep_t0.
  * The workspace is read (lists) and written (one row per position, in a part of it that the
  * backward calls do not use); the backward call that follows takes the same workspace, of the same
- * workspace_bytes: below 32768 positions a call with a kept T0, no cache and a workspace too small for the
- * lists (smaller than the query says) is tt_emb_fwd_keep_t0, although tt_emb_fwd_uses_lists answers 1.
+ * workspace_bytes: below 32768 positions, or with a cache, a call with a kept T0 and a workspace too small for the
+ * lists of distinct rows (smaller than the query says) is tt_emb_fwd_keep_t0, although tt_emb_fwd_uses_lists answers 1.
  * Same results as tt_emb_fwd up to the order of the fp32 sums over the rank indices.
  */
 /* 1 if tt_emb_fwd_prepared works from the pre-pass's lists for such a call (then the forward pass has to

@@ -610,7 +610,8 @@ static int bwd_common(const tt_shape_t *shape, const float *const cores[3],
     if (fused && !fast && !flex)
         for (int k = 0; k < 3; ++k) g_bytes[k] = align256((size_t)core_floats[k] * 4);
     // long streams with a kept T0: the products of Eq. 4 over tiles of positions, on the matrix cores (tt_bwd_owner.h)
-    // (with a cache the list owners stay: the cached rows' sums ride along in their launches, multi-hot table 0: 113 against 140 us)
+    // (with a cache the list owners are ahead of these: the cached rows' sums ride along in their launches, 113 against 140 us for
+    // the multi-hot table 0; the passes over distinct rows are ahead of both)
     const bool tiled = grouped && t0 && (!cd.K || g_bwd_tiles) && bwd_tiles_wanted(p, L);
     // (with a cache, a workspace without room for the passes over distinct rows is one for the list owners: both calls of a pair
     // decide by the same size)
