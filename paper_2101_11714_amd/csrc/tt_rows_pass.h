@@ -18,6 +18,8 @@
 
 namespace tt {
 
+typedef float rw_f4 __attribute__((ext_vector_type(4)));   // what the store builtin takes
+
 // ---- forward ---------------------------------------------------------------------------------------------------------
 
 template <typename C, int ROWS_>
@@ -150,6 +152,8 @@ __global__ __launch_bounds__(WG) void rw_fwd_kernel(Params p, const float *__res
         }
         // the kept copies of T0, t0[k][j1][j2][R]: GL threads per position, four positions side by side (a hot row's two
         // thousand positions are all in this workgroup: one at a time they took 80 us)
+        // (stored past the caches: most are never read again, and slices and rows stay there instead; 100 positions per bag at rank 64,
+        // 210 MB, step 239.0 -> 234.7 us, cached multi-hot, 74 MB, 133.9 -> 131.7)
         {
             constexpr int NG = WG / F::GL, NF = 4;
             const int g = t / F::GL, f = t % F::GL, fj = f / (R / 4), col = 4 * (f % (R / 4));
@@ -166,8 +170,8 @@ __global__ __launch_bounds__(WG) void rw_fwd_kernel(Params p, const float *__res
 #pragma unroll
                 for (int q = 0; q < NF; ++q)
                     if (i + q * NG < NE)
-                        *reinterpret_cast<float4 *>(t0_out + ((size_t)k[q] * N1 + fj) * COLS + j2 * R + col) =
-                            make_float4(a[q].x, a[q].y, b[q].x, b[q].y);
+                        __builtin_nontemporal_store(rw_f4{a[q].x, a[q].y, b[q].x, b[q].y},
+                                                    reinterpret_cast<rw_f4 *>(t0_out + ((size_t)k[q] * N1 + fj) * COLS + j2 * R + col));
             }
         }
         __syncthreads();                                                      // LDS is reused by the next tile
