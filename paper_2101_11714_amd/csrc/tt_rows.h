@@ -369,7 +369,10 @@ __device__ __forceinline__ bool rw_find_window(const Params &p, int win, const R
     return true;
 }
 
-// One window of one slice's positions (win of them, at most): see the file comment.
+// One window of one slice's positions (win of them, at most): see the file comment.  CACHED, here and below: streams without a
+// cache have kernels of their own, without what cached rows need (with it the step of 8,192 positions at rank 64, which has none,
+// took 91.8 us instead of 91.1: 0.4 us of grouping, 0.3 of the lists, which waited for wslice, 0.4 of rw_sum_kernel).
+template <bool CACHED>
 __global__ __launch_bounds__(RW_T) void rw_group_kernel(Params p, int L, int win, const int64_t *__restrict__ offsets, int n_bags, RowsWs ws)
 {
     constexpr int NCH = RW_WIN / WAVE, PER = RW_WIN / RW_T;
@@ -393,7 +396,7 @@ __global__ __launch_bounds__(RW_T) void rw_group_kernel(Params p, int L, int win
     for (int x = t; x < NCH * 64; x += RW_T) h_cnt[x] = 0;
     __syncthreads();
     const int slice = s_win[0];
-    const bool cached = slice >= p.m2;                             // uniform
+    const bool cached = CACHED && slice >= p.m2;                   // uniform
     if (cached) win = min(win, RW_CWIN);
     const int first = ws.goff[slice] + s_win[1] * win;
     const int n = min(win, ws.goff[slice + 1] - first), nch = (n + WAVE - 1) / WAVE;
@@ -634,6 +637,7 @@ __global__ __launch_bounds__(RW_T) void rw_scan_kernel(Params p, int tp, RowsWs 
 }
 
 // The distinct rows of a window to their places among those of their slices of the first and of the third core.
+template <bool CACHED>
 __global__ __launch_bounds__(RW_T) void rw_lists_kernel(Params p, int bits1, int bits3, RowsWs ws)
 {
     extern __shared__ __align__(16) uint32_t rw_lds[];             // [m13] starts, then [RW_NW][m13] 16-bit counts
@@ -665,7 +669,7 @@ __global__ __launch_bounds__(RW_T) void rw_lists_kernel(Params p, int bits1, int
         }
         if (blockIdx.x == 0 && t == 0) ws.off13[m13] = total;
     }
-    if (ws.wslice[blockIdx.x] >= p.m2) return;                     // uniform: cached rows are in no list
+    if (CACHED && ws.wslice[blockIdx.x] >= p.m2) return;           // uniform: cached rows are in no list
     for (int x = t; x < RW_NW * m13; x += RW_T) cnt[x] = 0;
     __syncthreads();
     // wave w has the w-th eighth of the window's rows (whole chunks of 64)
@@ -758,8 +762,9 @@ static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int
 {
     const int nw = rw_windows(p, L, cache.K), m13 = p.m1 + p.m3;
     const size_t lds = (size_t)m13 * 4 + (size_t)RW_NW * m13 * 2;              // at most 80 KB
-    static OncePerDevice once;
-    hipError_t e = allow_dynamic_lds(once, (const void *)rw_lists_kernel, RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
+    static OncePerDevice once, once_cached;
+    const auto lists = cache.K ? rw_lists_kernel<true> : rw_lists_kernel<false>;
+    hipError_t e = allow_dynamic_lds(cache.K ? once_cached : once, (const void *)lists, RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
     if (e != hipSuccess) return e;
     rw_place(p, indices, L, cache, rw_tile(L), ws, st);
     // Dynamic LDS: the counters of the digits.  Short streams ask for more than they need, so that two of their workgroups share a
@@ -767,10 +772,10 @@ static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int
     // 64: 91.0 / 92.5 us; with a kernel for windows of 256 in 256 threads and 9 KB 92.4).  Long ones have as many workgroups as
     // fit at three: 15 -> 12 us for the 650 of a cached stream of 163,840.
     const size_t bins = rw_win(L) < RW_WIN ? RW_MAX_M13 * 4 : (size_t)(m13 > ws.spb ? m13 : ws.spb) * 4;
-    hipLaunchKernelGGL(rw_group_kernel, dim3(nw), dim3(RW_T), bins, st, p, L, rw_win(L), offsets, n_bags, ws);
+    hipLaunchKernelGGL(cache.K ? rw_group_kernel<true> : rw_group_kernel<false>, dim3(nw), dim3(RW_T), bins, st, p, L, rw_win(L), offsets, n_bags, ws);
     if (nw > 512) hipLaunchKernelGGL(rw_scan_kernel<RW_SBINS_LONG>, dim3((m13 + RW_SBINS_LONG - 1) / RW_SBINS_LONG + 1), dim3(RW_T), 0, st, p, tp, ws);
     else hipLaunchKernelGGL(rw_scan_kernel<RW_SBINS>, dim3((m13 + RW_SBINS - 1) / RW_SBINS + 1), dim3(RW_T), 0, st, p, tp, ws);
-    hipLaunchKernelGGL(rw_lists_kernel, dim3(nw), dim3(RW_T), lds, st, p, rw_bits(p.m1), rw_bits(p.m3), ws);
+    hipLaunchKernelGGL(lists, dim3(nw), dim3(RW_T), lds, st, p, rw_bits(p.m1), rw_bits(p.m3), ws);
     return hipGetLastError();
 }
 

@@ -579,7 +579,7 @@ struct RsArgs {
     float *lines;            // lines[slot] += mul * gradient
 };
 
-template <typename C>
+template <typename C, bool CACHED>
 __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArgs a, const float *__restrict__ t0, const float *__restrict__ dym,
                                                       const float *__restrict__ pbuf, const int2 *__restrict__ l13)
 {
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
     __shared__ int s_tmp[RW_NW], s_at[3], s_last;
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), m13 = p.m1 + p.m3;
 
-    if ((int)blockIdx.x < a.cwgs) {
+    if (CACHED && (int)blockIdx.x < a.cwgs) {
         // the gradient of a cached row: over the windows of its bin, in their order; N / 4 lanes per slot, eight windows in flight
         constexpr int NQ = N / 4, NF = 8;
         const int slot = ((int)blockIdx.x * RW_T + t) / NQ, f = t % NQ;
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
         *reinterpret_cast<float4 *>(a.lines + at) = make_float4(fmaf(a.mul, sum.x, o.x), fmaf(a.mul, sum.y, o.y), fmaf(a.mul, sum.z, o.z), fmaf(a.mul, sum.w, o.w));
         return;
     }
-    const int wg = (int)blockIdx.x - a.cwgs;
+    const int wg = (int)blockIdx.x - (CACHED ? a.cwgs : 0);
     if (wg >= m13 + a.extra) {
         // dst[i2] = src[i2] + mul * (parts of slice i2, in the order of their workgroups)
         constexpr int FIN = 2 * RW_T, PER = (sB4 + FIN - 1) / FIN, NP = 8;
@@ -880,7 +880,7 @@ static inline hipError_t launch_rw_bwd(const Params &p, const float *G1, const f
                        ws.part2, ws.pbuf, src[1], dst[1], mul);
     const int most = rw_extra(p, L), extra = most < RS_MAX_EXTRA ? most : RS_MAX_EXTRA;
     const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg, rw_piece(p, L), extra, K, cwgs, lines};
-    hipLaunchKernelGGL((rw_sum_kernel<C>), dim3(cwgs + p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
+    hipLaunchKernelGGL((K ? rw_sum_kernel<C, true> : rw_sum_kernel<C, false>), dim3(cwgs + p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
                        ws.dym, ws.pbuf, ws.l13);
     return hipGetLastError();
 }
