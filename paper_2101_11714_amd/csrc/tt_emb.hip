@@ -416,12 +416,14 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
     return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, cache, output, nullptr, false, stream);
 }
 
+// (enough for every length up to L: from RF_SHORT_L on longer tiles need fewer counters)
 size_t tt_emb_fwd_rows_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags)
 {
     (void)n_bags;
     Params p;
     if (check_shape(shape, &p) != TT_OK || L <= 0 || L >= (1ll << 31) || !rw_supported(p)) return 0;
-    return rf_ws_layout(nullptr, p, L).bytes;
+    const size_t bytes = rf_ws_layout(nullptr, p, L).bytes;
+    return L >= RF_SHORT_L ? larger(bytes, rf_ws_layout(nullptr, p, RF_SHORT_L - 1).bytes) : bytes;
 }
 
 int tt_emb_fwd_rows_pays(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows)

@@ -306,6 +306,14 @@ def test_workspace_for_a_length_is_enough_for_every_shorter_one(K, mode):
         B.set_fast_path(old)
 
 
+def test_scratch_of_the_forward_over_rows_is_enough_for_every_shorter_length():
+    lengths = sorted({1} | {b + d for b in (512, 2048, 65_536, 131_072, 139_264, 262_144) for d in (-1, 0, 1)} | {2_000_000, 50_000_000})
+    for m, n, r in [((200, 220, 250), (2, 2, 4), 32), ((200, 1000, 250), (4, 4, 4), 32), ((20, 1024, 20), (2, 2, 4), 64), ((7, 1, 9), (4, 4, 4), 64)]:
+        s = B.make_shape(min(m[0] * m[1] * m[2], 2**31 - 1), m, n, (1, r, r, 1))
+        sizes = [B.fwd_rows_workspace_bytes(s, L, L) for L in lengths]
+        assert sizes[0] > 0 and sizes == sorted(sizes), (m, n, r, list(zip(lengths, sizes)))
+
+
 def test_workspace_holds_nothing_that_no_call_uses():
     # Kaggle-shaped, rank 32, 2,048 positions: the scanning owners' alone (7.6 MB with the row passes', which start at 16,384);
     # 40 M rows, (4,4,4), rank 64, 65,535 positions: the row passes' 124 MB and the grouped lists' (272 MB with the position tiles',

@@ -81,3 +81,12 @@ def test_scratch_memory_that_is_too_small_is_refused():
         assert e.value.code == -4
     torch.cuda.synchronize()
     assert float(out.abs().max()) == 0.0
+
+
+def test_scratch_for_a_longer_batch_is_enough():
+    # 131,071 positions have shorter tiles, and so more counters, in the counting pass than 131,072
+    d = _table("hot row", (2, 2, 4), 32, 131_071, 5000, m=(20, 1000, 40))
+    ws = torch.empty(B.fwd_rows_workspace_bytes(d.shape, d.L + 1, d.n_bags), dtype=torch.uint8, device=dev())
+    out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+    B.tt_emb_fwd_rows(d.shape, d.g, d.idx, d.off, d.n_bags, out, ws, alpha=d.alpha)
+    assert_close(out.cpu().numpy(), ora.fwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets, alpha=d.batch.alpha), "longer scratch")
