@@ -148,8 +148,8 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
  * tt_emb_fwd without a cache, over the distinct rows of the batch: the positions are grouped by the slice of the second
  * core they read, equal rows of up to 512 neighbouring positions of a slice are computed once, on the matrix cores, and the
  * bags are pooled from those rows in position order.  Same results as tt_emb_fwd up to the order of the fp32 sums over the
- * rank indices; bit-identical from run to run.  For n = (2,2,4) or (4,4,4), equal ranks 32 or 64, m2 <= 1024 and
- * m1 + m3 <= 4096; TT_ERR_UNSUPPORTED otherwise.  workspace: scratch memory of
+ * rank indices; bit-identical from run to run.  For n = (2,2,4) or (4,4,4), equal ranks 32 or 64, m2 <= 1024,
+ * m1 + m3 <= 4096 and L < 2^31 - 2^20; TT_ERR_UNSUPPORTED otherwise.  workspace: scratch memory of
  * tt_emb_fwd_rows_workspace_bytes bytes (0 for a shape or length without such a pass), 16-byte aligned.
  * tt_emb_fwd_rows_pays: 1 where the call was measured ahead of tt_emb_fwd, which is a question of the shape and of L.
  */

@@ -421,7 +421,7 @@ size_t tt_emb_fwd_rows_workspace_bytes(const tt_shape_t *shape, int64_t L, int64
 {
     (void)n_bags;
     Params p;
-    if (check_shape(shape, &p) != TT_OK || L <= 0 || L >= (1ll << 31) || !rw_supported(p)) return 0;
+    if (check_shape(shape, &p) != TT_OK || L <= 0 || L >= RF_MAX_L || !rw_supported(p)) return 0;
     const size_t bytes = rf_ws_layout(nullptr, p, L).bytes;
     return L >= RF_SHORT_L ? larger(bytes, rf_ws_layout(nullptr, p, RF_SHORT_L - 1).bytes) : bytes;
 }
@@ -429,7 +429,7 @@ size_t tt_emb_fwd_rows_workspace_bytes(const tt_shape_t *shape, int64_t L, int64
 int tt_emb_fwd_rows_pays(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows)
 {
     Params p;
-    if (L < FWD_ROWS_LEAST_L || cache_rows || g_fast_path != 1 || check_shape(shape, &p) != TT_OK || L >= (1ll << 31) || !rw_supported(p)) return 0;
+    if (L < FWD_ROWS_LEAST_L || cache_rows || g_fast_path != 1 || check_shape(shape, &p) != TT_OK || L >= RF_MAX_L || !rw_supported(p)) return 0;
     return L >= fwd_rows_min_l(p, L, n_bags) && rf_ws_layout(nullptr, p, L).bytes <= RF_MAX_BYTES ? 1 : 0;
 }
 
@@ -444,6 +444,7 @@ int tt_emb_fwd_rows(const tt_shape_t *shape, const float *const cores[3],
     if (!cores || !cores[0] || !cores[1] || !cores[2]) return fail(TT_ERR_NULL, "cores is NULL");
     if (n_bags > 0 && !output) return fail(TT_ERR_NULL, "output is NULL");
     if (!rw_supported(p)) return fail(TT_ERR_UNSUPPORTED, "no forward pass over distinct rows for this shape");
+    if (L >= RF_MAX_L) return fail(TT_ERR_UNSUPPORTED, "L >= 2^31 - 2^20");
     if (L == 0 || n_bags == 0)
         return fwd_common(shape, cores, indices, L, offsets, n_bags, alpha, nullptr, output, nullptr, false, stream);
     const size_t need = rf_ws_layout(nullptr, p, L).bytes;

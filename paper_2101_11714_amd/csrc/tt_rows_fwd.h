@@ -18,7 +18,11 @@ namespace tt {
 
 constexpr int RF_WIN = RW_T;                     // positions of a window: one per thread; a row that two windows share is computed twice
 constexpr int64_t RF_SHORT_L = 131072;           // up to here short tiles in the counting pass
-constexpr size_t RF_MAX_BYTES = (size_t)1 << 30; // scratch memory of a call, at most
+constexpr size_t RF_MAX_BYTES = (size_t)1 << 30; // scratch memory that a call is worth (tt_emb_fwd_rows_pays)
+// Positions of a call, fewer than this: up to there a tile past the last position is still an int, and a launch with 1,024 threads
+// per window of at least 512 positions, or per slice, has fewer than the 2^32 threads that a grid can have.
+constexpr int64_t RF_MAX_L = (1ll << 31) - (1ll << 20);
+static_assert(RF_MAX_L + RW_TILE <= (1ll << 31) && (RF_MAX_L / RF_WIN + RW_MAX_M2) * 1024 < (1ll << 32), "what the limit is for");
 
 static inline int rf_tile(int64_t L) { return L < RF_SHORT_L ? RW_TILE_SHORT : RW_TILE; }
 
@@ -109,6 +113,7 @@ struct RfCols {
     static constexpr int EU = C::R >= 64 ? 2 : 4;          // waves per SIMD that the slice leaves room for
     static constexpr int EB = 32 / C::N1;            // distinct rows of a block: 32 stacked rows (row, j1)
     static constexpr int PARTS = 128 / EB / NW;      // workgroups that share a window's blocks
+    static_assert(PARTS * NW * WAVE <= 1024, "threads per window: see RF_MAX_L");
     static constexpr int NBQ = WAVE / EB;            // lanes per row in the second product: a part of b each
     static constexpr int BQ = C::R / NBQ;            // values of b per lane
     static constexpr int KH = C::R / 2;              // steps of the first product: k values per half of the wave

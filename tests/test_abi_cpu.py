@@ -314,6 +314,17 @@ def test_scratch_of_the_forward_over_rows_is_enough_for_every_shorter_length():
         assert sizes[0] > 0 and sizes == sorted(sizes), (m, n, r, list(zip(lengths, sizes)))
 
 
+def test_forward_over_rows_refuses_lengths_that_its_grids_do_not_hold():
+    l, most = B.lib(), 2**31 - 2**20
+    s = B.make_shape(10_131_227, (200, 220, 250), (2, 2, 4), (1, 32, 32, 1))
+    arr, one = (C.c_void_p * 3)(16, 16, 16), C.c_void_p(16)
+    for L in (most, 2**31 - 1):
+        assert B.fwd_rows_workspace_bytes(s, L, 1) == 0 and not B.fwd_rows_pays(s, L, 1)
+        assert l.tt_emb_fwd_rows(C.byref(s), arr, one, L, one, 1, None, one, one, C.c_size_t(2**60), None) == -6
+    assert B.fwd_rows_workspace_bytes(s, most - 1, 1) > 64 * most and not B.fwd_rows_pays(s, most - 1, 1)      # (more than it is worth)
+    assert B.fwd_rows_workspace_bytes(s, 2_000_000, 1) > 0 and B.fwd_rows_pays(s, 2_000_000, 1)
+
+
 def test_workspace_holds_nothing_that_no_call_uses():
     # Kaggle-shaped, rank 32, 2,048 positions: the scanning owners' alone (7.6 MB with the row passes', which start at 16,384);
     # 40 M rows, (4,4,4), rank 64, 65,535 positions: the row passes' 124 MB and the grouped lists' (272 MB with the position tiles',
