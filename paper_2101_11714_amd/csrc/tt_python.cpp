@@ -211,11 +211,23 @@ TT_FUNCTION(guarded)
     return nullptr;
 }
 
+// The calling thread may allocate although a stream is captured somewhere: what is enqueued on a stream that is not captured is no
+// part of the graph, and by default an allocation of any thread would end the capture.
+struct CaptureElsewhere {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool on = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~CaptureElsewhere()
+    {
+        if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
 // Scratch memory of torch's allocator for the current stream (the kernels that use it are enqueued there before it is given
 // back), or nothing: while the stream is captured, since a graph's scratch memory has to live as long as the graph, and where
 // there is no room for it.
 at::DataPtr scratch(size_t bytes, void *st)
 {
+    const CaptureElsewhere guard;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (!bytes || hipStreamIsCapturing((hipStream_t)st, &status) != hipSuccess || status != hipStreamCaptureStatusNone) return {};
     try {

@@ -2,6 +2,8 @@
 one position, a window one short of full, full and one over, every row different, one row, one slice, empty and ragged bags,
 weights, few and many slices.  Against the oracle and bit for bit against itself; the binding's tt_emb_fwd takes it by the rule
 of tt_emb_fwd_rows_pays, and the wave per bag where the stream is captured."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -90,3 +92,37 @@ def test_scratch_for_a_longer_batch_is_enough():
     out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
     B.tt_emb_fwd_rows(d.shape, d.g, d.idx, d.off, d.n_bags, out, ws, alpha=d.alpha)
     assert_close(out.cpu().numpy(), ora.fwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets, alpha=d.batch.alpha), "longer scratch")
+
+
+def test_scratch_memory_leaves_captures_elsewhere_alone():
+    # a batch scored on a stream of its own, from another thread and from the same one, while a graph is recorded
+    d = _table("hot row", (4, 4, 4), 32, 60_000, 9000, m=(200, 200, 50), alpha=False)
+    assert B.fwd_rows_pays(d.shape, d.L, d.n_bags)
+    ref = _run(d)
+    got = [torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev()) for _ in range(2)]
+    count, errors = torch.zeros(100, device=dev()), []
+    own, side, g = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+
+    def score(out):
+        try:
+            with torch.cuda.stream(own):
+                B.tt_emb_fwd(d.shape, d.g, d.idx, d.off, d.n_bags, out)
+        except Exception as e:                               # (reported by the test's thread)
+            errors.append(e)
+
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()                                 # the scratch memory has to come from the device
+    with torch.cuda.graph(g, stream=side):
+        count += 1
+        t = threading.Thread(target=score, args=(got[0],))
+        t.start()
+        t.join()
+        score(got[1])
+    assert not errors
+    torch.cuda.synchronize()
+    for out in got:
+        assert np.array_equal(out.cpu().numpy(), ref)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+    assert float(count.min()) == float(count.max()) == 3.0   # (recorded, not run, the first time)
