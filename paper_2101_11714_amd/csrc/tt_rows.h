@@ -109,8 +109,9 @@ static inline int rw_pieces(const Params &p, int64_t L)
 }
 // Positions per workgroup of the counting pass, two per thread: a wave's rounds are one chain of LDS round trips (163,840
 // positions, a cache of 1,000 rows to probe: eight of them in 256 threads 13.7 us counting and 12.8 placing, two in 1,024 threads 7.0
-// and 11; 73,000 without a cache, 2,048 in 256 threads 10 us placing, 512 7.5); with more workgroups every one of them has more
-// counts to read.
+// and 11; 8,192 without a cache, 2,048 in 256 threads 9.8 us placing, 512 6.3; 73,000 10 and 7.5); with more workgroups every one
+// of them has more counts to read.  Beside a step that does not wait for them the two are alike (8,192 positions 91.8 us either
+// way, 6,500 85.9 with 512 / 86.6, 60,000 134.2 / 133.9): the shorter tiles are for the steps and forward passes that do wait.
 static inline int rw_tile(int64_t L) { return L < RW_LONG_MIN_L ? RW_TILE_SHORT : RW_TILE; }
 static inline int rw_hist_blocks(int64_t L) { return (int)((L + rw_tile(L) - 1) / rw_tile(L)); }
 
@@ -767,11 +768,10 @@ static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int
     hipError_t e = allow_dynamic_lds(cache.K ? once_cached : once, (const void *)lists, RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
     if (e != hipSuccess) return e;
     rw_place(p, indices, L, cache, rw_tile(L), ws, st);
-    // Dynamic LDS: the counters of the digits.  Short streams ask for more than they need, so that two of their workgroups share a
-    // compute unit and not three: they are done early enough, and the step that they run beside loses 2 % (8,192 positions at rank
-    // 64: 91.0 / 92.5 us; with a kernel for windows of 256 in 256 threads and 9 KB 92.4).  Long ones have as many workgroups as
-    // fit at three: 15 -> 12 us for the 650 of a cached stream of 163,840.
-    const size_t bins = rw_win(L) < RW_WIN ? RW_MAX_M13 * 4 : (size_t)(m13 > ws.spb ? m13 : ws.spb) * 4;
+    // Dynamic LDS: the counters of the digits, as many as there are (with 1,200 slices two workgroups share a compute unit, with 450
+    // three; room for 4,096 of them, so that it is two for every table, makes no difference to the steps beside which they run:
+    // 8,192 positions at rank 64 91.9 / 91.8 us, 60,000 at rank 32 134.1 / 134.2, of (2,2,4) 81.6 / 82.0, with a cache 80.8 / 81.1).
+    const size_t bins = (size_t)(m13 > ws.spb ? m13 : ws.spb) * 4;
     hipLaunchKernelGGL(cache.K ? rw_group_kernel<true> : rw_group_kernel<false>, dim3(nw), dim3(RW_T), bins, st, p, L, rw_win(L), offsets, n_bags, ws);
     if (nw > 512) hipLaunchKernelGGL(rw_scan_kernel<RW_SBINS_LONG>, dim3((m13 + RW_SBINS_LONG - 1) / RW_SBINS_LONG + 1), dim3(RW_T), 0, st, p, tp, ws);
     else hipLaunchKernelGGL(rw_scan_kernel<RW_SBINS>, dim3((m13 + RW_SBINS - 1) / RW_SBINS + 1), dim3(RW_T), 0, st, p, tp, ws);
