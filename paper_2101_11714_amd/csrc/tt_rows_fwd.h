@@ -144,7 +144,9 @@ __global__ __launch_bounds__(RfCols<C>::NW *WAVE) __attribute__((amdgpu_waves_pe
     const int ln = lane & 31, kh = lane >> 5, win = blockIdx.x / F::PARTS, part = blockIdx.x % F::PARTS;
     if (win >= *ws.nwin) return;                                              // uniform
     const int i2 = ws.wslice[win], first = ws.wfirst[win], D = ws.wd[win];
-    if ((unsigned)i2 >= (unsigned)p.m2 || first < 0 || D < 0 || first > L - D) return;   // (nothing that rf_group_kernel writes)
+    // (Never so.  But it has all three loaded by here: the compiler moves two of them below the next branch otherwise, which is a round
+    // trip of its own: 73,600 positions, (4,4,4) at rank 32, 41.1 us with this line, 41.4 without.)
+    if ((unsigned)i2 >= (unsigned)p.m2 || first < 0 || D < 0 || first > L - D) return;
     if (part * F::NW * EB >= D) return;                                       // uniform
     float *T = rf_slice + C::sB + w * 32 * LDT;
     const int ea = ln / N1, j1 = ln % N1;                                     // row and j1 of this lane in the first product
@@ -156,13 +158,13 @@ __global__ __launch_bounds__(RfCols<C>::NW *WAVE) __attribute__((amdgpu_waves_pe
     };
     float areg[KH], cv[F::BQ][4];
     auto fetch = [&]() __attribute__((always_inline)) {
-        const float *Ap = G1 + (size_t)min(max(i1, 0), p.m1 - 1) * C::sA + j1 * R + kh * KH;         // step s of the first product covers k = kh KH + s
+        const float *Ap = G1 + (size_t)i1 * C::sA + j1 * R + kh * KH;         // step s of the first product covers k = kh KH + s
 #pragma unroll
         for (int q = 0; q < KH / 4; ++q) {
             const float4 x = *reinterpret_cast<const float4 *>(Ap + 4 * q);
             areg[4 * q + 0] = x.x; areg[4 * q + 1] = x.y; areg[4 * q + 2] = x.z; areg[4 * q + 3] = x.w;
         }
-        const float4 *Cp = reinterpret_cast<const float4 *>(G3 + (size_t)min(max(i3, 0), p.m3 - 1) * C::sC) + bq;   // (the NBQ lanes of a row read neighbouring rows of G3[i3])
+        const float4 *Cp = reinterpret_cast<const float4 *>(G3 + (size_t)i3 * C::sC) + bq;   // (the NBQ lanes of a row read neighbouring rows of G3[i3])
 #pragma unroll
         for (int i = 0; i < F::BQ; ++i) {
             const float4 v = Cp[i * NBQ];
