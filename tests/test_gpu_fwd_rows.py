@@ -1,7 +1,7 @@
 """The forward pass over distinct rows (tt_rows_fwd.h, tt_emb_fwd_rows) at the edges of its windows, blocks and counting tiles:
 one position, a window one short of full, full and one over, every row different, one row, one slice, empty and ragged bags,
 weights, few and many slices.  Against the oracle and bit for bit against itself; the binding's tt_emb_fwd takes it by the rule
-of tt_emb_fwd_rows_pays, and the wave per bag where the stream is captured."""
+of tt_emb_fwd_rows_pays, and the wave per bag where the stream is captured or no scratch memory is to be had."""
 import threading
 
 import numpy as np
@@ -48,29 +48,79 @@ def test_forward_over_distinct_rows(n, R, kind, L, n_bags, m):
     assert_close(_run(d), ref, kind)
 
 
-def test_the_binding_takes_it_by_the_rule():
-    # either side of the longest limit, (4,4,4) with bags of one position (40,960), and of the counting pass's tiles (131,072 at (2,2,4), rank 32)
-    for n, R, L, n_bags in [((4, 4, 4), 32, 40_959, 40_959), ((4, 4, 4), 32, 40_960, 40_960), ((2, 2, 4), 32, 131_071, 9000), ((2, 2, 4), 32, 131_072, 9000)]:
+def _captured(call):
+    """A graph of one call, recorded on a stream of its own."""
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=side):
+        call()
+    return g
+
+
+# either side of every limit, bags of one position and of several, and of the counting pass's tiles (131,072)
+@pytest.mark.parametrize("n,R,L,n_bags", [((4, 4, 4), 32, 40_960, 40_960), ((4, 4, 4), 64, 40_960, 40_960), ((2, 2, 4), 32, 131_072, 9000),
+                                          ((4, 4, 4), 32, 28_672, 9000), ((4, 4, 4), 64, 12_288, 3000), ((2, 2, 4), 64, 14_336, 14_336)])
+def test_the_binding_takes_it_by_the_rule(n, R, L, n_bags):
+    for L, n_bags, pays in ((L - 1, min(n_bags, L - 1), False), (L, n_bags, True)):
         d = _table("hot row", n, R, L, n_bags, m=(200, 200, 50), alpha=False)
-        pays = B.fwd_rows_pays(d.shape, L, n_bags)
-        assert pays == (L in (40_960, 131_072)) and not B.fwd_rows_pays(d.shape, L, n_bags, 10)
+        assert B.fwd_rows_pays(d.shape, L, n_bags) == pays and not B.fwd_rows_pays(d.shape, L, n_bags, 10)
         out = d.fwd()
         assert_close(out, ora.fwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets), str((n, R, L)))
-        assert np.array_equal(out, _run(d)) == pays or L == n_bags         # (single rows may round alike)
         old = B.set_fast_path(2)
         wave = d.fwd()
         B.set_fast_path(old)
+        assert np.array_equal(out, _run(d) if pays else wave)
         got = torch.full((n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
-        side = torch.cuda.Stream()
-        side.wait_stream(torch.cuda.current_stream())
-        g = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(g, stream=side):
-            B.tt_emb_fwd(d.shape, d.g, d.idx, d.off, d.n_bags, got)
+        g = _captured(lambda: B.tt_emb_fwd(d.shape, d.g, d.idx, d.off, d.n_bags, got))
         for _ in range(3):
             got.fill_(float("nan"))
             g.replay()
             torch.cuda.synchronize()
             assert np.array_equal(got.cpu().numpy(), wave)
+
+
+def test_without_room_for_scratch_memory_the_wave_per_bag_runs():
+    d = _table("hot row", (4, 4, 4), 32, 60_000, 9000, m=(200, 200, 50))
+    assert B.fwd_rows_pays(d.shape, d.L, d.n_bags)
+    old = B.set_fast_path(2)
+    wave = d.fwd()
+    B.set_fast_path(old)
+    out = torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev())
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    try:                                                     # (room for a call's own tensors and no more)
+        torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / torch.cuda.get_device_properties(0).total_memory)
+        B.tt_emb_fwd(d.shape, d.g, d.idx, d.off, d.n_bags, out, alpha=d.alpha)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert np.array_equal(out.cpu().numpy(), wave) and not np.array_equal(_run(d), wave)
+
+
+def test_recorded_and_on_two_streams():
+    # every call with scratch memory of its own: replayed three times with eager work between, and side by side
+    d = _table("hot row", (2, 2, 4), 64, 20_000, 3000)
+    ref = _run(d)
+    ws = [torch.full((B.fwd_rows_workspace_bytes(d.shape, d.L, d.n_bags),), 0x7F, dtype=torch.uint8, device=dev()) for _ in range(2)]
+    out = [torch.full((d.n_bags, d.t.dim), float("nan"), dtype=torch.float32, device=dev()) for _ in range(2)]
+
+    def call(j):
+        B.tt_emb_fwd_rows(d.shape, d.g, d.idx, d.off, d.n_bags, out[j], ws[j], alpha=d.alpha)
+
+    g = _captured(lambda: call(0))
+    for _ in range(3):
+        out[0].fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(out[0].cpu().numpy(), ref) and np.array_equal(d.fwd(), ref)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for j, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                call(j)
+    torch.cuda.synchronize()
+    for o in out:
+        assert np.array_equal(o.cpu().numpy(), ref)
 
 
 def test_scratch_memory_that_is_too_small_is_refused():

@@ -144,8 +144,21 @@ def test_one_workspace_on_either_side_of_the_longer_windows():
                                            ((2, 2, 4), 64, 17_000, 1000, 0.0), ((4, 4, 4), 64, 16_500, 128, 1.0), ((2, 2, 4), 32, 16_400, 8192, 0.5),
                                            ((2, 2, 4), 32, 16_400, 8193, 0.5), ((4, 4, 4), 32, 262_144, 129, 0.99), ((2, 2, 4), 64, 300_001, 1000, 0.99)])
 def test_with_a_cache(n, R, L, K, share):
+    _with_a_cache(n, R, L, K, share, (30, 20, 40))
+
+
+# as many slices of the second core as leave room for the bins of cached rows, and one more (the list owners); more than 512 windows;
+# the longer windows beside those of cached rows, at rank 64
+@pytest.mark.parametrize("n,R,L,K,share,m", [((4, 4, 4), 32, 17_000, 300, 0.6, (9, 896, 11)), ((4, 4, 4), 32, 17_000, 300, 0.6, (9, 897, 11)),
+                                             ((2, 2, 4), 64, 5_000, 2000, 0.6, (9, 896, 11)), ((4, 4, 4), 32, 66_000, 500, 0.8, (30, 400, 40)),
+                                             ((4, 4, 4), 64, 65_535, 700, 0.9, (30, 20, 40)), ((4, 4, 4), 64, 65_536, 700, 0.9, (30, 20, 40))])
+def test_with_a_cache_in_tables_of_many_slices(n, R, L, K, share, m):
+    _with_a_cache(n, R, L, K, share, m)
+
+
+def _with_a_cache(n, R, L, K, share, m):
     rng = np.random.default_rng([L, K])
-    t = W.TableShape(30 * 20 * 40 - 3, (30, 20, 40), n, (1, R, R, 1))
+    t = W.TableShape(m[0] * m[1] * m[2] - 3, m, n, (1, R, R, 1))
     keys = np.sort(rng.choice(t.num_rows, K, replace=False)).astype(np.int64)
     other = np.setdiff1d(np.arange(t.num_rows), keys)
     idx = np.where(rng.random(L) < share, rng.choice(keys, L), rng.choice(other, L)).astype(np.int64)
@@ -189,9 +202,9 @@ def test_with_a_cache(n, R, L, K, share):
     assert_close(dc.cpu().numpy()[:K] - 0.5, rc, "dCache")
 
 
-@pytest.mark.parametrize("L", [5000, 16_384])       # the scanning owners, the list owners
-def test_with_a_cache_and_little_room_the_owners_run(L):
-    d = _table("hot row", (2, 2, 4), 32, L, 500, 9)
+@pytest.mark.parametrize("L,R", [(5000, 32), (16_384, 32), (5000, 64), (16_384, 64)])       # the scanning owners, the list owners
+def test_with_a_cache_and_little_room_the_owners_run(L, R):
+    d = _table("hot row", (2, 2, 4), R, L, 500, 9)
     rows, counts = np.unique(d.batch.indices, return_counts=True)
     cache, _, _ = d.build_cache(100, rows.astype(np.int64), counts.astype(np.int64))
     lines = cache.rows.clone()
