@@ -115,11 +115,15 @@ int64_t tt_cache_table_capacity(int64_t K);
  * positions in n_bags bags and a cache of cache_rows rows (0 = no cache).  tt_emb_fwd needs
  * none.  tt_emb_bwd needs none for a short index stream without a cache; with a cache, or from
  * 4096 positions on (from there on, depending on the shape, several workgroups share a slice and
- * leave partial sums in the workspace; from 32768 positions on, 16384 with a cache (4096 with a cache of
- * up to 8192 rows and a kept T0 at rank 32 or 64), the positions
- * are grouped first, by distinct row where the call brings a kept T0 at rank 32 or 64,
- * else with a device sort by slice), it reports TT_ERR_WORKSPACE if the workspace is missing
- * or too small.  That is said of the shapes with a specialised kernel; for the others see
+ * leave partial sums in the workspace; from 32768 positions on, 16384 with a cache, the positions are
+ * grouped first, with a device sort by slice), it reports TT_ERR_WORKSPACE if the workspace is missing
+ * or too small.
+ * A call with a kept T0 at rank 32 or 64 groups by distinct row instead, where m2 <= 1024 and
+ * m1 + m3 <= 4096, and, with a cache, from 4096 positions on, where it has at most 8192 rows and
+ * m2 <= 896.  With a cache the query then says up to 3.3 times what the other ways need (a cache of
+ * 1,000 rows, rank 32, Kaggle-shaped: 4,096 positions 8.8 MB instead of 2.7, 65,536 37 instead of 19;
+ * (4,4,4), 163,840 positions 191 instead of 119); a workspace with room for those ways alone takes
+ * those.  That is said of the shapes with a specialised kernel; for the others see
  * tt_emb_bwd.  Returns 0 on a bad shape. */
 size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows);
 
@@ -216,7 +220,7 @@ int tt_emb_mean_weights(const int64_t *offsets, int64_t n_bags, int64_t L, const
  * tt_emb_bwd_sgd_t0 are tt_emb_bwd and tt_emb_bwd_sgd given that array for the SAME
  * indices: the owners of the third core's slices read it instead of recomputing it
  * (they then read neither G1 nor G2).  Only for the shapes with a specialised kernel
- * (n = (2,2,4) or (4,4,4), equal ranks 8..64): TT_ERR_UNSUPPORTED otherwise.
+ * (n = (2,2,4), equal ranks 8, 16, 32 or 64; n = (4,4,4), equal ranks 32 or 64): TT_ERR_UNSUPPORTED otherwise.
  */
 int tt_emb_fwd_keep_t0(const tt_shape_t *shape, const float *const cores[3],
                        const int64_t *indices, int64_t L, const int64_t *offsets, int64_t n_bags,
@@ -380,13 +384,16 @@ int tt_emb_bwd_two_calls_group_earlier(const tt_shape_t *shape, int64_t L, int64
  * kernel, the forward pass works from its lists: a workgroup takes positions of one slice of the
  * second core, multiplies their stacked first-core rows with the slice on the matrix cores (Eq. 3,
  * first product), and the rows of each bag are pooled afterwards in position order.  With a kept T0
- * (and no cache, or one of up to 8192 rows) the lists are of distinct rows: a row is computed once, or once per few hundred to
- * two thousand positions of its slice, and its T0 copied to all its positions.  Otherwise the call is
- * tt_emb_fwd / tt_emb_fwd_keep_t0.
+ * (and no cache, or one of up to 8192 rows with m2 <= 896) the lists are of distinct rows: a row is computed once, or
+ * once per few hundred to two thousand positions of its slice, and its T0 copied to all its positions.  Otherwise the
+ * call is tt_emb_fwd / tt_emb_fwd_keep_t0.
  * The workspace is read (lists) and written (one row per position, in a part of it that the
  * backward calls do not use); the backward call that follows takes the same workspace, of the same
- * workspace_bytes: below 32768 positions, or with a cache, a call with a kept T0 and a workspace too small for the
- * lists of distinct rows (smaller than the query says) is tt_emb_fwd_keep_t0, although tt_emb_fwd_uses_lists answers 1.
+ * workspace_bytes.  A call with a kept T0 and a workspace too small for the lists of distinct rows (smaller than the
+ * query says): without a cache it is tt_emb_fwd_keep_t0 below 32768 positions and fails from there on; with a cache it is that too, except
+ * at rank 64 from 16384 positions on, where it works from the lists by slice that the pre-pass then leaves.
+ * tt_emb_fwd_uses_lists answers for a workspace of the queried size: where it says 1 the forward has to wait for the
+ * pre-pass, whatever the workspace.
  * Same results as tt_emb_fwd up to the order of the fp32 sums over the rank indices.
  */
 /* 1 if tt_emb_fwd_prepared works from the pre-pass's lists for such a call (then the forward pass has to

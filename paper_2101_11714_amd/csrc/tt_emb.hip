@@ -58,7 +58,13 @@ constexpr int64_t GROUP_MIN_L_CACHE = 16384;    // with a cache (the grouped pat
 // With a cache, a kept T0 and room for the passes over distinct rows (tt_rows.h), one call or two: without them the owners of the
 // cache's slots scan all positions, a hot slot's one after the other.  Step, scanning owners / rows, hit rates of 80, 45 and 5 %: (4,4,4)
 // rank 32 5,120 positions 296 / 55, 205 / 85, 100 / 87 us, 15,360 752 / 83, 455 / 97, 154 / 118; (2,2,4) rank 32 3,000 236 / 68,
-// 165 / 68, 52 / 67, 5,120 391 / 57, 249 / 65, 60 / 53; rank 64 4,000 317 / 65, 219 / 79, 120 / 96.
+// 165 / 68, 52 / 67, 5,120 391 / 57, 249 / 65, 60 / 53; rank 64 4,000 317 / 65, 219 / 79, 120 / 96.  At 4,096 positions with 1,000
+// cached rows used alike, hit rates of 0, 5 and 50 %: (4,4,4) rank 32 76 / 70, 81 / 71, 80 / 71, rank 64 133 / 91, 142 / 104, 118 / 76,
+// (2,2,4) rank 64 86 / 72, 93 / 72, 83 / 70; (2,2,4) rank 32, the one that is behind, 63 / 73, 62 / 72, 63 / 71: there the host's nine
+// launches bound it (the kernels on the step's stream take 28 us instead of 43 to 52), and no host can tell a hot slot in advance.
+// From 16,384 to 32,767 positions at rank 32 the forward is the wave per bag (rows_fwd_min_l), as it is on the lists by slice
+// with a cache; step, (4,4,4), 0, 5 and 80 % hits, list owners / rows: 16,400 105 / 104, 105 / 104, 78 / 76, 24,000 148 / 142,
+// 131 / 125, 88 / 80, 32,000 158.5 / 158.9, 155 / 156.5, 80 / 73.
 constexpr int64_t GROUP_MIN_L_CACHE_ROWS = 4096;
 // With a kept T0 and no cache the grouped backward runs on tiles (tt_bwd_owner.h), which are ahead of the scanning
 // owners much earlier, but only if the pre-pass (about 30 us of small kernels) does not count: so these limits hold

@@ -35,7 +35,7 @@ constexpr int RW_T = 512, RW_NW = RW_T / WAVE;   // threads / waves of the windo
 constexpr int RW_TILE = 2048, RW_TILE_SHORT = 512;   // positions per workgroup of the counting pass (see rw_tile)
 constexpr int RW_PER = 2;                        // positions per thread of it
 constexpr int RW_HASH = 4096;
-constexpr int RW_MAX_M2 = 1024;                  // bins of the counting pass
+constexpr int RW_MAX_M2 = 1024;                  // bins of the counting pass, those of cached positions among them
 constexpr int RW_MAX_M13 = 4096;                 // slices of the first and third core together
 constexpr int RW_OFF = 512;                      // samples of the offsets array kept in LDS
 constexpr int RW_PIECE = 512;                    // distinct rows per workgroup of the final sums, at most (see rw_piece)
@@ -47,14 +47,14 @@ struct RowsWs {
     int nb, spb;         // bins of cached positions (0: no cache), slots per bin
     int *cu;             // [windows][spb] u of a bin's slots in a window, -1: none
     int *cwin;           // [nb + 1] first window of every bin
-    uint32_t *hist;      // [tiles][m2 rounded up to 4]
-    uint32_t *lk, *lrow; // [L] positions and their rows grouped by second digit
-    int *goff;           // [m2 + 1] bounds of those groups
-    int *inv;            // [L] position -> u
+    uint32_t *hist;      // [tiles of the counting pass][m2 + nb rounded up to 4]
+    uint32_t *lk, *lrow; // [L] positions and their rows grouped by second digit, cached ones after them by bin
+    int *goff;           // [m2 + nb + 1] bounds of those groups
+    int *inv;            // [L] position -> u; ~slot of a cached row
     int2 *gkb;           // [L] {position, bag}: the positions of a row are neighbours
     int *gu;             // [L] u of the same places
-    int4 *rec;           // [L] by u: {first digit, third digit, first place in gkb, positions} (positions = 0: unused)
-    int *wd, *wfirst, *wslice;   // [windows] distinct rows, first place, slice
+    int4 *rec;           // [L] by u: {first digit, third digit, first place in gkb, positions} (positions = 0: unused); a slot: {slot, -1, ..}
+    int *wd, *wfirst, *wslice;   // [windows] distinct rows, first place, slice (m2 + bin)
     uint32_t *hist2;     // [windows][m1 + m3] distinct rows per slice, then those of earlier windows
     uint32_t *tot2;      // [m1 + m3]
     int *off13;          // [m1 + m3 + 1] bounds of the slices in l13
