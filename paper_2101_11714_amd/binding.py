@@ -221,7 +221,7 @@ def tt_emb_fwd(shape: TTShape, cores: Sequence[torch.Tensor], indices: torch.Ten
                workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Where tt_emb_fwd_rows_pays, tt_emb_fwd_rows in scratch memory of torch's allocator for the call's stream:
     fwd_rows_workspace_bytes, about 280 bytes per position at dimension 64, 90 at 16.  Under capture, and where there is no
-    such memory, tt_emb_fwd.  The workspace is not touched either way: a pre-pass may have left its lists there."""
+    such memory, tt_emb_fwd (the two add in another order).  The workspace is not touched either way: a pre-pass may have left its lists there."""
     rc = _call.emb_fwd(shape, cores, indices, offsets, n_bags, output, alpha, cache, workspace)
     if rc:
         _check(rc)
