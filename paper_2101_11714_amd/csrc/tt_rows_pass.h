@@ -843,12 +843,14 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
 // distinct rows per tile: 128 stacked rows
 static inline int rw_tp(const Params &p) { return 128 / p.n1; }
 
-// workgroups of the tile kernel: what the compute units hold, more only where one would get more tiles than it has room for
+// workgroups of the tile kernel: what the compute units hold, and where one would get more tiles than it has room for as often that as
+// it takes (524 for the 512 that run at once, as 1,000,000 positions with a cache had it, and the kernel takes twice as long: step at
+// (4,4,4) rank 32, hardly a row repeated or cached, 2,800 us, with 1,024 2,460; (2,2,4) rank 64 2,233 / 1,757)
 static inline int rw_tile_wgs(const Params &p, int64_t L, int64_t K)
 {
     const int n = (p.R1 >= 64 ? 1 : 2) * bo_compute_units();
     const int least = (rw_tiles(p, L, K, rw_tp(p)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
-    return n > least ? n : least;
+    return n > least ? n : (least + n - 1) / n * n;
 }
 
 template <typename C, int ROWS_>
