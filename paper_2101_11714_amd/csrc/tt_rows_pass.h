@@ -568,6 +568,13 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(BoCfg<C, ROW
 // for them as there can be, or as the device runs at once (with 64 of them a step of 300,000 uniform
 // positions, Kaggle-shaped at rank 32, took 901 us, 600 of them here; so it takes 290).
 constexpr int RS_MAX_EXTRA = 1024;
+// Windows of a cached row that its lanes add up alone: 16 rounds of loads.  A hot row's of a long stream would be hundreds.  (4,4,4) at
+// rank 32, step, slices' lists / alone / shared: the only cached row with 90 % of 300,000 positions 200 / 201 / 178 us, of 1,000,000
+// 549 / 608 / 520; one of 1,000 with 80 % 220 / 210 / 200 and 585 / 589 / 527, of 8,000 204 / 190 / 183 and 541 / 560 / 511; no hot row: as it
+// was (300,000 positions, 8,000 rows, 233 / 232).  Shorter streams do without, and without its code: with it, whether it
+// runs or not, 163,840 positions take 131 us instead of 130.
+constexpr int RW_ALONE = 128;
+constexpr int64_t RW_SHARE_MIN_L = 262144;
 
 struct RsArgs {
     const float *src[3];
@@ -575,34 +582,30 @@ struct RsArgs {
     float mul;
     int nwg;                 // workgroups of the tile kernel
     int piece, extra;        // rows of a piece (RW_PIECE at most); workgroups for the extra pieces
-    int K, cslots, cwgs;     // cached rows; how many of them a workgroup adds up the gradients of, and the workgroups for that
+    int K, cwgs;             // cached rows, and the workgroups that add their gradients up
     float *lines;            // lines[slot] += mul * gradient
 };
 
-template <typename C, bool CACHED>
+// CACHED: there is a cache; SHARE: lanes share the windows of its hot rows.
+template <typename C, bool CACHED, bool SHARE>
 __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArgs a, const float *__restrict__ t0, const float *__restrict__ dym,
                                                       const float *__restrict__ pbuf, const int2 *__restrict__ l13)
 {
     constexpr int N = C::N, R = C::R, NJ = C::N1 * C::N2, sA4 = C::sA / 4, sB4 = C::sB / 4;
     constexpr int WMAX = C::sA > C::sC ? C::sA : C::sC;
-    static_assert(RW_PIECE <= RW_T, "a list entry per thread");
+    static_assert(RW_PIECE == RW_T, "a list entry per thread");
     __shared__ __align__(16) float s_red[RW_T * 4];
     __shared__ int2 s_list[RW_PIECE];
     __shared__ int s_tmp[RW_NW], s_at[3], s_last;
-    int *s_any = reinterpret_cast<int *>(s_list);                  // [RW_T]
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), m13 = p.m1 + p.m3;
 
     if (CACHED && (int)blockIdx.x < a.cwgs) {
-        // the gradient of a cached row: over the windows of its bin, in their order; N / 4 lanes per slot, eight windows in flight,
-        // and where a workgroup has fewer slots than lanes for them, as many groups of lanes as there is room for share the windows
-        constexpr int NQ = N / 4, NF = 8;
-        const int lanes = a.cslots * NQ, groups = RW_T / lanes, g = t / lanes, slot = (int)blockIdx.x * a.cslots + t % lanes / NQ, f = t % NQ;
-        const int bin = slot % RW_CBINS, j = slot / RW_CBINS;
-        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-        int any = 0;
-        if (slot < a.K) {
-            const int b0 = ws.cwin[bin], n = ws.cwin[bin + 1] - b0, share = (n + groups - 1) / groups;
-            const int w0 = b0 + min(n, g * share), w1 = b0 + min(n, (g + 1) * share);
+        // The gradient of a cached row: over the windows of its bin, in their order; N / 4 lanes per slot, eight windows in flight.
+        // In a long stream what has more than RW_ALONE windows is then shared out among all lanes of the workgroup.
+        constexpr int NQ = N / 4, NF = 8, GROUPS = RW_T / NQ;
+        const int f = t % NQ, g = t / NQ, slot = (int)blockIdx.x * GROUPS + g;
+        auto add_up = [&](int j, int w0, int w1, float4 &sum) __attribute__((always_inline)) {
+            bool any = false;
             for (int x = w0; x < w1; x += NF) {
                 int u[NF];
                 float4 v[NF];
@@ -614,25 +617,49 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
                 for (int q = 0; q < NF; ++q)
                     if (x + q < w1 && u[q] >= 0) {
                         sum.x += v[q].x; sum.y += v[q].y; sum.z += v[q].z; sum.w += v[q].w;
-                        any = 1;
+                        any = true;
                     }
             }
-        }
-        if (groups > 1) {                                          // uniform
-            reinterpret_cast<float4 *>(s_red)[t] = sum;
-            s_any[t] = any;
+            return any;
+        };
+        auto update = [&](int slot, const float4 &sum) __attribute__((always_inline)) {
+            const size_t at = (size_t)slot * N + 4 * f;
+            const float4 o = *reinterpret_cast<const float4 *>(a.lines + at);
+            *reinterpret_cast<float4 *>(a.lines + at) = make_float4(fmaf(a.mul, sum.x, o.x), fmaf(a.mul, sum.y, o.y), fmaf(a.mul, sum.z, o.z), fmaf(a.mul, sum.w, o.w));
+        };
+        if constexpr (SHARE) {
+            if (t == 0) s_last = 0;
             __syncthreads();
-            if (g) return;
-            for (int x = t + lanes; x < RW_T; x += lanes) {
-                const float4 v = reinterpret_cast<float4 *>(s_red)[x];
-                sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-                any |= s_any[x];
+        }
+        if (slot < a.K) {
+            const int w0 = ws.cwin[slot % RW_CBINS], w1 = ws.cwin[slot % RW_CBINS + 1];
+            float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (SHARE && w1 - w0 > RW_ALONE) {
+                if (f == 0) s_list[atomicAdd(&s_last, 1)].x = slot;
+            } else if (add_up(slot / RW_CBINS, w0, w1, sum)) {
+                update(slot, sum);
             }
         }
-        if (!any) return;
-        const size_t at = (size_t)slot * N + 4 * f;
-        const float4 o = *reinterpret_cast<const float4 *>(a.lines + at);
-        *reinterpret_cast<float4 *>(a.lines + at) = make_float4(fmaf(a.mul, sum.x, o.x), fmaf(a.mul, sum.y, o.y), fmaf(a.mul, sum.z, o.z), fmaf(a.mul, sum.w, o.w));
+        if constexpr (!SHARE) return;
+        __syncthreads();
+        for (int q = 0, n = s_last; q < n; ++q) {                  // uniform
+            const int long_slot = s_list[q].x, bin = long_slot % RW_CBINS;
+            const int w0 = ws.cwin[bin], nw = ws.cwin[bin + 1] - w0, share = (nw + GROUPS - 1) / GROUPS;
+            float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+            bool any = add_up(long_slot / RW_CBINS, w0 + min(nw, g * share), w0 + min(nw, (g + 1) * share), sum);
+            reinterpret_cast<float4 *>(s_red)[t] = sum;
+            s_list[t].y = any;
+            __syncthreads();
+            if (g == 0) {
+                for (int x = t + NQ; x < RW_T; x += NQ) {
+                    const float4 v = reinterpret_cast<float4 *>(s_red)[x];
+                    sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+                    any |= s_list[x].y != 0;
+                }
+                if (any) update(long_slot, sum);
+            }
+            __syncthreads();                                       // (s_red is written again)
+        }
         return;
     }
     const int wg = (int)blockIdx.x - (CACHED ? a.cwgs : 0);
@@ -881,20 +908,6 @@ static inline hipError_t rw_fwd(const Params &p, const float *G1, const float *G
     }
 }
 
-// Cached rows per workgroup of rw_sum_kernel.  As many as there are lanes for, each adding up its windows alone, where the stream is
-// short; a hot slot of a longer one would be a chain of hundreds of loads.  (4,4,4) at rank 32, step, one of 1,000 cached rows at
-// 80 % of the positions: 1,000,000 positions 555 us, on the slices' lists 534, with 8 rows per workgroup and four groups of lanes 505,
-// 300,000 185, 199 and 176; with no hot slot 244 either way, and 163,840 positions 130 so and 131 shared.  Not more workgroups than
-// bins: more start for nothing (300,000 positions, 8,000 cached rows: 233 us, with 8 rows per workgroup 240, with one 277).
-constexpr int64_t RW_SPLIT_MIN_L = 262144;
-static inline int rw_slots_per_wg(int64_t L, int K, int N)
-{
-    const int all = 4 * RW_T / N;
-    int n = 1;
-    while (n < all && (L < RW_SPLIT_MIN_L || n * RW_CBINS < K)) n *= 2;
-    return n;
-}
-
 template <typename C, int ROWS_>
 static inline hipError_t launch_rw_bwd(const Params &p, const float *G1, const float *G2, const float *G3, int64_t L, const float *alpha,
                                        const float *go, const float *t0, const float *const src[3], float *const dst[3], float mul, int K, float *lines, const RowsWs &ws,
@@ -904,15 +917,16 @@ static inline hipError_t launch_rw_bwd(const Params &p, const float *G1, const f
     static OncePerDevice once;
     hipError_t e = allow_dynamic_lds(once, (const void *)rw_tile_kernel<C, ROWS_>, lds);
     if (e != hipSuccess) return e;
-    const int nwg = rw_tile_wgs(p, L, K), cslots = rw_slots_per_wg(L, K, C::N), cwgs = (K + cslots - 1) / cslots, per = (C::sB / 4 + 2 * RW_T - 1) / (2 * RW_T);
+    const int nwg = rw_tile_wgs(p, L, K), cwgs = (int)(((int64_t)K * (C::N / 4) + RW_T - 1) / RW_T), per = (C::sB / 4 + 2 * RW_T - 1) / (2 * RW_T);
     constexpr int MT = C::N > 16 ? 512 : 256;
     hipLaunchKernelGGL((rw_merge_kernel<C::N, MT>), dim3((unsigned)((L + RM_ROWS - 1) / RM_ROWS)), dim3(MT), 0, st, (int)L, ws.rec, ws.gkb, alpha, go,
                        ws.dym);
     hipLaunchKernelGGL((rw_tile_kernel<C, ROWS_>), dim3(nwg), dim3(WG), lds, st, p, G1, G2, G3, (int)L, ws.dym, ws.rec, ws.tiles, ws.tile_base,
                        ws.part2, ws.pbuf, src[1], dst[1], mul);
     const int most = rw_extra(p, L), extra = most < RS_MAX_EXTRA ? most : RS_MAX_EXTRA;
-    const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg, rw_piece(p, L), extra, K, cslots, cwgs, lines};
-    hipLaunchKernelGGL((K ? rw_sum_kernel<C, true> : rw_sum_kernel<C, false>), dim3(cwgs + p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
+    const RsArgs a{{src[0], src[1], src[2]}, {dst[0], dst[1], dst[2]}, mul, nwg, rw_piece(p, L), extra, K, cwgs, lines};
+    const auto sum = !K ? rw_sum_kernel<C, false, false> : L < RW_SHARE_MIN_L ? rw_sum_kernel<C, true, false> : rw_sum_kernel<C, true, true>;
+    hipLaunchKernelGGL(sum, dim3(cwgs + p.m1 + p.m3 + extra + p.m2 * per), dim3(RW_T), 0, st, p, ws, a, t0,
                        ws.dym, ws.pbuf, ws.l13);
     return hipGetLastError();
 }

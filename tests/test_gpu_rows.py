@@ -139,7 +139,7 @@ def test_one_workspace_on_either_side_of_the_longer_windows():
 
 # With a cache: slots in one bin of 128 and several, the last bin's slots missing, as many as the passes take and one more (the list owners);
 # no position cached, all of them, a hot slot over many windows; streams on either side of the window sizes; long ones, where groups of lanes
-# share a slot's windows: two slots per workgroup, eight; so long that the tiles are for more workgroups than run at once.
+# share a hot slot's windows, with one slot and with eight in a bin; so long that the tiles are for more workgroups than run at once.
 @pytest.mark.parametrize("n,R,L,K,share", [((4, 4, 4), 32, 4095, 50, 0.7), ((4, 4, 4), 32, 4096, 1, 0.7), ((4, 4, 4), 32, 20_001, 129, 0.8), ((2, 2, 4), 32, 66_000, 300, 0.9),
                                            ((2, 2, 4), 64, 17_000, 1000, 0.0), ((4, 4, 4), 64, 16_500, 128, 1.0), ((2, 2, 4), 32, 16_400, 8192, 0.5),
                                            ((2, 2, 4), 32, 16_400, 8193, 0.5), ((4, 4, 4), 32, 262_144, 129, 0.99), ((2, 2, 4), 64, 300_001, 1000, 0.99), ((4, 4, 4), 32, 1_050_000, 300, 0.995)])
