@@ -74,26 +74,26 @@ __global__ __launch_bounds__(WG) void freq_update_kernel(FreqDev f, const int64_
 // Long streams: a workgroup first counts its FQ_CHUNK positions in a small table in LDS (LDS
 // atomics; equal rows meet there), then adds every distinct row of the chunk to the device table
 // once.  The hottest row of a Zipf stream then costs one device atomic per chunk, not per wave.
-constexpr int FQ_PER = 4;                       // positions per thread
-constexpr int FQ_CHUNK = FQ_PER * WG;           // positions per workgroup
+constexpr int FQ_CHUNK = 1024;                   // positions per workgroup
 constexpr int FQ_T = 2 * FQ_CHUNK;              // LDS table entries (never full)
+constexpr int FQ_NT = 1024;                     // threads
 
-__global__ __launch_bounds__(WG) void freq_update_chunk_kernel(FreqDev f, const int64_t *__restrict__ indices, int L)
+__global__ __launch_bounds__(FQ_NT) void freq_update_chunk_kernel(FreqDev f, const int64_t *__restrict__ indices, int L)
 {
+    constexpr int NP = FQ_CHUNK / FQ_NT, PER = FQ_T / FQ_NT;
     __shared__ uint32_t lkey[FQ_T], lcnt[FQ_T];
+    __shared__ uint32_t s_new, s_lost;
     const int t = threadIdx.x;
-    for (int i = t; i < FQ_T; i += WG) { lkey[i] = 0xFFFFFFFFu; lcnt[i] = 0u; }
+    const uint32_t base = blockIdx.x * (uint32_t)FQ_CHUNK, end = (uint32_t)L;
+    uint32_t row[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) row[q] = (uint32_t)indices[min(base + q * FQ_NT + t, end - 1)];
+    for (int i = t; i < FQ_T; i += FQ_NT) { lkey[i] = 0xFFFFFFFFu; lcnt[i] = 0u; }
+    if (t == 0) s_new = s_lost = 0u;
     __syncthreads();
-    const int base = blockIdx.x * FQ_CHUNK;
-    uint32_t row[FQ_PER];
 #pragma unroll
-    for (int q = 0; q < FQ_PER; ++q) {
-        const int k = base + q * WG + t;
-        row[q] = k < L ? (uint32_t)indices[k] : 0xFFFFFFFFu;
-    }
-#pragma unroll
-    for (int q = 0; q < FQ_PER; ++q) {
-        if (row[q] == 0xFFFFFFFFu) continue;
+    for (int q = 0; q < NP; ++q) {
+        if (base + q * FQ_NT + t >= end) continue;
         uint32_t h = cache_hash(row[q], FQ_T - 1);
         for (;;) {                                                 // ends: at most FQ_CHUNK rows in 2 FQ_CHUNK entries
             const uint32_t old = atomicCAS(&lkey[h], 0xFFFFFFFFu, row[q]);
@@ -102,32 +102,50 @@ __global__ __launch_bounds__(WG) void freq_update_chunk_kernel(FreqDev f, const 
         }
     }
     __syncthreads();
-    // Every distinct row of the chunk to the device table.  The thread's table words are looked up together: a row that is
-    // tracked already, in its first place, is one load and one add that nothing waits for; the others walk on.  (One
-    // entry after the other, load - add - load - add: 33 us for 163,840 positions; so: 16 us.)
-    constexpr int PER = FQ_T / WG;
-    uint32_t key[PER], h[PER];
+    // Every distinct row of the chunk to the device table, all rows of a thread one place further in every round: their loads (and
+    // their compare-and-swaps) are in flight together, the adds are not waited for.  What bounds it is that chain of round trips, as long
+    // as the longest walk of a wave's rows.  (163,840 positions in a table of 2^20: one entry after the other 33 us; the first places of
+    // eight entries of 256 threads together, the walks one after the other 16; so, two entries of 1,024 threads, 10.)
+    uint32_t key[PER], h[PER], n[PER], fresh = 0, left = 0;
     unsigned long long e[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        key[q] = lkey[q * WG + t];
+        key[q] = lkey[q * FQ_NT + t];
+        n[q] = lcnt[q * FQ_NT + t];
         h[q] = cache_hash(key[q], f.mask);
-        e[q] = key[q] != 0xFFFFFFFFu ? __hip_atomic_load(&f.table[h[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : FREQ_EMPTY;
+        if (key[q] != 0xFFFFFFFFu) left |= 1u << q;
     }
-    uint32_t done = 0;
+    for (uint32_t probes = 0; left && probes <= f.mask; ++probes) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        if (key[q] == 0xFFFFFFFFu) continue;
-        if (e[q] != FREQ_EMPTY && (uint32_t)(e[q] >> 32) == key[q]) {
-            atomicAdd(&f.table[h[q]], (unsigned long long)lcnt[q * WG + t]);
-            done |= 1u << q;
+        for (int q = 0; q < PER; ++q)
+            if ((left >> q) & 1u) e[q] = __hip_atomic_load(&f.table[h[q]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (((left >> q) & 1u) && e[q] == FREQ_EMPTY) {
+                const unsigned long long entry = (unsigned long long)key[q] << 32;
+                e[q] = atomicCAS(&f.table[h[q]], (unsigned long long)FREQ_EMPTY, entry);
+                if (e[q] == FREQ_EMPTY) {
+                    e[q] = entry;
+                    ++fresh;
+                }
+            }
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (!((left >> q) & 1u)) continue;
+            if ((uint32_t)(e[q] >> 32) == key[q]) {
+                atomicAdd(&f.table[h[q]], (unsigned long long)n[q]);
+                left &= ~(1u << q);
+            }
+            h[q] = (h[q] + 1) & f.mask;
         }
     }
-#pragma unroll 1
-    for (int q = 0; q < PER; ++q) {
-        const int i = q * WG + t;
-        if (lkey[i] != 0xFFFFFFFFu && !((done >> q) & 1u)) freq_add(f, lkey[i], lcnt[i]);
-    }
+    if (fresh) atomicAdd(&s_new, fresh);
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+        if ((left >> q) & 1u) atomicAdd(&s_lost, n[q]);            // table full
+    __syncthreads();
+    if (t == 0 && s_new) atomicAdd(&f.stats[0], (unsigned long long)s_new);
+    if (t == 0 && s_lost) atomicAdd(&f.stats[1], (unsigned long long)s_lost);
 }
 
 // rows / counts of the occupied entries, in no particular order; *n_out = how many.  A workgroup compacts FQ_EXPORT
