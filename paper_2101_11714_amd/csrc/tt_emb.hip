@@ -1230,12 +1230,7 @@ int tt_cache_refill(const tt_shape_t *shape, const float *const cores[3],
     if (rc) return rc;
     // 3. the new set replaces the old one
     const int64_t nr = (int64_t)K * p.N;
-    const int64_t n4 = nr / 4 > cache->capacity ? nr / 4 : cache->capacity;
-    hipLaunchKernelGGL(cache_replace_kernel, dim3(cdiv(n4, WG) < 2048 ? cdiv(n4, WG) : 2048), dim3(WG), 0, st, new_keys, cache->keys, K,
-                       new_rows, cache->rows, nr, cache->table, cache->capacity);
-    hipLaunchKernelGGL(cache_insert_kernel, dim3(cdiv(K, WG)), dim3(WG), 0, st, cache->keys, K, cache->table,
-                       (uint32_t)(cache->capacity - 1));
-    e = hipGetLastError();
+    e = cache_replace(new_keys, cache->keys, K, new_rows, cache->rows, nr, cache->table, cache->capacity, st);
     return e == hipSuccess ? TT_OK : hip_fail(e, "cache refill launch");
 }
 

@@ -185,16 +185,68 @@ __global__ __launch_bounds__(WG) void freq_export_kernel(FreqDev f, int64_t *__r
 
 __global__ void freq_zero_kernel(unsigned long long *p) { if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0ull; }
 
-// What a refill puts in place of the old cached set: keys, lines (nr values, 16-byte aligned) and an empty row -> slot map.
-__global__ __launch_bounds__(WG) void cache_replace_kernel(const int64_t *__restrict__ new_keys, int64_t *__restrict__ keys, int K,
-                                                           const float *__restrict__ new_rows, float *__restrict__ rows, int64_t nr,
-                                                           uint64_t *__restrict__ table, int64_t capacity)
+// What a refill puts in place of the old cached set: keys, lines (nr values, 16-byte aligned) and the row -> slot map.  The map is
+// built in LDS by the first workgroup and written as a whole while the others copy (IN_LDS), up to CR_MAX_CAPACITY places; a larger
+// one is emptied here and filled by cache_insert_kernel.  4,000 rows: emptied, then filled by compare-and-swaps in device memory, a chain
+// of round trips per row, 3 + 8 us in two launches; so 6 in one.
+constexpr int CR_NT = 1024;
+constexpr int64_t CR_MAX_CAPACITY = 16384;       // 128 KB
+
+template <bool IN_LDS>
+__global__ __launch_bounds__(CR_NT) void cache_replace_kernel(const int64_t *__restrict__ new_keys, int64_t *__restrict__ keys, int K,
+                                                              const float *__restrict__ new_rows, float *__restrict__ rows, int64_t nr,
+                                                              uint64_t *__restrict__ table, int64_t capacity)
 {
-    const int64_t first = (int64_t)blockIdx.x * WG + threadIdx.x, step = (int64_t)gridDim.x * WG, n4 = nr / 4;
+    extern __shared__ __align__(16) unsigned long long cr_map[];              // [capacity]
+    const int t = threadIdx.x;
+    if (IN_LDS && blockIdx.x == 0) {
+        constexpr int NK = 4;                                                 // keys in flight per thread
+        const uint32_t mask = (uint32_t)(capacity - 1);
+        for (int x = t; x < capacity; x += CR_NT) cr_map[x] = CACHE_EMPTY;
+        for (int b = 0; b < K; b += NK * CR_NT) {                             // uniform
+            int64_t key[NK];
+#pragma unroll
+            for (int q = 0; q < NK; ++q) key[q] = new_keys[min(b + q * CR_NT + t, K - 1)];
+            __syncthreads();                                                  // (the first time: the map is empty)
+#pragma unroll
+            for (int q = 0; q < NK; ++q) {
+                const int s = b + q * CR_NT + t;
+                if (s >= K) continue;
+                keys[s] = key[q];
+                const unsigned long long entry = ((unsigned long long)(uint32_t)key[q] << 32) | (uint32_t)s;
+                uint32_t h = cache_hash((uint32_t)key[q], mask);
+                while (atomicCAS(&cr_map[h], (unsigned long long)CACHE_EMPTY, entry) != CACHE_EMPTY) h = (h + 1) & mask;   // ends: capacity >= 2 K
+            }
+        }
+        __syncthreads();
+        for (int x = t; x < capacity / 2; x += CR_NT) reinterpret_cast<ulonglong2 *>(table)[x] = reinterpret_cast<const ulonglong2 *>(cr_map)[x];
+        return;
+    }
+    const int64_t wg = (int64_t)blockIdx.x - (IN_LDS ? 1 : 0), wgs = (int64_t)gridDim.x - (IN_LDS ? 1 : 0);
+    const int64_t first = wg * CR_NT + t, step = wgs * CR_NT, n4 = nr / 4;
     for (int64_t i = first; i < n4; i += step) reinterpret_cast<float4 *>(rows)[i] = reinterpret_cast<const float4 *>(new_rows)[i];
     for (int64_t i = 4 * n4 + first; i < nr; i += step) rows[i] = new_rows[i];
+    if (IN_LDS) return;
     for (int64_t i = first; i < K; i += step) keys[i] = new_keys[i];
     for (int64_t i = first; i < capacity; i += step) table[i] = CACHE_EMPTY;
+}
+
+// (rows and table: see cache_replace_kernel)
+static inline hipError_t cache_replace(const int64_t *new_keys, int64_t *keys, int K, const float *new_rows, float *rows, int64_t nr, uint64_t *table,
+                                       int64_t capacity, hipStream_t st)
+{
+    const int64_t n4 = nr / 4 + 1, blocks = (n4 + CR_NT - 1) / CR_NT, copy = blocks < 1024 ? blocks : 1024;
+    if (capacity <= CR_MAX_CAPACITY && ((uintptr_t)table & 15) == 0) {
+        static OncePerDevice once;
+        const hipError_t e = allow_dynamic_lds(once, (const void *)cache_replace_kernel<true>, CR_MAX_CAPACITY * 8);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(cache_replace_kernel<true>, dim3((unsigned)copy + 1), dim3(CR_NT), (size_t)capacity * 8, st, new_keys, keys, K, new_rows, rows, nr,
+                           table, capacity);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(cache_replace_kernel<false>, dim3((unsigned)copy), dim3(CR_NT), 0, st, new_keys, keys, K, new_rows, rows, nr, table, capacity);
+    hipLaunchKernelGGL(cache_insert_kernel, dim3((K + WG - 1) / WG), dim3(WG), 0, st, keys, K, table, (uint32_t)(capacity - 1));
+    return hipGetLastError();
 }
 
 }  // namespace tt

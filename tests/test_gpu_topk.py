@@ -42,3 +42,29 @@ def _select(T, n, K, counts):
     B.tt_cache_build(B.shape_of(T), cores, torch.from_numpy(rows).to(dev()), torch.from_numpy(cnt).to(dev()), cache)
     torch.cuda.synchronize()
     assert np.array_equal(cache.keys.cpu().numpy()[:K], ora.cache_select(rows, cnt, K))
+
+
+# the refill's row -> slot map: the largest that is built in LDS (16,384 places), one larger, one with more places than are needed
+@pytest.mark.parametrize("K,places", [(1, 16), (5, 16), (4097, 16_384), (8192, 16_384), (8193, 32_768), (100, 32_768), (100, 16_384)])
+def test_refilled_map(K, places):
+    rng = np.random.default_rng(K + places)
+    cores = [torch.from_numpy(x).to(dev()) for x in W.make_cores(T, "normal0.1", 1)]
+    shape, n = B.shape_of(T), 3 * K
+    rows = rng.permutation(T.num_rows)[:n].astype(np.int64)
+    first, second = rng.permutation(n) + 1, rng.permutation(n) + 1
+    cache = B.Cache(K, T.dim, dev())
+    cache.table = torch.zeros(places, dtype=torch.int64, device=dev())
+    cache.c.table, cache.c.capacity = cache.table.data_ptr(), places
+    on = lambda x: torch.from_numpy(np.ascontiguousarray(x, dtype=np.int64)).to(dev())
+    B.tt_cache_build(shape, cores, on(rows), on(first), cache)
+    B.tt_cache_refill(shape, cores, on(rows), on(second), cache)
+    torch.cuda.synchronize()
+    keys = ora.cache_select(rows, second.astype(np.int64), K)
+    assert np.array_equal(cache.keys.cpu().numpy()[:K], keys)
+    asked = np.concatenate([rows, rng.integers(0, T.num_rows, 1000)])
+    slot = torch.empty(asked.size, dtype=torch.int32, device=dev())
+    B.tt_cache_lookup(cache, on(asked), slot)
+    assert np.array_equal(slot.cpu().numpy(), ora.cache_lookup(ora.Shape.of(T), keys, asked))
+    table = cache.table.cpu().numpy().view(np.uint64)
+    used = table[table != np.uint64(0xFFFFFFFFFFFFFFFF)]
+    assert np.array_equal(np.sort(used & np.uint64(0xFFFFFFFF)), np.arange(K)) and np.array_equal(np.sort(used >> np.uint64(32)), np.sort(keys.view(np.uint64)))
