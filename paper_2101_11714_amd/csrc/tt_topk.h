@@ -2,57 +2,56 @@
 // id; the key is the inverted count above the row id).  A full sort of the candidates orders all of them, eight passes
 // over 64-bit keys, for the few thousand that are kept.  Here one histogram over the leading bits of the counts finds the
 // class of counts that holds the K-th key; if the keys up to the end of that class are few enough they are compacted and
-// ranked by counting the smaller ones, else (thousands of candidates with the count of the K-th) a single workgroup
-// narrows the class down first, digit by digit.  40 M-row table, 77,000 candidates, K = 4,000: the sort took 104 us in 16
-// launches (its passes are chains of memory round trips), this 23 us in 5.
+// ranked by counting the smaller ones, else (thousands of candidates with the count of the K-th) the class is
+// narrowed down first, digit by digit.  40 M-row table, 77,000 candidates, K = 4,000: the sort took 104 us in 16
+// launches (its passes are chains of memory round trips), this 21 us in 3 (its five
+// launches, keys, class, narrowing, compaction and ranks each in one of their own, took 23 and two launches more).
 #pragma once
 
 #include "tt_common.h"
 #include "tt_sort.h"
+#include "tt_rows.h"
 
 namespace tt {
 
 constexpr int TK_BITS = 12, TK_BINS = 1 << TK_BITS;
-constexpr int TK_TILE = 2048;                    // keys per workgroup of a pass
+constexpr int TK_CLASSES = 33 * 64;              // classes of counts (topk_class)
+constexpr int TK_NT = 1024, TK_TILE = 4096;      // threads, and keys, per workgroup of a pass
 constexpr int TK_MAX_K = 8192;                   // ranking compares every pair: 5 us for 4,000 keys, 20 us for this many
 constexpr int TK_MAX_N = 1 << 18;                // more candidates than a single workgroup should have to narrow down
 constexpr int TK_RANK_KEYS = 8;                  // keys a workgroup ranks, 32 threads each
-constexpr int TK_NARROW_WG = 1024;
 
 struct TopkState {
-    uint64_t prefix;                             // the leading bits of the K-th key found so far ...
-    int shift;                                   // ... and how many bits follow
-    uint32_t before, remaining;                  // keys below that class, keys still to take inside it
-    uint32_t blocks, count;
+    uint32_t count;                              // keys taken
 };
 
 struct TopkWs {
     uint64_t *keys, *taken;                      // [n], [TK_MAX_K]
-    uint32_t *hist;                              // [TK_BINS]
+    uint32_t *hist;                              // [tiles][TK_CLASSES]
     TopkState *state;
 };
 
 // Everything lies in the workspace of a sort of n keys (n > TK_MAX_K).
-static inline TopkWs topk_ws(const SortWs &s)
+static inline TopkWs topk_ws(const SortWs &s, int n)
 {
-    static_assert(TK_MAX_K >= TK_BINS + 64, "the histogram and the state fit the n payload words");
-    return TopkWs{s.k0, s.k1, s.v0, (TopkState *)(s.v0 + TK_BINS)};
+    // tiles TK_CLASSES + 1 <= (n / TK_TILE + 1) TK_CLASSES + 1 <= n: the histograms and the state fit the n payload words
+    static_assert(TK_CLASSES < TK_TILE && (int64_t)TK_CLASSES * TK_TILE < (int64_t)TK_MAX_K * (TK_TILE - TK_CLASSES), "room");
+    const int tiles = (n + TK_TILE - 1) / TK_TILE;
+    return TopkWs{s.k0, s.k1, s.v0, (TopkState *)(s.v0 + tiles * TK_CLASSES)};
 }
 
-// key = inverted count (32 bits) above rb bits of the row; the first workgroup also clears the histogram and the state
-__global__ __launch_bounds__(WG) void topk_keys_kernel(const int64_t *__restrict__ rows, const int64_t *__restrict__ counts, int n,
-                                                       int rb, uint64_t *__restrict__ keys, uint32_t *__restrict__ hist,
-                                                       TopkState *__restrict__ state, int K)
+// key = inverted count (32 bits) above rb bits of the row
+__device__ __forceinline__ uint32_t topk_count(int64_t count) { return (uint64_t)count > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)count; }
+__device__ __forceinline__ uint64_t topk_key(int64_t row, int64_t count, int rb)
+{
+    return ((uint64_t)(~topk_count(count)) << rb) | ((uint64_t)row & ((1ull << rb) - 1ull));
+}
+
+__global__ __launch_bounds__(WG) void topk_keys_kernel(const int64_t *__restrict__ rows, const int64_t *__restrict__ counts, int n, int rb,
+                                                       uint64_t *__restrict__ keys)
 {
     const int i = blockIdx.x * WG + threadIdx.x;
-    if (hist && blockIdx.x == 0) {
-        for (int x = threadIdx.x; x < TK_BINS; x += WG) hist[x] = 0u;
-        if (threadIdx.x == 0) *state = TopkState{0ull, 0, 0u, (uint32_t)K, 0u, 0u};
-    }
-    if (i >= n) return;
-    const uint64_t c = (uint64_t)counts[i];
-    const uint32_t inv = 0xFFFFFFFFu - (uint32_t)(c > 0xFFFFFFFFull ? 0xFFFFFFFFull : c);
-    keys[i] = ((uint64_t)inv << rb) | ((uint64_t)rows[i] & ((1ull << rb) - 1ull));
+    if (i < n) keys[i] = topk_key(rows[i], counts[i], rb);
 }
 
 // Class of a count: its number of bits (0..32) and the 6 bits below the leading one, larger counts in smaller classes.
@@ -64,144 +63,141 @@ __device__ __forceinline__ uint32_t topk_class(uint32_t count)
     return (uint32_t)(32 - nb) * 64u + (63u - frac);
 }
 
-// Histogram of the classes; the workgroup that is done last picks the class with the K-th key.
-__global__ __launch_bounds__(WG) void topk_class_kernel(const uint64_t *__restrict__ keys, int n, int rb, uint32_t *__restrict__ hist,
-                                                        TopkState *__restrict__ state)
+// Keys, and the histogram of their classes, of a tile of candidates: hist[tile][TK_CLASSES].
+__global__ __launch_bounds__(TK_NT) void topk_class_kernel(const int64_t *__restrict__ rows, const int64_t *__restrict__ counts, int n, int rb,
+                                                           uint64_t *__restrict__ keys, uint32_t *__restrict__ hist, TopkState *__restrict__ state)
 {
-    constexpr int NB = 33 * 64, PER = (NB + WG - 1) / WG;
-    static_assert(NB <= TK_BINS, "the classes fit the histogram");
-    __shared__ uint32_t h[NB];
-    __shared__ int s_last;
-    __shared__ int s_tmp[NWAVE + 1];
-    const int t = threadIdx.x;
-    uint64_t k[TK_TILE / WG];
+    constexpr int PER = TK_TILE / TK_NT;
+    __shared__ uint32_t h[TK_CLASSES];
+    const int t = threadIdx.x, lane = t & 63, base = blockIdx.x * TK_TILE;
+    int64_t r[PER], c[PER];
 #pragma unroll
-    for (int q = 0; q < TK_TILE / WG; ++q) k[q] = keys[min((int)blockIdx.x * TK_TILE + q * WG + t, n - 1)];
-    for (int x = t; x < NB; x += WG) h[x] = 0u;
+    for (int q = 0; q < PER; ++q) { r[q] = rows[min(base + q * TK_NT + t, n - 1)]; c[q] = counts[min(base + q * TK_NT + t, n - 1)]; }
+    for (int x = t; x < TK_CLASSES; x += TK_NT) h[x] = 0u;
+    if (blockIdx.x == 0 && t == 0) state->count = 0u;
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < TK_TILE / WG; ++q)
-        if ((int)blockIdx.x * TK_TILE + q * WG + t < n) atomicAdd(&h[topk_class(~(uint32_t)(k[q] >> rb))], 1u);
-    __syncthreads();
-    for (int x = t; x < NB; x += WG)
-        if (h[x]) atomicAdd(&hist[x], h[x]);
-    // This workgroup's adds have to be performed before it counts itself as done.  A barrier alone does not wait for them; they
-    // and the loads below go to the point where the whole device meets, so that no fence has to write the caches back.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (t == 0) s_last = atomicAdd(&state->blocks, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (!s_last) return;
-    const uint32_t want = state->remaining;      // 1 <= want <= total; read by everyone before the scan's barriers, written after them
-    uint32_t v[PER];
-    int sum = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int x = t * PER + q;
-        v[q] = x < NB ? __hip_atomic_load(&hist[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-        sum += (int)v[q];
-    }
-    int total;
-    uint32_t before = (uint32_t)block_excl_scan(sum, s_tmp, &total);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        if (before < want && want <= before + v[q]) {                        // one thread, one class
-            // leading bits of the inverted counts of the class: nb bits of the count, the lower nb - 7 of them open
-            const int x = t * PER + q, nb = 32 - x / 64;
-            const uint32_t frac = 63u - (uint32_t)(x % 64);
-            const int open = nb > 7 ? nb - 7 : 0;
-            const uint64_t top = nb == 0 ? 0ull : (nb > 7 ? 64ull + frac : ((64ull + frac) >> (7 - nb)));   // the count without its open bits
-            state->prefix = (0xFFFFFFFFull >> open) - top;
-            state->shift = rb + open;
-            state->before = before;
-            state->remaining = want - before;
-            state->count = 0u;
-            state->blocks = v[q];                                            // keys in the class
+        const bool in = base + q * TK_NT + t < n;
+        const uint32_t x = topk_class(topk_count(c[q]));
+        if (in) keys[base + q * TK_NT + t] = topk_key(r[q], c[q], rb);
+        // (most rows have been used once or twice: lanes of one class, that of the first lane, add together)
+        const uint64_t same = __ballot(in && x == (uint32_t)__builtin_amdgcn_readfirstlane((int)x));
+        if ((same >> lane) & 1) {
+            if (!(same & lanemask_lt())) atomicAdd(&h[x], (uint32_t)__popcll(same));
+        } else if (in) {
+            atomicAdd(&h[x], 1u);
         }
-        before += v[q];
     }
+    __syncthreads();
+    for (int x = t; x < TK_CLASSES; x += TK_NT) hist[(size_t)blockIdx.x * TK_CLASSES + x] = h[x];
 }
 
-// Where the keys up to the end of the class are more than can be ranked, one workgroup finds more leading bits of the
-// K-th key: a histogram of the next bits over the keys of the class, as often as needed.
-__global__ __launch_bounds__(TK_NARROW_WG) void topk_narrow_kernel(const uint64_t *__restrict__ keys, int n, TopkState *__restrict__ state)
+// The keys up to the end of the class with the K-th key, in any order.  Every workgroup finds that class itself from all tiles'
+// histograms.  Where the keys up to its end are more than can be ranked, it then looks for more leading bits of the K-th key: a histogram of the
+// next bits over the keys of the class, as often as needed (all workgroups alike: no slower than one of them, and no launch of its own
+// for what is hardly ever needed).
+__global__ __launch_bounds__(TK_NT) void topk_take_kernel(const uint64_t *__restrict__ keys, int n, int K, int rb, const uint32_t *__restrict__ hist, TopkState *__restrict__ state, uint64_t *__restrict__ taken)
 {
-    constexpr int W = TK_NARROW_WG / WAVE, PER = TK_BINS / TK_NARROW_WG, NF = 8;
+    constexpr int W = TK_NT / WAVE, PER = TK_TILE / TK_NT, NF = 8, CPT = (TK_CLASSES + TK_NT - 1) / TK_NT, BPT = TK_BINS / TK_NT;
     __shared__ uint32_t h[TK_BINS];
-    __shared__ uint32_t s_wave[W];
-    __shared__ TopkState s;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    if (t == 0) s = *state;
-    __syncthreads();
-    while (s.before + s.blocks > TK_MAX_K && s.shift > 0) {                  // uniform; the shift falls in every round
-        const int bits = min(TK_BITS, s.shift), shift = s.shift - bits;
-        const uint64_t prefix = s.prefix;
-        for (int x = t; x < TK_BINS; x += TK_NARROW_WG) h[x] = 0u;
-        __syncthreads();
-        for (int b = t; b < n; b += NF * TK_NARROW_WG) {
-            uint64_t k[NF];
+    __shared__ int s_tmp[W];
+    __shared__ uint64_t s_prefix;
+    __shared__ int s_shift;
+    __shared__ uint32_t s_before, s_remaining, s_class, s_base;
+    const int t = threadIdx.x, tiles = gridDim.x, base = blockIdx.x * TK_TILE;
+    uint64_t k[PER];
+    {
 #pragma unroll
-            for (int q = 0; q < NF; ++q) k[q] = keys[min(b + q * TK_NARROW_WG, n - 1)];
+        for (int q = 0; q < PER; ++q) k[q] = keys[min(base + q * TK_NT + t, n - 1)];
+        uint32_t v[CPT], sum = 0;
+#pragma unroll
+        for (int x = 0; x < CPT; ++x) v[x] = 0u;
+        if (t * CPT < TK_CLASSES) {
+            static_assert(TK_CLASSES % CPT == 0, "whole threads");
+            for (int b = 0; b < tiles; b += NF) {
+                uint32_t u[NF][CPT];
+#pragma unroll
+                for (int q = 0; q < NF; ++q)
+#pragma unroll
+                    for (int x = 0; x < CPT; ++x) u[q][x] = hist[(size_t)min(b + q, tiles - 1) * TK_CLASSES + t * CPT + x];
+#pragma unroll
+                for (int q = 0; q < NF; ++q)
+#pragma unroll
+                    for (int x = 0; x < CPT; ++x) v[x] += b + q < tiles ? u[q][x] : 0u;
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < CPT; ++x) sum += v[x];
+        int total;
+        uint32_t before = (uint32_t)rw_scan_of<W>((int)sum, s_tmp, &total);
+#pragma unroll
+        for (int x = 0; x < CPT; ++x) {
+            if (before < (uint32_t)K && (uint32_t)K <= before + v[x]) {      // one thread, one class
+                // leading bits of the inverted counts of the class: nb bits of the count, the lower nb - 7 of them open
+                const int cl = t * CPT + x, nb = 32 - cl / 64;
+                const uint32_t frac = 63u - (uint32_t)(cl % 64);
+                const int open = nb > 7 ? nb - 7 : 0;
+                const uint64_t top = nb == 0 ? 0ull : (nb > 7 ? 64ull + frac : ((64ull + frac) >> (7 - nb)));   // the count without its open bits
+                s_prefix = (0xFFFFFFFFull >> open) - top;
+                s_shift = rb + open;
+                s_before = before;
+                s_remaining = (uint32_t)K - before;
+                s_class = v[x];
+            }
+            before += v[x];
+        }
+    }
+    __syncthreads();
+    while (s_before + s_class > TK_MAX_K && s_shift > 0) {                   // uniform; the shift falls in every round
+        const int bits = min(TK_BITS, s_shift), shift = s_shift - bits;
+        const uint64_t prefix = s_prefix;
+        for (int x = t; x < TK_BINS; x += TK_NT) h[x] = 0u;
+        __syncthreads();
+        for (int b = t; b < n; b += NF * TK_NT) {
+            uint64_t x[NF];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) x[q] = keys[min(b + q * TK_NT, n - 1)];
 #pragma unroll
             for (int q = 0; q < NF; ++q)
-                if (b + q * TK_NARROW_WG < n && (k[q] >> (shift + bits)) == prefix) atomicAdd(&h[(uint32_t)(k[q] >> shift) & ((1u << bits) - 1u)], 1u);
+                if (b + q * TK_NT < n && (x[q] >> (shift + bits)) == prefix) atomicAdd(&h[(uint32_t)(x[q] >> shift) & ((1u << bits) - 1u)], 1u);
         }
         __syncthreads();
-        uint32_t v[PER], sum = 0;
+        uint32_t v[BPT], sum = 0;
 #pragma unroll
-        for (int q = 0; q < PER; ++q) { v[q] = h[t * PER + q]; sum += v[q]; }
-        uint32_t inc = sum;
-#pragma unroll
-        for (int d = 1; d < WAVE; d <<= 1) {
-            const uint32_t o = __shfl_up(inc, d);
-            if (lane >= d) inc += o;
-        }
-        if (lane == 63) s_wave[w] = inc;
-        __syncthreads();
-        uint32_t before = inc - sum;
-        for (int q = 0; q < w; ++q) before += s_wave[q];
-        const uint32_t want = s.remaining, below = s.before;
+        for (int q = 0; q < BPT; ++q) { v[q] = h[t * BPT + q]; sum += v[q]; }
+        int total;
+        uint32_t before = (uint32_t)rw_scan_of<W>((int)sum, s_tmp, &total);
+        const uint32_t want = s_remaining, below = s_before;
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
+        for (int q = 0; q < BPT; ++q) {
             if (before < want && want <= before + v[q]) {                    // one thread
-                s.prefix = (prefix << bits) | (uint64_t)(t * PER + q);
-                s.shift = shift;
-                s.before = below + before;
-                s.remaining = want - before;
-                s.blocks = v[q];
+                s_prefix = (prefix << bits) | (uint64_t)(t * BPT + q);
+                s_shift = shift;
+                s_before = below + before;
+                s_remaining = want - before;
+                s_class = v[q];
             }
             before += v[q];
         }
         __syncthreads();
     }
-    if (t == 0) *state = s;
-}
-
-// the keys up to the end of the class, in any order
-__global__ __launch_bounds__(WG) void topk_take_kernel(const uint64_t *__restrict__ keys, int n, TopkState *__restrict__ state,
-                                                       uint64_t *__restrict__ taken)
-{
-    __shared__ int s_tmp[NWAVE + 1];
-    __shared__ uint32_t s_base;
-    const int t = threadIdx.x, shift = state->shift;
-    const uint64_t prefix = state->prefix;
-    uint64_t k[TK_TILE / WG];
+    const int shift = s_shift;
+    const uint64_t prefix = s_prefix;
     int mine = 0;
     uint32_t in = 0;
 #pragma unroll
-    for (int q = 0; q < TK_TILE / WG; ++q) k[q] = keys[min((int)blockIdx.x * TK_TILE + q * WG + t, n - 1)];
-#pragma unroll
-    for (int q = 0; q < TK_TILE / WG; ++q)
-        if ((int)blockIdx.x * TK_TILE + q * WG + t < n && (k[q] >> shift) <= prefix) { in |= 1u << q; ++mine; }
+    for (int q = 0; q < PER; ++q)
+        if (base + q * TK_NT + t < n && (k[q] >> shift) <= prefix) { in |= 1u << q; ++mine; }
     int total;
-    int at = block_excl_scan(mine, s_tmp, &total);
+    int at = rw_scan_of<W>(mine, s_tmp, &total);
     if (!total) return;                          // uniform
     if (t == 0) s_base = atomicAdd(&state->count, (uint32_t)total);
     __syncthreads();
     at += (int)s_base;
 #pragma unroll
-    for (int q = 0; q < TK_TILE / WG; ++q)
+    for (int q = 0; q < PER; ++q)
         if ((in >> q) & 1u) {
             if (at < TK_MAX_K) taken[at] = k[q]; // (more only if the candidates are not distinct)
             ++at;
@@ -250,7 +246,7 @@ __global__ __launch_bounds__(WG) void take_rows_kernel(const uint64_t *__restric
 
 // keys[0..K) = the rows of the K most used of n candidates (0 < K <= n), most used first, ties by row id.  s: the
 // workspace of a sort of n keys.  Up to TK_MAX_K candidates are ranked directly; beyond K = TK_MAX_K (ranking compares
-// pairs) or n = TK_MAX_N (see topk_narrow_kernel) all candidates are sorted.
+// pairs) or n = TK_MAX_N (see topk_take_kernel) all candidates are sorted.
 static inline hipError_t topk_rows(const SortWs &s, const int64_t *cand_rows, const int64_t *cand_counts, int n, int K, int64_t num_rows,
                                    int64_t *keys, hipStream_t st)
 {
@@ -258,17 +254,17 @@ static inline hipError_t topk_rows(const SortWs &s, const int64_t *cand_rows, co
     while ((1ll << rb) < num_rows) ++rb;         // rows are below 2^31: 33 to 63 bits in all
     const int blocks = (n + WG - 1) / WG, tiles = (n + TK_TILE - 1) / TK_TILE;
     const bool select = n > TK_MAX_K && K <= TK_MAX_K && n <= TK_MAX_N;
-    const TopkWs w = topk_ws(s);
-    hipLaunchKernelGGL(topk_keys_kernel, dim3(blocks), dim3(WG), 0, st, cand_rows, cand_counts, n, rb, s.k0, select ? w.hist : nullptr,
-                       w.state, K);
+    if (select) {
+        const TopkWs w = topk_ws(s, n);
+        hipLaunchKernelGGL(topk_class_kernel, dim3(tiles), dim3(TK_NT), 0, st, cand_rows, cand_counts, n, rb, w.keys, w.hist, w.state);
+        hipLaunchKernelGGL(topk_take_kernel, dim3(tiles), dim3(TK_NT), 0, st, w.keys, n, K, rb, w.hist, w.state, w.taken);
+        hipLaunchKernelGGL(topk_rank_kernel, dim3(TK_MAX_K / TK_RANK_KEYS), dim3(WG), 0, st, w.taken, 0, w.state, K, rb, keys);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(topk_keys_kernel, dim3(blocks), dim3(WG), 0, st, cand_rows, cand_counts, n, rb, s.k0);
     if (n <= TK_MAX_K) {
         hipLaunchKernelGGL(topk_rank_kernel, dim3((n + TK_RANK_KEYS - 1) / TK_RANK_KEYS), dim3(WG), 0, st, s.k0, n, (const TopkState *)nullptr,
                            K, rb, keys);
-    } else if (select) {
-        hipLaunchKernelGGL(topk_class_kernel, dim3(tiles), dim3(WG), 0, st, w.keys, n, rb, w.hist, w.state);
-        hipLaunchKernelGGL(topk_narrow_kernel, dim3(1), dim3(TK_NARROW_WG), 0, st, w.keys, n, w.state);
-        hipLaunchKernelGGL(topk_take_kernel, dim3(tiles), dim3(WG), 0, st, w.keys, n, w.state, w.taken);
-        hipLaunchKernelGGL(topk_rank_kernel, dim3(TK_MAX_K / TK_RANK_KEYS), dim3(WG), 0, st, w.taken, 0, w.state, K, rb, keys);
     } else {
         uint64_t *ks; uint32_t *vs;
         hipError_t e = radix_sort(s, n, 32 + rb, st, &ks, &vs);
