@@ -4,8 +4,7 @@
 // class of counts that holds the K-th key; if the keys up to the end of that class are few enough they are compacted and
 // ranked by counting the smaller ones, else (thousands of candidates with the count of the K-th) the class is
 // narrowed down first, digit by digit.  40 M-row table, 77,000 candidates, K = 4,000: the sort took 104 us in 16
-// launches (its passes are chains of memory round trips), this 21 us in 3 (its five
-// launches, keys, class, narrowing, compaction and ranks each in one of their own, took 23 and two launches more).
+// launches (its passes are chains of memory round trips), this 21 us in 3.
 #pragma once
 
 #include "tt_common.h"
