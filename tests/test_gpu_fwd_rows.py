@@ -176,3 +176,12 @@ def test_scratch_memory_leaves_captures_elsewhere_alone():
         g.replay()
         torch.cuda.synchronize()
     assert float(count.min()) == float(count.max()) == 3.0   # (recorded, not run, the first time)
+
+
+# pooling by a part of a wave per bag, up to an average of six positions (exclusive), or by a wave
+@pytest.mark.parametrize("n,R", [((2, 2, 4), 32), ((4, 4, 4), 32)])
+@pytest.mark.parametrize("L,n_bags", [(1, 1), (5, 1), (6, 1), (101, 17), (102, 17), (599, 100), (600, 100), (40, 4097)])
+def test_pooling_of_short_bags(n, R, L, n_bags):
+    d = _table("hot row", n, R, L, n_bags)
+    b = d.batch
+    assert_close(_run(d), ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha), "L %d n_bags %d" % (L, n_bags))
