@@ -86,12 +86,15 @@ constexpr int64_t ROWS_FWD_MIN_L_444 = 10240, ROWS_FWD_MIN_L_224 = GROUP_MIN_L_R
 // 1-8: 18,000 positions 27 / 32 us, 37,000 47 / 33 (47 / 44), 73,000 82 / 41 (82 / 61), of one: 16,384 25 / 34, 32,768 44 / 39 (45 / 49);
 // (4,4,4) rank 64, 1-8: 18,000 89 / 62 (125 / 64), of one: 16,384 50 / 62, 32,768 95 / 70 (97 / 106); (2,2,4) rank 64: 8,192
 // 21 / 29, 16,384 38 / 32 (38 / 33); (2,2,4) rank 32: 73,000 27 / 30, 81,000 34 / 29 (35 / 37), 204,800 58 / 40 (61 / 58).
-constexpr int64_t FWD_ROWS_LEAST_L = 12288;     // the shortest of these limits: below it nothing else is looked at
+// Bags of eight and more on average, where a wave has a chain of positions, earlier still.  Bags of 0-20: (4,4,4) rank 32 16,384 positions
+// 36 / 32.5, 24,576 47 / 32; rank 64 8,192 89 / 51, (2,2,4) rank 64 8,192 47 / 28; (2,2,4) rank 32 49,152 24 / 25, 98,304 38 / 34: as it is.
+constexpr int64_t FWD_ROWS_LEAST_L = 8192;      // the shortest of these limits: below it nothing else is looked at
 int64_t fwd_rows_min_l(const Params &p, int64_t L, int64_t n_bags)
 {
+    if (L >= 8 * n_bags && (p.n1 == 4 || p.R1 >= 64)) return p.R1 >= 64 ? FWD_ROWS_LEAST_L : 16384;
     if (p.n1 == 2) return p.R1 >= 64 ? 14336 : 131072;
     if (L < 2 * n_bags) return 40960;
-    return p.R1 >= 64 ? FWD_ROWS_LEAST_L : 28672;
+    return p.R1 >= 64 ? 12288 : 28672;
 }
 
 int64_t tiles_min_l(const Params &p) { return p.n1 == 4 ? GROUP_MIN_L_TILES_444 : GROUP_MIN_L_TILES_224; }

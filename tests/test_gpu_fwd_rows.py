@@ -185,3 +185,17 @@ def test_pooling_of_short_bags(n, R, L, n_bags):
     d = _table("hot row", n, R, L, n_bags)
     b = d.batch
     assert_close(_run(d), ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha), "L %d n_bags %d" % (L, n_bags))
+
+
+# bags of eight and more: either side of the limits of their own
+@pytest.mark.parametrize("n,R,L", [((4, 4, 4), 32, 16_384), ((4, 4, 4), 64, 8192), ((2, 2, 4), 64, 8192)])
+def test_the_rule_for_long_bags(n, R, L):
+    for L, n_bags, pays in ((L - 1, L // 8 - 1, False), (L, L // 8, True), (L, L // 8 + 1, False)):
+        d = _table("hot row", n, R, L, n_bags, m=(200, 200, 50), alpha=False)
+        assert B.fwd_rows_pays(d.shape, L, n_bags) == pays
+        out = d.fwd()
+        assert_close(out, ora.fwd(d.oshape, d.cores, d.batch.indices, d.batch.offsets), str((n, R, L)))
+        old = B.set_fast_path(2)
+        wave = d.fwd()
+        B.set_fast_path(old)
+        assert np.array_equal(out, _run(d) if pays else wave)
