@@ -373,17 +373,32 @@ __device__ __forceinline__ bool rw_find_window(const Params &p, int win, const R
 // One window of one slice's positions (win of them, at most): see the file comment.  CACHED, here and below: streams without a
 // cache have kernels of their own, without what cached rows need (with it the step of 8,192 positions at rank 64, which has none,
 // took 91.8 us instead of 91.1: 0.4 us of grouping, 0.3 of the lists, which waited for wslice, 0.4 of rw_sum_kernel).
+//
+// All its LDS is dynamic: with 52 KB that the compiler knows of it takes six waves per SIMD to be the most there can be and claims as
+// many registers as six leave room for, 80 instead of 48, and then not one workgroup fits beside the tile kernel's at rank 64 (400 of 512
+// registers), so that the whole rest of the pre-pass waits for that kernel to end.  100 positions per bag, (2,2,4) rank 64: its 320 workgroups
+// started when the tile kernel was done, 62 us after they could; so 3 us after, and the step takes 194 us instead of 206.
+struct RwGroupLds {
+    static constexpr int NCH = RW_WIN / WAVE;
+    uint32_t h_row[RW_HASH];
+    int h_min[RW_HASH];
+    uint16_t h_cnt[NCH * 64];
+    uint64_t s_heads[NCH];
+    uint16_t u_at[RW_WIN], u_rank[RW_WIN], s_start[RW_WIN + 4];
+    int s_off[RW_OFF + 1], s_tmp[RW_NW], s_win[2];
+    int bins[1];                                                   // [m1 + m3] rows per slice (or [spb] u of a slot)
+};
+
 template <bool CACHED>
 __global__ __launch_bounds__(RW_T) void rw_group_kernel(Params p, int L, int win, const int64_t *__restrict__ offsets, int n_bags, RowsWs ws)
 {
-    constexpr int NCH = RW_WIN / WAVE, PER = RW_WIN / RW_T;
-    extern __shared__ int rw_bins[];                               // [m1 + m3] rows per slice (or [spb] u of a slot)
-    __shared__ __align__(16) uint32_t h_row[RW_HASH];
-    __shared__ __align__(16) int h_min[RW_HASH];
-    __shared__ __align__(16) uint16_t h_cnt[NCH * 64];
-    __shared__ uint16_t u_at[RW_WIN], u_rank[RW_WIN], s_start[RW_WIN + 1];
-    __shared__ uint64_t s_heads[NCH];
-    __shared__ int s_off[RW_OFF + 1], s_tmp[RW_NW], s_win[2];
+    constexpr int NCH = RwGroupLds::NCH, PER = RW_WIN / RW_T;
+    extern __shared__ __align__(16) char rw_group_lds[];
+    RwGroupLds &lds = *reinterpret_cast<RwGroupLds *>(rw_group_lds);
+    uint32_t *h_row = lds.h_row;
+    int *h_min = lds.h_min, *s_off = lds.s_off, *s_tmp = lds.s_tmp, *s_win = lds.s_win, *rw_bins = lds.bins;
+    uint16_t *h_cnt = lds.h_cnt, *u_at = lds.u_at, *u_rank = lds.u_rank, *s_start = lds.s_start;
+    uint64_t *s_heads = lds.s_heads;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6, m13 = p.m1 + p.m3;
     if (!rw_find_window(p, win, ws, s_tmp, s_win)) return;          // uniform
     const int ostep = (n_bags + RW_OFF - 1) / RW_OFF;
@@ -763,16 +778,19 @@ static inline hipError_t rw_prepare(const Params &p, const int64_t *indices, int
 {
     const int nw = rw_windows(p, L, cache.K), m13 = p.m1 + p.m3;
     const size_t lds = (size_t)m13 * 4 + (size_t)RW_NW * m13 * 2;              // at most 80 KB
-    static OncePerDevice once, once_cached;
+    static OncePerDevice once, once_cached, once_group, once_group_cached;
+    const auto group = cache.K ? rw_group_kernel<true> : rw_group_kernel<false>;
     const auto lists = cache.K ? rw_lists_kernel<true> : rw_lists_kernel<false>;
     hipError_t e = allow_dynamic_lds(cache.K ? once_cached : once, (const void *)lists, RW_MAX_M13 * 4 + RW_NW * RW_MAX_M13 * 2);
     if (e != hipSuccess) return e;
+    e = allow_dynamic_lds(cache.K ? once_group_cached : once_group, (const void *)group, sizeof(RwGroupLds) + RW_MAX_M13 * 4);
+    if (e != hipSuccess) return e;
     rw_place(p, indices, L, cache, rw_tile(L), ws, st);
-    // Dynamic LDS: the counters of the digits, as many as there are (with 1,200 slices two workgroups share a compute unit, with 450
+    // LDS: the counters of the digits, as many as there are (with 1,200 slices two workgroups share a compute unit, with 450
     // three; room for 4,096 of them, so that it is two for every table, makes no difference to the steps beside which they run:
     // 8,192 positions at rank 64 91.9 / 91.8 us, 60,000 at rank 32 134.1 / 134.2, of (2,2,4) 81.6 / 82.0, with a cache 80.8 / 81.1).
-    const size_t bins = (size_t)(m13 > ws.spb ? m13 : ws.spb) * 4;
-    hipLaunchKernelGGL(cache.K ? rw_group_kernel<true> : rw_group_kernel<false>, dim3(nw), dim3(RW_T), bins, st, p, L, rw_win(L), offsets, n_bags, ws);
+    const size_t bins = sizeof(RwGroupLds) + (size_t)(m13 > ws.spb ? m13 : ws.spb) * 4;
+    hipLaunchKernelGGL(group, dim3(nw), dim3(RW_T), bins, st, p, L, rw_win(L), offsets, n_bags, ws);
     if (nw > 512) hipLaunchKernelGGL(rw_scan_kernel<RW_SBINS_LONG>, dim3((m13 + RW_SBINS_LONG - 1) / RW_SBINS_LONG + 1), dim3(RW_T), 0, st, p, tp, ws);
     else hipLaunchKernelGGL(rw_scan_kernel<RW_SBINS>, dim3((m13 + RW_SBINS - 1) / RW_SBINS + 1), dim3(RW_T), 0, st, p, tp, ws);
     hipLaunchKernelGGL(lists, dim3(nw), dim3(RW_T), lds, st, p, rw_bits(p.m1), rw_bits(p.m3), ws);
