@@ -607,7 +607,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(BoCfg<C, ROW
 }
 
 // ---- the sums that finish the three cores -----------------------------------------------------------------------------
-// Workgroups [0, cwgs): gradients of cached rows; then, counted from there, [0, m1 + m3): the first piece (rw_piece rows) of a slice of the first (third) core; the next `extra`: what slices
+// Workgroups [0, cwgs): gradients of cached rows; then, counted from there, [0, m1 + m3): the first piece (rw_piece rows) of a slice of the third core, which take longest, or of the first; the next `extra`: what slices
 // have beyond that; the rest: the parts of the slices of the second core.  A slice of one piece (nearly all, where rows repeat:
 // equal rows are one) is finished on the spot; of a longer one every piece leaves a partial sum and the workgroup that arrives
 // last adds them, in their order.  How many extra pieces there are is only known on the device: as many workgroups are started
@@ -634,14 +634,16 @@ struct RsArgs {
 
 // CACHED: there is a cache; SHARE: lanes share the windows of its hot rows.
 template <typename C, bool CACHED, bool SHARE>
-__global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArgs a, const float *__restrict__ t0, const float *__restrict__ dym,
+__global__ __launch_bounds__(RW_T) __attribute__((amdgpu_waves_per_eu(4))) void rw_sum_kernel(Params p, RowsWs ws, RsArgs a, const float *__restrict__ t0, const float *__restrict__ dym,
                                                       const float *__restrict__ pbuf, const int2 *__restrict__ l13)
 {
     constexpr int N = C::N, R = C::R, NJ = C::N1 * C::N2, sA4 = C::sA / 4, sB4 = C::sB / 4;
     constexpr int WMAX = C::sA > C::sC ? C::sA : C::sC;
+    static_assert(N <= WAVE, "a lane per value of a row");
     static_assert(RW_PIECE == RW_T, "a list entry per thread");
     __shared__ __align__(16) float s_red[RW_T * 4];
     __shared__ int2 s_list[RW_PIECE];
+    __shared__ __align__(16) float s_dy[RW_NW][4 * N];
     __shared__ int s_tmp[RW_NW], s_at[3], s_last;
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), m13 = p.m1 + p.m3;
 
@@ -802,35 +804,44 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
                 }
             }
         } else {
-            // lane (h, b): rows jj = h NJ / H .. of T0 at column b against the upstream gradient, which is the same for the
-            // whole wave (scalar loads); the wave takes every RW_NW-th row of the slice
+            // lane (h, b): rows jj = h NJ / H .. of T0 at column b against the upstream gradient, which the wave fetches together with them
+            // and reads back from LDS, the same 16 bytes for all lanes of an h; the wave takes every RW_NW-th row of the slice.  (By scalar
+            // loads, which come one row at a time when T0 is there, and whose two halves every lane chose between: 164 registers, one workgroup
+            // per compute unit, 29 us of this kernel for 8,192 bags of 20 with a cache at (4,4,4) rank 32; so 97, two, 19.  20,000 positions, (2,2,4)
+            // rank 32, 6.7 / 5.1; 204,800 at rank 64 30 / 28.)
             constexpr int H = WAVE / R > 0 ? WAVE / R : 1, NJH = NJ / H, NF = NJH > 8 ? 2 : 4;
             const int h = H > 1 ? lane / R : 0, b = lane % R;
+            float *dyl = s_dy[w];
             for (int i = w; i < n; i += NF * RW_NW) {
                 float tv[NF][NJH];
-                int uu[NF];
+                float dv[NF];
 #pragma unroll
                 for (int q = 0; q < NF; ++q) {
                     const int2 e = s_list[min(i + q * RW_NW, n - 1)];
-                    uu[q] = __builtin_amdgcn_readfirstlane(e.x);
+                    const int uu = __builtin_amdgcn_readfirstlane(e.x);
+                    dv[q] = dym[(size_t)uu * N + min(lane, N - 1)];
                     const float *T = t0 + (size_t)__builtin_amdgcn_readfirstlane(e.y) * (NJ * R) + h * NJH * R + b;
 #pragma unroll
                     for (int j = 0; j < NJH; ++j) tv[q][j] = T[j * R];
                 }
 #pragma unroll
+                for (int q = 0; q < NF; ++q)
+                    if (lane < N) dyl[q * N + lane] = dv[q];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");        // (LDS of one wave is in order: only the compiler has to keep it)
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
                 for (int q = 0; q < NF; ++q) {
                     if (i + q * RW_NW < n) {                                  // uniform in the wave
-                    const float *dy = dym + (size_t)uu[q] * N;
 #pragma unroll
                     for (int j = 0; j < NJH; ++j) {
-                        float d[4];
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) d[x] = H > 1 && h ? dy[4 * (NJH + j) + x] : dy[4 * j + x];
-                        tot.x = fmaf(tv[q][j], d[0], tot.x); tot.y = fmaf(tv[q][j], d[1], tot.y);
-                        tot.z = fmaf(tv[q][j], d[2], tot.z); tot.w = fmaf(tv[q][j], d[3], tot.w);
+                        const float4 d = *reinterpret_cast<const float4 *>(dyl + q * N + 4 * (h * NJH + j));
+                        tot.x = fmaf(tv[q][j], d.x, tot.x); tot.y = fmaf(tv[q][j], d.y, tot.y);
+                        tot.z = fmaf(tv[q][j], d.z, tot.z); tot.w = fmaf(tv[q][j], d.w, tot.w);
                     }
                     }
                 }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                __builtin_amdgcn_wave_barrier();                              // the next rows take their place
             }
             if (H > 1) {
                 tot.x += __shfl_xor(tot.x, R); tot.y += __shfl_xor(tot.y, R); tot.z += __shfl_xor(tot.z, R); tot.w += __shfl_xor(tot.w, R);
@@ -893,7 +904,7 @@ __global__ __launch_bounds__(RW_T) void rw_sum_kernel(Params p, RowsWs ws, RsArg
     };
 
     if (wg < m13) {
-        const int bin = wg, i0 = ws.off13[bin], i1 = ws.off13[bin + 1];
+        const int bin = wg < p.m3 ? p.m1 + wg : wg - p.m3, i0 = ws.off13[bin], i1 = ws.off13[bin + 1];
         const float4 sum = add_up(bin, i0, min(i1, i0 + a.piece));
         if (i1 - i0 <= a.piece) finish(bin, sum, i1 == i0);
         else leave(bin, sum, bin, -1);
@@ -919,11 +930,14 @@ static inline int rw_tp(const Params &p) { return 128 / p.n1; }
 // workgroups of the tile kernel: what the compute units hold, and where one would get more tiles than it has room for as often that as
 // it takes (524 for the 512 that run at once, as 1,000,000 positions with a cache had it, and the kernel takes twice as long: step at
 // (4,4,4) rank 32, hardly a row repeated or cached, 2,800 us, with 1,024 2,460; (2,2,4) rank 64 2,233 / 1,757)
+// Below RW_SHARE_MIN_L positions at rank 32 three for two compute units: two workgroups leave a compute unit no registers for another
+// kernel's, one does, and the next batch's pre-pass, which the next step waits for, runs on those.  Step, two per unit / three for
+// two: 2,048 bags of 100, (2,2,4), 124 / 120 us; 8,192 of 20 with a cache, (4,4,4), 121 / 118; others as they were.
 static inline int rw_tile_wgs(const Params &p, int64_t L, int64_t K)
 {
-    const int n = (p.R1 >= 64 ? 1 : 2) * bo_compute_units();
+    const int cu = bo_compute_units(), n = (p.R1 >= 64 ? 1 : 2) * cu, few = p.R1 < 64 && L < RW_SHARE_MIN_L ? cu + cu / 2 : n;
     const int least = (rw_tiles(p, L, K, rw_tp(p)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
-    return n > least ? n : (least + n - 1) / n * n;
+    return few > least ? few : (least + n - 1) / n * n;
 }
 
 template <typename C, int ROWS_>
