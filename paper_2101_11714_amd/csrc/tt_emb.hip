@@ -343,11 +343,14 @@ static size_t rows_ws_bytes(const Params &p, int64_t L, int64_t K)
     return rw_supported(p) && rw_cache_supported(p, K) ? 256 + rw_ws_layout(nullptr, p, L, K, rw_tile_wgs(p, L, K)).bytes : 0;
 }
 // What the queries say for it, enough for every length up to L: nothing below the first length at which a step can group its
-// positions, and from RW_LONG_MIN_L on, where longer windows need fewer counters, not less than just below it.
+// positions, and where longer windows need fewer counters not less than just below the length at which they begin.
 static size_t rows_ws_query(const Params &p, int64_t L, int64_t K)
 {
     if (!rw_supported(p) || !rw_cache_supported(p, K) || !bwd_tiles_wanted(p, L) || (g_fast_path == 1 && L < group_min_l(p, K, true, true))) return 0;
-    return larger(rows_ws_bytes(p, L, K), L >= RW_LONG_MIN_L ? rows_ws_bytes(p, RW_LONG_MIN_L - 1, K) : 0);
+    size_t bytes = rows_ws_bytes(p, L, K);
+    for (int64_t step : {RW_LONG_MIN_L, RW_LONGEST_MIN_L})
+        if (L >= step) bytes = larger(bytes, rows_ws_bytes(p, step - 1, K));
+    return bytes;
 }
 
 size_t tt_emb_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows)

@@ -82,9 +82,12 @@ static inline bool rw_cache_supported(const Params &p, int64_t K) { return !K ||
 
 // Positions per window.  Longer windows merge more; shorter ones cut a hot row's positions into pieces that different
 // workgroups handle, which is what short streams need (8,192 positions, a hot row of 740: one workgroup added these up
-// for 13 us).
-constexpr int64_t RW_LONG_MIN_L = 65536;
-static inline int rw_win(int64_t L) { return L < RW_LONG_MIN_L ? 256 : RW_WIN; }
+// for 13 us).  Up to 262,143 positions half of the longest: a hot row's 2,000 positions are one workgroup's in the forward pass and
+// in the sums of the gradients, and that one is the last to finish; longer streams have enough other work and repeat more.  Step, windows of
+// 2,048 / 1,024 / 512: 204,800 positions (2,2,4) rank 64 192 / 188 / 204 us, rank 32 121 / 112 / 120; 82,000 in bags of 0-40
+// 146 / 128 / 123 and 100 / 94 / 95; uniform rows 417 / 417 / 420; rank 32, 300,000 147 / 139, uniform 233 / 238, 1,000,000 374 / 387.
+constexpr int64_t RW_LONG_MIN_L = 65536, RW_LONGEST_MIN_L = 262144;
+static inline int rw_win(int64_t L) { return L < RW_LONG_MIN_L ? 256 : L < RW_LONGEST_MIN_L ? RW_WIN / 2 : RW_WIN; }
 static inline int rw_windows_of(const Params &p, int64_t L, int win) { return (int)(L / win) + p.m2; }
 static inline int rw_windows(const Params &p, int64_t L, int64_t K)
 {

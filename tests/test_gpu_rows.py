@@ -95,7 +95,7 @@ def test_tables_at_the_limits(n, R, m, always_rows):
 
 @pytest.mark.parametrize("kind", ["hot row", "first digit"])
 def test_long_streams_with_long_windows(kind):
-    # 70,000 positions: windows of 2,048, by the library's own choice
+    # 70,000 positions: windows of 1,024, by the library's own choice
     _check(_table(kind, (2, 2, 4), 32, 70_000, 9_000, 62), "%s long" % kind)
 
 
@@ -130,8 +130,16 @@ def test_rank_64_by_choice(n, L):
 
 
 def test_one_workspace_on_either_side_of_the_longer_windows():
-    # 65,536 positions on: windows of 2,048 instead of 256, and fewer counters; a workspace for the longer batch does for the shorter
+    # 65,536 positions on: windows of 1,024 instead of 256, and fewer counters; a workspace for the longer batch does for the shorter
     a, b = _table("hot row", (2, 2, 4), 32, 65_536, 9_000, 64), _table("hot row", (2, 2, 4), 32, 65_535, 9_000, 65)
+    ws = torch.full((B.bwd_sgd_workspace_bytes(a.shape, a.L, a.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
+    for d in (a, b):
+        _check(d, "%d positions" % d.L, ws=ws)
+
+
+def test_one_workspace_on_either_side_of_the_longest_windows():
+    # 262,144 positions on: windows of 2,048 instead of 1,024
+    a, b = _table("hot row", (2, 2, 4), 32, 262_144, 30_000, 67), _table("hot row", (2, 2, 4), 32, 262_143, 30_000, 68)
     ws = torch.full((B.bwd_sgd_workspace_bytes(a.shape, a.L, a.n_bags, 0),), 0x7F, dtype=torch.uint8, device=dev())
     for d in (a, b):
         _check(d, "%d positions" % d.L, ws=ws)
