@@ -5,7 +5,7 @@
 //                           numbered, every position is told the number of its row
 //   rf_rows_kernel          tiles of distinct rows of one slice: T0 = A Bm (Eq. 3, first product) on the matrix cores, one j2
 //                           at a time, then the row itself (second product)
-//   rw_pool_kernel          (tt_rows_pass.h) a wave per bag adds the weighted rows of its positions, in their order
+//   rw_pool_kernel          (tt_rows_pass.h) a wave per bag, or a part of one, adds the weighted rows of its positions
 //
 // The number of a row decides where it is kept and which tile it is in, nothing else; results repeat bit for bit.
 // (One workgroup per slice that looks through all indices, in place of the first three launches: 6 against 14 us at 4,096

@@ -2,7 +2,7 @@
 //
 // Forward (two launches).  rw_fwd_kernel: a workgroup takes a tile of distinct rows of one slice of the second core and one
 // value of j2, computes their T0 = A Bm (Eq. 3, first product) on the matrix cores and their row from it, and copies T0 to
-// all their positions; rw_pool_kernel: a wave per bag adds the weighted rows of its positions, in their order.
+// all their positions; rw_pool_kernel: a wave per bag, or a part of one, adds the weighted rows of its positions.
 // Backward (three launches).  rw_merge_kernel: the upstream gradients of a distinct row added up over its positions;
 // rw_tile_kernel: Eq. 4's two large products over tiles of distinct rows,
 //     dG2[i2][a][(j2,b)] += sum_rows A[(e,j1)][a] dT0'[(e,j1)][(j2,b)],   P[(e,j1)][a] = sum_(j2,b) dT0'[(e,j1)][(j2,b)] Bm[a][(j2,b)],
@@ -178,19 +178,15 @@ __global__ __launch_bounds__(WG) void rw_fwd_kernel(Params p, const float *__res
     }
 }
 
-// out[bag] = sum over the bag's positions of alpha[k] rows[inv[k]], one wave per bag: the wave looks at up to 64 positions
-// at once, then lane (sub, f) adds float4 f of every (64 / (N/4))-th of them, four in flight.  With a cache (lines), the line
-// ~inv[k] where that is not negative.
-__global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
-                                                     const int64_t *__restrict__ offsets, int n_bags, const float *__restrict__ alpha,
-                                                     float *__restrict__ out)
+// The sum over positions [k0, k1) of alpha[k] rows[inv[k]] by a wave (k0 and k1 the same for all its lanes): it looks at up to 64 positions
+// at once, then lane (sub, f) adds float4 f of every (64 / (N/4))-th of them, four in flight; every sub ends with the sum.  With a cache
+// (lines), the line ~inv[k] where that is not negative.
+__device__ __forceinline__ float4 rw_pool_wave(int N, const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
+                                               const float *__restrict__ alpha, int k0, int k1)
 {
     const int lane = threadIdx.x & 63;
-    const int bag = blockIdx.x * NWAVE + (threadIdx.x >> 6);
-    if (bag >= n_bags) return;
     const int nq = N / 4, per = WAVE / nq;                                    // N a power of two <= 256
     const int f = lane % nq, sub = lane / nq;
-    const int k0 = offsets ? (int)offsets[bag] : bag, k1 = offsets ? (int)offsets[bag + 1] : bag + 1;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int kc = k0; kc < k1; kc += WAVE) {
         const int cnt = min(WAVE, k1 - kc), pc = kc + min(lane, cnt - 1);
@@ -219,11 +215,25 @@ __global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restr
         acc.x += __shfl_xor(acc.x, d); acc.y += __shfl_xor(acc.y, d);
         acc.z += __shfl_xor(acc.z, d); acc.w += __shfl_xor(acc.w, d);
     }
-    if (sub == 0) *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * f) = acc;
+    return acc;
+}
+
+// out[bag] = sum over the bag's positions of alpha[k] rows[inv[k]], one wave per bag
+__global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
+                                                     const int64_t *__restrict__ offsets, int n_bags, const float *__restrict__ alpha,
+                                                     float *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    const int bag = blockIdx.x * NWAVE + (threadIdx.x >> 6);
+    if (bag >= n_bags) return;                                                // uniform in the wave
+    const int k0 = offsets ? (int)offsets[bag] : bag, k1 = offsets ? (int)offsets[bag + 1] : bag + 1;
+    const float4 acc = rw_pool_wave(N, rows, inv, lines, alpha, k0, k1);
+    if (lane < N / 4) *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * lane) = acc;
 }
 
 // The same for short bags, fewer than RW_POOL_SHORT positions on average: N / 4 lanes per bag, its positions one after the other, four in
-// flight, so that a wave has several bags and few of its lanes idle.  A forward pass, a wave per bag / this: (4,4,4) rank 32, 45,000 bags of one
+// flight, so that a wave has several bags and few of its lanes idle; a bag of more than WAVE positions among them is the whole wave's.
+// A forward pass, a wave per bag / this: (4,4,4) rank 32, 45,000 bags of one
 // 44 / 35 us, 16,384 of 1-8 41.6 / 39.6; (2,2,4) rank 32, 32,768 of 1-8 44 / 36; bags of 0-20, 10 on average, 40.6 / 42.7, rank 64 29 / 33.
 constexpr int RW_POOL_SHORT = 6;
 __global__ __launch_bounds__(WG) void rw_pool_short_kernel(int N, const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
@@ -231,12 +241,13 @@ __global__ __launch_bounds__(WG) void rw_pool_short_kernel(int N, const float *_
                                                            float *__restrict__ out)
 {
     constexpr int NF = 4;
-    const int nq = N / 4, f = threadIdx.x % nq;
+    const int nq = N / 4, f = threadIdx.x % nq, lane = threadIdx.x & 63;
     const int64_t bag = (int64_t)blockIdx.x * (WG / nq) + threadIdx.x / nq;
-    if (bag >= n_bags) return;
-    const int k0 = offsets ? (int)offsets[bag] : (int)bag, k1 = offsets ? (int)offsets[bag + 1] : (int)bag + 1;
+    const bool on = bag < n_bags;
+    const int k0 = !on ? 0 : offsets ? (int)offsets[bag] : (int)bag, k1 = !on ? 0 : offsets ? (int)offsets[bag + 1] : (int)bag + 1;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k = k0; k < k1; k += NF) {
+    const bool wide = k1 - k0 > WAVE;
+    for (int k = k0; k < k1 && !wide; k += NF) {
         int u[NF];
         float wgt[NF];
         float4 x[NF];
@@ -256,7 +267,14 @@ __global__ __launch_bounds__(WG) void rw_pool_short_kernel(int N, const float *_
                 acc.z = fmaf(wgt[q], x[q].z, acc.z); acc.w = fmaf(wgt[q], x[q].w, acc.w);
             }
     }
-    *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * f) = acc;
+    uint64_t left = __ballot(wide && f == 0);
+    while (left) {                                                            // uniform
+        const int j = __builtin_ctzll(left);
+        left &= left - 1;
+        const float4 sum = rw_pool_wave(N, rows, inv, lines, alpha, __builtin_amdgcn_readlane(k0, j), __builtin_amdgcn_readlane(k1, j));
+        if (lane / nq == j / nq) acc = sum;
+    }
+    if (on) *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * f) = acc;
 }
 
 static inline void rw_pool(int N, const float *rows, const int *inv, const float *lines, const int64_t *off, int n_bags, int64_t L, const float *alpha,

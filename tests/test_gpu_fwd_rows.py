@@ -187,6 +187,18 @@ def test_pooling_of_short_bags(n, R, L, n_bags):
     assert_close(_run(d), ora.fwd(d.oshape, d.cores, b.indices, b.offsets, alpha=b.alpha), "L %d n_bags %d" % (L, n_bags))
 
 
+# one bag of nearly everything among empty ones and bags of 64 and 65: a whole wave's, a part's, a whole wave's
+@pytest.mark.parametrize("n,R", [((2, 2, 4), 32), ((4, 4, 4), 32)])
+def test_pooling_of_a_long_bag_among_short_ones(n, R):
+    lens = np.zeros(1500, np.int64)
+    lens[[3, 4, 5, 700, 1499]] = [64, 65, 1, 5000, 66]
+    d = _table("hot row", n, R, int(lens.sum()), lens.size)
+    off = np.concatenate([[0], lens.cumsum()])
+    d.off, d.batch = torch.from_numpy(off).to(dev()), W.Batch(d.batch.indices, off, d.batch.grad_output, d.batch.alpha)
+    assert d.L < 6 * lens.size
+    assert_close(_run(d), ora.fwd(d.oshape, d.cores, d.batch.indices, off, alpha=d.batch.alpha), "long bag")
+
+
 # bags of eight and more: either side of the limits of their own
 @pytest.mark.parametrize("n,R,L", [((4, 4, 4), 32, 16_384), ((4, 4, 4), 64, 8192), ((2, 2, 4), 64, 8192)])
 def test_the_rule_for_long_bags(n, R, L):
