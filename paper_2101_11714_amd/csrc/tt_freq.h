@@ -93,7 +93,8 @@ __global__ __launch_bounds__(FQ_NT) void freq_update_chunk_kernel(FreqDev f, con
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
-        if (base + q * FQ_NT + t >= end) continue;
+        // (-1, a free entry's key, is no row: as one it would leave its count in a free entry, for whichever row comes there)
+        if (base + q * FQ_NT + t >= end || row[q] == 0xFFFFFFFFu) continue;
         uint32_t h = cache_hash(row[q], FQ_T - 1);
         for (;;) {                                                 // ends: at most FQ_CHUNK rows in 2 FQ_CHUNK entries
             const uint32_t old = atomicCAS(&lkey[h], 0xFFFFFFFFu, row[q]);

@@ -37,3 +37,22 @@ def test_long_streams(L, rows, capacity):
         assert stats[1] == 0 and {int(a): int(b) for a, b in zip(r, c)} == true
     else:
         assert all(1 <= b <= true[int(a)] for a, b in zip(r, c))
+
+
+def test_padding_of_a_long_stream_is_in_no_rows_count():
+    # -1 is no row (and, as a key, the counting kernel's mark of a free entry): every chunk has some before, between and after its rows
+    rng = np.random.default_rng(5)
+    idx = rng.integers(0, 900, 20_001).astype(np.int64)
+    idx[rng.random(idx.size) < 0.3] = -1
+    idx[:50] = -1
+    freq = B.Freq(1 << 12, dev())
+    B.tt_freq_reset(freq)
+    B.tt_freq_update(freq, torch.from_numpy(idx).to(dev()))
+    got_r, got_c = (torch.empty(freq.capacity, dtype=torch.int64, device=dev()) for _ in range(2))
+    n_out = torch.zeros(1, dtype=torch.int64, device=dev())
+    B.tt_freq_export(freq, got_r, got_c, n_out)
+    n, stats = int(n_out.item()), freq.stats.cpu().numpy()
+    order = np.argsort(got_r[:n].cpu().numpy())
+    rows, counts = np.unique(idx[idx >= 0], return_counts=True)
+    assert np.array_equal(got_r[:n].cpu().numpy()[order], rows) and np.array_equal(got_c[:n].cpu().numpy()[order], counts)
+    assert stats[0] == rows.size and stats[1] == 0
