@@ -948,14 +948,16 @@ static inline int rw_tp(const Params &p) { return 128 / p.n1; }
 // workgroups of the tile kernel: what the compute units hold, and where one would get more tiles than it has room for as often that as
 // it takes (524 for the 512 that run at once, as 1,000,000 positions with a cache had it, and the kernel takes twice as long: step at
 // (4,4,4) rank 32, hardly a row repeated or cached, 2,800 us, with 1,024 2,460; (2,2,4) rank 64 2,233 / 1,757)
-// Below RW_SHARE_MIN_L positions at rank 32 three for two compute units: two workgroups leave a compute unit no registers for another
-// kernel's, one does, and the next batch's pre-pass, which the next step waits for, runs on those.  Step, two per unit / three for
-// two: 2,048 bags of 100, (2,2,4), 124 / 120 us; 8,192 of 20 with a cache, (4,4,4), 121 / 118; others as they were.
+// As many whether a pre-pass runs beside it or not: one call and the two calls of a step have the same sums.  Three for two units below
+// 262,144 positions at rank 32, which leave registers for the next batch's pre-pass, against two for one: in two calls on two streams
+// 2,048 bags of 100, (2,2,4), 112.7 / 116.1 us, 8,192 of 20, (4,4,4), with a cache 117.5 / 121.6, without 211.5 / 204.9; in two calls on one
+// stream 134.2 / 128.4, 144.1 / 135.0, 234.0 / 226.5; one call 163.3 / 157.6, 166.3 / 156.4, 336 / 326; 60,000 positions, (4,4,4),
+// 113.4 / 115.9, 134.9 / 126.0, 168.8 / 159.8.
 static inline int rw_tile_wgs(const Params &p, int64_t L, int64_t K)
 {
-    const int cu = bo_compute_units(), n = (p.R1 >= 64 ? 1 : 2) * cu, few = p.R1 < 64 && L < RW_SHARE_MIN_L ? cu + cu / 2 : n;
+    const int n = (p.R1 >= 64 ? 1 : 2) * bo_compute_units();
     const int least = (rw_tiles(p, L, K, rw_tp(p)) + BO_MAX_CHUNK - 1) / BO_MAX_CHUNK;
-    return few > least ? few : (least + n - 1) / n * n;
+    return n > least ? n : (least + n - 1) / n * n;
 }
 
 template <typename C, int ROWS_>

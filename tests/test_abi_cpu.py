@@ -331,3 +331,10 @@ def test_workspace_holds_nothing_that_no_call_uses():
     # which such a call never takes)
     assert _queries((200, 220, 250), (2, 2, 4), 32, 2048, 0)[1] < 3e6
     assert _queries((200, 200, 1000), (4, 4, 4), 64, 65_535, 0)[1] < 140e6
+
+
+def test_the_parts_of_the_second_core_have_as_much_room_below_long_streams():
+    # one more position is one more position: the tile kernel has as many workgroups, each with room for its part, for the shorter stream
+    for m, n, r in [((200, 220, 250), (2, 2, 4), 32), ((200, 200, 1000), (4, 4, 4), 32), ((200, 200, 1000), (4, 4, 4), 64)]:
+        short, long = _queries(m, n, r, 262_143, 1000)[1], _queries(m, n, r, 262_144, 1000)[1]
+        assert 0 <= long - short < 32_768, (m, n, r, short, long)
