@@ -255,7 +255,7 @@ static inline hipError_t launch_rows_fwd(const Params &p, const float *G1, const
     rw_place(p, indices, (int)L, none, rf_tile(L), ws, st);
     hipLaunchKernelGGL(rf_group_kernel, dim3(nw), dim3(RW_T), 0, st, p, ws);
     hipLaunchKernelGGL(rf_rows_kernel<C>, dim3(nw * F::PARTS), dim3(F::NW * WAVE), F::LDS, st, p, G1, G2, G3, (int)L, ws);
-    rw_pool(C::N, ws.rows, ws.inv, nullptr, off, n_bags, L, alpha, out, st);
+    rw_pool<C::N>(ws.rows, ws.inv, nullptr, off, n_bags, L, alpha, out, st);
     return hipGetLastError();
 }
 

@@ -231,57 +231,96 @@ __global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restr
     if (lane < N / 4) *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * lane) = acc;
 }
 
-// The same for short bags, fewer than RW_POOL_SHORT positions on average: N / 4 lanes per bag, its positions one after the other, four in
-// flight, so that a wave has several bags and few of its lanes idle; a bag of more than WAVE positions among them is the whole wave's.
-// A forward pass, a wave per bag / this: (4,4,4) rank 32, 45,000 bags of one
-// 44 / 35 us, 16,384 of 1-8 41.6 / 39.6; (2,2,4) rank 32, 32,768 of 1-8 44 / 36; bags of 0-20, 10 on average, 40.6 / 42.7, rank 64 29 / 33.
-constexpr int RW_POOL_SHORT = 6;
-__global__ __launch_bounds__(WG) void rw_pool_short_kernel(int N, const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
+// The same for short bags, fewer than RW_POOL_SHORT positions on average: LANES lanes per bag, so that a wave has several bags and few of
+// its lanes idle.  A bag's sums are those of rw_pool_wave, in its order, so that its result does not depend on the other bags: sum s of the
+// PER = WAVE / (N / 4) is of positions s, s + PER, ..., and they are added in pairs.  Four times as many sums as lanes have a float4: a lane has
+// four of them.  Fewer lanes (PAIRS): a bag has at most one position for every sum, and four of them are added as soon as they are there.
+// A bag of more than MOST positions is the whole wave's.
+// A forward pass, a wave per bag / this: (4,4,4) rank 32, 16,384 bags of 1-8 39.6 / 36.9 us, of none or 20 38.0 / 38.0, of none or 40 37.4 / 39.5, by a
+// Pareto law up to 64 39.0 / 39.5; (2,2,4) rank 32, 32,768 of 1-8 43.1 / 35.0, of none or 20 39.0 / 35.4, 196,608 of one 95 / 39.7 (16 lanes
+// 50.6), 65,536 by a Pareto law up to 64 58.4 / 45.3.  Beyond six on average: (4,4,4) 8,192 of 0-20 43.0 / 43.8, rank 64 4,096 64.2 / 65.4; (2,2,4),
+// where it is ahead still, 16,384 of 0-20 40.5 / 38.0.
+constexpr int RW_POOL_SHORT = 6, RW_POOL_SHORTEST = 2, RW_POOL_LANES = 16, RW_POOL_MOST = 32;
+template <int N, int LANES, int MOST>
+__global__ __launch_bounds__(WG) void rw_pool_short_kernel(const float *__restrict__ rows, const int *__restrict__ inv, const float *__restrict__ lines,
                                                            const int64_t *__restrict__ offsets, int n_bags, const float *__restrict__ alpha,
                                                            float *__restrict__ out)
 {
-    constexpr int NF = 4;
-    const int nq = N / 4, f = threadIdx.x % nq, lane = threadIdx.x & 63;
-    const int64_t bag = (int64_t)blockIdx.x * (WG / nq) + threadIdx.x / nq;
+    constexpr int NQ = N / 4, PER = WAVE / NQ, BAGS = WAVE / LANES, SUBS = LANES / NQ, NA = 4;
+    constexpr bool PAIRS = NA * SUBS < PER;
+    constexpr int NF = SUBS == 1 && !PAIRS ? 2 * NA : NA;                     // rows in flight
+    static_assert(PAIRS ? LANES == NA && PER == 4 * NA && MOST <= PER : NA * SUBS == PER, "the sums of rw_pool_wave");
+    const int lane = threadIdx.x & 63, l = lane % LANES, f = lane % NQ, sub = l / NQ;
+    const int wave = blockIdx.x * NWAVE + (threadIdx.x >> 6), waves = (int)(((int64_t)n_bags + BAGS - 1) / BAGS);
+    if (wave >= waves) return;                                                // uniform in the wave
+    const int64_t bag = (int64_t)wave * BAGS + lane / LANES;
     const bool on = bag < n_bags;
     const int k0 = !on ? 0 : offsets ? (int)offsets[bag] : (int)bag, k1 = !on ? 0 : offsets ? (int)offsets[bag + 1] : (int)bag + 1;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    const bool wide = k1 - k0 > WAVE;
-    for (int k = k0; k < k1 && !wide; k += NF) {
-        int u[NF];
-        float wgt[NF];
-        float4 x[NF];
+    const bool wide = k1 - k0 > MOST;
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [](const float4 &x, const float4 &y) { return make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w); };
+    float4 acc[NA], half[2] = {zero, zero};
 #pragma unroll
-        for (int q = 0; q < NF; ++q) {
-            const int at = min(k + q, k1 - 1);
-            u[q] = inv[at];
-            wgt[q] = alpha ? alpha[at] : 1.f;
-        }
+    for (int q = 0; q < NA; ++q) acc[q] = zero;
+    for (int kc = k0; kc < k1 && !wide; kc += LANES) {                        // (all lanes of a bag go the same way)
+        const int cnt = min(LANES, k1 - kc), pc = kc + min(l, cnt - 1);
+        const int myu = inv[pc];
+        const float myw = alpha ? alpha[pc] : 1.f;
+        for (int qb = 0; qb < cnt; qb += NF * SUBS) {
+            const int q0 = qb + NF * sub;
+            float wgt[NF];
+            float4 x[NF];
 #pragma unroll
-        for (int q = 0; q < NF; ++q)
-            x[q] = *reinterpret_cast<const float4 *>((lines && u[q] < 0 ? lines + (size_t)~u[q] * N : rows + (size_t)u[q] * N) + 4 * f);
-#pragma unroll
-        for (int q = 0; q < NF; ++q)
-            if (k + q < k1) {
-                acc.x = fmaf(wgt[q], x[q].x, acc.x); acc.y = fmaf(wgt[q], x[q].y, acc.y);
-                acc.z = fmaf(wgt[q], x[q].z, acc.z); acc.w = fmaf(wgt[q], x[q].w, acc.w);
+            for (int q = 0; q < NF; ++q) {
+                const int pi = lane - l + min(q0 + q, cnt - 1), u = __shfl(myu, pi);
+                wgt[q] = __shfl(myw, pi);
+                x[q] = *reinterpret_cast<const float4 *>((lines && u < 0 ? lines + (size_t)~u * N : rows + (size_t)u * N) + 4 * f);
             }
+#pragma unroll
+            for (int q = 0; q < NF; ++q)
+                if (q0 + q < cnt) {
+                    float4 &to = acc[q % NA];
+                    to.x = fmaf(wgt[q], x[q].x, to.x); to.y = fmaf(wgt[q], x[q].y, to.y);
+                    to.z = fmaf(wgt[q], x[q].z, to.z); to.w = fmaf(wgt[q], x[q].w, to.w);
+                }
+        }
+        if constexpr (PAIRS) {
+            const float4 four = add(add(acc[0], acc[1]), add(acc[2], acc[3]));
+            if (kc - k0 < PER / 2) half[0] = add(half[0], four);
+            else half[1] = add(half[1], four);
+#pragma unroll
+            for (int q = 0; q < NA; ++q) acc[q] = zero;
+        }
     }
-    uint64_t left = __ballot(wide && f == 0);
+    float4 sum = PAIRS ? add(half[0], half[1]) : add(add(acc[0], acc[1]), add(acc[2], acc[3]));
+#pragma unroll
+    for (int d = NQ; d < LANES; d <<= 1) {
+        sum.x += __shfl_xor(sum.x, d); sum.y += __shfl_xor(sum.y, d);
+        sum.z += __shfl_xor(sum.z, d); sum.w += __shfl_xor(sum.w, d);
+    }
+    uint64_t left = __ballot(wide && l == 0);
     while (left) {                                                            // uniform
         const int j = __builtin_ctzll(left);
         left &= left - 1;
-        const float4 sum = rw_pool_wave(N, rows, inv, lines, alpha, __builtin_amdgcn_readlane(k0, j), __builtin_amdgcn_readlane(k1, j));
-        if (lane / nq == j / nq) acc = sum;
+        const float4 all = rw_pool_wave(N, rows, inv, lines, alpha, __builtin_amdgcn_readlane(k0, j), __builtin_amdgcn_readlane(k1, j));
+        if (lane / LANES == j / LANES) sum = all;
     }
-    if (on) *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * f) = acc;
+    if (on && sub == 0) *reinterpret_cast<float4 *>(out + (size_t)bag * N + 4 * f) = sum;
 }
 
-static inline void rw_pool(int N, const float *rows, const int *inv, const float *lines, const int64_t *off, int n_bags, int64_t L, const float *alpha,
+template <int N>
+static inline void rw_pool(const float *rows, const int *inv, const float *lines, const int64_t *off, int n_bags, int64_t L, const float *alpha,
                            float *out, hipStream_t st)
 {
+    constexpr int LANES = RW_POOL_LANES;
+    auto grid = [&](int lanes) { return dim3((unsigned)(((int64_t)n_bags * lanes + WG - 1) / WG)); };
+    if constexpr (N / 4 < LANES)
+        if (L < (int64_t)RW_POOL_SHORTEST * n_bags) {
+            hipLaunchKernelGGL((rw_pool_short_kernel<N, N / 4, WAVE / (N / 4)>), grid(N / 4), dim3(WG), 0, st, rows, inv, lines, off, n_bags, alpha, out);
+            return;
+        }
     if (L < (int64_t)RW_POOL_SHORT * n_bags)
-        hipLaunchKernelGGL(rw_pool_short_kernel, dim3((unsigned)(((int64_t)n_bags * (N / 4) + WG - 1) / WG)), dim3(WG), 0, st, N, rows, inv, lines, off, n_bags, alpha, out);
+        hipLaunchKernelGGL((rw_pool_short_kernel<N, LANES, RW_POOL_MOST>), grid(LANES), dim3(WG), 0, st, rows, inv, lines, off, n_bags, alpha, out);
     else
         hipLaunchKernelGGL(rw_pool_kernel, dim3((n_bags + NWAVE - 1) / NWAVE), dim3(WG), 0, st, N, rows, inv, lines, off, n_bags, alpha, out);
 }
@@ -972,7 +1011,7 @@ static inline hipError_t launch_rw_fwd(const Params &p, const float *G1, const f
     const int tiles = rw_tiles(p, L, cache.K, ROWS_ / C::N1), started = tiles < 2048 ? tiles : 2048;
     hipLaunchKernelGGL((rw_fwd_kernel<C, ROWS_>), dim3(started * C::N2), dim3(WG), lds, st, p, G1, G2, G3, (int)L, ws.rec, ws.gkb, ws.gu,
                        ws.tiles, ws.tile_base, ws.rows, t0);
-    rw_pool(C::N, ws.rows, ws.inv, cache.K ? cache.rows : (const float *)nullptr, off, n_bags, L, alpha, out, st);
+    rw_pool<C::N>(ws.rows, ws.inv, cache.K ? cache.rows : (const float *)nullptr, off, n_bags, L, alpha, out, st);
     return hipGetLastError();
 }
 

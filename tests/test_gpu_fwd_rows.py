@@ -199,6 +199,24 @@ def test_pooling_of_a_long_bag_among_short_ones(n, R):
     assert_close(_run(d), ora.fwd(d.oshape, d.cores, d.batch.indices, off, alpha=d.batch.alpha), "long bag")
 
 
+# the same bags in a batch of long ones, of short ones and of hardly any: the same bits, whichever kernel pools them
+@pytest.mark.parametrize("n,R", [((2, 2, 4), 32), ((4, 4, 4), 32)])
+def test_a_bag_does_not_depend_on_the_length_of_the_others(n, R):
+    lens = np.array([*range(41), 63, 64, 65, 66, 100, 131])
+    d = _table("hot row", n, R, int(lens.sum()), lens.size)
+    ref = None
+    for empty in (0, 400, 1200):                             # on average 28, 2.9 and 1.05 positions
+        at = np.sort(np.random.default_rng(empty).choice(lens.size + empty, lens.size, replace=False))
+        every = np.zeros(lens.size + empty, np.int64)
+        every[at] = lens
+        off = np.concatenate([[0], every.cumsum()])
+        d.off, d.n_bags, d.batch = torch.from_numpy(off).to(dev()), every.size, W.Batch(d.batch.indices, off, d.batch.grad_output, d.batch.alpha)
+        out = _run(d)
+        ref = out if ref is None else ref
+        assert np.array_equal(out[at], ref) and not out[every == 0].any()
+    assert_close(out, ora.fwd(d.oshape, d.cores, d.batch.indices, off, alpha=d.batch.alpha), str(n))
+
+
 # bags of eight and more: either side of the limits of their own
 @pytest.mark.parametrize("n,R,L", [((4, 4, 4), 32, 16_384), ((4, 4, 4), 64, 8192), ((2, 2, 4), 64, 8192)])
 def test_the_rule_for_long_bags(n, R, L):
