@@ -236,9 +236,12 @@ __global__ __launch_bounds__(WG) void rw_pool_kernel(int N, const float *__restr
 // PER = WAVE / (N / 4) is of positions s, s + PER, ..., and they are added in pairs.  Four times as many sums as lanes have a float4: a lane has
 // four of them.  Fewer lanes (PAIRS): a bag has at most one position for every sum, and four of them are added as soon as they are there.
 // A bag of more than MOST positions is the whole wave's.
-// A forward pass, a wave per bag / this: (4,4,4) rank 32, 16,384 bags of 1-8 39.6 / 36.9 us, of none or 20 38.0 / 38.0, of none or 40 37.4 / 39.5, by a
-// Pareto law up to 64 39.0 / 39.5; (2,2,4) rank 32, 32,768 of 1-8 43.1 / 35.0, of none or 20 39.0 / 35.4, 196,608 of one 95 / 39.7 (16 lanes
-// 50.6), 65,536 by a Pareto law up to 64 58.4 / 45.3.  Beyond six on average: (4,4,4) 8,192 of 0-20 43.0 / 43.8, rank 64 4,096 64.2 / 65.4; (2,2,4),
+// Neighbouring bags are in different waves: batches come sorted by length, and a wave adds up its long bags one after the other.  A wave per
+// bag / neighbours in a wave / this: 16,384 bags sorted by length, Pareto law up to 500, (4,4,4) 66.5 / 126.5 / 65.0 us, 32,768 of (2,2,4)
+// 52.4 / 67.4 / 45.5, 16 of 1,000 positions side by side among 98,288 of one 69 / 276 / 52; where no long ones meet 0 to 2 us more than neighbours.
+// A forward pass, a wave per bag / this: (4,4,4) rank 32, 16,384 bags of 1-8 39.6 / 37.0 us, of none or 20 38.0 / 38.1, of none or 40 37.4 / 39.5, by a
+// Pareto law up to 64 39.0 / 39.8; (2,2,4) rank 32, 32,768 of 1-8 43.1 / 35.3, of none or 20 39.0 / 35.4, 196,608 of one 95 / 41.8 (16 lanes
+// 50.6), 65,536 by a Pareto law up to 64 58.4 / 45.9.  Beyond six on average: (4,4,4) 8,192 of 0-20 43.0 / 43.8, rank 64 4,096 64.2 / 65.4; (2,2,4),
 // where it is ahead still, 16,384 of 0-20 40.5 / 38.0.
 constexpr int RW_POOL_SHORT = 6, RW_POOL_SHORTEST = 2, RW_POOL_LANES = 16, RW_POOL_MOST = 32;
 template <int N, int LANES, int MOST>
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(WG) void rw_pool_short_kernel(const float *__restri
     const int lane = threadIdx.x & 63, l = lane % LANES, f = lane % NQ, sub = l / NQ;
     const int wave = blockIdx.x * NWAVE + (threadIdx.x >> 6), waves = (int)(((int64_t)n_bags + BAGS - 1) / BAGS);
     if (wave >= waves) return;                                                // uniform in the wave
-    const int64_t bag = (int64_t)wave * BAGS + lane / LANES;
+    const int64_t bag = (int64_t)(lane / LANES) * waves + wave;
     const bool on = bag < n_bags;
     const int k0 = !on ? 0 : offsets ? (int)offsets[bag] : (int)bag, k1 = !on ? 0 : offsets ? (int)offsets[bag + 1] : (int)bag + 1;
     const bool wide = k1 - k0 > MOST;

@@ -199,6 +199,21 @@ def test_pooling_of_a_long_bag_among_short_ones(n, R):
     assert_close(_run(d), ora.fwd(d.oshape, d.cores, d.batch.indices, off, alpha=d.batch.alpha), "long bag")
 
 
+# long bags side by side among bags of one: shared out over waves, whose bags are as many as there are waves apart (the last wave has fewer)
+@pytest.mark.parametrize("n,R", [((2, 2, 4), 32), ((4, 4, 4), 32)])
+@pytest.mark.parametrize("n_bags,long", [(1001, 40), (1500, 200), (16, 33), (3, 64)])
+def test_pooling_of_long_bags_side_by_side(n, R, n_bags, long):
+    lens = np.ones(n_bags, np.int64)
+    lens[n_bags // 3:n_bags // 3 + 16] = long
+    empty = max(0, int(lens.sum()) // 5 - n_bags + 1)        # as many empty ones as make the batch a short one
+    lens = np.concatenate([lens, np.zeros(empty, np.int64)])
+    d = _table("hot row", n, R, int(lens.sum()), lens.size)
+    off = np.concatenate([[0], lens.cumsum()])
+    d.off, d.batch = torch.from_numpy(off).to(dev()), W.Batch(d.batch.indices, off, d.batch.grad_output, d.batch.alpha)
+    assert d.L < 6 * lens.size
+    assert_close(_run(d), ora.fwd(d.oshape, d.cores, d.batch.indices, off, alpha=d.batch.alpha), "%d bags" % n_bags)
+
+
 # the same bags in a batch of long ones, of short ones and of hardly any: the same bits, whichever kernel pools them
 @pytest.mark.parametrize("n,R", [((2, 2, 4), 32), ((4, 4, 4), 32)])
 def test_a_bag_does_not_depend_on_the_length_of_the_others(n, R):
