@@ -86,12 +86,16 @@ constexpr int64_t ROWS_FWD_MIN_L_444 = 10240, ROWS_FWD_MIN_L_224 = GROUP_MIN_L_R
 // 1-8: 18,000 positions 27 / 32 us, 37,000 47 / 33 (47 / 44), 73,000 82 / 41 (82 / 61), of one: 16,384 25 / 34, 32,768 44 / 39 (45 / 49);
 // (4,4,4) rank 64, 1-8: 18,000 89 / 62 (125 / 64), of one: 16,384 50 / 62, 32,768 95 / 70 (97 / 106); (2,2,4) rank 64: 8,192
 // 21 / 29, 16,384 38 / 32 (38 / 33); (2,2,4) rank 32: 73,000 27 / 30, 81,000 34 / 29 (35 / 37), 204,800 58 / 40 (61 / 58).
-// Bags of eight and more on average, where a wave has a chain of positions, earlier still.  Bags of 0-20: (4,4,4) rank 32 16,384 positions
-// 36 / 32.5, 24,576 47 / 32; rank 64 8,192 89 / 51, (2,2,4) rank 64 8,192 47 / 28; (2,2,4) rank 32 49,152 24 / 25, 98,304 38 / 34: as it is.
+// At rank 64 earlier still for bags of eight and more on average, where a wave has a chain of positions.  Zipf-distributed and (uniform) rows,
+// bags of one length, as many as run at once being the wave per bag's best case: (4,4,4) 8,192 positions in eights 48 / 44 (56 / 59), 9,216 in
+// nines 52.5 / 51 (62 / 60), 10,240 in eights 60 / 51 (71 / 60), 8,192 in tens 56 / 44 (64 / 59), of 0-20 89 / 44.5 (92.5 / 60); (2,2,4) 8,192 in
+// eights 23.5 / 28 (24.5 / 29), 9,216 in nines 26 / 28 (27 / 29), 10,240 in tens 28.4 / 28.2 (29.7 / 29.4), 8,800 in eights 34 / 28, 8,192 of 0-20
+// 44 / 28 (48 / 29).  Not at rank 32: (4,4,4), of 0-20, 16,384 positions 36 / 32, 24,576 48 / 32, but in eights 19.5 / 32 and 27 / 31 (27 / 35),
+// in pieces of 32 19.5 / 32 and 27 / 32, and the host knows no lengths; (2,2,4), of 0-20, 49,152 24 / 25, 98,304 38 / 34.
 constexpr int64_t FWD_ROWS_LEAST_L = 8192;      // the shortest of these limits: below it nothing else is looked at
 int64_t fwd_rows_min_l(const Params &p, int64_t L, int64_t n_bags)
 {
-    if (L >= 8 * n_bags && (p.n1 == 4 || p.R1 >= 64)) return p.R1 >= 64 ? FWD_ROWS_LEAST_L : 16384;
+    if (p.R1 >= 64 && L >= 8 * n_bags) return L >= 10 * n_bags ? FWD_ROWS_LEAST_L : 10240;
     if (p.n1 == 2) return p.R1 >= 64 ? 14336 : 131072;
     if (L < 2 * n_bags) return 40960;
     return p.R1 >= 64 ? 12288 : 28672;

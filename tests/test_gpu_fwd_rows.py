@@ -232,10 +232,11 @@ def test_a_bag_does_not_depend_on_the_length_of_the_others(n, R):
     assert_close(out, ora.fwd(d.oshape, d.cores, d.batch.indices, off, alpha=d.batch.alpha), str(n))
 
 
-# bags of eight and more: either side of the limits of their own
-@pytest.mark.parametrize("n,R,L", [((4, 4, 4), 32, 16_384), ((4, 4, 4), 64, 8192), ((2, 2, 4), 64, 8192)])
-def test_the_rule_for_long_bags(n, R, L):
-    for L, n_bags, pays in ((L - 1, L // 8 - 1, False), (L, L // 8, True), (L, L // 8 + 1, False)):
+# rank 64: bags of ten and more, and of eight and more: either side of the limits of their own; rank 32 has none
+@pytest.mark.parametrize("n,R,L,mean", [((4, 4, 4), 64, 8192, 10), ((2, 2, 4), 64, 8192, 10), ((4, 4, 4), 64, 10_240, 8), ((2, 2, 4), 64, 10_240, 8),
+                                        ((4, 4, 4), 32, 28_672, 8), ((4, 4, 4), 32, 28_672, 32)])
+def test_the_rule_for_long_bags(n, R, L, mean):
+    for L, n_bags, pays in ((L - 1, L // mean - 1, False), (L, L // mean, True), (L, L // mean + 1, R == 32)):
         d = _table("hot row", n, R, L, n_bags, m=(200, 200, 50), alpha=False)
         assert B.fwd_rows_pays(d.shape, L, n_bags) == pays
         out = d.fwd()
