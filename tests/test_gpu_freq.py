@@ -33,10 +33,8 @@ def test_long_streams(L, rows, capacity):
     r, c = got_r[:n].cpu().numpy(), got_c[:n].cpu().numpy()
     assert np.unique(r).size == n == stats[0] == min(len(true), capacity)
     assert int(c.sum()) + int(stats[1]) == 2 * L                             # every access is counted or reported dropped
-    if len(true) <= capacity:
-        assert stats[1] == 0 and {int(a): int(b) for a, b in zip(r, c)} == true
-    else:
-        assert all(1 <= b <= true[int(a)] for a, b in zip(r, c))
+    # a row that is in the table has all of its accesses: none is ever taken out, and where it is full none comes in
+    assert all(b == true[int(a)] for a, b in zip(r, c))
 
 
 def test_padding_of_a_long_stream_is_in_no_rows_count():

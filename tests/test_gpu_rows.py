@@ -233,3 +233,31 @@ def test_with_a_cache_and_little_room_the_owners_run(L, R):
     for x, y in zip(*out):
         assert np.isfinite(x).all()
         assert_close(x, y, "rows against list owners")
+
+
+@pytest.mark.parametrize("n,R,L", [((4, 4, 4), 64, 10_300), ((2, 2, 4), 64, 12_400), ((4, 4, 4), 32, 32_801), ((2, 2, 4), 32, 32_801)])
+@pytest.mark.parametrize("mean", [4, 1.5])
+def test_short_bags_are_pooled_from_rows_and_from_the_caches_lines(n, R, L, mean):
+    # hits and misses in the same bags, bags of 0 to 9 and of 33 to 300 among them, two long ones side by side
+    t = W.TableShape(30 * 20 * 40 - 3, (30, 20, 40), n, (1, R, R, 1))
+    rng = np.random.default_rng([L, R])
+    K = 300
+    keys = np.sort(rng.choice(t.num_rows, K, replace=False)).astype(np.int64)
+    idx = np.where(rng.random(L) < 0.4, rng.choice(keys, L), rng.integers(0, t.num_rows, L)).astype(np.int64)
+    n_bags = int(L / mean)
+    lens = rng.multinomial(L - 700, np.full(n_bags, 1 / n_bags)).astype(np.int64)
+    lens[[7, n_bags // 2, n_bags // 2 + 1, n_bags - 1]] += (33, 300, 300, 67)
+    off = np.concatenate([[0], lens.cumsum()])
+    batch = W.Batch(idx, off, np.zeros((n_bags, t.dim), np.float32), (0.5 + rng.random(L)).astype(np.float32))
+    d = DeviceTable(W.Workload("rows", (t,), n_bags, (0, 9), "uniform", 0.0, "normal0.1", 4), batch=batch)
+    counts = np.arange(K, 0, -1).astype(np.int64)
+    cache, _, _ = d.build_cache(K, keys, counts)
+    cache.rows += 0.01                                       # (what the lines have learned; a row of the cores is another)
+    assert B.fwd_uses_lists(d.shape, L, K, True)
+    ws = torch.full((B.bwd_sgd_workspace_bytes(d.shape, L, n_bags, K),), 0x7F, dtype=torch.uint8, device=dev())
+    out = torch.full((n_bags, t.dim), float("nan"), dtype=torch.float32, device=dev())
+    t0 = torch.empty((L, B.t0_floats(d.shape)), dtype=torch.float32, device=dev())
+    B.tt_emb_bwd_prepare(d.shape, d.idx, d.off, n_bags, cache=cache, workspace=ws, kept_t0=True)
+    B.tt_emb_fwd_prepared(d.shape, d.g, d.idx, d.off, n_bags, out, ws, t0=t0, alpha=d.alpha, cache=cache)
+    ref = ora.fwd(d.oshape, d.cores, idx, off, alpha=batch.alpha, cache_keys=ora.cache_select(keys, counts, K), cache_rows=cache.rows.cpu().numpy()[:K])
+    assert_close(out.cpu().numpy(), ref, "forward")
