@@ -151,11 +151,12 @@ int tt_emb_fwd(const tt_shape_t *shape, const float *const cores[3],
 /*
  * tt_emb_fwd without a cache, over the distinct rows of the batch: the positions are grouped by the slice of the second
  * core they read, equal rows of up to 512 neighbouring positions of a slice are computed once, on the matrix cores, and the
- * bags are pooled from those rows in position order.  Same results as tt_emb_fwd up to the order of the fp32 sums over the
- * rank indices; bit-identical from run to run.  For n = (2,2,4) or (4,4,4), equal ranks 32 or 64, m2 <= 1024,
- * m1 + m3 <= 4096 and L < 2^31 - 2^20; TT_ERR_UNSUPPORTED otherwise.  workspace: scratch memory of
- * tt_emb_fwd_rows_workspace_bytes bytes (0 for a shape or length without such a pass), 16-byte aligned.
- * tt_emb_fwd_rows_pays: 1 where the call was measured ahead of tt_emb_fwd, which is a question of the shape and of L.
+ * bags are pooled from those rows, each in an order that its own length decides.  Same results as tt_emb_fwd up to the
+ * order of the fp32 sums over the rank indices and over a bag; bit-identical from run to run.  For n = (2,2,4) or (4,4,4),
+ * equal ranks 32 or 64, m2 <= 1024, m1 + m3 <= 4096 and L < 2^31 - 2^20; TT_ERR_UNSUPPORTED otherwise.  workspace: scratch
+ * memory of tt_emb_fwd_rows_workspace_bytes bytes (0 for a shape or length without such a pass), 16-byte aligned.
+ * tt_emb_fwd_rows_pays: 1 where the call was measured ahead of tt_emb_fwd, which is a question of the shape, of L and of
+ * L / n_bags.
  */
 size_t tt_emb_fwd_rows_workspace_bytes(const tt_shape_t *shape, int64_t L, int64_t n_bags);
 int tt_emb_fwd_rows_pays(const tt_shape_t *shape, int64_t L, int64_t n_bags, int64_t cache_rows);
@@ -383,8 +384,8 @@ int tt_emb_bwd_two_calls_group_earlier(const tt_shape_t *shape, int64_t L, int64
  * groups the positions (long index streams, tt_emb_bwd_has_prepass) and the shape has such a
  * kernel, the forward pass works from its lists: a workgroup takes positions of one slice of the
  * second core, multiplies their stacked first-core rows with the slice on the matrix cores (Eq. 3,
- * first product), and the rows of each bag are pooled afterwards in position order.  With a kept T0
- * (and no cache, or one of up to 8192 rows with m2 <= 896) the lists are of distinct rows: a row is computed once, or
+ * first product), and the rows of each bag are pooled afterwards, in an order that the bag's length
+ * decides.  With a kept T0 (and no cache, or one of up to 8192 rows with m2 <= 896) the lists are of distinct rows: a row is computed once, or
  * once per few hundred to two thousand positions of its slice, and its T0 copied to all its positions.  Otherwise the
  * call is tt_emb_fwd / tt_emb_fwd_keep_t0.
  * The workspace is read (lists) and written (one row per position, in a part of it that the

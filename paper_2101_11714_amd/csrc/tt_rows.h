@@ -84,8 +84,11 @@ static inline bool rw_cache_supported(const Params &p, int64_t K) { return !K ||
 // workgroups handle, which is what short streams need (8,192 positions, a hot row of 740: one workgroup added these up
 // for 13 us).  Up to 262,143 positions half of the longest: a hot row's 2,000 positions are one workgroup's in the forward pass and
 // in the sums of the gradients, and that one is the last to finish; longer streams have enough other work and repeat more.  Step, windows of
-// 2,048 / 1,024 / 512: 204,800 positions (2,2,4) rank 64 192 / 188 / 204 us, rank 32 121 / 112 / 120; 82,000 in bags of 0-40
-// 146 / 128 / 123 and 100 / 94 / 95; uniform rows 417 / 417 / 420; rank 32, 300,000 147 / 139, uniform 233 / 238, 1,000,000 374 / 387.
+// 2,048 / 1,024, Zipf-distributed and (uniform) rows: 70,000 positions (2,2,4) rank 64 137 / 121.5 us (188 / 188), rank 32 94 / 93 (101 / 101),
+// (4,4,4) rank 64 258 / 237 (508 / 507.5), rank 32 138 / 128 (189.5 / 190); 200,000 192 / 188 (361.6 / 360.4), 125 / 117 (175 / 175),
+// 501 / 484 (1,257 / 1,255), 252 / 236 (470 / 471), with a cache 139 / 140; of 512 204 us at rank 64, 204,800 positions.  The two cross later, by
+// shape and rank: 270,000 227.6 / 229, 138 / 132, 679 / 668.5, 314 / 302; 400,000 311 / 313, 171 / 170 (365 / 359), 870.5 / 862, 437 / 419
+// (939 / 945); 600,000 434 / 457, 277 / 277, 1,231 / 1,313, 603 / 613.  The line is below all of these.
 constexpr int64_t RW_LONG_MIN_L = 65536, RW_LONGEST_MIN_L = 262144;
 static inline int rw_win(int64_t L) { return L < RW_LONG_MIN_L ? 256 : L < RW_LONGEST_MIN_L ? RW_WIN / 2 : RW_WIN; }
 static inline int rw_windows_of(const Params &p, int64_t L, int win) { return (int)(L / win) + p.m2; }

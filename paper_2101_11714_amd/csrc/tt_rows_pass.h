@@ -867,8 +867,9 @@ __global__ __launch_bounds__(RW_T) __attribute__((amdgpu_waves_per_eu(4))) void 
             // lane (h, b): rows jj = h NJ / H .. of T0 at column b against the upstream gradient, which the wave fetches together with them
             // and reads back from LDS, the same 16 bytes for all lanes of an h; the wave takes every RW_NW-th row of the slice.  (By scalar
             // loads, which come one row at a time when T0 is there, and whose two halves every lane chose between: 164 registers, one workgroup
-            // per compute unit, 29 us of this kernel for 8,192 bags of 20 with a cache at (4,4,4) rank 32; so 97, two, 19.  20,000 positions, (2,2,4)
-            // rank 32, 6.7 / 5.1; 204,800 at rank 64 30 / 28.)
+            // per compute unit, 29 us of this kernel for 8,192 bags of 20 with a cache at (4,4,4) rank 32; so 96, two, 19.  20,000 positions, (2,2,4)
+            // rank 32, 6.7 / 5.1; 204,800 at rank 64 30 / 28.  (4,4,4) rank 64 without a cache 88 registers and 118 so, two workgroups either way:
+            // held to 93 a step of 8,192 positions takes 85.3 instead of 87.5 us, of 6,500 81.7 instead of 80.4, of 12,000 102.8 instead of 102.2.)
             constexpr int H = WAVE / R > 0 ? WAVE / R : 1, NJH = NJ / H, NF = NJH > 8 ? 2 : 4;
             const int h = H > 1 ? lane / R : 0, b = lane % R;
             float *dyl = s_dy[w];
@@ -992,9 +993,9 @@ static inline int rw_tp(const Params &p) { return 128 / p.n1; }
 // (4,4,4) rank 32, hardly a row repeated or cached, 2,800 us, with 1,024 2,460; (2,2,4) rank 64 2,233 / 1,757)
 // As many whether a pre-pass runs beside it or not: one call and the two calls of a step have the same sums.  Three for two units below
 // 262,144 positions at rank 32, which leave registers for the next batch's pre-pass, against two for one: in two calls on two streams
-// 2,048 bags of 100, (2,2,4), 112.7 / 116.1 us, 8,192 of 20, (4,4,4), with a cache 117.5 / 121.6, without 211.5 / 204.9; in two calls on one
-// stream 134.2 / 128.4, 144.1 / 135.0, 234.0 / 226.5; one call 163.3 / 157.6, 166.3 / 156.4, 336 / 326; 60,000 positions, (4,4,4),
-// 113.4 / 115.9, 134.9 / 126.0, 168.8 / 159.8.
+// 2,048 bags of 100, (2,2,4), 112.7 / 116.1 us, 8,192 of 20, (4,4,4), with a cache 117.5 / 121.6 (on new batches 143.6 / 137.0), without
+// 211.5 / 204.9, 10,000 of 20 uniform rows 522 / 470; on one stream 134.2 / 128.4, 144.1 / 135.0, 234.0 / 226.5; in one call 163.3 / 157.6,
+// 166.3 / 156.4, 336 / 326; 60,000 positions, (4,4,4), 113.4 / 115.9, 134.9 / 126.0, 168.8 / 159.8.
 static inline int rw_tile_wgs(const Params &p, int64_t L, int64_t K)
 {
     const int n = (p.R1 >= 64 ? 1 : 2) * bo_compute_units();

@@ -1,6 +1,6 @@
 """The selection behind tt_cache_build / tt_cache_refill (tt_topk.h) at the borders of its three forms: all candidates
 ranked, the class of the K-th count and the keys up to it ranked (narrowed down first where ties fill the class), a full
-sort (more rows than are ranked, or more candidates than one workgroup narrows down); with ties everywhere, all counts
+sort (more rows than are ranked, or more candidates than are narrowed down); with ties everywhere, all counts
 equal, counts on class borders, and the largest counts."""
 import numpy as np
 import pytest
